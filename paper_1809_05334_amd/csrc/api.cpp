@@ -1354,7 +1354,7 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
   return VIE_OK;
 }
 
-// After the panels: the inverses of the 256-row diagonal blocks of L and U and
+// After the panels: the inverses of the 512-row diagonal blocks of L and U and
 // the coupling blocks of the triangular solves, the pivots read back (zero pivot: VIE_ESINGULAR), each block's row
 // permutation built on the host and uploaded; the context becomes S_FACTORED.
 int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
@@ -1362,33 +1362,55 @@ int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
   const Layout &L = ctx->L;
   const bool f32 = fp32_factors(ctx);
   int32_t *ipiv = ctx->ptr<int32_t>(L.ipiv), *perm = ctx->ptr<int32_t>(L.perm), *info = ctx->ptr<int32_t>(L.info);
+  // storage of domain d's inverses and coupling blocks: L's, then U's
+  struct Prep {
+    int n, nbk;
+    void *DL, *DU, *GL, *GU;
+  };
+  std::vector<Prep> prep;
   for (int d = 0; d < t.ndom; ++d) {
     const int n = doms[d].n;
     if (n == 0) continue;
     const int nbk = (n + kTrsvNB - 1) / kTrsvNB;
-    const int64_t mlast = n - (int64_t)(nbk - 1) * kTrsvNB;
-    void *DL = factor_ptr(ctx, L.dinv, L.doff[d]);
-    void *DU = factor_ptr(ctx, L.dinv, L.doff[d] + (int64_t)(nbk - 1) * kTrsvNB * kTrsvNB + mlast * mlast);
-    void *GL = factor_ptr(ctx, L.gcpl, L.goff[d]);
-    void *GU = factor_ptr(ctx, L.gcpl, L.goff[d] + (int64_t)(nbk - 1) * kTrsvNB * kTrsvNB);
-    const dim3 ig(nbk, kTrsvNB / kInvColsH), ib(4 * kInvColsH);   // kInvColsH columns of one inverse per block
-    const dim3 cg(nbk - 1, (kTrsvNB / 64) * (kTrsvNB / 64)), cb(256);   // 64 x 64 tiles of each coupling block
+    const int64_t mlast = n - (int64_t)(nbk - 1) * kTrsvNB, nb2 = (int64_t)(nbk - 1) * kTrsvNB * kTrsvNB;
+    prep.push_back({n, nbk, factor_ptr(ctx, L.dinv, L.doff[d]), factor_ptr(ctx, L.dinv, L.doff[d] + nb2 + mlast * mlast),
+                    factor_ptr(ctx, L.gcpl, L.goff[d]), factor_ptr(ctx, L.gcpl, L.goff[d] + nb2)});
+  }
+  {
+    TrsvPrep st{};
+    int total = 0;
+    auto flush = [&]() {
+      if (st.ndom == 0) return;
+      const dim3 ig(total, kTrsvNB / 16, 2), ib(256);
+      if (f32) hipLaunchKernelGGL(k_diag_inv_c, ig, ib, 0, ctx->stream, st);
+      else hipLaunchKernelGGL(k_diag_inv_z, ig, ib, 0, ctx->stream, st);
+      st.ndom = total = 0;
+    };
+    size_t q = 0;
+    for (int d = 0; d < t.ndom; ++d) {
+      if (doms[d].n == 0) continue;
+      const Prep &p = prep[q++];
+      st.d[st.ndom] = TrsvPrepDom{doms[d].A, doms[d].ld, p.n, total, p.DL, p.DU};
+      total += p.nbk;
+      if (++st.ndom == kLuMaxDom) flush();
+    }
+    flush();
+    LAUNCHCK();
+  }
+  size_t q = 0;
+  for (int d = 0; d < t.ndom; ++d) {
+    if (doms[d].n == 0) continue;
+    const Prep &p = prep[q++];
+    if (p.nbk < 2) continue;
+    const dim3 cg(p.nbk - 1, (kTrsvNB / 64) * (kTrsvNB / 64)), cb(256);   // 64 x 64 tiles of each coupling block
     if (f32) {
       const fz *A = (const fz *)doms[d].A;
-      hipLaunchKernelGGL(k_diag_inv_c, ig, ib, 0, ctx->stream, A, doms[d].ld, n, kTrsvNB, 1, (fz *)DL);
-      hipLaunchKernelGGL(k_diag_inv_c, ig, ib, 0, ctx->stream, A, doms[d].ld, n, kTrsvNB, 0, (fz *)DU);
-      if (nbk > 1) {
-        hipLaunchKernelGGL(k_trsv_coupling_c, cg, cb, 0, ctx->stream, A, doms[d].ld, n, 1, (const fz *)DL, (fz *)GL);
-        hipLaunchKernelGGL(k_trsv_coupling_c, cg, cb, 0, ctx->stream, A, doms[d].ld, n, 0, (const fz *)DU, (fz *)GU);
-      }
+      hipLaunchKernelGGL(k_trsv_coupling_c, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 1, (const fz *)p.DL, (fz *)p.GL);
+      hipLaunchKernelGGL(k_trsv_coupling_c, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 0, (const fz *)p.DU, (fz *)p.GU);
     } else {
       const dz *A = (const dz *)doms[d].A;
-      hipLaunchKernelGGL(k_diag_inv_z, ig, ib, 0, ctx->stream, A, doms[d].ld, n, kTrsvNB, 1, (dz *)DL);
-      hipLaunchKernelGGL(k_diag_inv_z, ig, ib, 0, ctx->stream, A, doms[d].ld, n, kTrsvNB, 0, (dz *)DU);
-      if (nbk > 1) {
-        hipLaunchKernelGGL(k_trsv_coupling_z, cg, cb, 0, ctx->stream, A, doms[d].ld, n, 1, (const dz *)DL, (dz *)GL);
-        hipLaunchKernelGGL(k_trsv_coupling_z, cg, cb, 0, ctx->stream, A, doms[d].ld, n, 0, (const dz *)DU, (dz *)GU);
-      }
+      hipLaunchKernelGGL(k_trsv_coupling_z, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 1, (const dz *)p.DL, (dz *)p.GL);
+      hipLaunchKernelGGL(k_trsv_coupling_z, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 0, (const dz *)p.DU, (dz *)p.GU);
     }
     LAUNCHCK();
   }

@@ -22,77 +22,107 @@ __global__ void k_permute(int n, int64_t off, const int32_t *__restrict__ perm, 
 // Inverses of the kTrsvNB x kTrsvNB diagonal blocks of L (unit lower) and U
 // (upper), computed once per factorisation: block b of INV, at b nb^2,
 // holds inv(T_bb) row-major with its own size m (nb but for a domain's last
-// block) as leading dimension, T_bb the diagonal block at row b*nb.  A
-// thread block forms 32 columns of one inverse by substitution; the columns
-// live in LDS, and each column's dot products are split over 4 lanes
-// (residues of the summation index mod 4, combined by shuffles).  A lane only
-// reads back the entries it wrote itself, so no barrier is needed inside the
-// substitution.
-constexpr int kInvCols = kInvColsH;
+// block) as leading dimension, T_bb the diagonal block at row b*nb.
+//
+// A thread block forms 16 columns of one inverse by substitution over 16-row
+// strips, the columns held in LDS in FP64 (128 KB: one thread block per CU).
+// Strip r is rhs - sum_l T[r, l] X[l] over the strips l solved so far, on the
+// FP64 matrix cores: the four waves take the strips l in turn, their partial
+// sums meet in LDS, and wave 0 finishes the strip with its 16 x 16 diagonal
+// block, four rows and one column per lane.  U is taken with rows and columns
+// reversed, where it is a lower triangle too.  What bounds it is the chain of
+// up to 32 strips: a substitution with one lane quad per column, a chain of
+// 512 rows, took 1.9-4.1 ms per launch and two launches per domain.  The L and
+// U inverses of up to kLuMaxDom domains share one launch: 0.20 ms for N = 416
+// (3.98 before), 0.98 ms for N = 15,840 in three domains, FP64 (24.4 before).
+typedef double v4d __attribute__((ext_vector_type(4)));
 
 template <typename C>
-__device__ __forceinline__ void diag_inv_body(const C *__restrict__ F, int64_t ld, int n, int nb, int lower,
-                                              C *__restrict__ INV) {
-  __shared__ dz X[kInvCols][kTrsvNB];
-  const int b = blockIdx.x;
-  const int b0 = b * nb;
-  const int m = min(nb, n - b0);
-  const int cl = threadIdx.x >> 2, t = threadIdx.x & 3;
-  const int j = blockIdx.y * kInvCols + cl;      // column of the inverse
-  for (int i = t; i < nb; i += 4) X[cl][i] = mk(0, 0);
-  const C *T = F + (int64_t)b0 * ld + b0;
-  auto inv = [](dz d) {
-    const double den = d.re * d.re + d.im * d.im;
-    return mk(d.re / den, -d.im / den);
-  };
-  if (j < m) {
-    if (lower) {
-      if ((j & 3) == t) X[cl][j] = mk(1, 0);
-      for (int i = j + 1; i < m; ++i) {
-        const C *Ti = T + (int64_t)i * ld;
-        dz s0 = mk(0, 0), s1 = mk(0, 0);
-        int l = j + ((t - j) & 3);                 // first l >= j with l = t (mod 4)
-        for (; l + 4 < i; l += 8) {
-          s0 = s0 + to_dz(Ti[l]) * X[cl][l];
-          s1 = s1 + to_dz(Ti[l + 4]) * X[cl][l + 4];
-        }
-        if (l < i) s0 = s0 + to_dz(Ti[l]) * X[cl][l];
-        dz s = s0 + s1;
-        s = s + mk(__shfl_xor(s.re, 1), __shfl_xor(s.im, 1));
-        s = s + mk(__shfl_xor(s.re, 2), __shfl_xor(s.im, 2));
-        if ((i & 3) == t) X[cl][i] = mk(0, 0) - s;
-      }
-    } else {
-      if ((j & 3) == t) X[cl][j] = inv(to_dz(T[(int64_t)j * ld + j]));
-      for (int i = j - 1; i >= 0; --i) {
-        const C *Ti = T + (int64_t)i * ld;
-        dz s0 = mk(0, 0), s1 = mk(0, 0);
-        int l = (i + 1) + ((t - (i + 1)) & 3);     // first l > i with l = t (mod 4)
-        for (; l + 4 <= j; l += 8) {
-          s0 = s0 + to_dz(Ti[l]) * X[cl][l];
-          s1 = s1 + to_dz(Ti[l + 4]) * X[cl][l + 4];
-        }
-        if (l <= j) s0 = s0 + to_dz(Ti[l]) * X[cl][l];
-        dz s = s0 + s1;
-        s = s + mk(__shfl_xor(s.re, 1), __shfl_xor(s.im, 1));
-        s = s + mk(__shfl_xor(s.re, 2), __shfl_xor(s.im, 2));
-        if ((i & 3) == t) X[cl][i] = mk(0, 0) - s * inv(to_dz(Ti[i]));
+__device__ __forceinline__ void diag_inv_body(const TrsvPrep &st) {
+  constexpr int S = 16, NS = kTrsvNB / S;
+  __shared__ dz X[kTrsvNB][S];
+  __shared__ dz P[4][S][S];
+  __shared__ dz Td[S][S + 1];
+  int dd = 0;
+  while (dd + 1 < st.ndom && (int)blockIdx.x >= st.d[dd + 1].first_block) ++dd;
+  const TrsvPrepDom &D = st.d[dd];
+  const int b = blockIdx.x - D.first_block, n = D.n;
+  const bool lower = blockIdx.z == 0;
+  const int b0 = b * kTrsvNB, m = min(kTrsvNB, n - b0), c = blockIdx.y;
+  if (c * S >= m) return;
+  const int64_t ld = D.ld;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, col = lane & 15, g = lane >> 4;
+  // element (i, l) of the (reversed, for U) lower triangle: base + dir (i ld + l)
+  const int64_t dir = lower ? 1 : -1;
+  const C *__restrict__ T = (const C *)D.F + (int64_t)b0 * ld + b0 + (lower ? 0 : (int64_t)(m - 1) * (ld + 1));
+  const int ns = (m + S - 1) / S;
+  for (int r = c; r < ns; ++r) {
+    // the strip's diagonal block, one entry per thread (identity past the block's size)
+    {
+      const int i = r * S + tid / S, l = r * S + tid % S;
+      const dz t = to_dz(T[dir * (min(i, m - 1) * ld + min(l, m - 1))]);
+      Td[tid / S][tid % S] = i < m && l < m ? t : mk(i == l ? 1.0 : 0.0, 0.0);
+    }
+    v4d cre = {0, 0, 0, 0}, cim = {0, 0, 0, 0};
+    const int row = min(r * S + col, m - 1);   // (rows past the block repeat its last; their strip rows are not stored)
+    for (int l = c + wave; l < r; l += 4) {
+      // the k index of MFMA step s is 4 g + s in both operands: a lane reads four neighbours of its row
+      const C *Tl = T + dir * (row * ld + l * S + 4 * g);
+      C a[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) a[s] = Tl[dir * s];
+#pragma unroll
+      for (int s = 0; s < 4; ++s) {
+        const dz av = to_dz(a[s]), x = X[l * S + 4 * g + s][col];
+        cre = __builtin_amdgcn_mfma_f64_16x16x4f64(av.re, x.re, cre, 0, 0, 0);
+        cim = __builtin_amdgcn_mfma_f64_16x16x4f64(av.re, x.im, cim, 0, 0, 0);
+        cre = __builtin_amdgcn_mfma_f64_16x16x4f64(-av.im, x.im, cre, 0, 0, 0);
+        cim = __builtin_amdgcn_mfma_f64_16x16x4f64(av.im, x.re, cim, 0, 0, 0);
       }
     }
+#pragma unroll
+    for (int q = 0; q < 4; ++q) P[wave][4 * q + g][col] = mk(cre[q], cim[q]);
+    __syncthreads();
+    if (wave == 0) {
+      dz v[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = 4 * g + q;
+        const dz s = (P[0][i][col] + P[1][i][col]) + (P[2][i][col] + P[3][i][col]);
+        v[q] = mk((r == c && i == col ? 1.0 : 0.0) - s.re, -s.im);
+      }
+#pragma unroll
+      for (int k = 0; k < S; ++k) {
+        dz xk = v[k & 3];
+        if (!lower) {   // U: divide by the diagonal entry
+          const dz d = Td[k][k];
+          const double den = d.re * d.re + d.im * d.im;
+          xk = xk * mk(d.re / den, -d.im / den);
+        }
+        if (g == k >> 2) v[k & 3] = xk;
+        const int src = (k >> 2) * S + col;
+        xk = mk(__shfl(xk.re, src), __shfl(xk.im, src));
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+          if (4 * g + q > k) cmac(v[q], mk(-Td[4 * g + q][k].re, -Td[4 * g + q][k].im), xk);
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) X[r * S + 4 * g + q][col] = v[q];
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  if (j < m) {
-    C *inv_b = INV + (int64_t)b * nb * nb;   // the inverse of block b, m x m row-major: its column j
-    for (int i = t; i < m; i += 4) inv_b[(int64_t)i * m + j] = cx<C>::of(X[cl][i]);
+  // the inverse of block b, m x m row-major: its columns c S .. (zero above the first strip)
+  C *__restrict__ inv_b = (C *)(lower ? D.INVL : D.INVU) + (int64_t)b * kTrsvNB * kTrsvNB;
+  const int j = c * S + tid % S;
+  if (j >= m) return;
+  for (int i = tid / S; i < m; i += S) {
+    const dz v = i >= c * S ? X[i][tid % S] : mk(0, 0);
+    inv_b[lower ? (int64_t)i * m + j : (int64_t)(m - 1 - i) * m + (m - 1 - j)] = cx<C>::of(v);
   }
 }
 
-__global__ __launch_bounds__(4 * kInvCols) void k_diag_inv_z(const dz *F, int64_t ld, int n, int nb, int lower, dz *INV) {
-  diag_inv_body(F, ld, n, nb, lower, INV);
-}
-__global__ __launch_bounds__(4 * kInvCols) void k_diag_inv_c(const fz *F, int64_t ld, int n, int nb, int lower, fz *INV) {
-  diag_inv_body(F, ld, n, nb, lower, INV);
-}
+__global__ __launch_bounds__(256) void k_diag_inv_z(TrsvPrep st) { diag_inv_body<dz>(st); }
+__global__ __launch_bounds__(256) void k_diag_inv_c(TrsvPrep st) { diag_inv_body<fz>(st); }
 
 // Coupling blocks of one domain's sweep: for the matrix blocks b that follow
 // another in the sweep's order (b >= 1 for L, b <= nbk - 2 for U), with p =

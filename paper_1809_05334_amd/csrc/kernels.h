@@ -122,7 +122,6 @@ __global__ void k_gather(ZOut Z, const int64_t *rows, const int64_t *cols, int64
 
 // block LU (k_lu.hip) and its application (k_trsv.hip)
 constexpr int kTrsvNB = 512;                   // diagonal-block size of the triangular solves
-constexpr int kInvColsH = 8192 / kTrsvNB;      // columns of one inverse per k_diag_inv block (128 KB of LDS)
 // FP64 (_z) and FP32 (_c) factor storage
 __global__ void k_copy_block_z(ZOut Z, int64_t start, int n, dz *A, int64_t lda);
 __global__ void k_copy_block_c(ZOut Z, int64_t start, int n, fz *A, int64_t lda);
@@ -177,8 +176,22 @@ VIE_DECL_LU(c)
 #undef VIE_DECL_LU
 // (k_trsv.hip)
 __global__ void k_permute(int n, int64_t off, const int32_t *perm, const dz *v, dz *z);
-__global__ void k_diag_inv_z(const dz *F, int64_t ld, int n, int nb, int lower, dz *Dinv);
-__global__ void k_diag_inv_c(const fz *F, int64_t ld, int n, int nb, int lower, fz *Dinv);
+// Inverses of the diagonal blocks of L (blockIdx.z 0) and U (1) of up to
+// kLuMaxDom domains: blockIdx.x counts the diagonal blocks over the domains,
+// blockIdx.y the 16-column panels of one inverse.
+struct TrsvPrepDom {
+  const void *F;      // the domain's LU factors (dz or fz, row-major, leading dimension ld)
+  int64_t ld;
+  int n;
+  int first_block;    // first diagonal block of this domain in the launch
+  void *INVL, *INVU;
+};
+struct TrsvPrep {
+  TrsvPrepDom d[kLuMaxDom];
+  int ndom;
+};
+__global__ void k_diag_inv_z(TrsvPrep st);
+__global__ void k_diag_inv_c(TrsvPrep st);
 // coupling blocks G_b = T[b, p] inv(T_pp) of one domain's L (p = b - 1, b >= 1) or U
 // (p = b + 1, b <= nbk - 2) sweep, each kTrsvNB x kTrsvNB (k_trsv.hip)
 __global__ void k_trsv_coupling_z(const dz *F, int64_t ld, int n, int lower, const dz *INV, dz *G);

@@ -148,3 +148,22 @@ def test_tournament_and_partial_pivoting_agree(vie, prec):
         e_t = np.linalg.norm(z_t - zs) / np.linalg.norm(zs)
         e_p = np.linalg.norm(z_p - zs) / np.linalg.norm(zs)
         assert e_p < 1e-3 and e_t < 3 * e_p + 1e-6, (e_t, e_p)
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(2, 2, 1), (3, 3, 1), (4, 4, 2), (5, 4, 4), (4, 4, 6), (5, 5, 5)])
+def test_diagonal_block_inverses_at_strip_and_block_edges(vie, nx, ny, nz):
+    """One domain whose last diagonal block ends at, before and after a 16-row
+    strip and a 512-row block (N = 56 to 1,550): M^{-1} v against a dense
+    solve of the library's Z.  Tolerance: the backward error of an FP64 LU of
+    this size, a few N u growth (N u = 1.4e-13), times the condition of Z
+    (below 1e3 on these slabs)."""
+    m = W.slab_mesh(nx=nx, ny=ny, nz=nz)
+    s = solver(vie, m, 20)
+    s.fill(600.0, 0.3, 0.2, W.slab_eps(m))
+    s.factor()
+    N = s.num_unknowns()
+    rng = np.random.default_rng(3)
+    v = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    z = s.precond_apply(v)
+    ref = np.linalg.solve(read_block(s, 0, N), v)
+    assert np.linalg.norm(z - ref) < 1e-10 * np.linalg.norm(ref), N
