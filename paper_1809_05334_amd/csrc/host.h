@@ -76,12 +76,6 @@ inline int touching_mask(const int32_t *ct, const int32_t *ot, int nt_, const in
 
 void build_quadrature(QuadRules &q);
 
-// Special functions (host, FP64): complex erfc and erfcx from their integral
-// definitions evaluated by Gauss-Legendre quadrature.
-zd erfc_c(zd z);
-zd erfcx_c(zd z);
-double erfi_r(double y);
-
 // Ewald split and per-fill tables.  zspan = zmax - zmin of the mesh.
 // Returns "" or an error; sets *wood_margin = min_{(p,q)!=(0,0)} |gamma_pq|/k0.
 std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, double lambda, double theta,

@@ -3,8 +3,6 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
-#include <atomic>
-#include <thread>
 #include <vector>
 
 #include "host.h"
@@ -12,122 +10,39 @@
 namespace vie {
 
 static const double kPi = 3.14159265358979323846;
-static const double kSqrtPi = 1.77245385090551602730;
 
-// ---------------------------------------------------------------- Gauss-Legendre
-// Nodes/weights on [0, 1] by Newton iteration on the Legendre three-term
-// recurrence, in extended precision.
 using ld = long double;
-using zl = std::complex<long double>;
-
-static void gauss_legendre01(int n, std::vector<ld> &x, std::vector<ld> &w) {
-  x.resize(n);
-  w.resize(n);
-  const ld pi = 3.141592653589793238462643383279502884L;
-  for (int i = 0; i < n; ++i) {
-    ld z = std::cos(pi * (i + 0.75L) / (n + 0.5L));
-    ld dp = 1;
-    for (int it = 0; it < 100; ++it) {
-      ld p0 = 1, p1 = 0;
-      for (int k = 1; k <= n; ++k) {
-        ld p2 = p1;
-        p1 = p0;
-        p0 = ((2 * k - 1) * z * p1 - (k - 1) * p2) / k;
-      }
-      dp = n * (z * p0 - p1) / (z * z - 1);
-      ld dz = p0 / dp;
-      z -= dz;
-      if (std::fabs(dz) < 1e-19L) break;
-    }
-    ld p0 = 1, p1 = 0;
-    for (int k = 1; k <= n; ++k) {
-      ld p2 = p1;
-      p1 = p0;
-      p0 = ((2 * k - 1) * z * p1 - (k - 1) * p2) / k;
-    }
-    dp = n * (z * p0 - p1) / (z * z - 1);
-    x[i] = 0.5L * (1 - z);
-    w[i] = 1.0L / ((1 - z * z) * dp * dp);  // (2 / ((1-z^2) P'^2)) / 2
-  }
-}
-
-struct GL {
-  std::vector<ld> x32, w32, x24, w24;
-  GL() {
-    gauss_legendre01(32, x32, w32);
-    gauss_legendre01(24, x24, w24);
-  }
-};
-static const GL &gl() {
-  static GL g;
-  return g;
-}
 
 // ---------------------------------------------------------------- special functions
-// erfcx(z) = (2/sqrt(pi)) int_0^inf exp(-s^2 - 2 z s) ds, used for Re z >= 0 (the
-// integrand is bounded by 1 there).  Composite Gauss-Legendre up to where the
-// integrand falls below 1e-20, accumulated in extended precision.
+// The Ewald terms are integrals over the split variable (in units of E) with
+// a real wavenumber, so their expansion in the wavenumber,
+//   int_1^inf s^(-2 first) exp(-x^2 s^2 + c / s^2) ds = sum_n c^n / n! J_{n+first}(x),
+//   J_n(x) = int_1^inf s^(-2n) exp(-x^2 s^2) ds,
+// has terms of one sign for c >= 0 and needs nothing but erfc: J_1 = e^{-x^2}
+// - sqrt(pi) x erfc(x) and, by parts, J_{n+1} = (e^{-x^2} - 2 x^2 J_n) /
+// (2n + 1).  The recurrence loses at most a factor e^{x^2} of terms of size
+// e^{-x^2}, so a sum is good to some 1e-19 absolute (extended precision),
+// where the fits resolve 1e-15.  This is a few dozen operations per value:
+// quadrature of the complex erfcx integrals took 60 ms of host time per fill
+// (16-18 ms on 16 threads), the tables now take 2 ms on one.
+// Sum over n >= n0 of c^n / n! J_{n + first}(x), n0 + first >= 1.
 static const ld kSqrtPiL = 1.772453850905516027298167483341145183L;
 
-static zl erfcx_integral(zl z) {
-  const GL &g = gl();
-  ld x = z.real();
-  ld S = -x + std::sqrt(x * x + 46.0L);
-  const int panels = 12;
-  zl acc = 0;
-  for (int p = 0; p < panels; ++p) {
-    ld lo = S * p / panels, h = S / panels;
-    for (size_t i = 0; i < g.x24.size(); ++i) {
-      ld s = lo + h * g.x24[i];
-      acc += h * g.w24[i] * std::exp(-s * s - 2.0L * z * s);
-    }
+static ld tail_sum(ld x, ld c, int first, int n0) {
+  const ld e = std::exp(-x * x), x2 = 2 * x * x;
+  ld J = e - kSqrtPiL * x * std::erfc(x);   // J_1
+  for (int k = 1; k < n0 + first; ++k) J = (e - x2 * J) / (2 * k + 1);
+  ld coef = 1, sum = 0;
+  for (int n = 1; n <= n0; ++n) coef *= c / n;
+  for (int n = n0; n < 400; ++n) {
+    const ld term = coef * J;
+    sum += term;
+    if (n > c && term < 1e-22L * sum) break;
+    J = (e - x2 * J) / (2 * (n + first) + 1);
+    coef *= c / (n + 1);
   }
-  return acc * (2.0L / kSqrtPiL);
+  return sum;
 }
-
-// erf(z) = (2 z / sqrt(pi)) int_0^1 exp(-z^2 t^2) dt  (moderate |z|)
-static zl erf_integral(zl z) {
-  const GL &g = gl();
-  zl acc = 0;
-  for (size_t i = 0; i < g.x32.size(); ++i) {
-    ld t = g.x32[i];
-    acc += g.w32[i] * std::exp(-z * z * (t * t));
-  }
-  return acc * z * (2.0L / kSqrtPiL);
-}
-
-static zl erfcx_l(zl z) {
-  if (z.real() >= 0) return erfcx_integral(z);
-  return 2.0L * std::exp(z * z) - erfcx_integral(-z);
-}
-
-static zl erfc_l(zl z) {
-  if (z.real() >= 0.5L) return std::exp(-z * z) * erfcx_integral(z);
-  if (z.real() <= -0.5L) return 2.0L - std::exp(-z * z) * erfcx_integral(-z);
-  return 1.0L - erf_integral(z);
-}
-
-zd erfcx_c(zd z) {
-  zl r = erfcx_l(zl(z.real(), z.imag()));
-  return zd((double)r.real(), (double)r.imag());
-}
-
-zd erfc_c(zd z) {
-  zl r = erfc_l(zl(z.real(), z.imag()));
-  return zd((double)r.real(), (double)r.imag());
-}
-
-static ld erfi_l(ld y) {
-  const GL &g = gl();
-  ld acc = 0;
-  for (size_t i = 0; i < g.x32.size(); ++i) {
-    ld t = g.x32[i];
-    acc += g.w32[i] * std::exp(y * y * t * t);
-  }
-  return acc * y * (2.0L / kSqrtPiL);
-}
-
-double erfi_r(double y) { return (double)erfi_l(y); }
 
 // ---------------------------------------------------------------- quadrature
 static double tet14_residual(const double p[6], double r[6]) {
@@ -258,21 +173,36 @@ void build_quadrature(QuadRules &q) {
 // the last eight coefficients sit at that noise level.  The kept degree is
 // the last counting coefficient.  Returns the degree, or -1 if neither 48 nor
 // 96 nodes converge within maxdeg.
+// cos(pi i / 2n), i < 4n, for n = 48 and 96: the nodes and the transform
+struct CosTable {
+  std::vector<ld> c48, c96;
+  CosTable() {
+    const ld pi = 3.141592653589793238462643383279502884L;
+    for (int i = 0; i < 4 * 48; ++i) c48.push_back(std::cos(pi * i / (2 * 48)));
+    for (int i = 0; i < 4 * 96; ++i) c96.push_back(std::cos(pi * i / (2 * 96)));
+  }
+};
+
 template <class F>
 static int cheb_fit(F f, double lo, double hi, double abs_tol, double rel_tol, double *out, int maxdeg) {
+  static const CosTable cosines;
   for (int n : {48, 96}) {
-    std::vector<ld> fx(n);
-    std::vector<double> c(n);
+    const std::vector<ld> &cs = n == 48 ? cosines.c48 : cosines.c96;
+    ld fx[96];
+    double c[96];
     double fmax = 0;
     for (int j = 0; j < n; ++j) {
-      double t = (double)std::cos(3.141592653589793238462643383279502884L * (j + 0.5L) / n);
+      const double t = (double)cs[2 * j + 1];
       fx[j] = f(lo + 0.5 * (t + 1) * (hi - lo));
       fmax = std::max(fmax, (double)std::fabs(fx[j]));
     }
-    const ld pi = 3.141592653589793238462643383279502884L;
     for (int k = 0; k < n; ++k) {
       ld s = 0;
-      for (int j = 0; j < n; ++j) s += fx[j] * std::cos(pi * k * (j + 0.5L) / n);
+      for (int j = 0, i = k; j < n; ++j) {
+        s += fx[j] * cs[i];   // i = k (2j + 1) mod 4n
+        i += 2 * k;
+        if (i >= 4 * n) i -= 4 * n;
+      }
       c[k] = (double)(2.0L * s / n);
     }
     c[0] *= 0.5;
@@ -292,20 +222,6 @@ static int cheb_fit(F f, double lo, double hi, double abs_tol, double rel_tol, d
     }
   }
   return -1;
-}
-
-// Run body(i) for i in [0, n) on up to 16 host threads.
-template <class Fn>
-static void parallel_for(int n, Fn body) {
-  const int nth = std::max(1, std::min<int>({16, n, (int)std::thread::hardware_concurrency()}));
-  std::atomic<int> next(0);
-  auto work = [&]() {
-    for (int i = next++; i < n; i = next++) body(i);
-  };
-  std::vector<std::thread> th;
-  for (int k = 1; k < nth; ++k) th.emplace_back(work);
-  work();
-  for (auto &t : th) t.join();
 }
 
 // ---------------------------------------------------------------- Ewald tables
@@ -354,32 +270,14 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
   const double sig = 1e-16 * G;
   const double fit_abs = 1e-15, fit_rel = 1e-14;
 
+  // F(x) = (2x / sqrt(pi)) int_1^inf exp(-x^2 s^2 + y^2 / s^2) ds, and H = (F - 1) / x with
+  // the n = 0 term erfc(x) - 1 = -erf(x) taken out: no cancellation near x = 0
   const ld yl = y;
-  const ld erfi_y = erfi_l(yl);
-  auto Fx = [&](double x) -> ld {
-    // exp(y^2 - x^2) Re erfcx(x - j y) = Re[e^{-2jxy} erfc(x - jy)]   (x >= 0.5)
-    const ld xl = x;
-    return std::exp(yl * yl - xl * xl) * erfcx_integral(zl(xl, -yl)).real();
-  };
+  auto Fx = [&](double x) -> ld { return std::erfc((ld)x) + 2 * (ld)x / kSqrtPiL * tail_sum(x, yl * yl, 0, 1); };
   auto Hx = [&](double x) -> ld {
-    // (F(x) - 1)/x = [-2 sin^2(xy) + sin(2xy) erfi(y) - Re(e^{-2jxy} I(x))]/x,
-    // I(x) = (2/sqrt(pi)) int_0^x exp(-(s - jy)^2) ds  (no cancellation near x = 0)
-    const ld xl = x;
-    if (x > 3.0) return (Fx(x) - 1.0L) / xl;
-    if (x == 0.0) return 2 * yl * erfi_y - 2 * std::exp(yl * yl) / kSqrtPiL;
-    const GL &g = gl();
-    zl I = 0;
-    for (size_t i = 0; i < g.x32.size(); ++i) {
-      ld s = xl * g.x32[i];
-      zl d(s, -yl);
-      I += g.w32[i] * std::exp(-d * d);
-    }
-    I *= xl * 2.0L / kSqrtPiL;
-    ld sxy = std::sin(xl * yl);
-    ld val = -2 * sxy * sxy + std::sin(2 * xl * yl) * erfi_y - (std::exp(zl(0, -2 * xl * yl)) * I).real();
-    return val / xl;
+    const ld xl = x, e0 = x == 0.0 ? 2 / kSqrtPiL : std::erf(xl) / xl;
+    return 2 / kSqrtPiL * tail_sum(xl, yl * yl, 0, 1) - e0;
   };
-  auto Ffull = [&](double x) -> ld { return x >= 0.5 ? Fx(x) : 1.0L + (ld)x * Hx(x); };
 
   // ---- spatial images: significance cut first, then the fits in parallel
   struct ImgJob {
@@ -400,28 +298,36 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
       jobs.push_back({m, n, xlo, xhi, touching_class});
     }
   tab.nimg = (int)jobs.size();
-  std::atomic<int> bad(0);
-  parallel_for((int)jobs.size(), [&](int i) {
+  bool bad = false;
+  for (int i = 0; i < tab.nimg; ++i) {
     const ImgJob &jb = jobs[i];
     PgfImage &im = tab.img[i];
+    // the fit depends on |m|, |n| alone: an earlier image with the same gives it
+    for (int k = 0; k < i; ++k)
+      if (std::abs(jobs[k].m) == std::abs(jb.m) && std::abs(jobs[k].n) == std::abs(jb.n)) {
+        im = tab.img[k];
+        break;
+      }
+    if (im.xs == 0) {
+      im.xa = jb.xlo;
+      im.xs = 2.0 / (jb.xhi - jb.xlo);
+      im.deg = cheb_fit(Fx, jb.xlo, jb.xhi, fit_abs, fit_rel, im.f, kPgfMaxDeg - 1);
+      im.hdeg = -1;
+      if (jb.touching) im.hdeg = cheb_fit(Hx, jb.xlo, jb.xhi, 0.0, fit_rel, im.h, kPgfMaxDeg - 1);
+      if (im.deg < 0 || (jb.touching && im.hdeg < 0)) bad = true;
+    }
     im.m = jb.m;
     im.n = jb.n;
-    im.xa = jb.xlo;
-    im.xs = 2.0 / (jb.xhi - jb.xlo);
     double ph = kx * jb.m * a + ky * jb.n * b;
     im.cre = std::cos(ph) / (4 * kPi);
     im.cim = std::sin(ph) / (4 * kPi);
-    im.deg = cheb_fit(Ffull, jb.xlo, jb.xhi, fit_abs, fit_rel, im.f, kPgfMaxDeg - 1);
-    im.hdeg = -1;
-    if (jb.touching) im.hdeg = cheb_fit(Hx, jb.xlo, jb.xhi, 0.0, fit_rel, im.h, kPgfMaxDeg - 1);
-    if (im.deg < 0 || (jb.touching && im.hdeg < 0)) bad = 1;
-  });
+  }
   if (bad) return "lattice-sum table: spatial fit did not converge";
 
   // ---- spectral modes, K_pq as a function of w = (z E)^2 on [0, (zspan E)^2]
   const double wmax = std::max(1e-30, zspan * E * zspan * E) * (1 + 1e-9);
   tab.ws = 2.0 / wmax;
-  parallel_for(kPgfTerms, [&](int idx) {
+  for (int idx = 0; idx < kPgfTerms; ++idx) {
       const int p = idx / kPgfSide - kPgfM, q = idx % kPgfSide - kPgfM;
       double tx = kx + 2 * kPi * p / a, ty = ky + 2 * kPi * q / b;
       double kt2 = tx * tx + ty * ty;
@@ -435,33 +341,31 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
         double pref = 1.0 / (4 * a * b * gam);
         auto K = [&](double w) -> ld {
           const ld v = std::sqrt(std::max(0.0L, (ld)w)), ul = u;
-          const ld t1 = std::exp(-ul * ul - v * v) * erfcx_l(zl(ul + v, 0)).real();
-          const ld t2 = std::exp(-ul * ul - v * v) * erfcx_l(zl(ul - v, 0)).real();
-          return (ld)pref * (t1 + t2);
+          return (ld)pref * (std::exp(2 * ul * v) * std::erfc(ul + v) + std::exp(-2 * ul * v) * std::erfc(ul - v));
         };
-        double kmax = 0;
-        for (int j = 0; j <= 16; ++j) kmax = std::max(kmax, (double)std::fabs(K(wmax * j / 16.0)));
-        if (kmax < sig) return;  // deg stays -1
+        if ((double)K(0.0) < sig) continue;  // K falls with z; deg stays -1
         md.cplx = 0;
         md.deg = cheb_fit(K, 0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
-        if (md.deg < 0) bad = 1;
+        if (md.deg < 0) bad = true;
       } else {
-        // propagating order: gamma = +j beta
-        double beta = std::sqrt(k0 * k0 - kt2);
-        double bb = beta / (2 * E);
-        const zl pref = 1.0L / (4.0L * a * b * zl(0, beta));
-        auto Kc = [&](double w) -> zl {
-          const ld v = std::sqrt(std::max(0.0L, (ld)w)), bl = bb;
-          const zl e1 = std::exp(zl(0, 2 * bl * v)), e2 = std::exp(zl(0, -2 * bl * v));
-          return pref * (e1 * erfc_l(zl(v, bl)) + e2 * erfc_l(zl(-v, bl)));
-        };
+        // propagating order, gamma = +j beta: the whole transform e^{-j beta z} / (2 j beta)
+        // less its part beyond the split, int_E^inf exp(-z^2 s^2 + beta^2 / 4 s^2) / (2 sqrt(pi) s^2) ds
+        const double beta = std::sqrt(k0 * k0 - kt2);
+        const ld bb = beta / (2 * E), area = a * b;
         md.cplx = 1;
-        int d1 = cheb_fit([&](double w) { return Kc(w).real(); }, 0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
-        int d2 = cheb_fit([&](double w) { return Kc(w).imag(); }, 0.0, wmax, sig, fit_rel, md.kim, kPgfMaxDeg - 1);
-        if (d1 < 0 || d2 < 0) bad = 1;
+        const int d1 = cheb_fit(
+            [&](double w) {
+              const ld v = std::sqrt(std::max(0.0L, (ld)w));
+              return -(std::sin(2 * bb * v) / (2 * beta) + tail_sum(v, bb * bb, 1, 0) / (2 * kSqrtPiL * E)) / area;
+            },
+            0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
+        const int d2 = cheb_fit(
+            [&](double w) { return -std::cos(2 * bb * std::sqrt(std::max(0.0L, (ld)w))) / (2 * beta * area); }, 0.0,
+            wmax, sig, fit_rel, md.kim, kPgfMaxDeg - 1);
+        if (d1 < 0 || d2 < 0) bad = true;
         md.deg = std::max(d1, d2);
       }
-    });
+  }
   if (bad) return "lattice-sum table: spectral fit did not converge";
   return "";
 }
