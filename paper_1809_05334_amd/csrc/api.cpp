@@ -846,9 +846,7 @@ int fill_upload(vie_ctx *ctx) {
   // half-SWG face) pair likewise yields the (face, tet) entry, by the same
   // two forms.  Zt is added transposed after the face kernels.
   const bool kt0 = kx == 0.0 && ky == 0.0;
-  // (the oblique form keeps 32 KB per block of the swapped moments in LDS
-  // beside the table; a table too large for both runs the plain fill)
-  ctx->fill_sym = L.Zt.bytes > 0 && (kt0 || ctx->fill_lds + kFarRevLds <= 65536);
+  ctx->fill_sym = L.Zt.bytes > 0;
   ctx->fill_sym_face = ctx->fill_sym;
   ctx->fill_rev = kt0 ? 0 : 1;
   ctx->last_sym = ctx->fill_sym;
@@ -900,14 +898,16 @@ int fill_kernels(vie_ctx *ctx) {
       if (sym && cs < ct) continue;   // covered by the launch of (cs, ct)
       const int nT = ctx->color_off[ct + 1] - ctx->color_off[ct], nS = ctx->color_off[cs + 1] - ctx->color_off[cs];
       const int mode = !sym ? 0 : (ct == cs ? 2 : 1);
+      const int tper = far_tper(nS, nT);
+      const dim3 fgrid(nblk(nS, 8), nblk(nT, 4 * tper));
       if (sym && rev)
-        hipLaunchKernelGGL(k_tt_far_rev, dim3(nblk(nS, 64), nblk(nT, 4)), dim3(256), lds + kFarRevLds, ctx->stream,
-                           pk_, pkl, qr, tg, t2f, colors + ctx->color_off[ct], nT, colors + ctx->color_off[cs], nS,
-                           alpha, gsrc, kappa, k0sq9, zo, zt, mode);
+        hipLaunchKernelGGL(k_tt_far_rev, fgrid, dim3(256), lds, ctx->stream, pk_, pkl, qr, tg, t2f,
+                           colors + ctx->color_off[ct], nT, colors + ctx->color_off[cs], nS, alpha, gsrc, kappa, k0sq9, zo,
+                           zt, mode, tper);
       else
-        hipLaunchKernelGGL(k_tt_far, dim3(nblk(nS, 64), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl, qr, tg,
-                           t2f, colors + ctx->color_off[ct], nT, colors + ctx->color_off[cs], nS, alpha, gsrc, kappa,
-                           k0sq9, zo, zt, mode);
+        hipLaunchKernelGGL(k_tt_far, fgrid, dim3(256), lds, ctx->stream, pk_, pkl, qr, tg, t2f,
+                           colors + ctx->color_off[ct], nT, colors + ctx->color_off[cs], nS, alpha, gsrc, kappa, k0sq9, zo,
+                           zt, mode, tper);
       LAUNCHCK();
       ++far_launches;
     }
@@ -916,7 +916,7 @@ int fill_kernels(vie_ctx *ctx) {
   for (int g = 0; g < C * C; ++g) {
     const int np = ctx->near_off[g + 1] - ctx->near_off[g];
     if (!np) continue;
-    hipLaunchKernelGGL(k_tt_near, dim3(nblk(16 * (int64_t)np, 256)), dim3(256), lds, ctx->stream, pk_, pkl, qr, tg, t2f,
+    hipLaunchKernelGGL(k_tt_near, dim3(nblk(np, 4)), dim3(256), lds, ctx->stream, pk_, pkl, qr, tg, t2f,
                        ctx->ptr<int32_t>(L.near_t) + ctx->near_off[g], ctx->ptr<int32_t>(L.near_s) + ctx->near_off[g],
                        ctx->ptr<int32_t>(L.near_m) + ctx->near_off[g], np, alpha, gsrc, kappa, inveps, k0sq9, zo);
     LAUNCHCK();
@@ -931,15 +931,15 @@ int fill_kernels(vie_ctx *ctx) {
       if (grid)
         ;
       else if (sym_face && rev)
-        hipLaunchKernelGGL(k_tet_face_rev, dim3(nblk(ctx->nface, 64), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
+        hipLaunchKernelGGL(k_tet_face_rev, dim3(nblk(ctx->nface, 16), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
                            qr, tg, t2f, colors + ctx->color_off[ct], nT, fg, ctx->nface, alpha, sigma, gsrc, kappa, zo, zt);
       else
-        hipLaunchKernelGGL(k_tet_face, dim3(nblk(ctx->nface, 64), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl, qr,
+        hipLaunchKernelGGL(k_tet_face, dim3(nblk(ctx->nface, 16), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl, qr,
                            tg, t2f, colors + ctx->color_off[ct], nT, fg, ctx->nface, alpha, sigma, gsrc, kappa, zo, zt,
                            sym_face ? 1 : 0);
       const int np = ctx->tf_off[ct + 1] - ctx->tf_off[ct];
       if (np)
-        hipLaunchKernelGGL(k_tet_face_near, dim3(nblk(np, 256)), dim3(256), lds, ctx->stream, pk_, pkl, qr, tg, t2f,
+        hipLaunchKernelGGL(k_tet_face_near, dim3(nblk(np, 16)), dim3(256), lds, ctx->stream, pk_, pkl, qr, tg, t2f,
                            (const int32_t *)ctx->ptr<int32_t>(L.near_tf) + 2 * (int64_t)ctx->tf_off[ct], np, fg,
                            alpha, sigma, zo);
       LAUNCHCK();
@@ -948,12 +948,12 @@ int fill_kernels(vie_ctx *ctx) {
       for (int cs = 0; cs < C; ++cs) {
         const int nS = ctx->color_off[cs + 1] - ctx->color_off[cs];
         if (!sym_face && !grid)   // (with the staging the far pairs came from k_tet_face)
-          hipLaunchKernelGGL(k_face_tet, dim3(nblk(nS, 64), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
+          hipLaunchKernelGGL(k_face_tet, dim3(nblk(nS, 16), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
                              qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, tg, t2f, colors + ctx->color_off[cs], nS,
                              gsrc, kappa, zo);
         const int np = ctx->ft_off[cs + 1] - ctx->ft_off[cs];
         if (np)
-          hipLaunchKernelGGL(k_face_tet_near, dim3(nblk(np, 256)), dim3(256), lds, ctx->stream, pk_, pkl, qr, fg,
+          hipLaunchKernelGGL(k_face_tet_near, dim3(nblk(np, 8)), dim3(256), lds, ctx->stream, pk_, pkl, qr, fg,
                              ctx->ptr<int32_t>(L.half), tg, t2f,
                              (const int32_t *)ctx->ptr<int32_t>(L.near_ft) + 2 * (int64_t)ctx->ft_off[cs], np, gsrc,
                              kappa, zo);
@@ -1017,26 +1017,25 @@ int fill_finish(vie_ctx *ctx, bool timed) {
     st.t_face_ms = mface;
   }
   // algorithmic work of the far tet-pair kernel (cost model, FMA = 2 FLOPs):
-  // per point pair: separation and wrap 12; per image 27 + 3 deg (X, Y, R^2,
-  // rsqrt counted as 8, the fit argument from R, Clenshaw, scale,
-  // accumulate); spectral set-up 212 (four sincos counted as 40 each, phase
-  // powers; 132 at normal incidence, where the two sincos of kt vanish); per
-  // mode 13 + 3 deg (twice the Clenshaw for a complex order); final phase 6.
-  // Per tet pair:
+  // per point pair: separation and wrap 12; per image 21 + 2 deg (R^2 5, rsqrt
+  // counted as 8, R and the fit argument 3, Horner, scale and accumulate 5);
+  // two sincos counted as 40 each (three at oblique incidence); per order
+  // 2 + 2 deg (twice the Horner for a complex order, + 4), 4 per order for the
+  // phases and 8 per row; final phases 14.  Per tet pair:
   // 16 point pairs + 1200 for moments and the 16-entry scatter (+ 1200 for
   // the swapped pair's scatter when one evaluation serves both).  At oblique
   // incidence one evaluation serving both also forms g_p at the reversed
   // separations (per point pair 4 per propagating order + 10) and the swapped
   // pair's moments (16 x 36 per tet pair).
-  double pp = 12 + (rev ? 212 : 132) + 6;
+  double pp = 12 + (rev ? 120 : 80) + 14 + 8 * kPgfSide;
   const PgfTable &tb = *ctx->tab;
-  for (int i = 0; i < tb.nimg; ++i) pp += 27 + 3 * tb.img[i].deg;
+  for (int i = 0; i < tb.nimg; ++i) pp += 21 + 2 * tb.img[i].deg;
   int nmodes = 0, ncplx = 0;
   for (int i = 0; i < kPgfTerms; ++i)
     if (tb.mode[i].deg >= 0) {
       ++nmodes;
       ncplx += tb.mode[i].cplx ? 1 : 0;
-      pp += 13 + 3 * tb.mode[i].deg * (tb.mode[i].cplx ? 2 : 1) + (tb.mode[i].cplx ? 4 : 0);
+      pp += 6 + 2 * tb.mode[i].deg * (tb.mode[i].cplx ? 2 : 1) + (tb.mode[i].cplx ? 4 : 0);
     }
   if (sym && rev) pp += 10 + 4 * ncplx;
   int64_t nnear = 0;

@@ -247,7 +247,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
   std::vector<Rec> recs;
   int maxC = 0;
   for (vie_ctx *x : b->cells) maxC = std::max(maxC, x->topo.ncolors);
-  enum { K_FAR, K_FAR_REV, K_NEAR, K_TF, K_TFN, K_FT, K_FTN, K_FF };
+  enum { K_FAR, K_FAR_REV, K_NEAR, K_TF, K_TF_REV, K_TFN, K_FT, K_FTN, K_FF };
   auto put = [&](const auto &L, int kind) {
     if (L.segs.empty()) return;
     recs.push_back({st.add(L.segs.data(), sizeof(L.segs[0]) * L.segs.size()), (int)L.segs.size(), L.blocks, L.lds,
@@ -293,9 +293,8 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
         const auto c = P(x);
         const int nT = x->color_off[ct + 1] - x->color_off[ct], nS = x->color_off[cs + 1] - x->color_off[cs];
         FarSeg s{c.pk, c.pkl, c.qr, c.tg, c.t2f, c.colors + x->color_off[ct], nT, c.colors + x->color_off[cs], nS,
-                 c.alpha, c.gsrc, c.kappa, x->fill_k0sq9, c.zo, c.zt, !x->fill_sym ? 0 : (ct == cs ? 2 : 1), 0, 0};
-        if (x->fill_sym && x->fill_rev) rev.add(s, (int)nblk(nS, 64), (int)nblk(nT, 4), x->fill_lds + kFarRevLds);
-        else plain.add(s, (int)nblk(nS, 64), (int)nblk(nT, 4), x->fill_lds);
+                 c.alpha, c.gsrc, c.kappa, x->fill_k0sq9, c.zo, c.zt, !x->fill_sym ? 0 : (ct == cs ? 2 : 1), far_tper(nS, nT), 0, 0};
+        (x->fill_sym && x->fill_rev ? rev : plain).add(s, (int)nblk(nS, 8), (int)nblk(nT, 4 * s.tper), x->fill_lds);
       }
       put(plain, K_FAR);
       put(rev, K_FAR_REV);
@@ -314,14 +313,14 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
         NearSeg s{c.pk, c.pkl, c.qr, c.tg, c.t2f, x->ptr<int32_t>(x->L.near_t) + x->near_off[g],
                   x->ptr<int32_t>(x->L.near_s) + x->near_off[g], x->ptr<int32_t>(x->L.near_m) + x->near_off[g], np,
                   c.alpha, c.gsrc, c.kappa, c.inveps, x->fill_k0sq9, c.zo, 0, 0};
-        L.add(s, (int)nblk(16 * (int64_t)np, 256), 1, x->fill_lds);
+        L.add(s, (int)nblk(np, 4), 1, x->fill_lds);
       }
       put(L, K_NEAR);
     }
   // face pairs: per test colour the far and touching (tet, face) pairs, per
   // source colour the (half-SWG face, tet) pairs, then the face-face pairs
   for (int ct = 0; ct < maxC; ++ct) {
-    Launch<TetFaceSeg> tf;
+    Launch<TetFaceSeg> tf, tfr;
     Launch<TetFaceNearSeg> tfn;
     for (vie_ctx *x : b->cells) {
       if (!x->nface || ct >= x->topo.ncolors) continue;
@@ -329,16 +328,17 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       const int nT = x->color_off[ct + 1] - x->color_off[ct];
       TetFaceSeg s{c.pk, c.pkl, c.qr, c.tg, c.t2f, c.colors + x->color_off[ct], nT, c.fg, x->nface, c.alpha,
                    c.sigma, c.gsrc, c.kappa, c.zo, c.zt, x->fill_sym_face ? (x->fill_rev ? 2 : 1) : 0, 0, 0};
-      tf.add(s, (int)nblk(x->nface, 64), (int)nblk(nT, 4), x->fill_lds);
+      (s.swap == 2 ? tfr : tf).add(s, (int)nblk(x->nface, 16), (int)nblk(nT, 4), x->fill_lds);
       const int np = x->tf_off[ct + 1] - x->tf_off[ct];
       if (np) {
         TetFaceNearSeg n{c.pk, c.pkl, c.qr, c.tg, c.t2f,
                          (const int32_t *)x->ptr<int32_t>(x->L.near_tf) + 2 * (int64_t)x->tf_off[ct], np, c.fg,
                          c.alpha, c.sigma, c.zo, 0, 0};
-        tfn.add(n, (int)nblk(np, 256), 1, x->fill_lds);
+        tfn.add(n, (int)nblk(np, 16), 1, x->fill_lds);
       }
     }
     put(tf, K_TF);
+    put(tfr, K_TF_REV);
     put(tfn, K_TFN);
   }
   for (int cs = 0; cs < maxC; ++cs) {
@@ -351,14 +351,14 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       if (!x->fill_sym_face) {
         FaceTetSeg s{c.pk, c.pkl, c.qr, c.fg, c.half, x->nhalf, c.tg, c.t2f, c.colors + x->color_off[cs], nS,
                      c.gsrc, c.kappa, c.zo, 0, 0};
-        ft.add(s, (int)nblk(nS, 64), (int)nblk(x->nhalf, 4), x->fill_lds);
+        ft.add(s, (int)nblk(nS, 16), (int)nblk(x->nhalf, 4), x->fill_lds);
       }
       const int np = x->ft_off[cs + 1] - x->ft_off[cs];
       if (np) {
         FaceTetNearSeg n{c.pk, c.pkl, c.qr, c.fg, c.half, c.tg, c.t2f,
                          (const int32_t *)x->ptr<int32_t>(x->L.near_ft) + 2 * (int64_t)x->ft_off[cs], np, c.gsrc,
                          c.kappa, c.zo, 0, 0};
-        ftn.add(n, (int)nblk(np, 256), 1, x->fill_lds);
+        ftn.add(n, (int)nblk(np, 8), 1, x->fill_lds);
       }
     }
     put(ft, K_FT);
@@ -383,6 +383,9 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       case K_FAR_REV: hipLaunchKernelGGL(k_tt_far_rev_seg, g, t, r.lds, b->stream, (const FarSeg *)p, r.nseg); break;
       case K_NEAR: hipLaunchKernelGGL(k_tt_near_seg, g, t, r.lds, b->stream, (const NearSeg *)p, r.nseg); break;
       case K_TF: hipLaunchKernelGGL(k_tet_face_seg, g, t, r.lds, b->stream, (const TetFaceSeg *)p, r.nseg); break;
+      case K_TF_REV:
+        hipLaunchKernelGGL(k_tet_face_rev_seg, g, t, r.lds, b->stream, (const TetFaceSeg *)p, r.nseg);
+        break;
       case K_TFN:
         hipLaunchKernelGGL(k_tet_face_near_seg, g, t, r.lds, b->stream, (const TetFaceNearSeg *)p, r.nseg);
         break;

@@ -5,6 +5,8 @@
 #pragma once
 #include <hip/hip_runtime.h>
 
+#include <type_traits>
+
 #include "common.h"
 
 namespace vie {
@@ -75,52 +77,10 @@ template <> struct cx<fz> {
 __device__ __forceinline__ dz to_dz(dz v) { return v; }
 __device__ __forceinline__ dz to_dz(fz v) { return dz{v.re, v.im}; }
 
-// f(t) = sum_{k=0}^{deg} c_k T_k(t), c_0 already halved (Clenshaw recurrence).
-// f(t) = sum_{k=0}^{K} c_k T_k(t) by the Clenshaw recurrence for a
-// zero-padded coefficient run, K a multiple of 4: four steps per iteration
-// with the next four coefficients fetched before the current ones are used.
-__device__ __forceinline__ double clenshaw4(const double *__restrict__ c, int K, double t) {
-  double b1 = 0.0, b2 = 0.0;
-  const double t2 = t + t;
-  if (K >= 4) {
-    double c3 = c[K], c2 = c[K - 1], c1 = c[K - 2], c0 = c[K - 3];
-#pragma unroll 1
-    for (int k = K;; k -= 4) {
-      const bool more = k >= 8;
-      double d3 = 0.0, d2 = 0.0, d1 = 0.0, d0 = 0.0;
-      if (more) {
-        d3 = c[k - 4];
-        d2 = c[k - 5];
-        d1 = c[k - 6];
-        d0 = c[k - 7];
-      }
-      double b0 = fma(t2, b1, c3 - b2);
-      b2 = b1;
-      b1 = b0;
-      b0 = fma(t2, b1, c2 - b2);
-      b2 = b1;
-      b1 = b0;
-      b0 = fma(t2, b1, c1 - b2);
-      b2 = b1;
-      b1 = b0;
-      b0 = fma(t2, b1, c0 - b2);
-      b2 = b1;
-      b1 = b0;
-      if (!more) break;
-      c3 = d3;
-      c2 = d2;
-      c1 = d1;
-      c0 = d0;
-    }
-  }
-  return fma(t, b1, c[0] - b2);
-}
-
-// Packed lattice-sum table (layout written by the host: header, per-mode
-// offsets, image records, mode records; see host.h).
+// Packed lattice-sum table (layout written by the host, see host.h).
 namespace pk {
-constexpr int E = 0, A = 1, B = 2, IA = 3, IB = 4, KX = 5, KY = 6, TPA = 7, TPB = 8, WS = 9, PHRE = 10, PHIM = 19,
-              NIMG = 28, MODES = 32, ROWS = 116, IMAGES = 128;
+constexpr int E = 0, A = 1, B = 2, IA = 3, IB = 4, KXP = 5, KYP = 6, FORM = 7, MODES = 8, WS = 9, PHRE = 10, PHIM = 19,
+              PROPS = 28, ROWN = 29, IMAGES = 40;
 }
 
 // Stage the packed table into LDS (all threads of the block participate).
@@ -142,56 +102,209 @@ __device__ __forceinline__ double rsqrt_pos(double x) {
   return fma(r * e, fma(e, 0.375, 0.5), r);
 }
 
-// W Chebyshev series with the same coefficients c[0..K] (K even, zero-padded)
-// at W arguments t[w]: interleaved Clenshaw recurrences, two coefficients per
-// step, each coefficient read once for all W.
-template <int W>
-__device__ __forceinline__ void clenshaw_w(const double *__restrict__ c, int K, const double (&t)[W], double (&f)[W]) {
-  double b1[W], b2[W], t2[W];
+// One series of the packed table, [K, e_0, e_1 .. e_K] (K even, coefficients of
+// the highest degree first), at NC arguments: each coefficient is read once
+// for all of them, the next pair while the current one is used.  Monomials by
+// Horner's rule, one FMA per coefficient, or (a table whose monomials would
+// round worse, see pack_pgf_table) Chebyshev coefficients by Clenshaw's
+// recurrence, an addition more.
+template <int NC>
+__device__ __forceinline__ void series(const double *__restrict__ q, bool cheb, const double (&t)[NC], double (&f)[NC]) {
+  const int K = pint(q[0]);
+  const double top = q[1];
+  const double *__restrict__ c = q + 2;
+  double x = c[0], y = c[1];   // (K = 0: the record after this one, unused)
+  if (!cheb) {
 #pragma unroll
-  for (int w = 0; w < W; ++w) {
-    b1[w] = b2[w] = 0.0;
-    t2[w] = t[w] + t[w];
+    for (int i = 0; i < NC; ++i) f[i] = top;
+    // (four coefficients per pass, the pairs read in turn into two sets of registers)
+#pragma unroll 1
+    for (int k = 4; k <= K; k += 4) {
+      const double u = c[k - 2], v = c[k - 1];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) f[i] = fma(f[i], t[i], x);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) f[i] = fma(f[i], t[i], y);
+      x = c[k];   // (past the last pair: the next record, unused)
+      y = c[k + 1];
+#pragma unroll
+      for (int i = 0; i < NC; ++i) f[i] = fma(f[i], t[i], u);
+#pragma unroll
+      for (int i = 0; i < NC; ++i) f[i] = fma(f[i], t[i], v);
+    }
+    if (K & 2) {
+#pragma unroll
+      for (int i = 0; i < NC; ++i) f[i] = fma(fma(f[i], t[i], x), t[i], y);
+    }
+    return;
   }
-  // four coefficients per pass, all read before the first is used, so one
-  // read's latency is exposed per four coefficients rather than per two
-  const auto pair = [&](double ck, double ck1) {
+  if (K == 0) {
+#pragma unroll
+    for (int i = 0; i < NC; ++i) f[i] = top;
+    return;
+  }
+  // (two arguments at a time: this form must not set the kernels' register need)
+  const auto clenshaw = [&](auto width, int i0) {
+    constexpr int N = decltype(width)::value;
+    double b1[N], b2[N], u = x, v = y;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      b1[i] = top;
+      b2[i] = 0.0;
+    }
+    const auto step = [&](double ck) {
+#pragma unroll
+      for (int i = 0; i < N; ++i) {
+        const double n = fma(t[i0 + i] + t[i0 + i], b1[i], ck - b2[i]);
+        b2[i] = b1[i];
+        b1[i] = n;
+      }
+    };
+#pragma unroll 1
+    for (int k = 2;; k += 2) {   // the pair (u, v) = (c_j, c_{j-1}); the last v is c_0
+      step(u);
+      if (k >= K) break;
+      step(v);
+      u = c[k];
+      v = c[k + 1];
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) f[i0 + i] = fma(t[i0 + i], b1[i], v - b2[i]);
+  };
+#pragma unroll
+  for (int i = 0; i + 1 < NC; i += 2) clenshaw(std::integral_constant<int, 2>(), i);
+  if (NC & 1) clenshaw(std::integral_constant<int, 1>(), NC - 1);
+}
+
+// Two series of one degree at the same arguments, [K, 0, (s_0, d_0) .. (s_K, d_K)]:
+// one read gives a coefficient of both.
+template <int W>
+__device__ __forceinline__ void series_pair(const double *__restrict__ q, bool cheb, const double (&t)[W], double (&s)[W],
+                                            double (&d)[W]) {
+  const int K = pint(q[0]);
+  const double *__restrict__ c = q + 2;
+  if (!cheb) {
+    double x = c[0], y = c[1];
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const double bk = fma(t2[w], b1[w], ck - b2[w]);
-      const double bk1 = fma(t2[w], bk, ck1 - b1[w]);
-      b2[w] = bk;
-      b1[w] = bk1;
+      s[w] = x;
+      d[w] = y;
     }
-  };
-  int k = K;
+    x = c[2];   // (K = 0: the next record, unused)
+    y = c[3];
 #pragma unroll 1
-  for (; k >= 8; k -= 8) {
-    const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-    const double c4 = c[k - 4], c5 = c[k - 5], c6 = c[k - 6], c7 = c[k - 7];
-    pair(c0, c1);
-    pair(c2, c3);
-    pair(c4, c5);
-    pair(c6, c7);
-  }
-  if (k >= 4) {   // (K is a multiple of 4: what remains is 4 or 0)
-    const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-    pair(c0, c1);
-    pair(c2, c3);
-    k -= 4;
-  }
-#pragma unroll 1
-  for (; k >= 2; k -= 2) pair(c[k], c[k - 1]);
+    for (int k = 2; k <= K; k += 2) {
+      const double u = c[2 * k], v = c[2 * k + 1];
 #pragma unroll
-  for (int w = 0; w < W; ++w) f[w] = fma(t[w], b1[w], c[0] - b2[w]);
+      for (int w = 0; w < W; ++w) {
+        s[w] = fma(s[w], t[w], x);
+        d[w] = fma(d[w], t[w], y);
+      }
+      x = c[2 * k + 2];
+      y = c[2 * k + 3];
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        s[w] = fma(s[w], t[w], u);
+        d[w] = fma(d[w], t[w], v);
+      }
+    }
+    return;
+  }
+#pragma unroll 1
+  for (int h = 0; h < 2; ++h) {   // Clenshaw, one series after the other
+    double b1[W], b2[W], f[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) b1[w] = b2[w] = 0.0;
+#pragma unroll 1
+    for (int k = 0; k < K; ++k) {
+      const double ck = c[2 * k + h];
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        const double n = fma(t[w] + t[w], b1[w], ck - b2[w]);
+        b2[w] = b1[w];
+        b1[w] = n;
+      }
+    }
+    const double last = c[2 * K + h];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      f[w] = fma(t[w], b1[w], last - b2[w]);
+      if (h) d[w] = f[w];
+      else s[w] = f[w];
+    }
+  }
+}
+
+// the next record after a series at offset `off`
+__device__ __forceinline__ int after_series(const double *__restrict__ P, int off) { return off + 2 + pint(P[off]); }
+
+// The NS images (+-m, +-n) of one record at W separations: f(t) / R (or, for a
+// touching image, E times the H series), added to the spatial sum with the
+// image phases.  Images (s m, s n) and (-s m, -s n) have conjugate phases.
+template <bool TOUCH, int W, int NS>
+__device__ __forceinline__ void image_group(const double *__restrict__ R, bool cheb, double E, const double (&R2)[NS * W],
+                                            const bool (&touch)[TOUCH ? NS * W : 1], double (&sre)[W], double (&sim)[W]) {
+  double t[NS * W], sc[NS * W], f[NS * W];
+#pragma unroll
+  for (int i = 0; i < NS * W; ++i) {
+    double Rw;
+    if (TOUCH) {   // a touching image can sit at R = 0 (its H series is evaluated at x = 0)
+      sc[i] = rsqrt(R2[i]);
+      Rw = R2[i] > 0.0 ? R2[i] * sc[i] : 0.0;
+    } else {       // separations of non-touching elements never vanish
+      sc[i] = rsqrt_pos(R2[i]);
+      Rw = R2[i] * sc[i];
+    }
+    t[i] = fma(Rw, R[0], R[1]);   // the fit's argument
+  }
+  series<NS * W>(R + 6, cheb, t, f);
+  if (TOUCH) {
+    bool any = false;
+#pragma unroll
+    for (int i = 0; i < NS * W; ++i) any = any || touch[i];
+    if (any) {
+      double h[NS * W];
+      series<NS * W>(R + after_series(R, 6), cheb, t, h);
+#pragma unroll
+      for (int i = 0; i < NS * W; ++i)
+        if (touch[i]) {
+          f[i] = h[i];
+          sc[i] = E;
+        }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < NS; s += 2) {
+    const double cre = R[2 + s], cim = R[3 + s];
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      const double g = f[s * W + w] * sc[s * W + w];
+      if (NS == 1) {
+        sre[w] = fma(cre, g, sre[w]);
+      } else {
+        const double g2 = f[(s + 1) * W + w] * sc[(s + 1) * W + w];
+        sre[w] = fma(cre, g + g2, sre[w]);
+        sim[w] = fma(cim, g - g2, sim[w]);
+      }
+    }
+  }
 }
 
 // g_p at W separations d[w] = r - r'_w at once (one test point, W source
-// points), from the packed table P.  The table entries are read once for
-// all W separations and the W Clenshaw recurrences run interleaved.  When
-// TOUCH is true, `mask` lists the lattice images (bit (m+1)*3 + (n+1)) whose
-// 1/(4 pi R) part is integrated in closed form elsewhere; for those images
-// the remainder H(x) E/(4 pi) is used, so the value returned is
+// points), from the packed table P.
+//
+// Images: (+-m, +-n) lie in the same range of R and share one series, so the
+// record's coefficients are read once for the up to 4 W arguments, which is
+// what keeps the LDS reads (one per coefficient and wave) below the FMAs.
+// Orders: with the terms K_pq real (the imaginary parts of the propagating
+// orders apart), sum_q K_pq e^{-j 2 pi q dy/b} = K_p0 + sum_{q>0} (S_q cos -
+// j D_q sin), S and D the sums and differences of the series of (p, q) and
+// (p, -q), and the rows p are summed by Horner's rule in e^{-j 2 pi dx/a}.
+// An FP64 FMA issues every four cycles per SIMD, and this is bound by them.
+//
+// When TOUCH is true, `mask` lists the lattice images (bit (m+1)*3 + (n+1))
+// whose 1/(4 pi R) part is integrated in closed form elsewhere; for those
+// images the remainder H(x) E/(4 pi) is used, so the value returned is
 // g_p - sum_touching e^{j kt.rho}/(4 pi R).
 //
 // REV (non-touching separations only): also g_p at -d[w] into rev[w].  For a
@@ -202,12 +315,12 @@ __device__ __forceinline__ void clenshaw_w(const double *__restrict__ c, int K, 
 // evanescent order, so it too conjugates, except for the propagating orders,
 // whose K_pq is complex.  Hence
 //   g_p(-d) = conj(g_p(d)) + conj(ph0) 2j sum_{propagating} conj(e^{-j k_tpq.Delta}) Im K_pq(z),
-// with ph0 the phase of the nearest-image shift (which flips with d).  The
-// reverse value costs two FMAs per propagating order on top of g_p(d).
+// with ph0 the phase of the nearest-image shift (which flips with d).
 template <bool TOUCH, int W, bool REV = false>
 __device__ __forceinline__ void pgf_eval_w(const double *__restrict__ P, const double (&d)[W][3], int mask,
                                            dz (&out)[W], dz *rev = nullptr) {
   const double a = P[pk::A], b = P[pk::B], E = P[pk::E];
+  const bool cheb = pint(P[pk::FORM]) != 0;
   double dx[W], dy[W], dz2[W], sre[W], sim[W];
   int im0[W], in0[W];
 #pragma unroll
@@ -221,181 +334,181 @@ __device__ __forceinline__ void pgf_eval_w(const double *__restrict__ P, const d
     sre[w] = 0.0;
     sim[w] = 0.0;
   }
-  // spatial series
-  const int nimg = pint(P[pk::NIMG]);
+  // spatial series: rows m = 0, 1, ... of the records n = 0 .. P[ROWN + m] - 1
   int off = pk::IMAGES;
 #pragma unroll 1
-  for (int i = 0; i < nimg; ++i) {
-    const double *R = P + off;
-    const double ts = R[0], t0 = R[1], cre = R[2], cim = R[3];   // t = ts R + t0
-    const int im = pint(R[4]), in = pint(R[5]), K = pint(R[6]);
-    off += pint(R[7]);
-    double t[W], sc[W];
-    bool touch[W];
+  for (int m = 0; m <= kPgfM; ++m) {
+    const int nn = pint(P[pk::ROWN + m]);
+    double xp[W], xm[W];   // (dx +- m a)^2 + dz^2
+    const double ma = (double)m * a;
 #pragma unroll
     for (int w = 0; w < W; ++w) {
-      const double X = fma((double)im, a, dx[w]), Y = fma((double)in, b, dy[w]);
-      const double R2 = fma(X, X, fma(Y, Y, dz2[w]));
-      touch[w] = false;
-      if (TOUCH) {
-        const int um = im - im0[w], un = in - in0[w];
-        touch[w] = um >= -1 && um <= 1 && un >= -1 && un <= 1 && ((mask >> ((um + 1) * 3 + (un + 1))) & 1);
-      }
-      double rinv, Rw;
-      if (TOUCH) {   // a touching image can sit at R = 0 (its H fit is evaluated at x = 0)
-        rinv = rsqrt(R2);
-        Rw = R2 > 0.0 ? R2 * rinv : 0.0;
-      } else {       // separations of non-touching elements never vanish
-        rinv = rsqrt_pos(R2);
-        Rw = R2 * rinv;
-      }
-      t[w] = fma(Rw, ts, t0);
-      sc[w] = touch[w] ? E : rinv;
+      const double X = dx[w] + ma, Y = dx[w] - ma;
+      xp[w] = fma(X, X, dz2[w]);
+      xm[w] = fma(Y, Y, dz2[w]);
     }
-    // W interleaved Clenshaw recurrences on the F coefficients
-    double b1[W], b2[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) b1[w] = b2[w] = 0.0;
-    const double *c = R + 8;
-    // four coefficients per pass, read before the first is used (as in clenshaw_w)
-    double t2[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) t2[w] = t[w] + t[w];
-    const auto pair = [&](double ck, double ck1) {
-#pragma unroll
-      for (int w = 0; w < W; ++w) {
-        const double bk = fma(t2[w], b1[w], ck - b2[w]);
-        const double bk1 = fma(t2[w], bk, ck1 - b1[w]);
-        b2[w] = bk;
-        b1[w] = bk1;
-      }
+    const auto touching = [&](int w, int sm, int sn) {   // image (sm, sn) of the wrapped separation
+      const int um = sm - im0[w], un = sn - in0[w];
+      return um >= -1 && um <= 1 && un >= -1 && un <= 1 && ((mask >> ((um + 1) * 3 + (un + 1))) & 1);
     };
-    int k = K;
 #pragma unroll 1
-    for (; k >= 8; k -= 8) {
-      const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-      const double c4 = c[k - 4], c5 = c[k - 5], c6 = c[k - 6], c7 = c[k - 7];
-      pair(c0, c1);
-      pair(c2, c3);
-      pair(c4, c5);
-      pair(c6, c7);
-    }
-    if (k >= 4) {   // (K is a multiple of 4: what remains is 4 or 0)
-      const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-      pair(c0, c1);
-      pair(c2, c3);
-      k -= 4;
-    }
-#pragma unroll 1
-    for (; k >= 2; k -= 2) pair(c[k], c[k - 1]);
-    double f[W];
+    for (int n = 0; n < nn; ++n) {
+      const double *R = P + off;
+      const double nb = (double)n * b;
+      off += ufirst(__double2hiint(R[6]));   // the record's length
+      const bool fit = TOUCH && m <= 1 && n <= 1;   // the records with an H series
+      if (m > 0 && n > 0) {
+        double R2[4 * W];
+        bool tc[TOUCH ? 4 * W : 1] = {};
 #pragma unroll
-    for (int w = 0; w < W; ++w) f[w] = fma(t[w], b1[w], c[0] - b2[w]);
-    if (TOUCH) {
-      bool any = false;
+        for (int w = 0; w < W; ++w) {
+          const double yp = dy[w] + nb, ym = dy[w] - nb;
+          R2[w] = fma(yp, yp, xp[w]);
+          R2[W + w] = fma(ym, ym, xm[w]);
+          R2[2 * W + w] = fma(ym, ym, xp[w]);
+          R2[3 * W + w] = fma(yp, yp, xm[w]);
+          if (fit) {
+            tc[w] = touching(w, m, n);
+            tc[TOUCH ? W + w : 0] = touching(w, -m, -n);
+            tc[TOUCH ? 2 * W + w : 0] = touching(w, m, -n);
+            tc[TOUCH ? 3 * W + w : 0] = touching(w, -m, n);
+          }
+        }
+        image_group<TOUCH, W, 4>(R, cheb, E, R2, tc, sre, sim);
+      } else if (m > 0 || n > 0) {
+        double R2[2 * W];
+        bool tc[TOUCH ? 2 * W : 1] = {};
 #pragma unroll
-      for (int w = 0; w < W; ++w) any = any || touch[w];
-      if (any) {
-        // touching images use the H fit (extracted 1/(4 pi R))
-        const double *Hb = R + 8 + K + 4;
-        const int HK = pint(Hb[0]);
+        for (int w = 0; w < W; ++w) {
+          const double yp = dy[w] + nb, ym = dy[w] - nb;
+          R2[w] = fma(yp, yp, xp[w]);
+          R2[W + w] = fma(ym, ym, xm[w]);
+          if (fit) {
+            tc[w] = touching(w, m, n);
+            tc[TOUCH ? W + w : 0] = touching(w, -m, -n);
+          }
+        }
+        image_group<TOUCH, W, 2>(R, cheb, E, R2, tc, sre, sim);
+      } else {
+        double R2[W];
+        bool tc[TOUCH ? W : 1] = {};
 #pragma unroll
-        for (int w = 0; w < W; ++w)
-          if (touch[w]) f[w] = clenshaw4(Hb + 4, HK, t[w]);
+        for (int w = 0; w < W; ++w) {
+          R2[w] = fma(dy[w], dy[w], xp[w]);
+          if (fit) tc[w] = touching(w, 0, 0);
+        }
+        image_group<TOUCH, W, 1>(R, cheb, E, R2, tc, sre, sim);
       }
-    }
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const double g = f[w] * sc[w];
-      sre[w] = fma(cre, g, sre[w]);
-      sim[w] = fma(cim, g, sim[w]);
     }
   }
 
-  // spectral series: the W separations share every mode's coefficient reads
-  // and run W interleaved Clenshaw recurrences in w = (z E)^2; the Floquet
-  // phases e^{-j k_tpq . Delta_t} of each separation by recurrence in p and q
-  double tw[W], kre[W], kim[W], cre_[W], cim_[W];
-  dz erow[W], bx[W], by[W];   // erow: phase of (p, q = -4); steps in p and in q
-  const bool kt0 = P[pk::KX] == 0.0 && P[pk::KY] == 0.0;   // normal incidence: e^{-j kt.Delta} = 1
+  // spectral series in w = (z E)^2
+  double tw[W];
+  dz bx[W], by[W], acc[W];
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    tw[w] = fma(dz2[w] * E * E, P[pk::WS], -1.0);
-    double s0, c0, s1, c1;
-    sincos(-P[pk::TPA] * dx[w], &s1, &c1);
+    tw[w] = fma(dz2[w], P[pk::WS], -1.0);
+    double s1, c1;
+    sincospi(-2.0 * dx[w] * P[pk::IA], &s1, &c1);
     bx[w] = mk(c1, s1);
-    sincos(-P[pk::TPB] * dy[w], &s1, &c1);
+    sincospi(-2.0 * dy[w] * P[pk::IB], &s1, &c1);
     by[w] = mk(c1, s1);
-    const dz bx4 = conjz(bx[w] * bx[w] * bx[w] * bx[w]), by4 = conjz(by[w] * by[w] * by[w] * by[w]);
-    if (kt0) {
-      erow[w] = bx4 * by4;   // (p, q) = (-4, -4)
-    } else {
-      sincos(-P[pk::KX] * dx[w], &s0, &c0);
-      const dz ex = mk(c0, s0) * bx4;   // p = -4
-      sincos(-P[pk::KY] * dy[w], &s0, &c0);
-      erow[w] = ex * (mk(c0, s0) * by4);
-    }
-    kre[w] = 0.0;
-    kim[w] = 0.0;
-    cre_[w] = 0.0;
-    cim_[w] = 0.0;
+    acc[w] = mk(0.0, 0.0);
   }
-  // rows of the grid: only the slots from the row's first to its last mode
-  // (the phases of the slots below reached by the same products as before)
+  off = pint(P[pk::MODES]);
+  const int hd = ufirst(__double2hiint(P[pk::MODES]));   // rows p = plo .. phi: plo + 8 | (phi + 8) << 8
+  const int plo = (hd & 0xff) - 8, phi = (hd >> 8) - 8;
 #pragma unroll 1
-  for (int p = 0; p < kPgfSide; ++p) {
-    const int rr = pint(P[pk::ROWS + p]);
-    const int qlo = rr & 0xff, qend = rr >> 8;
+  for (int p = phi; p >= plo; --p) {
+    const int nq = pint(P[off]);
+    const bool odd = ufirst(__double2hiint(P[off])) != 0;   // the row has differences
+    off += 2;
+    double k0[W];
+    series<W>(P + off, cheb, tw, k0);
+    off = after_series(P, off);
+#pragma unroll
+    for (int w = 0; w < W; ++w)
+      acc[w] = mk(fma(acc[w].re, bx[w].re, fma(-acc[w].im, bx[w].im, k0[w])), fma(acc[w].re, bx[w].im, acc[w].im * bx[w].re));
     dz e[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) e[w] = erow[w];
+    for (int w = 0; w < W; ++w) e[w] = by[w];
 #pragma unroll 1
-    for (int q = 0; q < qlo; ++q) {
+    for (int q = 1; q <= nq; ++q) {
+      if (odd) {
+        double s[W], d[W];
+        series_pair<W>(P + off, cheb, tw, s, d);
+        off += 2 + 2 * (pint(P[off]) + 1);
 #pragma unroll
-      for (int w = 0; w < W; ++w) e[w] = e[w] * by[w];
-    }
-#pragma unroll 1
-    for (int q = qlo; q < qend; ++q) {
-      const double slot = P[pk::MODES + p * kPgfSide + q];
-      const int moff = pint(slot);
-      if (moff > 0) {
-        const double *M = P + moff;
-        const int kc = ufirst(__double2hiint(slot));   // K | cplx << 16
-        const int K = kc & 0xffff;
-        double kr[W];
-        clenshaw_w<W>(M + 4, K, tw, kr);
-        if ((kc >> 16) != 0) {
-          double ki[W];
-          clenshaw_w<W>(M + 4 + K + 4, K, tw, ki);
-#pragma unroll
-          for (int w = 0; w < W; ++w) {
-            kre[w] += e[w].re * kr[w] - e[w].im * ki[w];
-            kim[w] += e[w].re * ki[w] + e[w].im * kr[w];
-            if (REV) {   // conj(e) Im K_pq of a propagating order
-              cre_[w] = fma(e[w].re, ki[w], cre_[w]);
-              cim_[w] = fma(-e[w].im, ki[w], cim_[w]);
-            }
-          }
-        } else {
-#pragma unroll
-          for (int w = 0; w < W; ++w) {
-            kre[w] = fma(e[w].re, kr[w], kre[w]);
-            kim[w] = fma(e[w].im, kr[w], kim[w]);
-          }
+        for (int w = 0; w < W; ++w) {
+          acc[w].re = fma(s[w], e[w].re, acc[w].re);
+          acc[w].im = fma(d[w], e[w].im, acc[w].im);
         }
+      } else {
+        double s[W];
+        series<W>(P + off, cheb, tw, s);
+        off = after_series(P, off);
+#pragma unroll
+        for (int w = 0; w < W; ++w) acc[w].re = fma(s[w], e[w].re, acc[w].re);
       }
 #pragma unroll
       for (int w = 0; w < W; ++w) e[w] = e[w] * by[w];
     }
-#pragma unroll
-    for (int w = 0; w < W; ++w) erow[w] = erow[w] * bx[w];
   }
+  // times bx^plo (plo <= 0)
+#pragma unroll 1
+  for (int p = plo; p < 0; ++p) {
+#pragma unroll
+    for (int w = 0; w < W; ++w) acc[w] = acc[w] * conjz(bx[w]);
+  }
+  // propagating orders: e^{-j k_pq Delta} j Im K_pq
+  double pr[W], pi[W];
+#pragma unroll
+  for (int w = 0; w < W; ++w) pr[w] = pi[w] = 0.0;
+  off = pint(P[pk::PROPS]);
+  const int np = ufirst(__double2hiint(P[pk::PROPS]));
+#pragma unroll 1
+  for (int i = 0; i < np; ++i) {
+    const int p = pint(P[off]), q = ufirst(__double2hiint(P[off]));
+    off += 2;
+    double ki[W];
+    series<W>(P + off, cheb, tw, ki);
+    off = after_series(P, off);
+    dz e[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) e[w] = mk(1.0, 0.0);
+#pragma unroll 1
+    for (int j = 0; j < (p < 0 ? -p : p); ++j) {
+#pragma unroll
+      for (int w = 0; w < W; ++w) e[w] = e[w] * (p < 0 ? conjz(bx[w]) : bx[w]);
+    }
+#pragma unroll 1
+    for (int j = 0; j < (q < 0 ? -q : q); ++j) {
+#pragma unroll
+      for (int w = 0; w < W; ++w) e[w] = e[w] * (q < 0 ? conjz(by[w]) : by[w]);
+    }
+#pragma unroll
+    for (int w = 0; w < W; ++w) {
+      pr[w] = fma(e[w].re, ki[w], pr[w]);
+      pi[w] = fma(e[w].im, ki[w], pi[w]);
+    }
+  }
+  const bool kt0 = P[pk::KXP] == 0.0 && P[pk::KYP] == 0.0;   // normal incidence: e^{-j kt.Delta} = 1
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const int pi = (im0[w] + 1) * 3 + (in0[w] + 1);
-    const dz ph = mk(P[pk::PHRE + pi], P[pk::PHIM + pi]);
-    out[w] = ph * mk(sre[w] + kre[w], sim[w] + kim[w]);
-    if (REV) rev[w] = conjz(out[w]) + conjz(ph) * mk(-2.0 * cim_[w], 2.0 * cre_[w]);
+    dz u = mk(1.0, 0.0);
+    if (!kt0) {
+      double s1, c1;
+      sincospi(-fma(P[pk::KXP], dx[w], P[pk::KYP] * dy[w]), &s1, &c1);
+      u = mk(c1, s1);
+    }
+    const dz k = u * mk(acc[w].re - pi[w], acc[w].im + pr[w]);
+    const int i0 = (im0[w] + 1) * 3 + (in0[w] + 1);
+    const dz ph = mk(P[pk::PHRE + i0], P[pk::PHIM + i0]);
+    out[w] = ph * mk(sre[w] + k.re, sim[w] + k.im);
+    if (REV) {
+      const dz c = conjz(u) * mk(pr[w], -pi[w]);   // conj(e^{-j k_pq Delta}) Im K_pq, summed
+      rev[w] = conjz(out[w]) + conjz(ph) * mk(-2.0 * c.im, 2.0 * c.re);
+    }
   }
 }
 
@@ -479,37 +592,31 @@ __device__ inline void tri_potentials(const double *A, const double *B, const do
   ione = (d * d * sinv + 0.5 * sedge) / 3.0;
 }
 
-// Integrals of 1/|r - r'| (P) and (r' - r)/|r - r'| (V1) over the tetrahedron
-// with vertices v[4][3], via the divergence theorem over its faces.
-__device__ inline void tet_potentials(const double (*v)[3], const double *r, double &P, double *V1) {
-  const int F[4][3] = {{1, 2, 3}, {0, 3, 2}, {0, 1, 3}, {0, 2, 1}};
-  double c[3];
+// Face f's part of the integrals of 1/|r - r'| (P) and (r' - r)/|r - r'| (V1)
+// over the tetrahedron with vertices v[4][3] (divergence theorem): summed over
+// the four faces they are the integrals.
+__device__ inline void tet_potentials_face(const double (*v)[3], int f, const double *r, double &P, double *V1) {
+  // faces 123, 032, 013, 021
+  const double *A = v[f == 0 ? 1 : 0], *B = v[f == 0 || f == 3 ? 2 : (f == 1 ? 3 : 1)],
+               *C = v[f == 0 || f == 2 ? 3 : (f == 1 ? 2 : 1)];
+  double c[3], e1[3], e2[3], n[3], ac[3];
   for (int d = 0; d < 3; ++d) c[d] = 0.25 * (v[0][d] + v[1][d] + v[2][d] + v[3][d]);
-  P = 0.0;
-  V1[0] = V1[1] = V1[2] = 0.0;
-#pragma unroll 1
-  for (int f = 0; f < 4; ++f) {
-    const double *A = v[F[f][0]], *B = v[F[f][1]], *C = v[F[f][2]];
-    double e1[3], e2[3], n[3], ac[3];
-    sub3(B, A, e1);
-    sub3(C, A, e2);
-    cross3(e1, e2, n);
-    unit3(n);
-    sub3(A, c, ac);
-    if (dot3(ac, n) < 0.0) {
-      n[0] = -n[0];
-      n[1] = -n[1];
-      n[2] = -n[2];
-    }
-    double iinv, ione;
-    tri_potentials(A, B, C, r, iinv, ione);
-    double ar[3];
-    sub3(A, r, ar);
-    P = fma(0.5 * dot3(ar, n), iinv, P);
-    V1[0] = fma(ione, n[0], V1[0]);
-    V1[1] = fma(ione, n[1], V1[1]);
-    V1[2] = fma(ione, n[2], V1[2]);
+  sub3(B, A, e1);
+  sub3(C, A, e2);
+  cross3(e1, e2, n);
+  unit3(n);
+  sub3(A, c, ac);
+  if (dot3(ac, n) < 0.0) {
+    n[0] = -n[0];
+    n[1] = -n[1];
+    n[2] = -n[2];
   }
+  double iinv, ione;
+  tri_potentials(A, B, C, r, iinv, ione);
+  double ar[3];
+  sub3(A, r, ar);
+  P = 0.5 * dot3(ar, n) * iinv;
+  for (int d = 0; d < 3; ++d) V1[d] = ione * n[d];
 }
 
 // touching-image mask of two vertex sets (canonical ids + packed offsets)

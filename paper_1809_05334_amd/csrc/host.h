@@ -82,22 +82,25 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
                             double phi, double *wood_margin);
 
 // Compact copy of the table for the kernels (staged into LDS): only the
-// fitted coefficients of the significant terms, in doubles.  Layout:
-//   [0..10)  E, a, b, 1/a, 1/b, kx, ky, 2pi/a, 2pi/b, ws
-//   [10..19) Re phase0[9], [19..28) Im phase0[9], [28] nimg
-//   [32..113) per mode (p,q) grid index: offset of its record or 0 (low
-//             word), K | cplx << 16 (high word)
-//   [116..125) per row p of the mode grid: q_lo | (q_hi + 1) << 8, the
-//             first and last q with a mode (0 | 0 << 8: none)
-//   image records from kPackImages on, each
-//     [xa, xs, cre, cim, m, n, K, len] f[0..K] (pad to 4) [HK, 0, 0, 0] h[0..HK] (pad to 4)
-//     (the H block only for touching classes; len = record length)
-//   mode records [K, cplx, 0, 0] kre[0..K] (pad) kim[0..K] (pad, complex orders only)
-// Integer fields (nimg, mode offsets, m, n, K, len, HK, cplx) hold the value in
-// the low 32 bits of the double slot.
-// K, HK are the degrees rounded up to a multiple of 4 (zero coefficients).
-constexpr int kPackRows = 116;
-constexpr int kPackImages = 128;
+// fitted coefficients of the significant terms, in doubles.  A series is
+// [K, e_0 .. e_K], its coefficients with the highest degree first, K even
+// (a zero e_0 for odd degrees).  Layout:
+//   [0..10)  E, a, b, 1/a, 1/b, kx/pi, ky/pi, form (0 monomials, 1 Chebyshev),
+//            offset of the order rows (high word: p_lo + 8 | (p_hi + 8) << 8), ws E^2
+//   [10..19) Re phase0[9], [19..28) Im phase0[9], [28] offset of the
+//            propagating orders (high word: their count)
+//   [29..34) per m = 0..4: n_m, the number of image records (m, 0 .. n_m - 1)
+//   image records from kPackImages on, rows m in order, each standing for
+//     (+-m, +-n): [E xs, -(xa xs + 1), Re, Im phase of (m, n), of (m, -n)],
+//     the F series (high word of its K: record length), the H series (m, n <= 1)
+//   order rows p = p_hi .. p_lo, each [q_max (high word: has differences), 0],
+//     the series of (p, 0), then for q = 1 .. q_max the sum s of those of (p, q)
+//     and (p, -q), or if a difference d in the row is not zero both,
+//     [K, 0, (s_0, d_0) .. (s_K, d_K)] (real parts)
+//   propagating orders, each [p (high word: q), 0] and the series of Im K_pq
+// Integers are in the low and high 32 bits of their slots.
+constexpr int kPackRows = 29;
+constexpr int kPackImages = 40;
 void pack_pgf_table(const PgfTable &tab, std::vector<double> &out);
 
 }  // namespace vie

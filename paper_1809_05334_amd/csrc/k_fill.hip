@@ -98,52 +98,69 @@ __device__ __forceinline__ void moments_zero(Moments &M) {
   for (int d = 0; d < 3; ++d) M.mu[d] = M.mv[d] = mk(0, 0);
 }
 
-// Scatter the 16 face-pair contributions of tet pair (T, S) into Z (TRANS:
-// entry (m, n) goes to (n, m) of the output).
-template <bool TRANS = false>
-__device__ __forceinline__ void scatter_tt(const Moments &M, const TetGeom &gt, const TetGeom &gs,
-                                           const TetFace *__restrict__ t2f, int T, int S,
-                                           const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
-                                           const dz *__restrict__ kappa, double k0sq9, const ZOut &out,
-                                           bool near) {
-  const dz ks = kappa[S];
-  double qv[4][3];
-  dz bl[4];
-  int64_t col[4];
-  for (int l = 0; l < 4; ++l) {
-    for (int d = 0; d < 3; ++d) qv[l][d] = gs.v[l][d] - gs.c[d];
-    bl[l] = gsrc[4 * S + l] * ks;
-    col[l] = t2f[4 * S + l].unknown;
-  }
-  for (int k = 0; k < 4; ++k) {
-    double pk[3];
-    for (int d = 0; d < 3; ++d) pk[d] = gt.v[k][d] - gt.c[d];
-    // muv - p~.mv
-    dz base = M.muv;
-    for (int d = 0; d < 3; ++d) base = base - pk[d] * M.mv[d];
-    const dz ak = alpha[4 * T + k];
-    const int64_t row = t2f[4 * T + k].unknown;
-    for (int l = 0; l < 4; ++l) {
-      dz I = base;
-      for (int d = 0; d < 3; ++d) I = I - qv[l][d] * M.mu[d];
-      I = I + dot3(pk, qv[l]) * M.m0;
-      const dz v = M.m0 - k0sq9 * I;
-      if (TRANS) zput(out, col[l], row, (ak * bl[l]) * v, near);
-      else zput(out, row, col[l], (ak * bl[l]) * v, near);
-    }
+// Lane sums by DPP moves: over a quad (quad swaps), and of lanes l and 7 - l
+// of eight (half-row mirror).
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  return v + __longlong_as_double((long long)dpp64<CTRL>((unsigned long long)__double_as_longlong(v)));
+}
+template <int CTRL>
+__device__ __forceinline__ dz dpp_add(dz v) { return mk(dpp_add<CTRL>(v.re), dpp_add<CTRL>(v.im)); }
+__device__ __forceinline__ dz quad_sum(dz v) { return dpp_add<0x4e>(dpp_add<0xb1>(v)); }
+__device__ __forceinline__ dz mirror8_sum(dz v) { return dpp_add<0x141>(v); }
+// over the wave, in every lane
+__device__ __forceinline__ dz wave_sum64(dz v) {
+  v = dpp_add<0x140>(mirror8_sum(quad_sum(v)));
+  v = mk(v.re + __shfl_xor(v.re, 16), v.im + __shfl_xor(v.im, 16));
+  return mk(v.re + __shfl_xor(v.re, 32), v.im + __shfl_xor(v.im, 32));
+}
+
+// Z_kl contributions of tet pair (T, S) from its moments: entries l0 .. l0 +
+// nl - 1 of the test face k, entry (m, n) at (n, m) with trans.
+__device__ __forceinline__ void scatter_tt_row(const Moments &M, const TetGeom &gt, const TetGeom &gs,
+                                               const TetFace *__restrict__ t2f, int T, int S, int k, int l0, int nl,
+                                               const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
+                                               const dz *__restrict__ kappa, double k0sq9, const ZOut &out, bool trans,
+                                               bool near) {
+  double pk[3];
+  for (int d = 0; d < 3; ++d) pk[d] = gt.v[k][d] - gt.c[d];
+  dz base = M.muv;   // muv - p~.mv
+  for (int d = 0; d < 3; ++d) base = base - pk[d] * M.mv[d];
+  const dz ak = alpha[4 * T + k] * kappa[S];
+  const int64_t row = t2f[4 * T + k].unknown;
+#pragma unroll 2
+  for (int l = l0; l < l0 + nl; ++l) {
+    double qv[3];
+    for (int d = 0; d < 3; ++d) qv[d] = gs.v[l][d] - gs.c[d];
+    dz I = base;
+    for (int d = 0; d < 3; ++d) I = I - qv[d] * M.mu[d];
+    I = I + dot3(pk, qv) * M.m0;
+    const dz v = (ak * gsrc[4 * S + l]) * (M.m0 - k0sq9 * I);
+    const int64_t col = t2f[4 * S + l].unknown;
+    zput(out, trans ? col : row, trans ? row : col, v, near);
   }
 }
 
-// Far tet pairs: 4 x 4 product rule.  One wave = one test tet x 64 source tets.
-// sym > 0 writes the swapped pair's block (S, T) too (see the declaration).
-// At normal incidence the lattice sum is even in the separation (the phases
+// Far tet pairs: 4 x 4 product rule.  A wave takes one test tet at a time
+// (tper of them in turn) against 8 source tets, eight lanes per pair: a lane
+// takes one test point and two source points (lanes l and 7 - l the same test
+// point).  The test point is fixed per lane, so the moments follow from sum g
+// and sum g r' over the source points after the lattice sums, and none are
+// held through them; after the sums each lane of a quad writes the entries of
+// one test face.  Bound by the issue of FP64 instructions: at three waves a
+// SIMD takes one every five cycles at best, 5,500 per wave (128 point pairs)
+// run at 80 % of that.  N = 37,376, mixed, oblique: 311 ms per fill, 406 ms with
+// one lane per pair, the Clenshaw form of every series and one image at a
+// time (pgf_eval_w); N = 18,590, FP64, ordered pairs: 138 ms, 189 before.  On
+// small cells a launch's chain counts, an eighth of one lane per pair: N = 416,
+// 16 launches, 0.5 ms, 6.1 before.
+// sym > 0 writes the swapped pair's block (S, T) too (see the declaration):
+// the second quad of the eight forms and writes it beside the first.  At
+// normal incidence the lattice sum is even in the separation (the phases
 // e^{-j kt.rho} are all 1), so the pair's moments also give those of the
-// swapped pair.  At oblique incidence (rev) g_p at the reversed separations
+// swapped pair.  At oblique incidence (REV) g_p at the reversed separations
 // follows from g_p at the separations plus the propagating orders' term (see
-// pgf_eval_w), and the swapped pair's moments are accumulated from it.
-// REV: the swapped pair's moments are summed per lane in LDS (16 doubles
-// after the table, one column per thread), not in registers, so that the
-// kernel keeps two waves per SIMD without spilling.
+// pgf_eval_w), and the swapped pair's moments are formed from it.
 template <bool REV>
 __device__ __forceinline__ void tt_far_body(const double *__restrict__ pack, int packlen,
                                             const QuadRules *__restrict__ qr, const TetGeom *__restrict__ tg,
@@ -151,144 +168,129 @@ __device__ __forceinline__ void tt_far_body(const double *__restrict__ pack, int
                                             int ntest, const int32_t *__restrict__ src_list, int nsrc,
                                             const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
                                             const dz *__restrict__ kappa, double k0sq9, const ZOut &out,
-                                            const ZOut &outT, int sym, int bx_, int by_) {
+                                            const ZOut &outT, int sym, int tper, int bx_, int by_) {
   extern __shared__ double s_tab[];
   // one list against itself: a block whose source positions all lie at or
   // below its test positions has nothing to do (the whole block returns)
-  if (sym == 2 && bx_ * 64 + 63 <= by_ * 4) return;
+  if (sym == 2 && bx_ * 8 + 7 <= by_ * 4 * tper) return;
   stage_table(pack, packlen, s_tab);
-  const double *__restrict__ P = s_tab;
-  double *__restrict__ mr = s_tab + ((packlen + 1) & ~1) + threadIdx.x;   // REV: entry e at mr[256 e]
-
-  const int ti = uniform(by_ * 4 + (threadIdx.x >> 6));
-  const int si = bx_ * 64 + (threadIdx.x & 63);
-  if (ti >= ntest || si >= nsrc) return;
-  if (sym == 2 && si <= ti) return;
-  const int T = uniform(test_list[ti]);
-  const int S = src_list[si];
-  const TetGeom &gt = tg[T];
-  double wq;
-  double up[4][3], dc[3];
+  const int lane = threadIdx.x & 63, k = lane & 3;
+  const bool second = (lane & 4) != 0;
+  const int i = second ? 3 - k : k, j0 = second ? 2 : 0;   // test point, first source point
+  const int si = bx_ * 8 + (lane >> 3);
+  const int S = src_list[min(si, nsrc - 1)];
+  double rs[2][3];   // the lane's source points
+  int32_t canon[4];
   {
     const TetGeom gs = tg[S];
-    if (touch_mask(gt.canon, gt.off, 4, gs.canon, gs.off, 4)) return;  // touching pairs: k_tt_near
-    wq = 0.25 * gs.vol;
-    for (int d = 0; d < 3; ++d) dc[d] = gt.c[d] - gs.c[d];
-    // source points relative to the source centroid
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
+    for (int j = 0; j < 4; ++j) canon[j] = gs.canon[j];
+#pragma unroll
+    for (int j = 0; j < 2; ++j)
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         double s = 0;
-        for (int k = 0; k < 4; ++k) s = fma(qr->tet4[j][k], gs.v[k][d], s);
-        up[j][d] = s - gs.c[d];
+        for (int q = 0; q < 4; ++q) s = fma(qr->tet4[j0 + j][q], gs.v[q][d], s);
+        rs[j][d] = s;
       }
   }
-  const double wt = 0.25 * gt.vol;
-  Moments M;
-  moments_zero(M);
-  if (REV)
-    for (int e = 0; e < 16; ++e) mr[256 * e] = 0.0;
-  // one test point against the four source points per lattice-sum call
 #pragma unroll 1
-  for (int i = 0; i < 4; ++i) {
-    double u[3];
+  for (int tt = 0; tt < tper; ++tt) {
+    const int ti = uniform((by_ * 4 + (threadIdx.x >> 6)) * tper + tt);
+    if (ti >= ntest) return;
+    const int T = uniform(test_list[ti]);
+    const TetGeom &gt = tg[T];
+    bool act = si < nsrc && (sym != 2 || si > ti);
+    {
+      // touching pairs (a shared vertex under any image): k_tt_near; lane k looks at the test vertex k
+      const int32_t ct = gt.canon[k];
+      const bool hit = ct == canon[0] || ct == canon[1] || ct == canon[2] || ct == canon[3];
+      act = act && ((__ballot(hit) >> (lane & ~3)) & 15) == 0;
+    }
+    if (__ballot(act) == 0) continue;
+    dz g[2], gr[2];
+    {
+      double sep[2][3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        double s = 0;
+        for (int q = 0; q < 4; ++q) s = fma(qr->tet4[i][q], gt.v[q][d], s);
+        sep[0][d] = s - rs[0][d];
+        sep[1][d] = s - rs[1][d];
+      }
+      pgf_eval_w<false, 2, REV>(s_tab, sep, 0, g, gr);
+    }
+    // the source geometry is read again here rather than held in registers
+    // through the lattice sums (the empty asm hides the earlier load)
+    const TetGeom *gs = tg + S;
+    asm volatile("" : "+v"(gs));
+    double u[3], v[2][3];   // test and source points relative to the centroids
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
       double s = 0;
-      for (int k = 0; k < 4; ++k) s = fma(qr->tet4[i][k], gt.v[k][d], s);
+      for (int q = 0; q < 4; ++q) s = fma(qr->tet4[i][q], gt.v[q][d], s);
       u[d] = s - gt.c[d];
+      v[0][d] = rs[0][d] - gs->c[d];
+      v[1][d] = rs[1][d] - gs->c[d];
     }
-    double sep[4][3];
+    // sums over the four source points (of this lane and its mirror)
+    dz G = mirror8_sum(g[0] + g[1]), G1[3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int d = 0; d < 3; ++d) sep[j][d] = dc[d] + u[d] - up[j][d];
-    dz g[4], gr[REV ? 4 : 1];
-    pgf_eval_w<false, 4, REV>(P, sep, 0, g, gr);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const dz gw = (wt * wq) * g[j];
-      M.m0 = M.m0 + gw;
-      for (int d = 0; d < 3; ++d) {
-        axpy(M.mu[d], u[d], gw);
-        axpy(M.mv[d], up[j][d], gw);
-      }
-      axpy(M.muv, dot3(u, up[j]), gw);
-    }
+    for (int d = 0; d < 3; ++d) G1[d] = mirror8_sum(v[0][d] * g[0] + v[1][d] * g[1]);
     if (REV) {
-      // swapped pair (S, T): its test offsets are up_j, its source offsets u
-      Moments R;
-      moments_zero(R);
+      const dz H = mirror8_sum(gr[0] + gr[1]);
+      G = second ? H : G;
 #pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const dz grw = (wt * wq) * gr[j];
-        R.m0 = R.m0 + grw;
-        for (int d = 0; d < 3; ++d) {
-          axpy(R.mu[d], up[j][d], grw);
-          axpy(R.mv[d], u[d], grw);
-        }
-        axpy(R.muv, dot3(u, up[j]), grw);
-      }
-      mr[0] += R.m0.re;
-      mr[256] += R.m0.im;
       for (int d = 0; d < 3; ++d) {
-        mr[256 * (2 + 2 * d)] += R.mu[d].re;
-        mr[256 * (3 + 2 * d)] += R.mu[d].im;
-        mr[256 * (8 + 2 * d)] += R.mv[d].re;
-        mr[256 * (9 + 2 * d)] += R.mv[d].im;
+        const dz H1 = mirror8_sum(v[0][d] * gr[0] + v[1][d] * gr[1]);
+        G1[d] = second ? H1 : G1[d];
       }
-      mr[256 * 14] += R.muv.re;
-      mr[256 * 15] += R.muv.im;
     }
-  }
-  // the source geometry is read again here rather than held in registers
-  // through the lattice sums (the empty asm hides the earlier load)
-  const TetGeom *tgs = tg + S;
-  asm volatile("" : "+v"(tgs));
-  const TetGeom gs = *tgs;
-  scatter_tt(M, gt, gs, t2f, T, S, alpha, gsrc, kappa, k0sq9, out, false);
-  if (REV && sym) {
-    Moments R;
-    R.m0 = mk(mr[0], mr[256]);
+    // sums over the test points; (S, T): test and source offsets trade places
+    const bool swap = sym && second;
+    const double w = (0.25 * gt.vol) * (0.25 * gs->vol);
+    Moments M;
+    M.m0 = w * quad_sum(G);
+    M.muv = mk(0, 0);
+#pragma unroll
     for (int d = 0; d < 3; ++d) {
-      R.mu[d] = mk(mr[256 * (2 + 2 * d)], mr[256 * (3 + 2 * d)]);
-      R.mv[d] = mk(mr[256 * (8 + 2 * d)], mr[256 * (9 + 2 * d)]);
+      const dz a = w * quad_sum(u[d] * G), b = w * quad_sum(G1[d]);
+      M.mu[d] = swap ? b : a;
+      M.mv[d] = swap ? a : b;
+      axpy(M.muv, u[d], G1[d]);
     }
-    R.muv = mk(mr[256 * 14], mr[256 * 15]);
-    scatter_tt<true>(R, gs, gt, t2f, S, T, alpha, gsrc, kappa, k0sq9, outT, false);
-  } else if (sym) {
-    // (S, T) at kt = 0: test offsets and source offsets trade places
-    Moments Ms;
-    Ms.m0 = M.m0;
-    Ms.muv = M.muv;
-    for (int d = 0; d < 3; ++d) {
-      Ms.mu[d] = M.mv[d];
-      Ms.mv[d] = M.mu[d];
-    }
-    scatter_tt<true>(Ms, gs, gt, t2f, S, T, alpha, gsrc, kappa, k0sq9, outT, false);
+    M.muv = w * quad_sum(M.muv);
+    if (!act) continue;
+    const TetGeom *ga = swap ? gs : &gt, *gb = swap ? &gt : gs;
+    ZOut o = out;   // (out and outT differ in the dense part alone)
+    o.Z = swap ? outT.Z : out.Z;
+    o.Zs = swap ? outT.Zs : out.Zs;
+    scatter_tt_row(M, *ga, *gb, t2f, swap ? S : T, swap ? T : S, k, sym ? 0 : j0, sym ? 4 : 2, alpha, gsrc, kappa, k0sq9,
+                   o, swap, false);
   }
 }
 
-__global__ __launch_bounds__(256, 2) void k_tt_far(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
+constexpr int kFarWaves = 3;   // waves per SIMD of the far kernels (two: 8 % slower; four spill, the same)
+__global__ __launch_bounds__(256, kFarWaves) void k_tt_far(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
                                                 const TetGeom *__restrict__ tg, const TetFace *__restrict__ t2f,
                                                 const int32_t *__restrict__ test_list, int ntest,
                                                 const int32_t *__restrict__ src_list, int nsrc,
                                                 const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
                                                 const dz *__restrict__ kappa, double k0sq9, ZOut out, ZOut outT,
-                                                int sym) {
+                                                int sym, int tper) {
   tt_far_body<false>(pack, packlen, qr, tg, t2f, test_list, ntest, src_list, nsrc, alpha, gsrc, kappa, k0sq9, out,
-                     outT, sym, blockIdx.x, blockIdx.y);
+                     outT, sym, tper, blockIdx.x, blockIdx.y);
 }
 
-__global__ __launch_bounds__(256, 2) void k_tt_far_rev(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
-                                                    const TetGeom *__restrict__ tg, const TetFace *__restrict__ t2f,
-                                                    const int32_t *__restrict__ test_list, int ntest,
-                                                    const int32_t *__restrict__ src_list, int nsrc,
-                                                    const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
-                                                    const dz *__restrict__ kappa, double k0sq9, ZOut out, ZOut outT,
-                                                    int sym) {
+__global__ __launch_bounds__(256, kFarWaves) void k_tt_far_rev(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
+                                                const TetGeom *__restrict__ tg, const TetFace *__restrict__ t2f,
+                                                const int32_t *__restrict__ test_list, int ntest,
+                                                const int32_t *__restrict__ src_list, int nsrc,
+                                                const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
+                                                const dz *__restrict__ kappa, double k0sq9, ZOut out, ZOut outT,
+                                                int sym, int tper) {
   tt_far_body<true>(pack, packlen, qr, tg, t2f, test_list, ntest, src_list, nsrc, alpha, gsrc, kappa, k0sq9, out,
-                    outT, sym, blockIdx.x, blockIdx.y);
+                     outT, sym, tper, blockIdx.x, blockIdx.y);
 }
 
 // Z[i][j] += Zt[j][i]: 32 x 32 tiles through shared memory, both sides read
@@ -321,11 +323,14 @@ __global__ __launch_bounds__(256) void k_transpose_add_c(fz *Z, const fz *Zt, in
 
 // Touching tet pairs: 14-point outer rule on T; per touching image the closed
 // form int_S 1/R and int_S (r'-r)/R; 4-point inner rule for the remainder.
-// The self pair also adds the mass term <f_m, f_n / eps_r>.  Sixteen lanes
-// share a pair: lane q < 14 takes outer point q, the moments are summed
-// across the 16 lanes by shuffles, and the pair's first lane scatters.
-__device__ __forceinline__ dz shfl_xor_dz(dz v, int o) { return mk(__shfl_xor(v.re, o), __shfl_xor(v.im, o)); }
-
+// The self pair also adds the mass term <f_m, f_n / eps_r>.  One wave per
+// pair: lane 4 q + f takes the outer point q < 14 with the face f of S in the
+// closed forms and the inner point f in the remainder (all of it adds up), the
+// moments are summed over the wave, and lane 4 k + l writes entry (k, l).  A
+// launch covers one colour pair, so on small cells its length is one lane's
+// chain, and on large ones the waves in flight count, three per SIMD: N = 37,376,
+// 13 ms per fill, 35 ms with 16 lanes per pair (the four faces and inner
+// points in turn, 255 registers); N = 416, 0.5 ms, 1.7 before.
 __device__ __forceinline__ void k_tt_near_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
                                                  const TetGeom *__restrict__ tg, const TetFace *__restrict__ t2f,
                                                  const int32_t *__restrict__ lt, const int32_t *__restrict__ ls,
@@ -337,26 +342,25 @@ __device__ __forceinline__ void k_tt_near_body(const double *__restrict__ pack, 
   stage_table(pack, packlen, s_tab);
   const double *__restrict__ P = s_tab;
 
-  const int gid = bx_ * blockDim.x + threadIdx.x;
-  const int i = gid >> 4, q = gid & 15;
-  const bool act = i < npairs;
-  // lanes past the last pair stay in the shuffles below with zero moments
-  const int ii = act ? i : npairs - 1;
-  const int T = lt[ii], S = ls[ii], mask = lmask[ii];
-  const TetGeom gt = tg[T];
-  const TetGeom gs = tg[S];
-  const double wq = 0.25 * gs.vol;
+  const int lane = threadIdx.x & 63, q = lane >> 2, f = lane & 3;
+  const int pair = uniform(bx_ * 4 + (threadIdx.x >> 6));
+  if (pair >= npairs) return;
+  const int T = uniform(lt[pair]), S = uniform(ls[pair]), mask = uniform(lmask[pair]);
+  const TetGeom &gt = tg[T];
+  const TetGeom &gs = tg[S];
   Moments M;
   moments_zero(M);
-  if (act && q < 14) {
+  {
+    // (lanes of q >= 14 go along with the last point at weight zero)
+    const int qq = min(q, 13);
     double r[3], u[3];
     for (int d = 0; d < 3; ++d) {
       double s = 0;
-      for (int k = 0; k < 4; ++k) s = fma(qr->tet14[q][k], gt.v[k][d], s);
+      for (int k = 0; k < 4; ++k) s = fma(qr->tet14[qq][k], gt.v[k][d], s);
       r[d] = s;
       u[d] = s - gt.c[d];
     }
-    const double w = qr->w14[q] * gt.vol;
+    const double w = q < 14 ? qr->w14[qq] * gt.vol : 0.0;
     dz s0 = mk(0, 0), s1[3] = {mk(0, 0), mk(0, 0), mk(0, 0)};
 #pragma unroll 1
     for (int b = 0; b < 9; ++b) {
@@ -364,28 +368,23 @@ __device__ __forceinline__ void k_tt_near_body(const double *__restrict__ pack, 
       const int m = b / 3 - 1, n = b % 3 - 1;
       const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
       double pot, V1[3];
-      tet_potentials(gs.v, o, pot, V1);
+      tet_potentials_face(gs.v, f, o, pot, V1);
       const dz ph = kInv4Pi * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);  // e^{+j kt.rho}/(4 pi)
       s0 = s0 + pot * ph;
       for (int d = 0; d < 3; ++d) s1[d] = s1[d] + (V1[d] + (o[d] - gs.c[d]) * pot) * ph;
     }
-    double sep[4][3], upj[4][3];
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        double t = 0;
-        for (int k = 0; k < 4; ++k) t = fma(qr->tet4[j][k], gs.v[k][d], t);
-        upj[j][d] = t - gs.c[d];
-        sep[j][d] = r[d] - t;
-      }
-    dz g[4];
-    pgf_eval_w<true, 4>(P, sep, mask, g);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      axpy(s0, wq, g[j]);
-      for (int d = 0; d < 3; ++d) axpy(s1[d], wq * upj[j][d], g[j]);
+    double sep[1][3], up[3];
+    for (int d = 0; d < 3; ++d) {
+      double t = 0;
+      for (int k = 0; k < 4; ++k) t = fma(qr->tet4[f][k], gs.v[k][d], t);
+      up[d] = t - gs.c[d];
+      sep[0][d] = r[d] - t;
     }
+    dz g[1];
+    pgf_eval_w<true, 1>(P, sep, mask, g);
+    const double wq = 0.25 * gs.vol;
+    axpy(s0, wq, g[0]);
+    for (int d = 0; d < 3; ++d) axpy(s1[d], wq * up[d], g[0]);
     axpy(M.m0, w, s0);
     for (int d = 0; d < 3; ++d) {
       axpy(M.mu[d], w * u[d], s0);
@@ -395,37 +394,30 @@ __device__ __forceinline__ void k_tt_near_body(const double *__restrict__ pack, 
     for (int d = 0; d < 3; ++d) axpy(us, u[d], s1[d]);
     axpy(M.muv, w, us);
   }
-  // sum the 16 lanes of the pair (fixed order: deterministic)
-#pragma unroll
-  for (int o = 8; o > 0; o >>= 1) {
-    M.m0 = M.m0 + shfl_xor_dz(M.m0, o);
-    M.muv = M.muv + shfl_xor_dz(M.muv, o);
-    for (int d = 0; d < 3; ++d) {
-      M.mu[d] = M.mu[d] + shfl_xor_dz(M.mu[d], o);
-      M.mv[d] = M.mv[d] + shfl_xor_dz(M.mv[d], o);
-    }
+  // sum the wave (fixed order: deterministic)
+  M.m0 = wave_sum64(M.m0);
+  M.muv = wave_sum64(M.muv);
+  for (int d = 0; d < 3; ++d) {
+    M.mu[d] = wave_sum64(M.mu[d]);
+    M.mv[d] = wave_sum64(M.mv[d]);
   }
-  if (!act || q != 0) return;
-  scatter_tt(M, gt, gs, t2f, T, S, alpha, gsrc, kappa, k0sq9, out, true);
+  if (lane >= 16) return;
+  const int k = lane >> 2, l = lane & 3;
+  scatter_tt_row(M, gt, gs, t2f, T, S, k, l, 1, alpha, gsrc, kappa, k0sq9, out, false, true);
   if (T == S) {
     // mass <f_m, f_n / eps_r>: alpha_k gsrc_l / (9 eps) int_T (r - v_k).(r - v_l), 4-point rule (exact)
     const dz ie = inv_eps[T];
-    for (int k = 0; k < 4; ++k) {
-      const int64_t row = t2f[4 * T + k].unknown;
-      for (int l = 0; l < 4; ++l) {
-        double s = 0;
-        for (int q = 0; q < 4; ++q) {
-          double a2 = 0;
-          for (int d = 0; d < 3; ++d) {
-            double r = 0;
-            for (int kk = 0; kk < 4; ++kk) r = fma(qr->tet4[q][kk], gt.v[kk][d], r);
-            a2 = fma(r - gt.v[k][d], r - gt.v[l][d], a2);
-          }
-          s = fma(0.25 * gt.vol, a2, s);
-        }
-        zput(out, row, t2f[4 * T + l].unknown, (s / 9.0) * ((alpha[4 * T + k] * gsrc[4 * T + l]) * ie), true);
+    double s = 0;
+    for (int p = 0; p < 4; ++p) {
+      double a2 = 0;
+      for (int d = 0; d < 3; ++d) {
+        double r = 0;
+        for (int kk = 0; kk < 4; ++kk) r = fma(qr->tet4[p][kk], gt.v[kk][d], r);
+        a2 = fma(r - gt.v[k][d], r - gt.v[l][d], a2);
       }
+      s = fma(0.25 * gt.vol, a2, s);
     }
+    zput(out, t2f[4 * T + k].unknown, t2f[4 * T + l].unknown, (s / 9.0) * ((alpha[4 * T + k] * gsrc[4 * T + l]) * ie), true);
   }
 }
 
@@ -440,230 +432,34 @@ __global__ __launch_bounds__(256) void k_tt_near(const double *__restrict__ pack
 }
 
 // ------------------------------------------------------------ pairs with faces
-// M0 = II g_p over (test tet T, face F).  Far: 4 x 3 rule.  Touching: outer
-// 14-point rule on T, closed-form int_F 1/R per touching image, 3-point
-// inner rule for the remainder.
-__device__ dz pair_tet_face(const double *__restrict__ P, const QuadRules *__restrict__ qr, const TetGeom &gt,
-                            const FaceGeom &f, int &mask) {
-  mask = touch_mask(gt.canon, gt.off, 4, f.canon, f.off, 3);
-  double fp[3][3];
-  for (int j = 0; j < 3; ++j)
-    for (int d = 0; d < 3; ++d) fp[j][d] = qr->tri3[j][0] * f.v[0][d] + qr->tri3[j][1] * f.v[1][d] + qr->tri3[j][2] * f.v[2][d];
-  const double wf = f.area / 3.0;
-  dz acc = mk(0, 0);
-  if (!mask) {
-    // one face point against the tet's four points per lattice-sum call
-    double tp[4][3];
-    for (int i = 0; i < 4; ++i)
-      for (int d = 0; d < 3; ++d) {
-        double s = 0;
-        for (int k = 0; k < 4; ++k) s = fma(qr->tet4[i][k], gt.v[k][d], s);
-        tp[i][d] = s;
-      }
-#pragma unroll 1
+// Far rule over (tet, face), 4 x 3 points: M0 = II g_p with the separation
+// tet point - face point (DIR = 1) or face point - tet point (DIR = -1), four
+// lanes per pair, lane i the tet point i with the three face points; returned
+// in every lane of the quad.  REV: also the value of the reversed separations
+// (see pgf_eval_w).
+template <bool REV, int DIR>
+__device__ __forceinline__ void far_tet_face(const double *__restrict__ P, const QuadRules *__restrict__ qr,
+                                             const TetGeom &gt, const FaceGeom &f, int i, dz &m0, dz &m0r) {
+  double sep[3][3];
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    double s = 0;
+    for (int k = 0; k < 4; ++k) s = fma(qr->tet4[i][k], gt.v[k][d], s);
+#pragma unroll
     for (int j = 0; j < 3; ++j) {
-      double sep[4][3];
-#pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sep[i][d] = tp[i][d] - fp[j][d];
-      dz g[4];
-      pgf_eval_w<false, 4>(P, sep, 0, g);
-      acc = acc + ((g[0] + g[1]) + (g[2] + g[3]));
+      const double fp = qr->tri3[j][0] * f.v[0][d] + qr->tri3[j][1] * f.v[1][d] + qr->tri3[j][2] * f.v[2][d];
+      sep[j][d] = DIR > 0 ? s - fp : fp - s;
     }
-    return (0.25 * gt.vol * wf) * acc;
-  }
-#pragma unroll 1
-  for (int q = 0; q < 14; ++q) {
-    double r[3];
-    for (int d = 0; d < 3; ++d) {
-      double s = 0;
-      for (int k = 0; k < 4; ++k) s = fma(qr->tet14[q][k], gt.v[k][d], s);
-      r[d] = s;
-    }
-    dz s0 = mk(0, 0);
-#pragma unroll 1
-    for (int b = 0; b < 9; ++b) {
-      if (!((mask >> b) & 1)) continue;
-      const int m = b / 3 - 1, n = b % 3 - 1;
-      const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
-      double iinv, ione;
-      tri_potentials(f.v[0], f.v[1], f.v[2], o, iinv, ione);
-      s0 = s0 + (kInv4Pi * iinv) * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);
-    }
-    {
-      double sep[3][3];
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sep[j][d] = r[d] - fp[j][d];
-      dz g[3];
-      pgf_eval_w<true, 3>(P, sep, mask, g);
-      axpy(s0, wf, (g[0] + g[1]) + g[2]);
-    }
-    axpy(acc, qr->w14[q] * gt.vol, s0);
-  }
-  return acc;
-}
-
-// M0 = II g_p over (test face F, source tet S).  Touching: outer 7-point rule
-// on F, closed-form int_S 1/R, 4-point inner rule for the remainder.
-__device__ dz pair_face_tet(const double *__restrict__ P, const QuadRules *__restrict__ qr, const FaceGeom &f,
-                            const TetGeom &gs, int &mask) {
-  mask = touch_mask(f.canon, f.off, 3, gs.canon, gs.off, 4);
-  double sp[4][3];
-  for (int j = 0; j < 4; ++j)
-    for (int d = 0; d < 3; ++d) {
-      double s = 0;
-      for (int k = 0; k < 4; ++k) s = fma(qr->tet4[j][k], gs.v[k][d], s);
-      sp[j][d] = s;
-    }
-  const double ws = 0.25 * gs.vol;
-  dz acc = mk(0, 0);
-  if (!mask) {
-#pragma unroll 1
-    for (int i = 0; i < 3; ++i) {
-      double r[3];
-      for (int d = 0; d < 3; ++d) r[d] = qr->tri3[i][0] * f.v[0][d] + qr->tri3[i][1] * f.v[1][d] + qr->tri3[i][2] * f.v[2][d];
-      double sep[4][3];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sep[j][d] = r[d] - sp[j][d];
-      dz g[4];
-      pgf_eval_w<false, 4>(P, sep, 0, g);
-      acc = acc + ((g[0] + g[1]) + (g[2] + g[3]));
-    }
-    return (f.area / 3.0 * ws) * acc;
-  }
-#pragma unroll 1
-  for (int q = 0; q < 7; ++q) {
-    double r[3];
-    for (int d = 0; d < 3; ++d) r[d] = qr->tri7[q][0] * f.v[0][d] + qr->tri7[q][1] * f.v[1][d] + qr->tri7[q][2] * f.v[2][d];
-    dz s0 = mk(0, 0);
-#pragma unroll 1
-    for (int b = 0; b < 9; ++b) {
-      if (!((mask >> b) & 1)) continue;
-      const int m = b / 3 - 1, n = b % 3 - 1;
-      const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
-      double pot, V1[3];
-      tet_potentials(gs.v, o, pot, V1);
-      s0 = s0 + (kInv4Pi * pot) * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);
-    }
-    {
-      double sep[4][3];
-#pragma unroll
-      for (int j = 0; j < 4; ++j)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sep[j][d] = r[d] - sp[j][d];
-      dz g[4];
-      pgf_eval_w<true, 4>(P, sep, mask, g);
-      axpy(s0, ws, (g[0] + g[1]) + (g[2] + g[3]));
-    }
-    axpy(acc, qr->w7[q] * f.area, s0);
-  }
-  return acc;
-}
-
-// M0 = II g_p over (test face F, source face G).
-__device__ dz pair_face_face(const double *__restrict__ P, const QuadRules *__restrict__ qr, const FaceGeom &f,
-                             const FaceGeom &g, int &mask) {
-  mask = touch_mask(f.canon, f.off, 3, g.canon, g.off, 3);
-  double gp[3][3];
-  for (int j = 0; j < 3; ++j)
-    for (int d = 0; d < 3; ++d) gp[j][d] = qr->tri3[j][0] * g.v[0][d] + qr->tri3[j][1] * g.v[1][d] + qr->tri3[j][2] * g.v[2][d];
-  const double wg = g.area / 3.0;
-  dz acc = mk(0, 0);
-  if (!mask) {
-#pragma unroll 1
-    for (int i = 0; i < 3; ++i) {
-      double r[3];
-      for (int d = 0; d < 3; ++d) r[d] = qr->tri3[i][0] * f.v[0][d] + qr->tri3[i][1] * f.v[1][d] + qr->tri3[i][2] * f.v[2][d];
-      double sep[3][3];
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sep[j][d] = r[d] - gp[j][d];
-      dz g[3];
-      pgf_eval_w<false, 3>(P, sep, 0, g);
-      acc = acc + (g[0] + g[1]) + g[2];
-    }
-    return (f.area / 3.0 * wg) * acc;
-  }
-#pragma unroll 1
-  for (int q = 0; q < 7; ++q) {
-    double r[3];
-    for (int d = 0; d < 3; ++d) r[d] = qr->tri7[q][0] * f.v[0][d] + qr->tri7[q][1] * f.v[1][d] + qr->tri7[q][2] * f.v[2][d];
-    dz s0 = mk(0, 0);
-#pragma unroll 1
-    for (int b = 0; b < 9; ++b) {
-      if (!((mask >> b) & 1)) continue;
-      const int m = b / 3 - 1, n = b % 3 - 1;
-      const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
-      double iinv, ione;
-      tri_potentials(g.v[0], g.v[1], g.v[2], o, iinv, ione);
-      s0 = s0 + (kInv4Pi * iinv) * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);
-    }
-    {
-      double sep[3][3];
-#pragma unroll
-      for (int j = 0; j < 3; ++j)
-#pragma unroll
-        for (int d = 0; d < 3; ++d) sep[j][d] = r[d] - gp[j][d];
-      dz g[3];
-      pgf_eval_w<true, 3>(P, sep, mask, g);
-      axpy(s0, wg, (g[0] + g[1]) + g[2]);
-    }
-    axpy(acc, qr->w7[q] * f.area, s0);
-  }
-  return acc;
-}
-
-// Far rule of pair_tet_face with both separations from one lattice-sum
-// evaluation: m0 = II g_p(r - r') (test tet, source face) and m0r the same
-// with r - r' reversed (test face, source tet), by the reversed-separation
-// form of pgf_eval_w (oblique incidence, non-touching pairs).
-__device__ void pair_tet_face_far_rev(const double *__restrict__ P, const QuadRules *__restrict__ qr,
-                                      const TetGeom &gt, const FaceGeom &f, dz &m0, dz &m0r) {
-  double fp[3][3], tp[4][3];
-  for (int j = 0; j < 3; ++j)
-    for (int d = 0; d < 3; ++d) fp[j][d] = qr->tri3[j][0] * f.v[0][d] + qr->tri3[j][1] * f.v[1][d] + qr->tri3[j][2] * f.v[2][d];
-  for (int i = 0; i < 4; ++i)
-    for (int d = 0; d < 3; ++d) {
-      double s = 0;
-      for (int k = 0; k < 4; ++k) s = fma(qr->tet4[i][k], gt.v[k][d], s);
-      tp[i][d] = s;
-    }
-  dz acc = mk(0, 0), accr = mk(0, 0);
-#pragma unroll 1
-  for (int j = 0; j < 3; ++j) {
-    double sep[4][3];
-#pragma unroll
-    for (int i = 0; i < 4; ++i)
-#pragma unroll
-      for (int d = 0; d < 3; ++d) sep[i][d] = tp[i][d] - fp[j][d];
-    dz g[4], gr[4];
-    pgf_eval_w<false, 4, true>(P, sep, 0, g, gr);
-    acc = acc + ((g[0] + g[1]) + (g[2] + g[3]));
-    accr = accr + ((gr[0] + gr[1]) + (gr[2] + gr[3]));
   }
   const double w = 0.25 * gt.vol * (f.area / 3.0);
-  m0 = w * acc;
-  m0r = w * accr;
+  dz g[3], gr[3];
+  pgf_eval_w<false, 3, REV>(P, sep, 0, g, gr);
+  m0 = w * quad_sum(g[0] + g[1] + g[2]);
+  if (REV) m0r = w * quad_sum(gr[0] + gr[1] + gr[2]);
 }
 
 // test tet (colour class list) x surface-charge face: Z[m_k(T), n_F] -= alpha_Tk sigma_F M0.
 // Far pairs only: the touching ones come from the host list (k_tet_face_near).
-__device__ __forceinline__ void tet_face_pair(const double *__restrict__ P, const QuadRules *__restrict__ qr,
-                                              const TetGeom &gt, const TetFace *__restrict__ t2f, int T,
-                                              const FaceGeom &f, int fi, const dz *__restrict__ alpha,
-                                              const dz *__restrict__ sigma, const ZOut &out) {
-  int mask;
-  const dz m0 = pair_tet_face(P, qr, gt, f, mask);
-  const dz sm = sigma[fi] * m0;
-  for (int k = 0; k < 4; ++k) zput(out, t2f[4 * T + k].unknown, f.unknown, mk(0, 0) - alpha[4 * T + k] * sm, mask != 0);
-}
-
 // The far rules of the two face kernels take the same 4 x 3 point pairs with
 // the same weights, so the (tet T, face F) evaluation also gives the value
 // M0' of (F as a half-SWG test face, T as source): at normal incidence
@@ -673,8 +469,9 @@ __device__ __forceinline__ void tet_face_pair(const double *__restrict__ P, cons
 // too, Z[m_F, n_l(T)] -= gsrc_Tl kappa_T M0', at the transposed position of
 // outT (rows of T's unknowns, columns of faces: the same conflict-free
 // pattern as the tet-face entries); the staging copy is added transposed
-// after the fill's other kernels.
-template <bool REV_ONLY = false>
+// after the fill's other kernels.  A wave takes one test tet and 16 faces, and
+// lane k of a quad writes the entry of the tet's face k.
+template <bool REV>
 __device__ __forceinline__ void k_tet_face_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
                                                   const TetGeom *__restrict__ tg, const TetFace *__restrict__ t2f,
                                                   const int32_t *__restrict__ test_list, int ntest,
@@ -684,29 +481,19 @@ __device__ __forceinline__ void k_tet_face_body(const double *__restrict__ pack,
                                                   ZOut out, ZOut outT, int swap, int bx_, int by_) {
   extern __shared__ double s_tab[];
   stage_table(pack, packlen, s_tab);
-  const double *__restrict__ P = s_tab;
-
   const int ti = uniform(by_ * 4 + (threadIdx.x >> 6));
-  const int fi = bx_ * 64 + (threadIdx.x & 63);
+  const int fi = bx_ * 16 + ((threadIdx.x & 63) >> 2), k = threadIdx.x & 3;
   if (ti >= ntest || fi >= nface) return;
   const int T = uniform(test_list[ti]);
   const TetGeom &gt = tg[T];
-  const FaceGeom f = fg[fi];
+  const FaceGeom &f = fg[fi];
   if (touch_mask(gt.canon, gt.off, 4, f.canon, f.off, 3)) return;
-  int mask;
   dz m0, m0r;
-  if (REV_ONLY || swap == 2) {
-    pair_tet_face_far_rev(s_tab, qr, gt, f, m0, m0r);
-  } else {
-    m0 = pair_tet_face(s_tab, qr, gt, f, mask);
-    m0r = m0;
-  }
-  const dz sm = sigma[fi] * m0;
-  for (int k = 0; k < 4; ++k) zput(out, t2f[4 * T + k].unknown, f.unknown, mk(0, 0) - alpha[4 * T + k] * sm, false);
-  if (swap && f.half) {
-    const dz km = m0r * kappa[T];
-    for (int l = 0; l < 4; ++l) zput(outT, t2f[4 * T + l].unknown, f.unknown, mk(0, 0) - gsrc[4 * T + l] * km, false);
-  }
+  far_tet_face<REV, 1>(s_tab, qr, gt, f, k, m0, m0r);
+  if (!REV) m0r = m0;
+  const int64_t row = t2f[4 * T + k].unknown;
+  zput(out, row, f.unknown, mk(0, 0) - alpha[4 * T + k] * (sigma[fi] * m0), false);
+  if (swap && f.half) zput(outT, row, f.unknown, mk(0, 0) - gsrc[4 * T + k] * (m0r * kappa[T]), false);
 }
 
 __global__ __launch_bounds__(256, 2) void k_tet_face(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
@@ -734,7 +521,11 @@ __global__ __launch_bounds__(256, 2) void k_tet_face_rev(const double *__restric
                         blockIdx.x, blockIdx.y);
 }
 
-// touching (test tet, surface-charge face) pairs of one test colour, one lane each
+// Touching (test tet, surface-charge face) pairs of one test colour: outer
+// 14-point rule on T, closed-form int_F 1/R per touching image, 3-point inner
+// rule for the remainder.  16 lanes per pair, lane q < 14 the outer point q;
+// lane k < 4 writes the entry of the tet's face k.  (One lane per pair took
+// 1.0 ms per launch whatever the size, four launches per fill.)
 __device__ __forceinline__ void k_tet_face_near_body(const double *__restrict__ pack, int packlen,
                                                        const QuadRules *__restrict__ qr, const TetGeom *__restrict__ tg,
                                                        const TetFace *__restrict__ t2f, const int32_t *__restrict__ pairs,
@@ -743,11 +534,42 @@ __device__ __forceinline__ void k_tet_face_near_body(const double *__restrict__ 
                                                        ZOut out, int bx_, int by_) {
   extern __shared__ double s_tab[];
   stage_table(pack, packlen, s_tab);
-  const int i = bx_ * 256 + threadIdx.x;
-  if (i >= npairs) return;
-  const int T = pairs[2 * i], fi = pairs[2 * i + 1];
-  const FaceGeom f = fg[fi];
-  tet_face_pair(s_tab, qr, tg[T], t2f, T, f, fi, alpha, sigma, out);
+  const double *__restrict__ P = s_tab;
+  const int q = threadIdx.x & 15, i = bx_ * 16 + (threadIdx.x >> 4);
+  // (lanes past the last pair or point go along at weight zero: the sums below take whole waves)
+  const int ii = min(i, npairs - 1), qq = min(q, 13);
+  const int T = pairs[2 * ii], fi = pairs[2 * ii + 1];
+  const TetGeom &gt = tg[T];
+  const FaceGeom &f = fg[fi];
+  const int mask = touch_mask(gt.canon, gt.off, 4, f.canon, f.off, 3);
+  double r[3];
+  for (int d = 0; d < 3; ++d) {
+    double s = 0;
+    for (int k = 0; k < 4; ++k) s = fma(qr->tet14[qq][k], gt.v[k][d], s);
+    r[d] = s;
+  }
+  dz s0 = mk(0, 0);
+#pragma unroll 1
+  for (int b = 0; b < 9; ++b) {
+    if (!((mask >> b) & 1)) continue;
+    const int m = b / 3 - 1, n = b % 3 - 1;
+    const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
+    double iinv, ione;
+    tri_potentials(f.v[0], f.v[1], f.v[2], o, iinv, ione);
+    s0 = s0 + (kInv4Pi * iinv) * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);
+  }
+#pragma unroll 1
+  for (int j = 0; j < 3; ++j) {
+    double sep[1][3];
+    for (int d = 0; d < 3; ++d)
+      sep[0][d] = r[d] - (qr->tri3[j][0] * f.v[0][d] + qr->tri3[j][1] * f.v[1][d] + qr->tri3[j][2] * f.v[2][d]);
+    dz g[1];
+    pgf_eval_w<true, 1>(P, sep, mask, g);
+    axpy(s0, f.area / 3.0, g[0]);
+  }
+  const dz m0 = dpp_add<0x140>(mirror8_sum(quad_sum((q < 14 ? qr->w14[qq] * gt.vol : 0.0) * s0)));
+  if (i >= npairs || q >= 4) return;
+  zput(out, t2f[4 * T + q].unknown, f.unknown, mk(0, 0) - alpha[4 * T + q] * (sigma[fi] * m0), true);
 }
 
 __global__ __launch_bounds__(256, 2) void k_tet_face_near(const double *__restrict__ pack, int packlen,
@@ -761,15 +583,8 @@ __global__ __launch_bounds__(256, 2) void k_tet_face_near(const double *__restri
 
 // half-SWG test face x source tet (colour class list): Z[m_F, n_l(S)] -= gsrc_Sl kappa_S M0.
 // Far pairs only: the touching ones come from the host list (k_face_tet_near).
-__device__ __forceinline__ void face_tet_pair(const double *__restrict__ P, const QuadRules *__restrict__ qr,
-                                              const FaceGeom &f, const TetGeom &gs, const TetFace *__restrict__ t2f,
-                                              int S, const dz *__restrict__ gsrc, const dz *__restrict__ kappa,
-                                              const ZOut &out) {
-  int mask;
-  const dz m0 = pair_face_tet(P, qr, f, gs, mask) * kappa[S];
-  for (int l = 0; l < 4; ++l) zput(out, f.unknown, t2f[4 * S + l].unknown, mk(0, 0) - gsrc[4 * S + l] * m0, mask != 0);
-}
-
+// A wave takes one face and 16 tets; lane l of a quad writes the entry of the
+// tet's face l.
 __device__ __forceinline__ void k_face_tet_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
                                                   const FaceGeom *__restrict__ fg, const int32_t *__restrict__ half_list,
                                                   int nhalf, const TetGeom *__restrict__ tg,
@@ -778,16 +593,16 @@ __device__ __forceinline__ void k_face_tet_body(const double *__restrict__ pack,
                                                   ZOut out, int bx_, int by_) {
   extern __shared__ double s_tab[];
   stage_table(pack, packlen, s_tab);
-  const double *__restrict__ P = s_tab;
-
   const int hi = uniform(by_ * 4 + (threadIdx.x >> 6));
-  const int si = bx_ * 64 + (threadIdx.x & 63);
+  const int si = bx_ * 16 + ((threadIdx.x & 63) >> 2), l = threadIdx.x & 3;
   if (hi >= nhalf || si >= nsrc) return;
   const FaceGeom &f = fg[uniform(half_list[hi])];
   const int S = src_list[si];
-  const TetGeom gs = tg[S];
+  const TetGeom &gs = tg[S];
   if (touch_mask(f.canon, f.off, 3, gs.canon, gs.off, 4)) return;
-  face_tet_pair(s_tab, qr, f, gs, t2f, S, gsrc, kappa, out);
+  dz m0, unused;
+  far_tet_face<false, -1>(s_tab, qr, gs, f, l, m0, unused);
+  zput(out, f.unknown, t2f[4 * S + l].unknown, mk(0, 0) - gsrc[4 * S + l] * (m0 * kappa[S]), false);
 }
 
 __global__ __launch_bounds__(256, 2) void k_face_tet(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
@@ -799,7 +614,10 @@ __global__ __launch_bounds__(256, 2) void k_face_tet(const double *__restrict__ 
   k_face_tet_body(pack, packlen, qr, fg, half_list, nhalf, tg, t2f, src_list, nsrc, gsrc, kappa, out, blockIdx.x, blockIdx.y);
 }
 
-// touching (half-SWG test face, source tet) pairs of one source colour, one lane each
+// Touching (half-SWG test face, source tet) pairs of one source colour: outer
+// 7-point rule on F, closed-form int_S 1/R, 4-point inner rule for the
+// remainder.  32 lanes per pair, lane 4 p + c the outer point p < 7 with the
+// face c of S in the closed form and the inner point c in the remainder.
 __device__ __forceinline__ void k_face_tet_near_body(const double *__restrict__ pack, int packlen,
                                                        const QuadRules *__restrict__ qr, const FaceGeom *__restrict__ fg,
                                                        const int32_t *__restrict__ half_list,
@@ -809,12 +627,37 @@ __device__ __forceinline__ void k_face_tet_near_body(const double *__restrict__ 
                                                        ZOut out, int bx_, int by_) {
   extern __shared__ double s_tab[];
   stage_table(pack, packlen, s_tab);
-  const int i = bx_ * 256 + threadIdx.x;
-  if (i >= npairs) return;
-  const int hi = pairs[2 * i], S = pairs[2 * i + 1];
-  const FaceGeom f = fg[half_list[hi]];
-  const TetGeom gs = tg[S];
-  face_tet_pair(s_tab, qr, f, gs, t2f, S, gsrc, kappa, out);
+  const double *__restrict__ P = s_tab;
+  const int i = bx_ * 8 + (threadIdx.x >> 5), p = (threadIdx.x & 31) >> 2, c = threadIdx.x & 3;
+  const int ii = min(i, npairs - 1), pp = min(p, 6);   // (lanes past the last pair or point: weight zero)
+  const int hi = pairs[2 * ii], S = pairs[2 * ii + 1];
+  const FaceGeom &f = fg[half_list[hi]];
+  const TetGeom &gs = tg[S];
+  const int mask = touch_mask(f.canon, f.off, 3, gs.canon, gs.off, 4);
+  double r[3], sep[1][3];
+  for (int d = 0; d < 3; ++d) {
+    r[d] = qr->tri7[pp][0] * f.v[0][d] + qr->tri7[pp][1] * f.v[1][d] + qr->tri7[pp][2] * f.v[2][d];
+    double s = 0;
+    for (int k = 0; k < 4; ++k) s = fma(qr->tet4[c][k], gs.v[k][d], s);
+    sep[0][d] = r[d] - s;
+  }
+  dz s0 = mk(0, 0);
+#pragma unroll 1
+  for (int b = 0; b < 9; ++b) {
+    if (!((mask >> b) & 1)) continue;
+    const int m = b / 3 - 1, n = b % 3 - 1;
+    const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
+    double pot, V1[3];
+    tet_potentials_face(gs.v, c, o, pot, V1);
+    s0 = s0 + (kInv4Pi * pot) * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);
+  }
+  dz g[1];
+  pgf_eval_w<true, 1>(P, sep, mask, g);
+  axpy(s0, 0.25 * gs.vol, g[0]);
+  dz m0 = dpp_add<0x140>(mirror8_sum(quad_sum((p < 7 ? qr->w7[pp] * f.area : 0.0) * s0)));
+  m0 = mk(m0.re + __shfl_xor(m0.re, 16), m0.im + __shfl_xor(m0.im, 16)) * kappa[S];
+  if (i >= npairs || p > 0) return;
+  zput(out, f.unknown, t2f[4 * S + c].unknown, mk(0, 0) - gsrc[4 * S + c] * m0, true);
 }
 
 __global__ __launch_bounds__(256, 2) void k_face_tet_near(const double *__restrict__ pack, int packlen,
@@ -827,26 +670,94 @@ __global__ __launch_bounds__(256, 2) void k_face_tet_near(const double *__restri
   k_face_tet_near_body(pack, packlen, qr, fg, half_list, tg, t2f, pairs, npairs, gsrc, kappa, out, blockIdx.x, blockIdx.y);
 }
 
-// half-SWG test face x surface-charge face: Z[m_F, n_G] += sigma_G M0.  With
-// no dense part in the destination (the structured-grid operator, whose far
-// pairs come from its FFT tables) only the touching pairs are written.
+// half-SWG test face x surface-charge face: Z[m_F, n_G] += sigma_G M0.  A wave
+// takes one test face and 64 source faces: first the far pairs, one lane each
+// (3 x 3 points; none with no dense part in the destination, the
+// structured-grid operator, whose far pairs come from its FFT tables), then
+// the few touching ones, three at a time: outer 7-point rule, lane 21 s + 3 p +
+// j the outer point p of the s-th pair and the inner point j of the 3-point
+// rule for the remainder, the closed form int_G 1/R with j = 0.
 __device__ __forceinline__ void k_face_face_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
                                                    const FaceGeom *__restrict__ fg,
                                                    const int32_t *__restrict__ half_list, int nhalf, int nface,
                                                    const dz *__restrict__ sigma, ZOut out, int bx_, int by_) {
   extern __shared__ double s_tab[];
+  __shared__ dz parts[4][64];
   stage_table(pack, packlen, s_tab);
   const double *__restrict__ P = s_tab;
 
+  const int lane = threadIdx.x & 63;
   const int hi = uniform(by_ * 4 + (threadIdx.x >> 6));
-  const int gi = bx_ * 64 + (threadIdx.x & 63);
-  if (hi >= nhalf || gi >= nface) return;
+  const int gi = bx_ * 64 + lane;
+  if (hi >= nhalf) return;
   const FaceGeom &f = fg[uniform(half_list[hi])];
-  const FaceGeom g = fg[gi];
-  int mask;
-  const dz m0 = pair_face_face(s_tab, qr, f, g, mask);
-  if (mask == 0 && !out.Z && !out.Zs) return;
-  zput(out, f.unknown, g.unknown, sigma[gi] * m0, mask != 0);
+  const FaceGeom &gl = fg[min(gi, nface - 1)];
+  const int mask = gi < nface ? touch_mask(f.canon, f.off, 3, gl.canon, gl.off, 3) : 0;
+  if (out.Z || out.Zs) {
+    if (gi < nface && mask == 0) {
+      dz acc = mk(0, 0);
+#pragma unroll 1
+      for (int i = 0; i < 3; ++i) {
+        double sep[3][3];
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          const double r = qr->tri3[i][0] * f.v[0][d] + qr->tri3[i][1] * f.v[1][d] + qr->tri3[i][2] * f.v[2][d];
+#pragma unroll
+          for (int j = 0; j < 3; ++j)
+            sep[j][d] = r - (qr->tri3[j][0] * gl.v[0][d] + qr->tri3[j][1] * gl.v[1][d] + qr->tri3[j][2] * gl.v[2][d]);
+        }
+        dz g[3];
+        pgf_eval_w<false, 3>(P, sep, 0, g);
+        acc = acc + (g[0] + g[1] + g[2]);
+      }
+      zput(out, f.unknown, gl.unknown, sigma[gi] * ((f.area / 3.0 * (gl.area / 3.0)) * acc), false);
+    }
+  }
+  const int s3 = min(lane / 21, 2), p = (lane - 21 * s3) / 3, j = (lane - 21 * s3) % 3;   // (lane 63: p = 7, idle)
+  for (unsigned long long todo = __ballot(mask != 0); todo != 0;) {
+    // the next three touching lanes (fewer at the end: the last one again, not stored)
+    int src[3], np = 0;
+    for (int s = 0; s < 3; ++s) {
+      if (todo != 0) {
+        src[s] = __ffsll((long long)todo) - 1;
+        todo &= todo - 1;
+        np = s + 1;
+      } else {
+        src[s] = src[np - 1];
+      }
+    }
+    const int mine = s3 == 0 ? src[0] : (s3 == 1 ? src[1] : src[2]);
+    const int tm = __shfl(mask, mine), ti = bx_ * 64 + mine;
+    const FaceGeom &g = fg[ti];
+    const int pp = min(p, 6);
+    double r[3], sep[1][3];
+    for (int d = 0; d < 3; ++d) {
+      r[d] = qr->tri7[pp][0] * f.v[0][d] + qr->tri7[pp][1] * f.v[1][d] + qr->tri7[pp][2] * f.v[2][d];
+      sep[0][d] = r[d] - (qr->tri3[j][0] * g.v[0][d] + qr->tri3[j][1] * g.v[1][d] + qr->tri3[j][2] * g.v[2][d]);
+    }
+    dz s0 = mk(0, 0);
+#pragma unroll 1
+    for (int b = 0; b < 9; ++b) {
+      if (!((tm >> b) & 1)) continue;
+      const int m = b / 3 - 1, n = b % 3 - 1;
+      const double o[3] = {r[0] + m * P[pk::A], r[1] + n * P[pk::B], r[2]};
+      double iinv, ione;
+      tri_potentials(g.v[0], g.v[1], g.v[2], o, iinv, ione);
+      if (j == 0) s0 = s0 + (kInv4Pi * iinv) * mk(P[pk::PHRE + b], -P[pk::PHIM + b]);
+    }
+    dz gv[1];
+    pgf_eval_w<true, 1>(P, sep, tm, gv);
+    axpy(s0, g.area / 3.0, gv[0]);
+    dz *part = parts[threadIdx.x >> 6];   // this wave's 64 slots
+    part[lane] = (p < 7 ? qr->w7[pp] * f.area : 0.0) * s0;
+    __builtin_amdgcn_wave_barrier();
+    if (p == 0 && j == 0 && s3 < np) {
+      dz m0 = mk(0, 0);
+      for (int e = 0; e < 21; ++e) m0 = m0 + part[21 * s3 + e];
+      zput(out, f.unknown, g.unknown, sigma[ti] * m0, true);
+    }
+    __builtin_amdgcn_wave_barrier();
+  }
 }
 
 __global__ __launch_bounds__(256, 2) void k_face_face(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
@@ -875,15 +786,15 @@ __device__ __forceinline__ int seg_of(const S *__restrict__ segs, int nseg, int 
   const int lb_ = (int)blockIdx.x - A.first;              \
   const int bx = lb_ % A.gx, by = lb_ / A.gx;
 
-__global__ __launch_bounds__(256, 2) void k_tt_far_seg(const FarSeg *__restrict__ segs, int nseg) {
+__global__ __launch_bounds__(256, kFarWaves) void k_tt_far_seg(const FarSeg *__restrict__ segs, int nseg) {
   VIE_SEG_BEGIN(FarSeg)
   tt_far_body<false>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.src_list, A.nsrc, A.alpha, A.gsrc,
-                     A.kappa, A.k0sq9, A.out, A.outT, A.sym, bx, by);
+                     A.kappa, A.k0sq9, A.out, A.outT, A.sym, A.tper, bx, by);
 }
-__global__ __launch_bounds__(256, 2) void k_tt_far_rev_seg(const FarSeg *__restrict__ segs, int nseg) {
+__global__ __launch_bounds__(256, kFarWaves) void k_tt_far_rev_seg(const FarSeg *__restrict__ segs, int nseg) {
   VIE_SEG_BEGIN(FarSeg)
   tt_far_body<true>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.src_list, A.nsrc, A.alpha, A.gsrc,
-                    A.kappa, A.k0sq9, A.out, A.outT, A.sym, bx, by);
+                    A.kappa, A.k0sq9, A.out, A.outT, A.sym, A.tper, bx, by);
 }
 __global__ __launch_bounds__(256) void k_tt_near_seg(const NearSeg *__restrict__ segs, int nseg) {
   VIE_SEG_BEGIN(NearSeg)
@@ -892,8 +803,13 @@ __global__ __launch_bounds__(256) void k_tt_near_seg(const NearSeg *__restrict__
 }
 __global__ __launch_bounds__(256, 2) void k_tet_face_seg(const TetFaceSeg *__restrict__ segs, int nseg) {
   VIE_SEG_BEGIN(TetFaceSeg)
-  k_tet_face_body(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.fg, A.nface, A.alpha, A.sigma, A.gsrc,
-                  A.kappa, A.out, A.outT, A.swap, bx, by);
+  k_tet_face_body<false>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.fg, A.nface, A.alpha, A.sigma,
+                         A.gsrc, A.kappa, A.out, A.outT, A.swap, bx, by);
+}
+__global__ __launch_bounds__(256, 2) void k_tet_face_rev_seg(const TetFaceSeg *__restrict__ segs, int nseg) {
+  VIE_SEG_BEGIN(TetFaceSeg)
+  k_tet_face_body<true>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.fg, A.nface, A.alpha, A.sigma,
+                        A.gsrc, A.kappa, A.out, A.outT, A.swap, bx, by);
 }
 __global__ __launch_bounds__(256, 2) void k_tet_face_near_seg(const TetFaceNearSeg *__restrict__ segs, int nseg) {
   VIE_SEG_BEGIN(TetFaceNearSeg)

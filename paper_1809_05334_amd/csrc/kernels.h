@@ -31,16 +31,23 @@ __global__ void k_zero(dz *p, int64_t n);
 // transposed pair's block into outT (stored untransposed); 2 (one list twice)
 // only pairs with source position > test position, both blocks as for 1.
 // k_tt_far: the swapped block from the same moments (kt = 0 only);
-// k_tt_far_rev (any incidence): from g_p at the reversed separations, with
-// 16 doubles per thread of dynamic LDS after the table (kFarRevLds bytes).
+// k_tt_far_rev (any incidence): from g_p at the reversed separations.
+// Blocks: 8 sources x (4 waves x tper test tets).
 __global__ void k_tt_far(const double *pack, int packlen, const QuadRules *qr, const TetGeom *tg, const TetFace *t2f,
                          const int32_t *test_list, int ntest, const int32_t *src_list, int nsrc, const dz *alpha,
-                         const dz *gsrc, const dz *kappa, double k0sq9, ZOut out, ZOut outT, int sym);
+                         const dz *gsrc, const dz *kappa, double k0sq9, ZOut out, ZOut outT, int sym, int tper);
 __global__ void k_tt_far_rev(const double *pack, int packlen, const QuadRules *qr, const TetGeom *tg,
                              const TetFace *t2f, const int32_t *test_list, int ntest, const int32_t *src_list, int nsrc,
                              const dz *alpha, const dz *gsrc, const dz *kappa, double k0sq9, ZOut out, ZOut outT,
-                             int sym);
-constexpr int kFarRevLds = 16 * 256 * 8 + 8;
+                             int sym, int tper);
+// Test tets per wave of a far launch over nsrc x ntest pairs: a block stages
+// the lattice-sum table once for 4 tper test tets, so more of them cost less,
+// as long as the launch still has some eight blocks per CU.
+inline int far_tper(int64_t nsrc, int64_t ntest) {
+  int t = 1;
+  while (t < 16 && (nsrc / 8) * (ntest / (8 * t)) >= 2048) t *= 2;
+  return t;
+}
 // Fused fill of many cells (the batch): one launch runs one fill kernel for
 // every cell that has work for it.  Each segment holds the arguments of one
 // cell's launch; it covers the fused grid's blocks [first, first + gx * gy)
@@ -50,7 +57,7 @@ constexpr int kFarRevLds = 16 * 256 * 8 + 8;
 struct FarSeg {
   const double *pack; int packlen; const QuadRules *qr; const TetGeom *tg; const TetFace *t2f;
   const int32_t *test_list; int ntest; const int32_t *src_list; int nsrc;
-  const dz *alpha, *gsrc, *kappa; double k0sq9; ZOut out, outT; int sym, gx, first;
+  const dz *alpha, *gsrc, *kappa; double k0sq9; ZOut out, outT; int sym, tper, gx, first;
 };
 struct NearSeg {
   const double *pack; int packlen; const QuadRules *qr; const TetGeom *tg; const TetFace *t2f;
@@ -83,7 +90,8 @@ struct FaceFaceSeg {
 __global__ void k_tt_far_seg(const FarSeg *segs, int nseg);
 __global__ void k_tt_far_rev_seg(const FarSeg *segs, int nseg);
 __global__ void k_tt_near_seg(const NearSeg *segs, int nseg);
-__global__ void k_tet_face_seg(const TetFaceSeg *segs, int nseg);
+__global__ void k_tet_face_seg(const TetFaceSeg *segs, int nseg);       // swap 0, 1
+__global__ void k_tet_face_rev_seg(const TetFaceSeg *segs, int nseg);   // swap 2
 __global__ void k_tet_face_near_seg(const TetFaceNearSeg *segs, int nseg);
 __global__ void k_face_tet_seg(const FaceTetSeg *segs, int nseg);
 __global__ void k_face_tet_near_seg(const FaceTetNearSeg *segs, int nseg);
@@ -105,8 +113,8 @@ __global__ void k_tet_face_rev(const double *pack, int packlen, const QuadRules 
 __global__ void k_face_tet(const double *pack, int packlen, const QuadRules *qr, const FaceGeom *fg, const int32_t *half_list,
                            int nhalf, const TetGeom *tg, const TetFace *t2f, const int32_t *src_list, int nsrc,
                            const dz *gsrc, const dz *kappa, ZOut out);
-// touching pairs from the host lists (lane = pair): (tet, surface-charge face
-// index) and (half-SWG face position, tet), interleaved
+// touching pairs from the host lists, (tet, surface-charge face index) and
+// (half-SWG face position, tet), interleaved: 16 and 32 lanes per pair
 __global__ void k_tet_face_near(const double *pack, int packlen, const QuadRules *qr, const TetGeom *tg,
                                 const TetFace *t2f, const int32_t *pairs, int npairs, const FaceGeom *fg,
                                 const dz *alpha, const dz *sigma, ZOut out);
