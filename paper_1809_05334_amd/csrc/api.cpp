@@ -1122,7 +1122,8 @@ void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &d
         else hipLaunchKernelGGL(k_lu_gemm2_z, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         break;
       case LU_TSEL:
-        if (f32) hipLaunchKernelGGL(k_lu_tsel_c, dim3(total), dim3(kTsRowsC * kTsLprC), 0, sm, st);
+        if (f32 && all_cols) hipLaunchKernelGGL(k_lu_tsel_wide_c, dim3(total), dim3(kTsRowsW * kTsLprC), 0, sm, st);
+        else if (f32) hipLaunchKernelGGL(k_lu_tsel_c, dim3(total), dim3(kTsRowsC * kTsLprC), 0, sm, st);
         else hipLaunchKernelGGL(k_lu_tsel_z, dim3(total), dim3(kTsRowsZ * kTsLprZ), 0, sm, st);
         break;
       case LU_TFIN:
@@ -1231,9 +1232,11 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
                   hipStream_t side, hipEvent_t ev_la, hipEvent_t ev_ts) {
   int maxn = 0;
   for (const LuDom &D : doms) maxn = std::max(maxn, D.n);
-  const int ts_rows = f32 ? kTsRowsC : kTsRowsZ;
+  const bool wide = f32 && maxn <= kTsWideMax;
+  const int ts_rows = wide ? kTsRowsW : (f32 ? kTsRowsC : kTsRowsZ);
   auto tsel = [&](int kp, hipStream_t sm) {
-    lu_launch(f32, sm, LU_TSEL, doms, kp, kp, [&](int d) { return doms[d].n > kp ? (int)nblk(doms[d].n - kp, ts_rows) : 0; });
+    lu_launch(f32, sm, LU_TSEL, doms, kp, kp, [&](int d) { return doms[d].n > kp ? (int)nblk(doms[d].n - kp, ts_rows) : 0; },
+              wide ? 1 : 0);
   };
   auto jb_of = [&](int d, int k0) { return std::min(kLuNB, doms[d].n - k0); };
   // single-panel update tiles of domain d at panel k0: row tiles (all, or grows)
@@ -1361,56 +1364,40 @@ int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
   const Layout &L = ctx->L;
   const bool f32 = fp32_factors(ctx);
   int32_t *ipiv = ctx->ptr<int32_t>(L.ipiv), *perm = ctx->ptr<int32_t>(L.perm), *info = ctx->ptr<int32_t>(L.info);
-  // storage of domain d's inverses and coupling blocks: L's, then U's
-  struct Prep {
-    int n, nbk;
-    void *DL, *DU, *GL, *GU;
-  };
-  std::vector<Prep> prep;
+  // the inverses, then the coupling blocks: L's of a domain, then U's
+  std::vector<TrsvPrepDom> prep;
   for (int d = 0; d < t.ndom; ++d) {
     const int n = doms[d].n;
     if (n == 0) continue;
-    const int nbk = (n + kTrsvNB - 1) / kTrsvNB;
-    const int64_t mlast = n - (int64_t)(nbk - 1) * kTrsvNB, nb2 = (int64_t)(nbk - 1) * kTrsvNB * kTrsvNB;
-    prep.push_back({n, nbk, factor_ptr(ctx, L.dinv, L.doff[d]), factor_ptr(ctx, L.dinv, L.doff[d] + nb2 + mlast * mlast),
-                    factor_ptr(ctx, L.gcpl, L.goff[d]), factor_ptr(ctx, L.gcpl, L.goff[d] + nb2)});
+    const int64_t nbk = (n + kTrsvNB - 1) / kTrsvNB, mlast = n - (nbk - 1) * kTrsvNB, nb2 = (nbk - 1) * kTrsvNB * kTrsvNB;
+    prep.push_back({doms[d].A, doms[d].ld, n, 0, factor_ptr(ctx, L.dinv, L.doff[d]),
+                    factor_ptr(ctx, L.dinv, L.doff[d] + nb2 + mlast * mlast), factor_ptr(ctx, L.gcpl, L.goff[d]),
+                    factor_ptr(ctx, L.gcpl, L.goff[d] + nb2)});
   }
-  {
+  for (int pass = 0; pass < 2; ++pass) {
     TrsvPrep st{};
     int total = 0;
     auto flush = [&]() {
       if (st.ndom == 0) return;
-      const dim3 ig(total, kTrsvNB / 16, 2), ib(256);
-      if (f32) hipLaunchKernelGGL(k_diag_inv_c, ig, ib, 0, ctx->stream, st);
-      else hipLaunchKernelGGL(k_diag_inv_z, ig, ib, 0, ctx->stream, st);
+      const dim3 ig(total, kTrsvNB / 16, 2), cg(total, (kTrsvNB / 64) * (kTrsvNB / 64), 2), b256(256);
+      if (pass == 0) {
+        if (f32) hipLaunchKernelGGL(k_diag_inv_c, ig, b256, 0, ctx->stream, st);
+        else hipLaunchKernelGGL(k_diag_inv_z, ig, b256, 0, ctx->stream, st);
+      } else {
+        if (f32) hipLaunchKernelGGL(k_trsv_coupling_c, cg, b256, 0, ctx->stream, st);
+        else hipLaunchKernelGGL(k_trsv_coupling_z, cg, b256, 0, ctx->stream, st);
+      }
       st.ndom = total = 0;
     };
-    size_t q = 0;
-    for (int d = 0; d < t.ndom; ++d) {
-      if (doms[d].n == 0) continue;
-      const Prep &p = prep[q++];
-      st.d[st.ndom] = TrsvPrepDom{doms[d].A, doms[d].ld, p.n, total, p.DL, p.DU};
-      total += p.nbk;
+    for (const TrsvPrepDom &p : prep) {
+      const int blocks = (p.n + kTrsvNB - 1) / kTrsvNB - pass;   // diagonal blocks; pairs of neighbours
+      if (blocks == 0) continue;
+      st.d[st.ndom] = p;
+      st.d[st.ndom].first_block = total;
+      total += blocks;
       if (++st.ndom == kLuMaxDom) flush();
     }
     flush();
-    LAUNCHCK();
-  }
-  size_t q = 0;
-  for (int d = 0; d < t.ndom; ++d) {
-    if (doms[d].n == 0) continue;
-    const Prep &p = prep[q++];
-    if (p.nbk < 2) continue;
-    const dim3 cg(p.nbk - 1, (kTrsvNB / 64) * (kTrsvNB / 64)), cb(256);   // 64 x 64 tiles of each coupling block
-    if (f32) {
-      const fz *A = (const fz *)doms[d].A;
-      hipLaunchKernelGGL(k_trsv_coupling_c, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 1, (const fz *)p.DL, (fz *)p.GL);
-      hipLaunchKernelGGL(k_trsv_coupling_c, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 0, (const fz *)p.DU, (fz *)p.GU);
-    } else {
-      const dz *A = (const dz *)doms[d].A;
-      hipLaunchKernelGGL(k_trsv_coupling_z, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 1, (const dz *)p.DL, (dz *)p.GL);
-      hipLaunchKernelGGL(k_trsv_coupling_z, cg, cb, 0, ctx->stream, A, doms[d].ld, p.n, 0, (const dz *)p.DU, (dz *)p.GU);
-    }
     LAUNCHCK();
   }
   HIPCK(hipEventRecord(ctx->ev1, ctx->stream));

@@ -303,24 +303,38 @@ __device__ __forceinline__ void lu_trsm_body(const LuStep &st) {
 //
 // Inside a node the rows stay in registers: TsCfg::lpr lanes per row, lane t
 // owning the contiguous columns [t W, (t+1) W), W = kLuNB / lpr.  Rows are not
-// moved: a pivot row is marked used and its step recorded.  Each step takes
-// one barrier: every wave publishes its best candidate (a 64-bit key of the
-// magnitude and the row) and that row's remaining columns in LDS,
-// double-buffered by the step's parity, and every thread then picks the
-// winner of the waves.
-template <typename C> struct TsCfg;
-template <> struct TsCfg<dz> {
+// moved: a pivot row is marked used and its step recorded.  Columns go in
+// blocks of kTsBlk: a step works on its block alone (one barrier: every wave
+// publishes its best candidate, a 64-bit key of the magnitude and the row,
+// that row's part of the block and its reciprocal pivot in LDS, double-buffered
+// by the step's parity, and every wave then picks the winner), and after the
+// block the other columns take its up to kTsBlk steps at once.  The chain of
+// steps bounds a panel, so a step does as little as it can: updating all 64
+// columns in each step, with the whole row published by one lane, a 64-bit
+// maximum and the pivot's division behind the barrier cost 3,200 cycles a step
+// (FP32) to 5,500 (FP64).  Alone, per panel: N = 15,840, FP64, 0.51 ms
+// (0.68 before); N = 37,376, FP32, 512-row nodes, 0.30 ms (0.44).
+template <typename C, bool WIDE> struct TsCfg;
+template <> struct TsCfg<dz, false> {
   static constexpr int lpr = kTsLprZ, fan = kTsFanZ, rows = kTsRowsZ;
 };
-template <> struct TsCfg<fz> {
+template <> struct TsCfg<fz, false> {
   static constexpr int lpr = kTsLprC, fan = kTsFanC, rows = kTsRowsC;
 };
-template <typename C>
+template <> struct TsCfg<fz, true> {
+  static constexpr int lpr = kTsLprC, fan = kTsFanW, rows = kTsRowsW;
+};
+constexpr int kTsBlk = 8;
+template <typename C, bool WIDE>
 struct TsShared {
-  static constexpr int kFan = TsCfg<C>::fan, kRows = TsCfg<C>::rows, kLpr = TsCfg<C>::lpr,
+  typedef C T;
+  static constexpr int kFan = TsCfg<C, WIDE>::fan, kRows = TsCfg<C, WIDE>::rows, kLpr = TsCfg<C, WIDE>::lpr,
                        kThreads = kRows * kLpr, kWaves = kThreads / 64, kW = kLuNB / kLpr;
-  C crow[2][kWaves][kLuNB];           // each wave's best candidate row, by step parity
+  C crow[2][kWaves][kTsBlk];          // each wave's best candidate row, columns j .. of the block, by step parity
+  C crinv[2][kWaves];                 // reciprocal of its pivot
   unsigned long long key[2][kWaves];
+  C U[kTsBlk][kLuNB];                 // the block's pivot rows, columns right of the block
+  C L11[kTsBlk][kTsBlk];              // the pivot rows' multipliers inside the block
   int rid[kRows];                     // the node's rows (rows of the domain)
   int order[kLuNB];                   // node rows in pivot order
   int zero;                           // first zero pivot of the last elimination (1-based), 0 if none
@@ -337,48 +351,45 @@ __device__ __forceinline__ C cinv(C d) {
   return cx<C>::make(d.re * s, -d.im * s);
 }
 
+// the value of the neighbouring lane (lane ^ 1)
+__device__ __forceinline__ double dpp_pair(double v) {
+  return __longlong_as_double((long long)dpp64<0xb1>((unsigned long long)__double_as_longlong(v)));
+}
+__device__ __forceinline__ dz dpp_pair(dz v) { return mk(dpp_pair(v.re), dpp_pair(v.im)); }
+__device__ __forceinline__ fz dpp_pair(fz v) {
+  return fz{__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.re), 0xb1, 0xf, 0xf, false)),
+            __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.im), 0xb1, 0xf, 0xf, false))};
+}
+
 // x - l p as four fused multiply-adds
 template <typename C>
 __device__ __forceinline__ C fms(C x, C l, C p) {
   return cx<C>::make(fma(-l.im, -p.im, fma(-l.re, p.re, x.re)), fma(-l.im, p.re, fma(-l.re, p.im, x.im)));
 }
 
-// Pivot key: the magnitude rounded to FP32 (its bits order like the value)
-// above the complement of the row, so a larger key is a larger magnitude, ties
-// to the smaller row; 0 = no candidate.
-__device__ __forceinline__ unsigned long long ts_key(double v, int r) {
-  return ((unsigned long long)__float_as_uint((float)v) << 32) | (unsigned)(0x7fffffff - r);
-}
-__device__ __forceinline__ int ts_key_row(unsigned long long k) { return 0x7fffffff - (int)(k & 0xffffffffu); }
+// Pivot candidate: the magnitude rounded to FP32 (its bits order like the
+// value) plus one, 0 = no candidate.
+__device__ __forceinline__ unsigned ts_mag(double v) { return __float_as_uint((float)v) + 1u; }
 
-// Maximum of a 64-bit key over the wave, returned to every lane: DPP lane
-// permutations inside each row of 16 lanes (quad swaps, half-row and row
-// mirrors), then the four row maxima read out of lanes 0, 16, 32, 48.
-__device__ __forceinline__ unsigned long long wave_max_u64(unsigned long long k) {
-  unsigned long long o;
-  o = dpp64<0xb1>(k);    // quad_perm [1,0,3,2]
-  k = o > k ? o : k;
-  o = dpp64<0x4e>(k);    // quad_perm [2,3,0,1]
-  k = o > k ? o : k;
-  o = dpp64<0x141>(k);   // row_half_mirror
-  k = o > k ? o : k;
-  o = dpp64<0x140>(k);   // row_mirror
-  k = o > k ? o : k;
-  unsigned long long m = readlane64(k, 0);
-  o = readlane64(k, 16);
-  m = o > m ? o : m;
-  o = readlane64(k, 32);
-  m = o > m ? o : m;
-  o = readlane64(k, 48);
-  return o > m ? o : m;
+// Maximum over the wave, in a scalar: DPP lane permutations inside each row of
+// 16 lanes (quad swaps, half-row and row mirrors), then the four row maxima.
+template <int CTRL>
+__device__ __forceinline__ unsigned dpp_max(unsigned v) {
+  return max(v, (unsigned)__builtin_amdgcn_update_dpp(0, (int)v, CTRL, 0xf, 0xf, false));
+}
+__device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
+  v = dpp_max<0x140>(dpp_max<0x141>(dpp_max<0x4e>(dpp_max<0xb1>(v))));
+  const unsigned a = __builtin_amdgcn_readlane(v, 0), b = __builtin_amdgcn_readlane(v, 16),
+                 c = __builtin_amdgcn_readlane(v, 32), d = __builtin_amdgcn_readlane(v, 48);
+  return max(max(a, b), max(c, d));
 }
 
 // This lane's columns of its row (row tid / lpr of S.rid, m valid rows; a
 // row outside the domain is read as zeros).
-template <typename C>
-__device__ __forceinline__ void ts_load(const TsShared<C> &S, const C *__restrict__ A, int64_t ld, int n, int k0,
-                                        int m, int jb, C (&x)[TsShared<C>::kW]) {
-  constexpr int L = TsShared<C>::kLpr, W = TsShared<C>::kW;
+template <class Sh, typename C = typename Sh::T>
+__device__ __forceinline__ void ts_load(const Sh &S, const C *__restrict__ A, int64_t ld, int n, int k0, int m, int jb,
+                                        C (&x)[Sh::kW]) {
+  constexpr int L = Sh::kLpr, W = Sh::kW;
   const int r = threadIdx.x / L, t = threadIdx.x % L;
   const int g = r < m ? S.rid[r] : -1;
   const bool ok = g >= 0 && g < n;
@@ -394,15 +405,17 @@ __device__ __forceinline__ void ts_load(const TsShared<C> &S, const C *__restric
 // b = (j mod W) / 8 of its owner lane o = j / W; the owner keeps column j in
 // the first register of that block by rotating the block one register per
 // step, so every register index is static with only the loop over blocks
-// unrolled (the loop over the 8 steps of a block is not: small code).
-template <typename C>
-__device__ __forceinline__ void ts_gepp(TsShared<C> &S, C (&x)[TsShared<C>::kW], int m, int jb, int *step) {
-  constexpr int L = TsShared<C>::kLpr, W = TsShared<C>::kW, NB = W / 8;
+// unrolled (the loop over the 8 steps of a block is not: small code).  Ties go
+// to the smaller row (rows ascend with the lanes and the waves).
+template <class Sh, typename C = typename Sh::T>
+__device__ __forceinline__ void ts_gepp(Sh &S, C (&x)[Sh::kW], int m, int jb, int *step) {
+  constexpr int L = Sh::kLpr, W = Sh::kW, NB = W / kTsBlk, NW = Sh::kWaves;
+  static_assert(kTsBlk == 8 && NW <= 8, "blocks of 8 registers; the waves' keys are reduced over 8 lanes");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r = tid / L, t = tid % L;
   const bool valid = r < m;
   const int steps = min(m, jb);
-  bool used = false;
+  bool used = !valid;
   int zero = 0;
   *step = -1;
 #pragma unroll
@@ -412,79 +425,49 @@ __device__ __forceinline__ void ts_gepp(TsShared<C> &S, C (&x)[TsShared<C>::kW],
     for (int b = 0; b < NB; ++b) {
       const int j0 = o * W + 8 * b;
       if (j0 >= steps) break;
+      const int nk = min(8, steps - j0);   // steps of this block
+      const bool before = used;            // pivot rows of earlier blocks and rows past m: untouched from here on
 #pragma clang loop unroll(disable)
       for (int jt = 0; jt < 8; ++jt) {
         const int j = j0 + jt;
-        if (j < steps) {
+        if (jt < nk) {
           const int buf = j & 1;
-          // the non-owner lanes of a row carry no candidate (key 0)
-          const unsigned long long k =
-              wave_max_u64((owner && valid && !used) ? ts_key(cabs1(x[8 * b]), r) : 0ull);
-          if (k != 0ull && r == ts_key_row(k)) {   // the wave's best row: columns j .. kLuNB-1
-            C *dst = S.crow[buf][wave];
-            if (owner) {
+          const unsigned mag = owner && !used ? ts_mag(cabs1(x[8 * b])) : 0u;
+          const C ri = cinv(x[8 * b]);   // (of every lane's own entry: ready when the winner is known)
+          const unsigned top = wave_max_u32(mag);
+          const unsigned long long at = __ballot(mag == top);
+          const int cl = __ffsll((long long)at) - 1;
+          if (top != 0u && lane == cl) {
 #pragma unroll
-              for (int kk = 0; kk < 8; ++kk)
-                if (kk + jt < 8) dst[j0 + kk + jt] = x[8 * b + kk];
-#pragma unroll
-              for (int bb = b + 1; bb < NB; ++bb)
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) dst[o * W + 8 * bb + kk] = x[8 * bb + kk];
-            } else if (t > o) {
-#pragma unroll
-              for (int i = 0; i < W; ++i) dst[t * W + i] = x[i];
-            }
+            for (int kk = 0; kk < 8; ++kk) S.crow[buf][wave][kk] = x[8 * b + kk];
+            S.crinv[buf][wave] = ri;
           }
-          if (lane == 0) S.key[buf][wave] = k;
+          if (lane == 0)
+            S.key[buf][wave] = (unsigned long long)top << 32 | (unsigned)((wave * 64 + cl) / L);
           __syncthreads();
-          unsigned long long best = S.key[buf][0];
-          int wb = 0;
-#pragma unroll
-          for (int w = 1; w < TsShared<C>::kWaves; ++w) {
-            const unsigned long long kw = S.key[buf][w];
-            if (kw > best) {
-              best = kw;
-              wb = w;
-            }
-          }
-          const int p = ts_key_row(best);
-          const bool nonzero = (best >> 32) != 0ull;
+          const unsigned long long kw = S.key[buf][lane & (NW - 1)];
+          const unsigned hi = (unsigned)(kw >> 32);
+          unsigned best = dpp_max<0x4e>(dpp_max<0xb1>(hi));
+          if (NW > 4) best = dpp_max<0x141>(best);
+          best = (unsigned)__builtin_amdgcn_readfirstlane((int)best);
+          const int wb = (__ffsll((long long)__ballot(hi == best)) - 1) & (NW - 1);
+          const int p = __builtin_amdgcn_readlane((int)(unsigned)kw, wb);
+          const bool nonzero = best > 1u;
           if (!nonzero && zero == 0) zero = j + 1;
-          if (r == p) {   // the pivot row: not updated any more
-            used = true;
-            *step = j;
-          }
-          if (tid == 0) S.order[j] = best != 0ull ? p : -1;
-          const C *prow = S.crow[buf][wb];
-          const C lraw = x[8 * b] * cinv(prow[j]);
-          C l = lraw;
-          if (L > 1) l = cx<C>::make(__shfl(lraw.re, (lane & ~(L - 1)) | o), __shfl(lraw.im, (lane & ~(L - 1)) | o));
-          if (valid && !used && nonzero) {
-            if (owner) {
-              C pv[8];
+          const bool now = r == p && best != 0u;
+          if (now) *step = j;   // the pivot row: not updated any more
+          used = used || now;
+          if (tid == 0) S.order[j] = best != 0u ? p : -1;
+          if (owner && !used && nonzero) {
+            const C *prow = S.crow[buf][wb];
+            const C l = x[8 * b] * S.crinv[buf][wb];
+            C pv[8];
 #pragma unroll
-              for (int kk = 1; kk < 8; ++kk) pv[kk] = prow[j0 + min(kk + jt, 7)];
+            for (int kk = 1; kk < 8; ++kk) pv[kk] = prow[kk];
 #pragma unroll
-              for (int kk = 1; kk < 8; ++kk)
-                if (kk + jt < 8) x[8 * b + kk] = fms(x[8 * b + kk], l, pv[kk]);
-#pragma unroll
-              for (int bb = b + 1; bb < NB; ++bb) {
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) pv[kk] = prow[o * W + 8 * bb + kk];
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) x[8 * bb + kk] = fms(x[8 * bb + kk], l, pv[kk]);
-              }
-              x[8 * b] = l;
-            } else if (t > o) {
-#pragma unroll
-              for (int bb = 0; bb < NB; ++bb) {
-                C pv[8];
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) pv[kk] = prow[t * W + 8 * bb + kk];
-#pragma unroll
-                for (int kk = 0; kk < 8; ++kk) x[8 * bb + kk] = fms(x[8 * bb + kk], l, pv[kk]);
-              }
-            }
+            for (int kk = 1; kk < 8; ++kk)
+              if (kk + jt < 8) x[8 * b + kk] = fms(x[8 * b + kk], l, pv[kk]);
+            x[8 * b] = l;
           }
         }
         // the owner rotates its block: column j + 1 to the front (after 8
@@ -496,6 +479,72 @@ __device__ __forceinline__ void ts_gepp(TsShared<C> &S, C (&x)[TsShared<C>::kW],
           x[8 * b + 7] = f;
         }
       }
+      if (j0 + 8 >= kLuNB) break;   // nothing right of the last block
+      // The block's steps on the columns right of it.  The pivot rows' parts
+      // and multipliers go to LDS, one thread per column solves for the U rows
+      // (each pivot row takes the steps before its own), and every other row
+      // takes them all.
+      const int own = *step - j0;   // this row's step in the block
+      const bool mine = !before && own >= 0 && own < 8;
+      if (mine) {
+        if (owner) {
+#pragma unroll
+          for (int kk = 0; kk < 8; ++kk) S.L11[own][kk] = x[8 * b + kk];
+#pragma unroll
+          for (int i = 8 * (b + 1); i < W; ++i) S.U[own][o * W + i] = x[i];
+        } else if (t > o) {
+#pragma unroll
+          for (int i = 0; i < W; ++i) S.U[own][t * W + i] = x[i];
+        }
+      }
+      C l[8];
+#pragma unroll
+      for (int kk = 0; kk < 8; ++kk) {
+        l[kk] = x[8 * b + kk];
+        if (L == 2 && o == 0) {   // the row's other lane takes the owner's multipliers (a pair of lanes)
+          const C v = dpp_pair(l[kk]);
+          if (!owner) l[kk] = v;
+        }
+      }
+      __syncthreads();
+      {
+        const int c = j0 + 8 + tid;
+        if (c < kLuNB) {
+          C u[8];
+#pragma unroll
+          for (int k = 0; k < 8; ++k)
+            if (k < nk) u[k] = S.U[k][c];
+#pragma unroll
+          for (int k = 1; k < 8; ++k)
+            if (k < nk) {
+#pragma unroll
+              for (int q = 0; q < k; ++q) u[k] = fms(u[k], S.L11[k][q], u[q]);
+              S.U[k][c] = u[k];
+            }
+        }
+      }
+      __syncthreads();
+      if (!before && t >= o) {
+#pragma unroll
+        for (int bb = 0; bb < NB; ++bb) {
+          if (t == o && bb <= b) continue;
+          const C *u = &S.U[0][t * W + 8 * bb];
+          if (mine) {
+#pragma unroll
+            for (int i = 0; i < 8; ++i) x[8 * bb + i] = u[own * kLuNB + i];
+          } else {
+#pragma unroll
+            for (int k = 0; k < 8; ++k)
+              if (k < nk) {
+                C pv[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) pv[i] = u[k * kLuNB + i];
+#pragma unroll
+                for (int i = 0; i < 8; ++i) x[8 * bb + i] = fms(x[8 * bb + i], l[k], pv[i]);
+              }
+          }
+        }
+      }
     }
   }
   __syncthreads();   // S.order complete; the LDS rows may be reused
@@ -504,23 +553,24 @@ __device__ __forceinline__ void ts_gepp(TsShared<C> &S, C (&x)[TsShared<C>::kW],
 
 // The row of the domain chosen at step j of the last elimination, -1 if the
 // record is out of range (a defect the root reports through info).
-template <typename C>
-__device__ __forceinline__ int ts_winner(const TsShared<C> &S, int j, int m) {
+template <class Sh>
+__device__ __forceinline__ int ts_winner(const Sh &S, int j, int m) {
   const int o = S.order[j];
   return (o >= 0 && o < m) ? S.rid[o] : -1;
 }
 
-template <typename C>
+template <typename C, bool WIDE>
 __device__ __forceinline__ void lu_tsel_body(const LuStep &st) {
-  __shared__ TsShared<C> S;
-  constexpr int kRows = TsShared<C>::kRows, kFan = TsShared<C>::kFan;
+  typedef TsShared<C, WIDE> Sh;
+  __shared__ Sh S;
+  constexpr int kRows = Sh::kRows, kFan = Sh::kFan;
   const int d = lu_domain(st);
   const LuDom &D = st.d[d];
   const C *A = (const C *)D.A;
   const int k0 = st.k0, n = D.n, jb = min(kLuNB, n - k0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int q = blockIdx.x - D.first_block;
-  C x[TsShared<C>::kW];
+  C x[Sh::kW];
   int step;
   // leaf: rows k0 + q kRows ...
   const int r0 = k0 + q * kRows;
@@ -577,7 +627,7 @@ __device__ __forceinline__ void lu_tsel_body(const LuStep &st) {
   }
   // root: the pivot rows in S.order, their LU in the registers of their lanes
   {
-    constexpr int L = TsShared<C>::kLpr, W = TsShared<C>::kW;
+    constexpr int L = Sh::kLpr, W = Sh::kW;
     C *T = (C *)D.tblk;
     const int t = tid % L;
     if (step >= 0)
@@ -979,8 +1029,9 @@ __global__ __launch_bounds__(256) void k_lu_swap_z(LuStep st) { lu_swap_body<dz>
 __global__ __launch_bounds__(256) void k_lu_swap_c(LuStep st) { lu_swap_body<fz>(st); }
 __global__ __launch_bounds__(256) void k_lu_trsm_z(LuStep st) { lu_trsm_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_lu_trsm_c(LuStep st) { lu_trsm_body<fz>(st); }
-__global__ __launch_bounds__(TsShared<dz>::kThreads) void k_lu_tsel_z(LuStep st) { lu_tsel_body<dz>(st); }
-__global__ __launch_bounds__(TsShared<fz>::kThreads) void k_lu_tsel_c(LuStep st) { lu_tsel_body<fz>(st); }
+__global__ __launch_bounds__(kTsRowsZ * kTsLprZ) void k_lu_tsel_z(LuStep st) { lu_tsel_body<dz, false>(st); }
+__global__ __launch_bounds__(kTsRowsC * kTsLprC) void k_lu_tsel_c(LuStep st) { lu_tsel_body<fz, false>(st); }
+__global__ __launch_bounds__(kTsRowsW * kTsLprC) void k_lu_tsel_wide_c(LuStep st) { lu_tsel_body<fz, true>(st); }
 __global__ __launch_bounds__(256) void k_lu_tfin_z(LuStep st) { lu_tfin_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_lu_tfin_c(LuStep st) { lu_tfin_body<fz>(st); }
 

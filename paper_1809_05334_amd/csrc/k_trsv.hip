@@ -124,20 +124,29 @@ __device__ __forceinline__ void diag_inv_body(const TrsvPrep &st) {
 __global__ __launch_bounds__(256) void k_diag_inv_z(TrsvPrep st) { diag_inv_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_diag_inv_c(TrsvPrep st) { diag_inv_body<fz>(st); }
 
-// Coupling blocks of one domain's sweep: for the matrix blocks b that follow
+// Coupling blocks of a domain's sweeps: for the matrix blocks b that follow
 // another in the sweep's order (b >= 1 for L, b <= nbk - 2 for U), with p =
 // b - 1 (L) or b + 1 (U), G_b = T[b, p] inv(T_pp), a kTrsvNB x kTrsvNB
 // product in FP64 (rounded to the factor type), written to slot b - 1 (L) or
 // b (U) of nb^2 entries, leading dimension nb.  A
 // thread block forms a 64 x 64 tile, 4 x 4 entries per thread, through
 // 16-deep slices of both operands in shared memory; entries past the blocks'
-// sizes are zero.
+// sizes are zero.  All domains' L and U blocks share a launch (one domain and
+// one triangle at a time left most CUs idle: a batch of six cells, 24 launches
+// of 0.21 ms).
 template <typename C>
-__device__ __forceinline__ void coupling_body(const C *__restrict__ F, int64_t ld, int n, int lower,
-                                              const C *__restrict__ INV, C *__restrict__ G) {
+__device__ __forceinline__ void coupling_body(const TrsvPrep &st) {
   constexpr int nb = kTrsvNB, TS = 64, KS = 16;
   __shared__ dz As[TS][KS + 1], Bs[KS][TS + 1];
-  const int b = lower ? blockIdx.x + 1 : blockIdx.x;
+  int dd = 0;
+  while (dd + 1 < st.ndom && (int)blockIdx.x >= st.d[dd + 1].first_block) ++dd;
+  const TrsvPrepDom &D = st.d[dd];
+  const bool lower = blockIdx.z == 0;
+  const C *__restrict__ F = (const C *)D.F, *__restrict__ INV = (const C *)(lower ? D.INVL : D.INVU);
+  C *__restrict__ G = (C *)(lower ? D.GL : D.GU);
+  const int64_t ld = D.ld;
+  const int n = D.n, pb = blockIdx.x - D.first_block;
+  const int b = lower ? pb + 1 : pb;
   const int p = lower ? b - 1 : b + 1;
   const int b0 = b * nb, p0 = p * nb;
   const int mr = min(nb, n - b0), mc = min(nb, n - p0);
@@ -185,12 +194,8 @@ __device__ __forceinline__ void coupling_body(const C *__restrict__ F, int64_t l
     for (int v = 0; v < 4; ++v)
       Gb[(int64_t)(tr * TS + ty * 4 + u) * nb + tc * TS + tx * 4 + v] = cx<C>::of(acc[u][v]);
 }
-__global__ __launch_bounds__(256) void k_trsv_coupling_z(const dz *F, int64_t ld, int n, int lower, const dz *INV, dz *G) {
-  coupling_body(F, ld, n, lower, INV, G);
-}
-__global__ __launch_bounds__(256) void k_trsv_coupling_c(const fz *F, int64_t ld, int n, int lower, const fz *INV, fz *G) {
-  coupling_body(F, ld, n, lower, INV, G);
-}
+__global__ __launch_bounds__(256) void k_trsv_coupling_z(TrsvPrep st) { coupling_body<dz>(st); }
+__global__ __launch_bounds__(256) void k_trsv_coupling_c(TrsvPrep st) { coupling_body<fz>(st); }
 
 __device__ __forceinline__ dz wave_sum(dz v) {
   for (int o = 32; o > 0; o >>= 1) {

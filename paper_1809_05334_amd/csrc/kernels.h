@@ -143,10 +143,16 @@ constexpr int kColRows = 64;    // rows per thread block of the panel column ker
 constexpr int kLuMaxDom = 8;
 constexpr int kGemm2Threads = 512;   // threads per block of the two-panel trailing update (k_lu_gemm2)
 // Tournament nodes: 256 rows and four children per node; a row takes two
-// lanes for FP64 factors (512 threads), one lane for FP32 (256 threads).
-constexpr int kTsFanZ = 4, kTsFanC = 4;
-constexpr int kTsRowsZ = kTsFanZ * kLuNB, kTsRowsC = kTsFanC * kLuNB;
+// lanes for FP64 factors (512 threads), one lane for FP32 (256 threads).  The
+// wide FP32 nodes, 512 rows and eight children, need fewer levels of 64 steps
+// but a whole CU per node, for which they queue behind the bulk update that
+// runs beside them: taken while the largest domain has at most kTsWideMax
+// unknowns (factor of six cells of up to 5,500: 56 ms against 62; N = 37,376,
+// largest domain 21,482: 427 ms against 386).
+constexpr int kTsFanZ = 4, kTsFanC = 4, kTsFanW = 8;
+constexpr int kTsRowsZ = kTsFanZ * kLuNB, kTsRowsC = kTsFanC * kLuNB, kTsRowsW = kTsFanW * kLuNB;
 constexpr int kTsLprZ = 2, kTsLprC = 1;
+constexpr int kTsWideMax = 8192;
 struct LuDom {
   void *A;            // the domain's block (dz or fz), row-major, leading dimension ld, factored in place
   int64_t ld;
@@ -182,6 +188,7 @@ struct LuStep {
 VIE_DECL_LU(z)
 VIE_DECL_LU(c)
 #undef VIE_DECL_LU
+__global__ void k_lu_tsel_wide_c(LuStep st);
 // (k_trsv.hip)
 __global__ void k_permute(int n, int64_t off, const int32_t *perm, const dz *v, dz *z);
 // Inverses of the diagonal blocks of L (blockIdx.z 0) and U (1) of up to
@@ -192,7 +199,8 @@ struct TrsvPrepDom {
   int64_t ld;
   int n;
   int first_block;    // first diagonal block of this domain in the launch
-  void *INVL, *INVU;
+  void *INVL, *INVU;  // inverses of the diagonal blocks of L and U
+  void *GL, *GU;      // coupling blocks
 };
 struct TrsvPrep {
   TrsvPrepDom d[kLuMaxDom];
@@ -200,10 +208,12 @@ struct TrsvPrep {
 };
 __global__ void k_diag_inv_z(TrsvPrep st);
 __global__ void k_diag_inv_c(TrsvPrep st);
-// coupling blocks G_b = T[b, p] inv(T_pp) of one domain's L (p = b - 1, b >= 1) or U
-// (p = b + 1, b <= nbk - 2) sweep, each kTrsvNB x kTrsvNB (k_trsv.hip)
-__global__ void k_trsv_coupling_z(const dz *F, int64_t ld, int n, int lower, const dz *INV, dz *G);
-__global__ void k_trsv_coupling_c(const fz *F, int64_t ld, int n, int lower, const fz *INV, fz *G);
+// Coupling blocks G_b = T[b, p] inv(T_pp) of the L (blockIdx.z 0; p = b - 1,
+// b >= 1) and U (1; p = b + 1, b <= nbk - 2) sweeps of the same domains, each
+// kTrsvNB x kTrsvNB: blockIdx.x counts pairs of neighbouring diagonal blocks
+// (first_block: the domain's first), blockIdx.y the 64 x 64 tiles.
+__global__ void k_trsv_coupling_z(TrsvPrep st);
+__global__ void k_trsv_coupling_c(TrsvPrep st);
 // One launch advances the blocked triangular solves of up to kTrsvMaxDom
 // domains by one diagonal block each (k_trsv.hip).
 constexpr int kTrsvGroupsH = kTrsvNB / 16;   // work items of 16 rows per diagonal block

@@ -167,3 +167,28 @@ def test_diagonal_block_inverses_at_strip_and_block_edges(vie, nx, ny, nz):
     z = s.precond_apply(v)
     ref = np.linalg.solve(read_block(s, 0, N), v)
     assert np.linalg.norm(z - ref) < 1e-10 * np.linalg.norm(ref), N
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(2, 2, 1), (4, 4, 2), (5, 4, 2), (5, 5, 2), (5, 4, 4), (8, 8, 6)])
+def test_fp32_tournament_at_node_edges(vie, nx, ny, nz):
+    """One domain of N = 56 to 4,736 unknowns, FP32 factors: panels below one
+    512-row node, at its edge and over several (a last panel of any width, a
+    tree with one lone child).  The tournament's error against a dense solve
+    stays within the small factor over partial pivoting that its growth bound
+    allows (both are backward-stable FP32 eliminations)."""
+    m = W.slab_mesh(nx=nx, ny=ny, nz=nz)
+    s = vie.Solver()
+    s.upload_mesh(m)
+    s.bind(vie.VIE_MIXED_FP32, 20)
+    s.fill(600.0, 0.3, 0.2, W.slab_eps(m))
+    N = s.num_unknowns()
+    rng = np.random.default_rng(6)
+    v = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    ref = np.linalg.solve(read_block(s, 0, N), v)
+    err = []
+    for pivot in (0, 1):
+        s.set_option(vie.VIE_OPT_LU_PIVOT, pivot)
+        s.factor()
+        z = s.precond_apply(v)
+        err.append(np.linalg.norm(z - ref) / np.linalg.norm(ref))
+    assert err[1] < 1e-3 and err[0] < 3 * err[1] + 1e-6, err
