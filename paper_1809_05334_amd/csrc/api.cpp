@@ -1728,12 +1728,13 @@ void launch_rhs(vie_ctx *ctx, int pol, dz *b) {
 }
 
 // One Arnoldi step of right-preconditioned GMRES for each Krylov process in
-// `mask` (bit k: process k), on the column j held in device memory (K[k].jd):
-// z = M^-1 V_j, w = Z z, CGS2 against V_0..V_j into H[:, j], h_{j+1,j} =
+// `mask` (bit k: process k), on the column j held in device memory (K[k].jd),
+// V_j also in K[k].vin: z = M^-1 V_j, w = Z z, CGS2 against V_0..V_j into H[:, j], h_{j+1,j} =
 // ||w||, Givens update of H and g (|g_{j+1}| into rhist[j]), V_{j+1} =
 // w / h_{j+1,j}, j += 1.  With both processes the preconditioner apply and the
-// matvec serve the two in one pass each; every other launch is per process,
-// so a process computes the same bits as alone.  The launches do not depend on
+// matvec serve the two in one pass each, and every other launch holds the
+// blocks of both, which do as they would alone: a process computes the same
+// bits as alone.  The launches do not depend on
 // j, so steps can be captured in a graph and replayed.
 int arnoldi_step(vie_ctx *ctx, int mask) {
   const Layout &L = ctx->L;
@@ -1752,8 +1753,6 @@ int arnoldi_step(vie_ctx *ctx, int mask) {
     w[i] = ctx->ptr<dz>(K.vw);
     tmp[i] = ctx->ptr<dz>(K.vt);
     u[i] = ctx->ptr<dz>(K.vu);
-    hipLaunchKernelGGL(k_arn_begin, dim3(nblk(N, 256)), dim3(256), 0, ctx->stream, (const dz *)ctx->ptr<dz>(K.V),
-                       L.ldv, (const int *)ctx->ptr<int>(K.jd), vi, N);
   }
   if (ctx->precond == 0) {
     if (int rc = apply_minv_n(ctx, np, vin, z, tmp, u)) return rc;
@@ -1770,27 +1769,29 @@ int arnoldi_step(vie_ctx *ctx, int mask) {
   } else if (int rc = matvec(ctx, z[0], nullptr, w[0])) {
     return rc;
   }
+  KryPair P{};
   for (int i = 0; i < np; ++i) {
     const Layout::Kry &K = L.K[ks[i]];
-    dz *V = ctx->ptr<dz>(K.V), *H = ctx->ptr<dz>(K.H), *g = ctx->ptr<dz>(K.g), *y = ctx->ptr<dz>(K.y);
-    double *cs = ctx->ptr<double>(K.cs), *scal = ctx->ptr<double>(K.scal);
-    dz *sn = ctx->ptr<dz>(K.sn), *part = ctx->ptr<dz>(K.dpart);
-    int *jd = ctx->ptr<int>(K.jd);
-    for (int pass = 0; pass < 2; ++pass) {
-      hipLaunchKernelGGL(k_dots_j, dim3(kRedBlocks, nblk(L.restart + 1, 8)), dim3(256), 0, ctx->stream, (const dz *)V, L.ldv,
-                         (const int *)jd, (const dz *)w[i], N, part);
-      hipLaunchKernelGGL(k_dots_reduce_j, dim3(nblk(L.restart + 1, 128)), dim3(128), 0, ctx->stream,
-                         (const dz *)part, kRedBlocks, (const int *)jd, H, ldh, y, pass);
-      hipLaunchKernelGGL(k_update_j, dim3(nblk(N, 256)), dim3(256), 0, ctx->stream, (const dz *)V, L.ldv,
-                         (const int *)jd, (const dz *)y, w[i], N);
-    }
-    if (int rc = norm_to(ctx, ks[i], w[i], N, scal + 2)) return rc;   // scal[2] = h_{j+1,j}
-    hipLaunchKernelGGL(k_givens_j, dim3(1), dim3(1), 0, ctx->stream, H, ldh, (const int *)jd,
-                       (const double *)(scal + 2), cs, sn, g, ctx->ptr<double>(K.rhist));
-    hipLaunchKernelGGL(k_scale_j, dim3(nblk(N, 256)), dim3(256), 0, ctx->stream, (const dz *)w[i],
-                       (const double *)(scal + 2), V, L.ldv, (const int *)jd, N);
-    hipLaunchKernelGGL(k_jinc, dim3(1), dim3(1), 0, ctx->stream, jd);
+    KryOp &p = P.p[i];
+    p.N = N;
+    p.ldv = L.ldv;
+    p.V = ctx->ptr<dz>(K.V);
+    p.jd = ctx->ptr<int>(K.jd);
+    p.vin = ctx->ptr<dz>(K.vin);
+    p.w = w[i];
+    p.H = ctx->ptr<dz>(K.H);
+    p.ldh = ldh;
+    p.cs = ctx->ptr<double>(K.cs);
+    p.sn = ctx->ptr<dz>(K.sn);
+    p.g = ctx->ptr<dz>(K.g);
+    p.rhist = ctx->ptr<double>(K.rhist);
+    kry_partials(ctx, K, p);
   }
+  for (int pass = 0; pass < 2; ++pass) {
+    hipLaunchKernelGGL(k_kry_dots, dim3(P.p[0].nd, nblk(L.restart + 1, 8), np), dim3(256), 0, ctx->stream, P);
+    hipLaunchKernelGGL(k_kry_update, dim3(P.p[0].nupd, np), dim3(256), 0, ctx->stream, P, pass);
+  }
+  hipLaunchKernelGGL(k_kry_finish, dim3(P.p[0].nupd, np), dim3(256), 0, ctx->stream, P);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return fail(ctx, VIE_EDEVICE, "Arnoldi step: %s", hipGetErrorString(e));
   return VIE_OK;
@@ -1886,7 +1887,7 @@ int gmres(vie_ctx *ctx, int np, Gmres *P, double tol, int max_iter, int restart)
       const Layout::Kry &K = L.K[p.k];
       // V0 = r / beta ; g = beta e1 ; j = 0
       hipLaunchKernelGGL(k_scale, dim3(nblk(N, 256)), dim3(256), 0, ctx->stream, (const dz *)ctx->ptr<dz>(K.vr),
-                         (const double *)(ctx->ptr<double>(K.scal) + 1), ctx->ptr<dz>(K.V), N);
+                         (const double *)(ctx->ptr<double>(K.scal) + 1), ctx->ptr<dz>(K.V), ctx->ptr<dz>(K.vin), N);
       hipLaunchKernelGGL(k_ginit, dim3(1), dim3(256), 0, ctx->stream, ctx->ptr<dz>(K.g), restart + 1,
                          (const double *)(ctx->ptr<double>(K.scal) + 1));
       hipLaunchKernelGGL(k_jset, dim3(1), dim3(1), 0, ctx->stream, ctx->ptr<int>(K.jd), 0);

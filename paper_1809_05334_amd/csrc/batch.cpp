@@ -455,8 +455,8 @@ namespace {
 // of each grid shape, the step flags and residual estimates, and the merged
 // plan of the triangular solves (every cell's domains per step).
 struct StepPlan {
-  size_t kc, pre_elem, pre_mv, pre_dots, pre_red, pre_norm, act, res, trsv;
-  int tot_elem, tot_mv, tot_dots, tot_red, tot_norm;
+  size_t kc, pre_elem, pre_mv, pre_dots, pre_upd, act, res, trsv;
+  int tot_elem, tot_mv, tot_dots, tot_upd;
   struct TStep {
     size_t off;
     int ndom, lower, blocks, chain, zend;   // reduction items first, solution items up to zend
@@ -469,7 +469,7 @@ int build_step_plan(vie_batch *b, StepPlan &sp) {
   const int nc = (int)b->cells.size();
   Stage st;
   std::vector<KryCell> kc(nc);
-  std::vector<int> pe(nc + 1, 0), pm(nc + 1, 0), pd(nc + 1, 0), pr(nc + 1, 0), pn(nc + 1, 0);
+  std::vector<int> pe(nc + 1, 0), pm(nc + 1, 0), pd(nc + 1, 0), pn(nc + 1, 0);
   sp.precond = false;
   for (int c = 0; c < nc; ++c) {
     vie_ctx *x = b->cells[c];
@@ -498,12 +498,8 @@ int build_step_plan(vie_batch *b, StepPlan &sp) {
     k.cs = x->ptr<double>(K.cs);
     k.sn = x->ptr<dz>(K.sn);
     k.g = x->ptr<dz>(K.g);
-    k.y = x->ptr<dz>(K.y);
     k.rhist = x->ptr<double>(K.rhist);
-    k.scal = x->ptr<double>(K.scal);
-    k.dpart = x->ptr<dz>(K.dpart);
-    k.npart = x->ptr<double>(K.npart);
-    k.nred = (int)std::min<int64_t>(kRedBlocks, nblk(N, 256));
+    kry_partials(x, K, k);
     k.perm = x->ptr<int32_t>(L.perm);
     k.ndom = x->topo.ndom;
     for (int d = 0; d < x->topo.ndom; ++d) k.dstart[d] = x->topo.dstart[d];
@@ -513,21 +509,18 @@ int build_step_plan(vie_batch *b, StepPlan &sp) {
     const int ngrp = (int)nblk(L.restart + 1, 8);
     pe[c + 1] = pe[c] + (int)nblk(N, 256);
     pm[c + 1] = pm[c] + (int)nblk(N, 4 * k.rpw);
-    pd[c + 1] = pd[c] + k.nred * ngrp;
-    pr[c + 1] = pr[c] + (int)nblk(L.restart + 1, 128);
-    pn[c + 1] = pn[c] + k.nred;
+    pd[c + 1] = pd[c] + k.nd * ngrp;
+    pn[c + 1] = pn[c] + k.nupd;
   }
   sp.kc = st.add(kc.data(), sizeof(KryCell) * nc);
   sp.pre_elem = st.add(pe.data(), 4 * (nc + 1));
   sp.pre_mv = st.add(pm.data(), 4 * (nc + 1));
   sp.pre_dots = st.add(pd.data(), 4 * (nc + 1));
-  sp.pre_red = st.add(pr.data(), 4 * (nc + 1));
-  sp.pre_norm = st.add(pn.data(), 4 * (nc + 1));
+  sp.pre_upd = st.add(pn.data(), 4 * (nc + 1));
   sp.tot_elem = pe[nc];
   sp.tot_mv = pm[nc];
   sp.tot_dots = pd[nc];
-  sp.tot_red = pr[nc];
-  sp.tot_norm = pn[nc];
+  sp.tot_upd = pn[nc];
   std::vector<int> zeros(nc, 0);
   sp.act = st.add(zeros.data(), 4 * nc);
   std::vector<double> zd(nc, 0.0);
@@ -582,7 +575,6 @@ int issue_step(vie_batch *b, const StepPlan &sp) {
   const int *act = (const int *)(b->ws + sp.act);
   auto pre = [&](size_t off) { return (const int *)(b->ws + off); };
   const dim3 t256(256);
-  hipLaunchKernelGGL(k_b_arn_begin, dim3(sp.tot_elem), t256, 0, b->stream, kc, pre(sp.pre_elem), nc, act);
   if (sp.precond) {
     hipLaunchKernelGGL(k_b_permute, dim3(sp.tot_elem), t256, 0, b->stream, kc, pre(sp.pre_elem), nc, act);
     const bool f32 = b->precision == VIE_MIXED_FP32;
@@ -598,15 +590,11 @@ int issue_step(vie_batch *b, const StepPlan &sp) {
   }
   hipLaunchKernelGGL(k_b_matvec, dim3(sp.tot_mv), t256, 0, b->stream, kc, pre(sp.pre_mv), nc, act);
   for (int pass = 0; pass < 2; ++pass) {
-    hipLaunchKernelGGL(k_b_dots_j, dim3(sp.tot_dots), t256, 0, b->stream, kc, pre(sp.pre_dots), nc, act);
-    hipLaunchKernelGGL(k_b_dots_reduce_j, dim3(sp.tot_red), dim3(128), 0, b->stream, kc, pre(sp.pre_red), nc, act,
-                       pass);
-    hipLaunchKernelGGL(k_b_update_j, dim3(sp.tot_elem), t256, 0, b->stream, kc, pre(sp.pre_elem), nc, act);
+    hipLaunchKernelGGL(k_b_dots, dim3(sp.tot_dots), t256, 0, b->stream, kc, pre(sp.pre_dots), nc, act);
+    hipLaunchKernelGGL(k_b_update, dim3(sp.tot_upd), t256, 0, b->stream, kc, pre(sp.pre_upd), nc, act, pass);
   }
-  hipLaunchKernelGGL(k_b_norm2, dim3(sp.tot_norm), t256, 0, b->stream, kc, pre(sp.pre_norm), nc, act);
-  hipLaunchKernelGGL(k_b_norm_givens, dim3(nblk(nc, 64)), dim3(64), 0, b->stream, kc, nc, act);
-  hipLaunchKernelGGL(k_b_scale_j, dim3(sp.tot_elem), t256, 0, b->stream, kc, pre(sp.pre_elem), nc, act);
-  hipLaunchKernelGGL(k_b_jinc, dim3(nblk(nc, 64)), dim3(64), 0, b->stream, kc, nc, act, (double *)(b->ws + sp.res));
+  hipLaunchKernelGGL(k_b_finish, dim3(sp.tot_upd), t256, 0, b->stream, kc, pre(sp.pre_upd), nc, act,
+                     (double *)(b->ws + sp.res));
   BLAUNCHCK();
   return VIE_OK;
 }
@@ -680,7 +668,7 @@ int vie_batch_solve(vie_batch *b, const int *polarisation, double tol, int max_i
         const Layout::Kry &K = x->L.K[0];
         const int64_t N = x->topo.N;
         hipLaunchKernelGGL(k_scale, dim3(nblk(N, 256)), dim3(256), 0, b->stream, (const dz *)x->ptr<dz>(K.vr),
-                           (const double *)(x->ptr<double>(K.scal) + 1), x->ptr<dz>(K.V), N);
+                           (const double *)(x->ptr<double>(K.scal) + 1), x->ptr<dz>(K.V), x->ptr<dz>(K.vin), N);
         hipLaunchKernelGGL(k_ginit, dim3(1), dim3(256), 0, b->stream, x->ptr<dz>(K.g), restart + 1,
                            (const double *)(x->ptr<double>(K.scal) + 1));
         hipLaunchKernelGGL(k_jset, dim3(1), dim3(1), 0, b->stream, x->ptr<int>(K.jd), 0);

@@ -24,6 +24,7 @@ enum State { S_NEW = 0, S_MESH = 1, S_BOUND = 2, S_FILLED = 3, S_FACTORED = 4, S
 
 constexpr int kMaxPack = 8192;     // doubles of the packed lattice-sum table (64 KB of LDS)
 constexpr int kRedBlocks = 240;   // blocks of the two-stage reductions
+static_assert((kRedBlocks - kKryDots) * 16 * 2 >= kKryUpd * 8, "the norm's partials fit behind the inner products'");
 constexpr int kMaxPlans = 4;      // cached cooperative triangular-solve plans per context
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
@@ -163,6 +164,17 @@ inline int fail(vie_ctx *c, int code, const char *fmt, ...) {
   va_end(ap);
   if (c) c->err = buf;
   return code;
+}
+
+// Chunks and row blocks of a process's inner products and updates, and their
+// partials in its dpart region: nd (restart + 1) complex values, then nupd doubles.
+template <class P>
+void kry_partials(const vie_ctx *c, const Layout::Kry &K, P &p) {
+  const int64_t blocks = std::max<int64_t>(1, (c->topo.N + 255) / 256);
+  p.nd = (int)std::min<int64_t>(kKryDots, blocks);
+  p.nupd = (int)std::min<int64_t>(kKryUpd, blocks);
+  p.dpart = c->ptr<dz>(K.dpart);
+  p.npart = reinterpret_cast<double *>(p.dpart + (int64_t)kKryDots * (c->L.restart + 1));
 }
 
 inline unsigned nblk(int64_t n, int b) { return (unsigned)std::max<int64_t>(1, (n + b - 1) / b); }

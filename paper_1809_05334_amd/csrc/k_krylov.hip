@@ -272,12 +272,14 @@ __global__ void k_norm_reduce(const double *__restrict__ part, int nblk, double 
   *out = sqrt(s);
 }
 
-// v = w / *nrm  (or v = w * scale when nrm == nullptr)
-__global__ void k_scale(const dz *__restrict__ w, const double *__restrict__ nrm, dz *__restrict__ v, int64_t N) {
+// v = vin = w / *nrm (the first basis vector, which the first step takes)
+__global__ void k_scale(const dz *__restrict__ w, const double *__restrict__ nrm, dz *__restrict__ v,
+                        dz *__restrict__ vin, int64_t N) {
   const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (k >= N) return;
-  const double s = 1.0 / *nrm;
-  v[k] = s * w[k];
+  const dz x = (1.0 / *nrm) * w[k];
+  v[k] = x;
+  vin[k] = x;
 }
 
 __global__ void k_axpy(dz *__restrict__ x, const dz *__restrict__ u, int64_t N) {
@@ -323,144 +325,178 @@ __global__ void k_copy(dz *__restrict__ d, const dz *__restrict__ s, int64_t N) 
 }
 
 // ------------------------------------------------------------ Arnoldi step
-// The kernels of one Arnoldi step read the column index j from device memory
-// (*jd), so the step issues the same launches for every j and can be
-// captured once in a HIP graph and replayed.  k_jinc advances *jd at the end
-// of the step.
+// After the preconditioner and the product, a step is five launches for all
+// its processes together (both polarisations of a pair, every cell of a
+// batch): partial inner products; their reduction and the update of w, twice
+// (CGS2), the second also with partial squared norms; then V_{j+1} and the
+// Givens update.  Each is a few microseconds of latency, not of bandwidth, so
+// reductions are finished by the blocks that use them (each reads all the
+// partials) rather than in launches of their own: one reduction or one scalar
+// kernel per process took 11 launches and 80 us per process and step at
+// N = 6,272 (five and 35 us now, for both).  The kernels read the column index j
+// from device memory, so the step issues the same launches for every j and can
+// be captured once in a HIP graph and replayed.  Nothing reads *jd in the last
+// launch, which advances it (j is handed to it in jd[1]).
 
-// vin = V_j
-__global__ void k_arn_begin(const dz *__restrict__ V, int64_t ldv, const int *__restrict__ jd, dz *__restrict__ vin,
-                            int64_t N) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k < N) vin[k] = V[(int64_t)(*jd) * ldv + k];
-}
-
-// partial inner products with V_0 .. V_j (k_dots with nv = j + 1): block
-// (x, y) sums chunk x of N for basis vectors 8 y .. 8 y + 7; the grid's y
-// extent covers the largest j (blocks past V_j return at once), so every
-// group of eight runs at the same time and the launch is the same for every j
-__global__ __launch_bounds__(256) void k_dots_j(const dz *__restrict__ V, int64_t ldv, const int *__restrict__ jd,
-                                                const dz *__restrict__ w, int64_t N, dz *__restrict__ part) {
-  // eight basis vectors per block: their loads are in flight together and one
-  // barrier serves the eight block sums (each sum as for one vector)
+// partial inner products with V_0 .. V_j: block (bx, by) sums chunk bx of the
+// nd chunks of N for basis vectors 8 by .. 8 by + 7 (their loads in flight
+// together, one barrier for the eight sums; blocks past V_j return at once)
+template <class K>
+__device__ __forceinline__ void kry_dots(const K &k, int bx, int by) {
   constexpr int G = 8;
   __shared__ dz red[G][4];
-  const int nv = *jd + 1;
-  const int i0 = blockIdx.y * G;
+  const int nv = *k.jd + 1;
+  const int i0 = by * G;
   if (i0 >= nv) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t chunk = (N + gridDim.x - 1) / gridDim.x;
-  const int64_t lo = blockIdx.x * chunk, hi = min<int64_t>(N, lo + chunk);
-  {
-    double sr[G], si[G];
+  const int64_t N = k.N, ldv = k.ldv;
+  const int64_t chunk = (N + k.nd - 1) / k.nd;
+  const int64_t lo = bx * chunk, hi = min<int64_t>(N, lo + chunk);
+  double sr[G], si[G];
 #pragma unroll
-    for (int g = 0; g < G; ++g) sr[g] = si[g] = 0.0;
-    for (int64_t k = lo + tid; k < hi; k += 256) {
-      const dz ww = w[k];
-      double vr[G], vi[G];
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        const dz v = V[(int64_t)min(i0 + g, nv - 1) * ldv + k];
-        vr[g] = v.re;
-        vi[g] = v.im;
-      }
-#pragma unroll
-      for (int g = 0; g < G; ++g) {
-        sr[g] = fma(vr[g], ww.re, fma(vi[g], ww.im, sr[g]));
-        si[g] = fma(vr[g], ww.im, fma(-vi[g], ww.re, si[g]));
-      }
-    }
+  for (int g = 0; g < G; ++g) sr[g] = si[g] = 0.0;
+  for (int64_t e = lo + tid; e < hi; e += 256) {
+    const dz ww = k.w[e];
+    double vr[G], vi[G];
 #pragma unroll
     for (int g = 0; g < G; ++g) {
-      const double a = wsum(sr[g]), b = wsum(si[g]);
-      if (lane == 0) red[g][wave] = mk(a, b);
-    }
-    __syncthreads();
-    if (tid < G && i0 + tid < nv)
-      part[(int64_t)blockIdx.x * nv + i0 + tid] = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
-  }
-}
-
-// s_i = sum_b part[b][i]; y_i = s_i; H[i][j] = s_i (pass 0) or += s_i (pass 1)
-__global__ void k_dots_reduce_j(const dz *__restrict__ part, int nblk, const int *__restrict__ jd,
-                                dz *__restrict__ H, int ldh, dz *__restrict__ y, int pass) {
-  const int j = *jd, nv = j + 1;
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= nv) return;
-  dz s = mk(0, 0);
-  for (int b0 = 0; b0 < nblk; b0 += 16) {   // sixteen loads in flight, summed in order
-    double pr[16], pi[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const dz p = part[(int64_t)min(b0 + u, nblk - 1) * nv + i];
-      pr[u] = p.re;
-      pi[u] = p.im;
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (b0 + u < nblk) s = s + mk(pr[u], pi[u]);
-  }
-  dz *h = H + (int64_t)j * ldh;
-  h[i] = pass ? h[i] + s : s;
-  y[i] = s;
-}
-
-// w[k] -= sum_{i<=j} V_i[k] c[i]
-__global__ __launch_bounds__(256) void k_update_j(const dz *__restrict__ V, int64_t ldv, const int *__restrict__ jd,
-                                                  const dz *__restrict__ c, dz *__restrict__ w, int64_t N) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= N) return;
-  const int nv = *jd + 1;
-  dz s = w[k];
-  // eight basis entries in flight at a time; the updates run in i order
-  for (int i0 = 0; i0 < nv; i0 += 8) {
-    double vr[8], vi[8];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const dz v = V[(int64_t)min(i0 + g, nv - 1) * ldv + k];
+      const dz v = k.V[(int64_t)min(i0 + g, nv - 1) * ldv + e];
       vr[g] = v.re;
       vi[g] = v.im;
     }
 #pragma unroll
-    for (int g = 0; g < 8; ++g)
-      if (i0 + g < nv) s = s - mk(vr[g], vi[g]) * c[i0 + g];
+    for (int g = 0; g < G; ++g) {
+      sr[g] = fma(vr[g], ww.re, fma(vi[g], ww.im, sr[g]));
+      si[g] = fma(vr[g], ww.im, fma(-vi[g], ww.re, si[g]));
+    }
   }
-  w[k] = s;
+#pragma unroll
+  for (int g = 0; g < G; ++g) {
+    const double a = wsum(sr[g]), b = wsum(si[g]);
+    if (lane == 0) red[g][wave] = mk(a, b);
+  }
+  __syncthreads();
+  if (tid < G && i0 + tid < nv)
+    k.dpart[(int64_t)bx * nv + i0 + tid] = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
 }
 
-// V_{j+1} = w / *nrm
-__global__ void k_scale_j(const dz *__restrict__ w, const double *__restrict__ nrm, dz *__restrict__ V, int64_t ldv,
-                          const int *__restrict__ jd, int64_t N) {
-  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= N) return;
-  const double s = 1.0 / *nrm;
-  V[(int64_t)(*jd + 1) * ldv + k] = s * w[k];
+// s_i = sum over the nd partials; w -= sum_{i<=j} V_i s_i over the rows of
+// block b (of nupd, strided); block 0 stores H[i][j] = s_i (pass 0) or += s_i
+// (pass 1).  64 basis vectors at a time: four waves sum a quarter of the
+// partials each (16 loads in flight), then every thread updates its rows.
+// Pass 1: also the block's sum of |w|^2 into npart[b], and j for the last launch.
+template <class K>
+__device__ __forceinline__ void kry_update(const K &k, int b, int pass) {
+  constexpr int T = 64;
+  __shared__ dz q[4][T], c[T];
+  __shared__ double red[4];
+  const int j = *k.jd, nv = j + 1;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int64_t N = k.N, first = (int64_t)b * 256 + tid, stride = (int64_t)k.nupd * 256;
+  if (b == 0 && tid == 0) k.jd[1] = j;
+  double nrm = 0.0;
+  for (int t0 = 0; t0 < nv; t0 += T) {
+    const int nt = min(T, nv - t0);
+    {
+      const int i = t0 + min(lane, nt - 1);
+      dz s = mk(0, 0);
+      for (int b0 = wave; b0 < k.nd; b0 += 64) {
+        double pr[16], pi[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+          const dz p = k.dpart[(int64_t)min(b0 + 4 * u, k.nd - 1) * nv + i];
+          pr[u] = p.re;
+          pi[u] = p.im;
+        }
+#pragma unroll
+        for (int u = 0; u < 16; ++u)
+          if (b0 + 4 * u < k.nd) s = s + mk(pr[u], pi[u]);
+      }
+      q[wave][lane] = s;
+    }
+    __syncthreads();
+    if (tid < nt) {
+      const dz s = (q[0][tid] + q[1][tid]) + (q[2][tid] + q[3][tid]);
+      c[tid] = s;
+      if (b == 0) {
+        dz *h = k.H + (int64_t)j * k.ldh + t0 + tid;
+        *h = pass ? *h + s : s;
+      }
+    }
+    __syncthreads();
+    const bool last = t0 + T >= nv;
+    for (int64_t e = first; e < N; e += stride) {
+      dz s = k.w[e];
+      // eight basis entries in flight at a time; the updates run in i order
+      for (int g0 = 0; g0 < nt; g0 += 8) {
+        double vr[8], vi[8];
+#pragma unroll
+        for (int g = 0; g < 8; ++g) {
+          const dz v = k.V[(int64_t)(t0 + min(g0 + g, nt - 1)) * k.ldv + e];
+          vr[g] = v.re;
+          vi[g] = v.im;
+        }
+#pragma unroll
+        for (int g = 0; g < 8; ++g)
+          if (g0 + g < nt) s = s - mk(vr[g], vi[g]) * c[g0 + g];
+      }
+      k.w[e] = s;
+      if (last) nrm = fma(s.re, s.re, fma(s.im, s.im, nrm));
+    }
+    __syncthreads();   // c and q may be reused
+  }
+  if (!pass) return;
+  nrm = wsum(nrm);
+  if (lane == 0) red[wave] = nrm;
+  __syncthreads();
+  if (tid == 0) k.npart[b] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
 __global__ void k_jset(int *__restrict__ jd, int v) {
   if (threadIdx.x == 0 && blockIdx.x == 0) *jd = v;
 }
 
-__global__ void k_jinc(int *__restrict__ jd) {
-  if (threadIdx.x == 0 && blockIdx.x == 0) *jd = *jd + 1;
-}
-
 // GMRES state on the device: H (ldh x m, column j holds h_{0..j+1, j}),
 // Givens cosines (real) and sines (complex), g (m+1).
 // Arnoldi column j: h[0..j] from CGS2, hn = ||w||.  Apply the previous
-// rotations to column j, form the new one, update g, write |g[j+1]|.
-__device__ void givens_step(dz *__restrict__ H, int ldh, int j, double hnv, double *__restrict__ cs,
-                            dz *__restrict__ sn, dz *__restrict__ g, double *__restrict__ res) {
+// rotations to column j, form the new one, update g, write |g[j+1]| (to *hist
+// and, if given, *res).  Called by a whole block of 256 threads: the column and
+// the rotations go through LDS, 128 at a time, and one thread applies them (a
+// chain over j; from global memory it was 8.8 us at j = 30).
+__device__ __forceinline__ void givens_step(dz *__restrict__ H, int ldh, int j, double hnv, double *__restrict__ cs,
+                                            dz *__restrict__ sn, dz *__restrict__ g, double *__restrict__ hist,
+                                            double *__restrict__ res) {
+  constexpr int T = 128;
+  __shared__ dz hh[T + 1], ss[T];
+  __shared__ double cc[T];
   dz *h = H + (int64_t)j * ldh;
-  h[j + 1] = mk(hnv, 0.0);
-  for (int i = 0; i < j; ++i) {
-    // [c  s; -conj(s) c] acting on (h_i, h_{i+1})
-    const dz a = h[i], b = h[i + 1];
-    h[i] = cs[i] * a + sn[i] * b;
-    h[i + 1] = cs[i] * b - conjz(sn[i]) * a;
+  const int tid = threadIdx.x;
+  dz a = mk(0, 0), b = mk(0, 0);   // thread 0: the entry carried to the next rotation
+  for (int i0 = 0; i0 < j; i0 += T) {
+    const int nt = min(T, j - i0);
+    if (tid < nt) {
+      ss[tid] = sn[i0 + tid];
+      cc[tid] = cs[i0 + tid];
+    }
+    if (tid <= nt) hh[tid] = h[i0 + tid];
+    __syncthreads();
+    if (tid == 0) {
+      a = i0 == 0 ? hh[0] : a;
+      for (int i = 0; i < nt; ++i) {
+        // [c  s; -conj(s) c] acting on (h_i, h_{i+1})
+        b = hh[i + 1];
+        hh[i] = cc[i] * a + ss[i] * b;
+        a = cc[i] * b - conjz(ss[i]) * a;
+      }
+    }
+    __syncthreads();
+    if (tid < nt) h[i0 + tid] = hh[tid];
+    __syncthreads();
   }
-  const dz a = h[j], b = h[j + 1];
-  const double na = sqrt(a.re * a.re + a.im * a.im), nb = sqrt(b.re * b.re + b.im * b.im);
+  if (tid != 0) return;
+  if (j == 0) a = h[0];
+  b = mk(hnv, 0.0);
+  const double na = sqrt(a.re * a.re + a.im * a.im), nb = hnv;
   double c;
   dz s;
   if (na == 0.0) {
@@ -479,18 +515,41 @@ __device__ void givens_step(dz *__restrict__ H, int ldh, int j, double hnv, doub
   sn[j] = s;
   const dz gj = g[j];
   g[j] = c * gj;
-  g[j + 1] = mk(0, 0) - conjz(s) * gj;
-  *res = sqrt(g[j + 1].re * g[j + 1].re + g[j + 1].im * g[j + 1].im);
+  const dz gn = mk(0, 0) - conjz(s) * gj;
+  g[j + 1] = gn;
+  const double r = sqrt(gn.re * gn.re + gn.im * gn.im);
+  *hist = r;
+  if (res) *res = r;
 }
 
-// k_givens for the j in *jd; also records |g[j+1]| in hist[j]
-__global__ void k_givens_j(dz *__restrict__ H, int ldh, const int *__restrict__ jd, const double *__restrict__ hn,
-                           double *__restrict__ cs, dz *__restrict__ sn, dz *__restrict__ g,
-                           double *__restrict__ hist) {
-  if (threadIdx.x != 0 || blockIdx.x != 0) return;
-  const int j = *jd;
-  givens_step(H, ldh, j, *hn, cs, sn, g, hist + j);
+// h_{j+1,j} = ||w|| from the nupd partials; V_{j+1} = w / h_{j+1,j}, also into
+// vin, over the rows of block b; block 0 then takes the Givens step on column
+// j (|g_{j+1}| into rhist[j] and *res) and advances *jd.
+template <class K>
+__device__ __forceinline__ void kry_finish(const K &k, int b, double *res) {
+  __shared__ double red[4];
+  const int j = k.jd[1];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  double s = 0.0;
+  for (int i = tid; i < k.nupd; i += 256) s += k.npart[i];
+  s = wsum(s);
+  if (lane == 0) red[wave] = s;
+  __syncthreads();
+  const double hn = sqrt((red[0] + red[1]) + (red[2] + red[3])), sc = 1.0 / hn;
+  dz *v = k.V + (int64_t)(j + 1) * k.ldv;
+  for (int64_t e = (int64_t)b * 256 + tid; e < k.N; e += (int64_t)k.nupd * 256) {
+    const dz x = sc * k.w[e];
+    v[e] = x;
+    k.vin[e] = x;
+  }
+  if (b > 0) return;
+  givens_step(k.H, k.ldh, j, hn, k.cs, k.sn, k.g, k.rhist + j, res);
+  if (tid == 0) k.jd[0] = j + 1;
 }
+
+__global__ __launch_bounds__(256) void k_kry_dots(KryPair P) { kry_dots(P.p[blockIdx.z], blockIdx.x, blockIdx.y); }
+__global__ __launch_bounds__(256) void k_kry_update(KryPair P, int pass) { kry_update(P.p[blockIdx.y], blockIdx.x, pass); }
+__global__ __launch_bounds__(256) void k_kry_finish(KryPair P) { kry_finish(P.p[blockIdx.y], blockIdx.x, nullptr); }
 
 // y = R^{-1} g for the leading k x k upper triangle of H (single thread).
 __global__ void k_backsolve(const dz *__restrict__ H, int ldh, int k, const dz *__restrict__ g, dz *__restrict__ y) {
@@ -514,8 +573,7 @@ __global__ void k_ginit(dz *__restrict__ g, int m1, const double *__restrict__ b
 // The Arnoldi step of many cells at once (one GMRES process per cell): each
 // kernel's grid is the concatenation of the cells' grids (pre[c] .. pre[c+1]
 // are cell c's blocks), and a cell whose flag act[c] is 0 skips the step.
-// Per cell the arithmetic is that of the single-cell kernels, with the
-// two-stage reductions over nred blocks of the cell.
+// Per cell the arithmetic is that of the single-cell kernels.
 
 __device__ __forceinline__ int cell_of(const int *__restrict__ pre, int nc, int b) {
   int lo = 0, hi = nc - 1;
@@ -532,14 +590,6 @@ __device__ __forceinline__ int cell_of(const int *__restrict__ pre, int nc, int 
   if (!act[c_]) return;                               \
   const KryCell &K = cells[c_];                       \
   const int lb = (int)blockIdx.x - pre[c_];
-
-// vin = V_j
-__global__ void k_b_arn_begin(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
-                              const int *__restrict__ act) {
-  VIE_CELL_BEGIN
-  const int64_t k = (int64_t)lb * blockDim.x + threadIdx.x;
-  if (k < K.N) K.vin[k] = K.V[(int64_t)(*K.jd) * K.ldv + k];
-}
 
 // rhs of the triangular solves: tmp[off + i] = vin[off + perm[off + i]] per domain
 __global__ void k_b_permute(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
@@ -571,152 +621,22 @@ __global__ __launch_bounds__(256) void k_b_matvec(const KryCell *__restrict__ ce
   }
 }
 
-// partial inner products with V_0 .. V_j: local block (x, y) = chunk x of the
-// cell's nred, basis vectors 8 y .. 8 y + 7
-__global__ __launch_bounds__(256) void k_b_dots_j(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
-                                                  const int *__restrict__ act) {
-  constexpr int G = 8;
-  __shared__ dz red[G][4];
+// the five launches of the step: local block lb of the cell
+__global__ __launch_bounds__(256) void k_b_dots(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
+                                                const int *__restrict__ act) {
   VIE_CELL_BEGIN
-  const int nv = *K.jd + 1;
-  const int bx = lb % K.nred, by = lb / K.nred;
-  const int i0 = by * G;
-  if (i0 >= nv) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t N = K.N, ldv = K.ldv;
-  const int64_t chunk = (N + K.nred - 1) / K.nred;
-  const int64_t lo = bx * chunk, hi = min<int64_t>(N, lo + chunk);
-  double sr[G], si[G];
-#pragma unroll
-  for (int g = 0; g < G; ++g) sr[g] = si[g] = 0.0;
-  for (int64_t k = lo + tid; k < hi; k += 256) {
-    const dz ww = K.w[k];
-    double vr[G], vi[G];
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      const dz v = K.V[(int64_t)min(i0 + g, nv - 1) * ldv + k];
-      vr[g] = v.re;
-      vi[g] = v.im;
-    }
-#pragma unroll
-    for (int g = 0; g < G; ++g) {
-      sr[g] = fma(vr[g], ww.re, fma(vi[g], ww.im, sr[g]));
-      si[g] = fma(vr[g], ww.im, fma(-vi[g], ww.re, si[g]));
-    }
-  }
-#pragma unroll
-  for (int g = 0; g < G; ++g) {
-    const double a = wsum(sr[g]), b = wsum(si[g]);
-    if (lane == 0) red[g][wave] = mk(a, b);
-  }
-  __syncthreads();
-  if (tid < G && i0 + tid < nv)
-    K.dpart[(int64_t)bx * nv + i0 + tid] = red[tid][0] + red[tid][1] + red[tid][2] + red[tid][3];
+  kry_dots(K, lb % K.nd, lb / K.nd);
 }
-
-// s_i = sum_b part[b][i]; y_i = s_i; H[i][j] = s_i (pass 0) or += s_i (pass 1)
-__global__ void k_b_dots_reduce_j(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
-                                  const int *__restrict__ act, int pass) {
+__global__ __launch_bounds__(256) void k_b_update(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
+                                                  const int *__restrict__ act, int pass) {
   VIE_CELL_BEGIN
-  const int j = *K.jd, nv = j + 1;
-  const int i = lb * blockDim.x + threadIdx.x;
-  if (i >= nv) return;
-  dz s = mk(0, 0);
-  for (int b0 = 0; b0 < K.nred; b0 += 16) {
-    double pr[16], pi[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) {
-      const dz p = K.dpart[(int64_t)min(b0 + u, K.nred - 1) * nv + i];
-      pr[u] = p.re;
-      pi[u] = p.im;
-    }
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (b0 + u < K.nred) s = s + mk(pr[u], pi[u]);
-  }
-  dz *h = K.H + (int64_t)j * K.ldh;
-  h[i] = pass ? h[i] + s : s;
-  K.y[i] = s;
+  kry_update(K, lb, pass);
 }
-
-// w -= sum_{i<=j} V_i y_i
-__global__ __launch_bounds__(256) void k_b_update_j(const KryCell *__restrict__ cells, const int *__restrict__ pre,
-                                                    int nc, const int *__restrict__ act) {
+// (the step's residual estimate |g_{j+1}| into res[c])
+__global__ __launch_bounds__(256) void k_b_finish(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
+                                                  const int *__restrict__ act, double *__restrict__ res) {
   VIE_CELL_BEGIN
-  const int64_t k = (int64_t)lb * blockDim.x + threadIdx.x;
-  if (k >= K.N) return;
-  const int nv = *K.jd + 1;
-  dz s = K.w[k];
-  for (int i0 = 0; i0 < nv; i0 += 8) {
-    double vr[8], vi[8];
-#pragma unroll
-    for (int g = 0; g < 8; ++g) {
-      const dz v = K.V[(int64_t)min(i0 + g, nv - 1) * K.ldv + k];
-      vr[g] = v.re;
-      vi[g] = v.im;
-    }
-#pragma unroll
-    for (int g = 0; g < 8; ++g)
-      if (i0 + g < nv) s = s - mk(vr[g], vi[g]) * K.y[i0 + g];
-  }
-  K.w[k] = s;
-}
-
-// partial squared norms of w over the cell's nred chunks
-__global__ __launch_bounds__(256) void k_b_norm2(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
-                                                 const int *__restrict__ act) {
-  __shared__ double red[4];
-  VIE_CELL_BEGIN
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int64_t chunk = (K.N + K.nred - 1) / K.nred;
-  const int64_t lo = lb * chunk, hi = min<int64_t>(K.N, lo + chunk);
-  double s = 0;
-  for (int64_t k = lo + tid; k < hi; k += 256) s = fma(K.w[k].re, K.w[k].re, fma(K.w[k].im, K.w[k].im, s));
-  s = wsum(s);
-  if (lane == 0) red[wave] = s;
-  __syncthreads();
-  if (tid == 0) K.npart[lb] = red[0] + red[1] + red[2] + red[3];
-}
-
-// per cell (one thread each): h_{j+1,j} = ||w|| from the partials, then the
-// Givens update of column j (|g_{j+1}| into rhist[j])
-__global__ void k_b_norm_givens(const KryCell *__restrict__ cells, int nc, const int *__restrict__ act) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc || !act[c]) return;
-  const KryCell &K = cells[c];
-  double s = 0;
-  for (int b0 = 0; b0 < K.nred; b0 += 16) {
-    double p[16];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) p[u] = K.npart[min(b0 + u, K.nred - 1)];
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-      if (b0 + u < K.nred) s += p[u];
-  }
-  const double hn = sqrt(s);
-  K.scal[2] = hn;
-  givens_step(K.H, K.ldh, *K.jd, hn, K.cs, K.sn, K.g, K.rhist + *K.jd);
-}
-
-// V_{j+1} = w / h_{j+1,j}
-__global__ void k_b_scale_j(const KryCell *__restrict__ cells, const int *__restrict__ pre, int nc,
-                            const int *__restrict__ act) {
-  VIE_CELL_BEGIN
-  const int64_t k = (int64_t)lb * blockDim.x + threadIdx.x;
-  if (k >= K.N) return;
-  const double s = 1.0 / K.scal[2];
-  K.V[(int64_t)(*K.jd + 1) * K.ldv + k] = s * K.w[k];
-}
-
-// per cell: the step's residual estimate |g_{j+1}| into res[c], then j += 1
-__global__ void k_b_jinc(const KryCell *__restrict__ cells, int nc, const int *__restrict__ act,
-                         double *__restrict__ res) {
-  const int c = blockIdx.x * blockDim.x + threadIdx.x;
-  if (c >= nc || !act[c]) return;
-  const KryCell &K = cells[c];
-  const int j = *K.jd;
-  res[c] = K.rhist[j];
-  *K.jd = j + 1;
+  kry_finish(K, lb, res + c_);
 }
 #undef VIE_CELL_BEGIN
 

@@ -320,22 +320,34 @@ struct KryCell {
   const fz *Zs; const int64_t *rowptr; const int32_t *cols; const dz *vals;
   int64_t ld, N, ldv;
   dz *V; int *jd; dz *vin, *z, *w, *tmp;
-  dz *H; int ldh; double *cs; dz *sn, *g, *y; double *rhist, *scal;
-  dz *dpart; double *npart; int nred;
+  dz *H; int ldh; double *cs; dz *sn, *g; double *rhist;
+  dz *dpart; double *npart; int nd, nupd;   // partials of the inner products [nd][j + 1] and of the norm [nupd]
   const int32_t *perm; int ndom; int64_t dstart[kCellMaxDom];
   int precond;                 // 1: no preconditioner (the product takes V_j itself)
   int rpw;                     // matvec rows per wave (2, 4, 8): 4 RPW rows per thread block
 };
-__global__ void k_b_arn_begin(const KryCell *cells, const int *pre, int nc, const int *act);
+// One Krylov process of an Arnoldi step (fields as in KryCell); one or two of them per launch.
+struct KryOp {
+  int64_t N, ldv;
+  dz *V; int *jd; dz *vin, *w;
+  dz *H; int ldh; double *cs; dz *sn, *g; double *rhist;
+  dz *dpart; double *npart; int nd, nupd;
+};
+struct KryPair {
+  KryOp p[2];
+};
+// chunks of a process's inner products, and row blocks of its updates (the
+// norm's partials lie behind the inner products' in dpart, which holds
+// kRedBlocks (restart + 1) complex values)
+constexpr int kKryDots = 64, kKryUpd = 512;
+__global__ void k_kry_dots(KryPair P);               // grid (nd, groups of 8 basis vectors, processes)
+__global__ void k_kry_update(KryPair P, int pass);   // grid (nupd, processes)
+__global__ void k_kry_finish(KryPair P);             // grid (nupd, processes)
+__global__ void k_b_dots(const KryCell *cells, const int *pre, int nc, const int *act);
+__global__ void k_b_update(const KryCell *cells, const int *pre, int nc, const int *act, int pass);
+__global__ void k_b_finish(const KryCell *cells, const int *pre, int nc, const int *act, double *res);
 __global__ void k_b_permute(const KryCell *cells, const int *pre, int nc, const int *act);
 __global__ void k_b_matvec(const KryCell *cells, const int *pre, int nc, const int *act);
-__global__ void k_b_dots_j(const KryCell *cells, const int *pre, int nc, const int *act);
-__global__ void k_b_dots_reduce_j(const KryCell *cells, const int *pre, int nc, const int *act, int pass);
-__global__ void k_b_update_j(const KryCell *cells, const int *pre, int nc, const int *act);
-__global__ void k_b_norm2(const KryCell *cells, const int *pre, int nc, const int *act);
-__global__ void k_b_norm_givens(const KryCell *cells, int nc, const int *act);
-__global__ void k_b_scale_j(const KryCell *cells, const int *pre, int nc, const int *act);
-__global__ void k_b_jinc(const KryCell *cells, int nc, const int *act, double *res);
 
 struct MvVecs {
   const dz *x[2];
@@ -356,7 +368,7 @@ VIE_DECL_MATVEC(8)
 __global__ void k_combine(const dz *V, int64_t ldv, int nv, const dz *c, dz *y, int64_t N);
 __global__ void k_norm2(const dz *w, int64_t N, double *part);
 __global__ void k_norm_reduce(const double *part, int nblk, double *out);
-__global__ void k_scale(const dz *w, const double *nrm, dz *v, int64_t N);
+__global__ void k_scale(const dz *w, const double *nrm, dz *v, dz *vin, int64_t N);
 __global__ void k_axpy(dz *x, const dz *u, int64_t N);
 // point-Jacobi preconditioner: dinv = 1 / Z_mm from the stored operator (dense
 // entry, or the FP32 dense part plus the CSR near part, or the CSR alone),
@@ -368,14 +380,7 @@ __global__ void k_fill_const(dz *x, int64_t N, double re, double im);
 __global__ void k_backsolve(const dz *H, int ldh, int k, const dz *g, dz *y);
 __global__ void k_ginit(dz *g, int m1, const double *beta);
 // one Arnoldi step with the column index j read from device memory
-__global__ void k_arn_begin(const dz *V, int64_t ldv, const int *jd, dz *vin, int64_t N);
-__global__ void k_dots_j(const dz *V, int64_t ldv, const int *jd, const dz *w, int64_t N, dz *part);
-__global__ void k_dots_reduce_j(const dz *part, int nblk, const int *jd, dz *H, int ldh, dz *y, int pass);
-__global__ void k_update_j(const dz *V, int64_t ldv, const int *jd, const dz *c, dz *w, int64_t N);
-__global__ void k_scale_j(const dz *w, const double *nrm, dz *V, int64_t ldv, const int *jd, int64_t N);
-__global__ void k_givens_j(dz *H, int ldh, const int *jd, const double *hn, double *cs, dz *sn, dz *g, double *hist);
 __global__ void k_jset(int *jd, int v);
-__global__ void k_jinc(int *jd);
 
 // outputs (k_absorb.hip)
 // (per_tet, nullable: each tetrahedron's term before the domain sums)
