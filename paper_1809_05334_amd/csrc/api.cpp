@@ -309,17 +309,17 @@ int grid_matvec(vie_ctx *ctx, const dz *x, const dz *b, dz *y) {
     return fail(ctx, VIE_EDEVICE, "grid matvec: forward FFT failed");
   const GridGeom &G = ctx->grid->g;
   if (ctx->grid_sym)
-    hipLaunchKernelGGL(k_grid_mul_sym, dim3(nblk(nf, 32)), dim3(256), 0, ctx->stream, nf, G.nx, G.ny, G.pz,
+    hipLaunchKernelGGL(k_grid_mul_sym, dim3(nblk(nf, kGridTile)), dim3(kGridMulThreads), 0, ctx->stream, nf, G.nx, G.ny, G.pz,
                        (const dz *)ctx->ptr<dz>(L.gtab), (const dz *)fin, fout);
   else
-    hipLaunchKernelGGL(k_grid_mul, dim3(nblk(nf, 32)), dim3(256), 0, ctx->stream, nf,
+    hipLaunchKernelGGL(k_grid_mul, dim3(nblk(nf, kGridTile)), dim3(kGridMulThreads), 0, ctx->stream, nf,
                        (const dz *)ctx->ptr<dz>(L.gtab), (const dz *)fin, fout);
   e = hipGetLastError();
   if (e != hipSuccess) return fail(ctx, VIE_EDEVICE, "grid matvec: %s", hipGetErrorString(e));
   if (hipfftExecZ2Z(ctx->fft_fld, (hipfftDoubleComplex *)fout, (hipfftDoubleComplex *)fout, HIPFFT_BACKWARD) !=
       HIPFFT_SUCCESS)
     return fail(ctx, VIE_EDEVICE, "grid matvec: inverse FFT failed");
-  hipLaunchKernelGGL(k_grid_apply, dim3(nblk(t.N, 4)), dim3(256), 0, ctx->stream, (int64_t)t.N, gg,
+  hipLaunchKernelGGL(k_grid_apply, dim3(nblk(t.N, 4 * kGridRows)), dim3(256), 0, ctx->stream, (int64_t)t.N, gg,
                      (const int32_t *)ctx->ptr<int32_t>(L.gtet), (const int32_t *)ctx->ptr<int32_t>(L.gface),
                      (const int32_t *)ctx->ptr<int32_t>(L.ghalf), (const int32_t *)ctx->ptr<int32_t>(L.utet),
                      (const int32_t *)ctx->ptr<int32_t>(L.uk), (const TetGeom *)ctx->ptr<TetGeom>(L.tg),

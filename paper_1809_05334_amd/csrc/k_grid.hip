@@ -130,16 +130,23 @@ __global__ __launch_bounds__(256) void k_grid_gather_face(int nface, const GridG
 // and each table entry is read once from HBM (the 32 lanes of an s-group
 // read kGridTile consecutive frequencies of one table row).  Thread t owns
 // frequency t % kGridTile of the tile and the sublattices s = t / kGridTile
-// + 8 i: the scalar potential from every charge field and, for tetrahedron
-// sublattices, the vector potential from the current fields.
-constexpr int kGridTile = 32;
+// + (threads / kGridTile) i: the scalar potential from every charge field and, for tetrahedron
+// sublattices, the vector potential from the current fields.  The table
+// (57.6 KB per frequency) bounds it: every entry serves all four potentials
+// while it is in a register (a second sweep for the vector potential found it
+// no longer in the L2), and kGridBatch entries per thread are in flight.
+// 16 x 16 x 50 frequencies (737 MB of table): 172 us, 4.8 TB/s in pieces of
+// 512 B (a sum over as many bytes in one piece: 130 us); two sweeps of batches
+// of four, 256 threads, took 178.
+constexpr int kGridBatch = 12;
+static_assert(kGridTetSub % kGridBatch == 0 && kGridSub % kGridBatch == 0, "whole batches of table entries");
 template <bool SYM>
 __device__ __forceinline__ void grid_mul_body(int64_t nf, int nx, int ny, int pz, const dz *__restrict__ tab,
                                               const dz *__restrict__ fin, dz *__restrict__ fout) {
   __shared__ dz sf[kGridFields][kGridTile];
   const int64_t f0 = (int64_t)blockIdx.x * kGridTile;
   const int nt = (int)min<int64_t>(kGridTile, nf - f0);
-  for (int e = threadIdx.x; e < kGridFields * kGridTile; e += 256) {
+  for (int e = threadIdx.x; e < kGridFields * kGridTile; e += kGridMulThreads) {
     const int c = e / kGridTile, fi = e % kGridTile;
     sf[c][fi] = fi < nt ? fin[(int64_t)c * nf + f0 + fi] : mk(0.0, 0.0);
   }
@@ -153,62 +160,63 @@ __device__ __forceinline__ void grid_mul_body(int64_t nf, int nx, int ny, int pz
     const int x = (int)(f % nx), y = (int)((f / nx) % ny), z = (int)(f / ((int64_t)nx * ny));
     fr = (nx - x) % nx + (int64_t)nx * ((ny - y) % ny + (int64_t)ny * ((pz - z) % pz));
   }
-  // Table row of output s: without SYM the 60 pairs (s, s2) at f, one table
-  // stride apart.  With SYM, for s2 < s the stored pair (s2, s) at -f (its
-  // slot advances by kGridSub - s2 - 1 from s2 to s2 + 1), and for
-  // s2 >= s the pairs (s, s2) at f, in consecutive slots.
-  auto entry = [&](int s, int s2) -> const dz * {
-    if (!SYM) return tab + ((int64_t)s * kGridSub + s2) * nf + f;
-    return s2 < s ? tab + (int64_t)grid_sym_pair(s2, s) * nf + fr : tab + (int64_t)grid_sym_pair(s, s2) * nf + f;
+  // Table entry of the pair (s, s2): without SYM at f; with SYM, for s2 < s the
+  // stored pair (s2, s) at -f, else the pair (s, s2) at f.
+  auto entry = [&](int s, int s2) -> dz {
+    if (!SYM) return tab[((int64_t)s * kGridSub + s2) * nf + f];
+    return s2 < s ? tab[(int64_t)grid_sym_pair(s2, s) * nf + fr] : tab[(int64_t)grid_sym_pair(s, s2) * nf + f];
   };
-  for (int s = sg; s < kGridSub; s += 256 / kGridTile) {
+  for (int s = sg; s < kGridSub; s += kGridMulThreads / kGridTile) {
     dz acc = mk(0.0, 0.0);
-    if (SYM) {
-      const dz *K = tab + (int64_t)s * nf + fr;   // slot of (0, s)
-#pragma unroll 4
-      for (int s2 = 0; s2 < s; ++s2) {
-        acc = acc + *K * sf[s2][fi];
-        K += (int64_t)(kGridSub - s2 - 1) * nf;   // (s2, s) -> (s2 + 1, s)
-      }
-      K = tab + (int64_t)grid_sym_pair(s, s) * nf + f;
-#pragma unroll 4
-      for (int s2 = s; s2 < kGridSub; ++s2, K += nf) acc = acc + *K * sf[s2][fi];
-    } else {
-      const dz *K = tab + (int64_t)s * kGridSub * nf + f;
-#pragma unroll 4
-      for (int s2 = 0; s2 < kGridSub; ++s2) acc = acc + K[(int64_t)s2 * nf] * sf[s2][fi];
-    }
-    fout[(int64_t)s * nf + f] = acc;
+    int s2 = 0;
     if (s < kGridTetSub) {
       dz a0 = mk(0.0, 0.0), a1 = mk(0.0, 0.0), a2 = mk(0.0, 0.0);
-#pragma unroll 4
-      for (int s2 = 0; s2 < kGridTetSub; ++s2) {
-        const dz k = *entry(s, s2);
-        a0 = a0 + k * sf[kGridSub + s2][fi];
-        a1 = a1 + k * sf[kGridSub + kGridTetSub + s2][fi];
-        a2 = a2 + k * sf[kGridSub + 2 * kGridTetSub + s2][fi];
+      for (; s2 < kGridTetSub; s2 += kGridBatch) {
+        dz k[kGridBatch];
+#pragma unroll
+        for (int u = 0; u < kGridBatch; ++u) k[u] = entry(s, s2 + u);
+#pragma unroll
+        for (int u = 0; u < kGridBatch; ++u) {
+          cmac(acc, k[u], sf[s2 + u][fi]);
+          cmac(a0, k[u], sf[kGridSub + s2 + u][fi]);
+          cmac(a1, k[u], sf[kGridSub + kGridTetSub + s2 + u][fi]);
+          cmac(a2, k[u], sf[kGridSub + 2 * kGridTetSub + s2 + u][fi]);
+        }
       }
       fout[(int64_t)(kGridSub + s) * nf + f] = a0;
       fout[(int64_t)(kGridSub + kGridTetSub + s) * nf + f] = a1;
       fout[(int64_t)(kGridSub + 2 * kGridTetSub + s) * nf + f] = a2;
     }
+    for (; s2 < kGridSub; s2 += kGridBatch) {
+      dz k[kGridBatch];
+#pragma unroll
+      for (int u = 0; u < kGridBatch; ++u) k[u] = entry(s, s2 + u);
+#pragma unroll
+      for (int u = 0; u < kGridBatch; ++u) cmac(acc, k[u], sf[s2 + u][fi]);
+    }
+    fout[(int64_t)s * nf + f] = acc;
   }
 }
 
-__global__ __launch_bounds__(256) void k_grid_mul(int64_t nf, const dz *__restrict__ tab, const dz *__restrict__ fin,
+__global__ __launch_bounds__(kGridMulThreads) void k_grid_mul(int64_t nf, const dz *__restrict__ tab, const dz *__restrict__ fin,
                                                   dz *__restrict__ fout) {
   grid_mul_body<false>(nf, 1, 1, 1, tab, fin, fout);
 }
-__global__ __launch_bounds__(256) void k_grid_mul_sym(int64_t nf, int nx, int ny, int pz, const dz *__restrict__ tab,
+__global__ __launch_bounds__(kGridMulThreads) void k_grid_mul_sym(int64_t nf, int nx, int ny, int pz, const dz *__restrict__ tab,
                                                       const dz *__restrict__ fin, dz *__restrict__ fout) {
   grid_mul_body<true>(nf, nx, ny, pz, tab, fin, fout);
 }
 
-// y = Z x (or b - Z x), one wave per unknown m: lanes 0-7 the far
-// potentials at the four points of each of m's tetrahedra (demodulated by
-// e^{-j kt.o}), lanes 8-10 those at the three points of m's face when it is a
-// half-SWG face, and all lanes m's row of the near part (CSR, FP64); the wave
-// sum is written by lane 0.
+// y = Z x (or b - Z x), kGridRows unknowns per wave.  Far part: eight lanes
+// per unknown, the far potentials at the four points of each of its
+// tetrahedra (demodulated by e^{-j kt.o}), the first three lanes also those at
+// the three points of its face when it is a half-SWG face.  Near part: the
+// unknowns' rows (CSR, FP64) one after another over all lanes, the next row's
+// entries in flight while this row's products are formed.  The chains of
+// dependent loads (4 KB of data per unknown) bound it, not the rate of the
+// memory, so a wave takes them once for its unknowns, with few registers.
+// N = 74,240: 82 us (one unknown per wave, its parts one after another: 99).
+constexpr int kGridRowBatch = 4;   // a row's entries per lane before the loop (a uniform mesh has about 190 per row)
 __global__ __launch_bounds__(256) void k_grid_apply(
     int64_t N, const GridGeom *__restrict__ gg, const int32_t *__restrict__ gtet, const int32_t *__restrict__ gface,
     const int32_t *__restrict__ ghalf, const int32_t *__restrict__ utet, const int32_t *__restrict__ uk,
@@ -217,42 +225,81 @@ __global__ __launch_bounds__(256) void k_grid_apply(
     const int32_t *__restrict__ cols, const dz *__restrict__ vals, const dz *__restrict__ x, const dz *__restrict__ b,
     dz *__restrict__ y) {
   const int lane = threadIdx.x & 63;
-  const int64_t m = (int64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (m >= N) return;   // the whole wave
-  const GridGeom &G = *gg;
-  const int64_t nf = G.nf;
-  dz acc = mk(0.0, 0.0);
-  if (lane < 8) {
-    const int h = lane >> 2, q = lane & 3;
-    const int T = utet[2 * m + h];
+  const int64_t m0 = ((int64_t)blockIdx.x * 4 + (threadIdx.x >> 6)) * kGridRows;
+  if (m0 >= N) return;   // the whole wave
+  const int nrow = (int)min<int64_t>(kGridRows, N - m0);
+  // row r holds the entries [ptr(r), ptr(r + 1)), at least its diagonal
+  const int64_t pv = rowptr[m0 + min(lane, nrow)];
+  const auto ptr = [&](int r) { return (int64_t)readlane64((unsigned long long)pv, r); };
+  int32_t col[kGridRowBatch];
+  dz val[kGridRowBatch];
+  const auto fetch = [&](int r) {
+    const int64_t e0 = ptr(r), e1 = ptr(r + 1);
+#pragma unroll
+    for (int u = 0; u < kGridRowBatch; ++u) {
+      const int64_t e = min(e0 + lane + 64 * u, e1 - 1);
+      col[u] = cols[e];
+      val[u] = vals[e];
+    }
+  };
+  fetch(0);
+  dz far = mk(0.0, 0.0);
+  {
+    const GridGeom &G = *gg;
+    const int64_t nf = G.nf;
+    const int64_t m = m0 + min(lane >> 3, nrow - 1);
+    const int h = (lane >> 2) & 1, q = lane & 3;
+    const int T = utet[2 * m + h], face = ghalf[m];
     if (T >= 0) {
       const int k = uk[2 * m + h];
       const int slot = gtet[2 * T], type = gtet[2 * T + 1];
-      const int bx = slot % G.nx, by = (slot / G.nx) % G.ny, bz = slot / (G.nx * G.ny);
       const int s = 4 * type + q;
+      const dz pot = fout[(int64_t)s * nf + slot];
+      dz cur[3];
+#pragma unroll
+      for (int d = 0; d < 3; ++d) cur[d] = fout[(int64_t)(kGridSub + kGridTetSub * d + s) * nf + slot];
+      const int bx = slot % G.nx, by = (slot / G.nx) % G.ny, bz = slot / (G.nx * G.ny);
       dz ra = mk(0.0, 0.0);
+#pragma unroll
       for (int d = 0; d < 3; ++d) {
         const double vk = tg[T].v[k][d] - (G.org[d] + (d == 0 ? bx : d == 1 ? by : bz) * G.h[d]);
-        ra = ra + (G.pos[s][d] - vk) * fout[(int64_t)(kGridSub + kGridTetSub * d + s) * nf + slot];
+        ra = ra + (G.pos[s][d] - vk) * cur[d];
       }
       const dz ph = cexpj(-(kx * bx * G.h[0] + ky * by * G.h[1]));
-      acc = ((0.25 * tg[T].vol) * alpha[4 * T + k]) * (ph * (fout[(int64_t)s * nf + slot] - k0sq9 * ra));
+      far = ((0.25 * tg[T].vol) * alpha[4 * T + k]) * (ph * (pot - k0sq9 * ra));
     }
-  } else if (lane < 11) {
-    const int i = ghalf[m];
-    if (i >= 0) {
-      const int bx = gface[4 * i], by = gface[4 * i + 1], bz = gface[4 * i + 2], type = gface[4 * i + 3];
+    if (face >= 0 && (lane & 7) < 3) {
+      const int bx = gface[4 * face], by = gface[4 * face + 1], bz = gface[4 * face + 2], type = gface[4 * face + 3];
       const int64_t slot = bx % G.nx + (int64_t)G.nx * (by % G.ny + (int64_t)G.ny * bz);
-      acc = (-fg[i].area / 3.0 * cexpj(-(kx * bx * G.h[0] + ky * by * G.h[1]))) *
-            fout[(int64_t)(kGridTetSub + 3 * type + (lane - 8)) * nf + slot];
+      far = far + (-fg[face].area / 3.0 * cexpj(-(kx * bx * G.h[0] + ky * by * G.h[1]))) *
+                      fout[(int64_t)(kGridTetSub + 3 * type + (lane & 7)) * nf + slot];
     }
   }
-  for (int64_t e = rowptr[m] + lane; e < rowptr[m + 1]; e += 64) acc = acc + vals[e] * x[cols[e]];
-  for (int o = 32; o > 0; o >>= 1) {
-    acc.re += __shfl_xor(acc.re, o);
-    acc.im += __shfl_xor(acc.im, o);
+  for (int o = 4; o > 0; o >>= 1) {
+    far.re += __shfl_xor(far.re, o);
+    far.im += __shfl_xor(far.im, o);
   }
-  if (lane == 0) y[m] = b ? b[m] - acc : acc;
+  for (int r = 0; r < nrow; ++r) {
+    const int64_t e0 = ptr(r), e1 = ptr(r + 1);
+    dz xv[kGridRowBatch], v[kGridRowBatch];
+#pragma unroll
+    for (int u = 0; u < kGridRowBatch; ++u) {
+      xv[u] = x[col[u]];
+      v[u] = val[u];
+    }
+    fetch(min(r + 1, nrow - 1));
+    dz acc = mk(0.0, 0.0);
+#pragma unroll
+    for (int u = 0; u < kGridRowBatch; ++u)
+      if (e0 + lane + 64 * u < e1) cmac(acc, v[u], xv[u]);
+    for (int64_t e = e0 + lane + 64 * kGridRowBatch; e < e1; e += 64) cmac(acc, vals[e], x[cols[e]]);
+    acc = wave_sum_dpp(acc);
+    if (lane >> 3 == r) far = far + acc;
+  }
+  if ((lane & 7) == 0 && lane >> 3 < nrow) {
+    const int64_t m = m0 + (lane >> 3);
+    y[m] = b ? b[m] - far : far;
+  }
 }
 
 }  // namespace vie

@@ -205,29 +205,6 @@ __device__ __forceinline__ dz wave_sum(dz v) {
   return v;
 }
 
-// Sums over a 16-lane row of the wave, in every lane of the row, by DPP
-// moves (no shared-memory traffic): lane pairs, quads, half rows, rows.
-template <int CTRL>
-__device__ __forceinline__ double dpp_d(double v) {
-  return __longlong_as_double((long long)dpp64<CTRL>((unsigned long long)__double_as_longlong(v)));
-}
-__device__ __forceinline__ double row16_sum(double v) {
-  v = v + dpp_d<0xb1>(v);    // quad_perm [1,0,3,2]
-  v = v + dpp_d<0x4e>(v);    // quad_perm [2,3,0,1]
-  v = v + dpp_d<0x141>(v);   // row_half_mirror
-  return v + dpp_d<0x140>(v);   // row_mirror
-}
-__device__ __forceinline__ dz row16_sum(dz v) { return mk(row16_sum(v.re), row16_sum(v.im)); }
-// the sum over the whole wave (uniform): the four row sums added in row order
-__device__ __forceinline__ double wave_sum_dpp(double v) {
-  v = row16_sum(v);
-  const auto rl = [](double x, int l) {
-    return __longlong_as_double((long long)readlane64((unsigned long long)__double_as_longlong(x), l));
-  };
-  return ((rl(v, 0) + rl(v, 16)) + rl(v, 32)) + rl(v, 48);
-}
-__device__ __forceinline__ dz wave_sum_dpp(dz v) { return mk(wave_sum_dpp(v.re), wave_sum_dpp(v.im)); }
-
 // One step of the blocked triangular solves (L forward or U backward) of
 // every material domain at once, with nb = kTrsvNB diagonal blocks.  Blocks
 // are numbered in the order of the sweep; step j of domain d reduces block j.

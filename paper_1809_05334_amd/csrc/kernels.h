@@ -406,6 +406,8 @@ __global__ void k_grid_gather_face(int nface, const GridGeom *gg, const int32_t 
                                    const dz *sigma, const dz *x, double kx, double ky, dz *fld);
 __global__ void k_grid_mul(int64_t nf, const dz *tab, const dz *fin, dz *fout);
 __global__ void k_grid_mul_sym(int64_t nf, int nx, int ny, int pz, const dz *tab, const dz *fin, dz *fout);
+constexpr int kGridTile = 32, kGridMulThreads = 512;   // frequencies and threads of a block of k_grid_mul
+constexpr int kGridRows = 8;           // unknowns per wave of k_grid_apply
 __global__ void k_grid_apply(int64_t N, const GridGeom *gg, const int32_t *gtet, const int32_t *gface,
                              const int32_t *ghalf, const int32_t *utet, const int32_t *uk, const TetGeom *tg,
                              const FaceGeom *fg, const dz *alpha, const dz *fout, double k0sq9, double kx, double ky,

@@ -236,3 +236,20 @@ def test_grid_and_jacobi_are_refused_where_not_offered(vie):
         b.solve([0], restart=40)
     assert e.value.code == vie.VIE_EINVAL and "Jacobi" in str(e.value)
     d.close()
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(3, 3, 1), (3, 3, 2), (5, 3, 1), (7, 5, 3)])
+@pytest.mark.parametrize("th", [0.0, 0.4])
+def test_grid_product_at_row_and_frequency_remainders(vie, nx, ny, nz, th):
+    """Unknowns not a multiple of a wave's rows, frequencies not one of a
+    tile's; theta = 0 reads the symmetric table.  The bar is the one of the
+    dense comparisons above (both operators hold rounding-level errors)."""
+    m = uniform_grid(nx, ny, nz, 20.0 * nx, 25.0 * ny, 15.0 * nz)
+    eps = np.array([2.4 + 0.2j, 3.3 + 0.05j])[m.tet_domain]
+    g, N = solver(vie, m, vie.VIE_GRID_FP64)
+    d, _ = solver(vie, m, vie.VIE_FP64)
+    g.fill(550.0, th, 0.3, eps)
+    d.fill(550.0, th, 0.3, eps)
+    x = seeded_x(N, 4)
+    assert rel(g.apply_Z(x), d.apply_Z(x)) < 1e-10
+    g.close(); d.close()
