@@ -208,6 +208,7 @@ Layout make_layout(const MeshTopology &t, int restart, int64_t nnear, int nface,
   put(L.kv, 8 * 3 * 2 * 32);
   // solver scratch; also the reduction target of the R/T projections (6 doubles per k-vector, <= 64)
   put(L.idx, std::max<size_t>(16 * (size_t)N, 8 * 6 * 64));
+  put(L.luq, 4 * (size_t)kLuQueue);
   L.total = off;
   return L;
 }
@@ -708,6 +709,7 @@ int bind_impl(vie_ctx *ctx, void *dev_ptr, size_t bytes, int precision, int rest
   if (rc) return rc;
   // the panel and tournament counters start (and always end) at zero
   HIPCK(hipMemsetAsync(ctx->ws + L.lucnt.off, 0, L.lucnt.bytes, ctx->stream));
+  HIPCK(hipMemsetAsync(ctx->ws + L.luq.off, 0, L.luq.bytes, ctx->stream));
   HIPCK(hipMemsetAsync(ctx->ws + L.ttcnt.off, 0, L.ttcnt.bytes, ctx->stream));
   HIPCK(hipStreamSynchronize(ctx->stream));   // host staging vectors go out of scope
   ctx->state = S_BOUND;
@@ -1084,8 +1086,10 @@ enum LuKernel { LU_PIVOT, LU_COL, LU_SWAP, LU_TRSM, LU_GEMM, LU_GEMM2, LU_TSEL, 
 // gcols - 1 of the trailing matrix, gcols <= 0 for all from gcol0.)
 template <typename BlocksOf>
 void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &doms, int j, int k0, BlocksOf blocks_of,
-               int all_cols = 0, int gcol0 = 0, int gcols = 0, int c_lo = 0, int c_hi = 0) {
+               int all_cols = 0, int gcol0 = 0, int gcols = 0, int c_lo = 0, int c_hi = 0, int *queue = nullptr) {
   LuStep st{};
+  st.queue = queue;
+  st.free_cus = kGemm2FreeCus;
   st.j = j;
   st.k0 = k0;
   st.all_cols = all_cols;
@@ -1118,7 +1122,11 @@ void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &d
         else hipLaunchKernelGGL(k_lu_gemm_z, dim3(total), dim3(256), 0, sm, st);
         break;
       case LU_GEMM2:
-        if (f32) hipLaunchKernelGGL(k_lu_gemm2_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
+        // a block per tile and per slot of the units left free (32 shader engines, two slots per unit)
+        if (queue) total = std::min(total + 64 * kGemm2FreeCus, kGemm2Slots);
+        if (queue && f32) hipLaunchKernelGGL(k_lu_gemm2q_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
+        else if (queue) hipLaunchKernelGGL(k_lu_gemm2q_z, dim3(total), dim3(kGemm2Threads), 0, sm, st);
+        else if (f32) hipLaunchKernelGGL(k_lu_gemm2_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         else hipLaunchKernelGGL(k_lu_gemm2_z, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         break;
       case LU_TSEL:
@@ -1285,7 +1293,7 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
       return nc > 0 ? 8 * (int)nblk(nr * nc, 8) : 0;
     };
     // each bulk update between an event pair of ctx's pool (its device time)
-    auto timed_gemm2 = [&](int k0, int gcol0, int gcols) -> int {
+    auto timed_gemm2 = [&](int k0, int gcol0, int gcols, int *queue = nullptr) -> int {
       if ((int)ctx->upd_ev.size() < 2 * (ctx->upd_n + 1)) {
         hipEvent_t e0 = nullptr, e1 = nullptr;
         HIPCK(hipEventCreate(&e0));
@@ -1295,11 +1303,12 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
       }
       HIPCK(hipEventRecord(ctx->upd_ev[2 * ctx->upd_n], stream));
       lu_launch(f32, stream, LU_GEMM2, doms, k0, k0, [&](int d) { return gemm2_blocks(d, k0, gcol0, gcols); }, 0, gcol0,
-                gcols);
+                gcols, 0, 0, queue);
       HIPCK(hipEventRecord(ctx->upd_ev[2 * ctx->upd_n + 1], stream));
       ++ctx->upd_n;
       return VIE_OK;
     };
+    int *queue = ctx->ptr<int>(ctx->L.luq);
     constexpr int kBig = 1 << 30;
     auto panels = [&](int k0, hipStream_t sm) {
       const int kb = k0 + kLuNB, pe = k0 + 2 * kLuNB;
@@ -1335,7 +1344,9 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
         HIPCK(hipStreamWaitEvent(side, ev_la, 0));
         panels(next, side);
         HIPCK(hipEventRecord(ev_ts, side));
-        if (int rc = timed_gemm2(k0, 2 * kLuNB / tn, 0)) return rc;
+        int64_t tiles = 0;
+        for (size_t d = 0; d < doms.size(); ++d) tiles += gemm2_blocks((int)d, k0, 2 * kLuNB / tn, 0);
+        if (int rc = timed_gemm2(k0, 2 * kLuNB / tn, 0, (wide || !f32) && tiles <= kGemm2QueueMax ? queue : nullptr)) return rc;
       }
       LAUNCHCK();
     }

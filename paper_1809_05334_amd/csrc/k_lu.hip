@@ -877,12 +877,54 @@ __global__ __launch_bounds__(256) void k_lu_gemm_c(LuStep st) { lu_gemm_body<fz>
 // domain's sequence (q = tiles / 8, rounded up), and the sequence walks
 // groups of 8 column tiles row by row, so the 64 or so blocks an XCD holds at
 // once share 8 row panels of L21 and 8 column panels of U12 in its L2.
+//
+// With QUEUE a launch has at most kGemm2Slots blocks, which take tiles in
+// turn from the lists of the eight XCDs (their own first), and a block that
+// starts on one of the compute units left to the panels of the next pair ends
+// at once: those units stay free for the side stream's kernels while the
+// update runs.  Which units those are is only a hint: at most half the blocks
+// may go, and the others take every tile wherever they run.
 template <typename C> struct Gemm2Cfg;
 template <> struct Gemm2Cfg<fz> { static constexpr int TM = 128, TN = 128, WR = 2, WC = 4; };
 template <> struct Gemm2Cfg<dz> { static constexpr int TM = 128, TN = 64, WR = 4, WC = 2; };
 constexpr int kGemm2K = 2 * kLuNB, kGemm2Group = 8;
+constexpr int kHwRegHwId = 4 | 0 << 6 | 31 << 11;   // s_getreg: the whole HW_ID register (compute unit in bits 11:8)
+constexpr int kGemm2FreeCu = 2;   // first of the compute units left free, by its number in its shader engine
 
+// Tiles of domain d in a launch.
 template <typename C>
+__device__ __forceinline__ int gemm2_tiles(const LuStep &st, int d) {
+  const int rest = st.d[d].n - st.k0 - kGemm2K;
+  if (rest <= 0) return 0;
+  const int nr = (rest + Gemm2Cfg<C>::TM - 1) / Gemm2Cfg<C>::TM, ntc = (rest + Gemm2Cfg<C>::TN - 1) / Gemm2Cfg<C>::TN;
+  return nr * max(0, st.gcols > 0 ? min(st.gcols, ntc - st.gcol0) : ntc - st.gcol0);
+}
+
+// The next tile of a launch with a queue (one thread): entry p of an XCD's
+// list, the eighths of the domains' tile sequences one after another; the
+// block's own XCD's list first, then the others' (bit x of `done`: list x is
+// empty).  Returns d << 24 | tile, or -1 when every list is empty.
+template <typename C>
+__device__ __forceinline__ int gemm2_claim(const LuStep &st, int xcd, unsigned &done) {
+  for (int k = 0; k < 8; ++k) {
+    const int x = (xcd + k) & 7;
+    while (!(done >> x & 1)) {
+      int p = __hip_atomic_fetch_add(st.queue + 16 * x, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      int d = 0, q = 0, total = 0;
+      for (; d < st.ndom; ++d) {
+        total = gemm2_tiles<C>(st, d);
+        q = (total + 7) / 8;
+        if (p < q) break;
+        p -= q;
+      }
+      if (d == st.ndom) done |= 1u << x;
+      else if (x * q + p < total) return d << 24 | (x * q + p);
+    }
+  }
+  return -1;
+}
+
+template <typename C, bool QUEUE>
 __device__ __forceinline__ void lu_gemm2_body(const LuStep &st) {
   typedef typename Mfma<C>::R R;
   typedef typename Mfma<C>::Acc Acc;
@@ -892,16 +934,41 @@ __device__ __forceinline__ void lu_gemm2_body(const LuStep &st) {
   constexpr int kPerA = TM * kGemmKC / NT, kPerB = kGemmKC * TN / NT;
   __shared__ R As[2][TM][kGemmKC + 1];   // [0]: real, [1]: imaginary parts
   __shared__ R Bs[2][kGemmKC][TN + 1];
-  const LuDom &D = st.d[lu_domain(st)];
+  __shared__ int s_next;
+  int d, t;
+  unsigned done = 0;
+  if (!QUEUE) {
+    d = lu_domain(st);
+    const int b = blockIdx.x - st.d[d].first_block, total = gemm2_tiles<C>(st, d);
+    t = (b & 7) * ((total + 7) / 8) + (b >> 3);
+    if (t >= total) return;
+  } else {
+    if (threadIdx.x == 0) {
+      // a block on one of the compute units left to the side stream's panels
+      // goes away, unless too many have
+      const int cu = __builtin_amdgcn_s_getreg(kHwRegHwId) >> 8 & 15;
+      const bool leave = cu >= kGemm2FreeCu && cu < kGemm2FreeCu + st.free_cus &&
+                         __hip_atomic_fetch_add(st.queue + 128, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
+                             (int)gridDim.x / 2;
+      s_next = leave ? -1 : gemm2_claim<C>(st, blockIdx.x & 7, done);
+    }
+    __syncthreads();
+  }
+  for (;;) {
+  if (QUEUE) {
+    const int c = __builtin_amdgcn_readfirstlane(s_next);
+    if (c < 0) break;
+    d = c >> 24;
+    t = c & 0xffffff;
+    __syncthreads();
+    if (threadIdx.x == 0) s_next = gemm2_claim<C>(st, blockIdx.x & 7, done);
+  }
+  const LuDom &D = st.d[d];
   const int k0 = st.k0, n = D.n, base = k0 + kGemm2K;
   const int64_t ld = D.ld;
   C *__restrict__ A = (C *)D.A;
   const int nr = (n - base + TM - 1) / TM, ntc = (n - base + TN - 1) / TN;
   const int nc = st.gcols > 0 ? min(st.gcols, ntc - st.gcol0) : ntc - st.gcol0;
-  const int total = nr * nc, q = (total + 7) / 8;
-  const int b = blockIdx.x - D.first_block;
-  const int t = (b & 7) * q + (b >> 3);
-  if (t >= total) return;
   const int g = t / (kGemm2Group * nr), rem = t - g * kGemm2Group * nr;
   const int gw = min(kGemm2Group, nc - g * kGemm2Group);
   const int r0 = base + (rem / gw) * TM;
@@ -1016,10 +1083,19 @@ __device__ __forceinline__ void lu_gemm2_body(const LuStep &st) {
           Cb[i * ld32 + j] = cx<C>::make(old[c][r].re - cre[a][c][r], old[c][r].im - cim[a][c][r]);
       }
   }
+  if (!QUEUE) return;
+  }
+  // the last block of the launch puts the counters back to zero
+  if (threadIdx.x == 0 &&
+      __hip_atomic_fetch_add(st.queue + 144, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) {
+    for (int x = 0; x < 10; ++x) __hip_atomic_store(st.queue + 16 * x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
 }
 
-__global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2_z(LuStep st) { lu_gemm2_body<dz>(st); }
-__global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2_c(LuStep st) { lu_gemm2_body<fz>(st); }
+__global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2_z(LuStep st) { lu_gemm2_body<dz, false>(st); }
+__global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2_c(LuStep st) { lu_gemm2_body<fz, false>(st); }
+__global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2q_z(LuStep st) { lu_gemm2_body<dz, true>(st); }
+__global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2q_c(LuStep st) { lu_gemm2_body<fz, true>(st); }
 
 __global__ __launch_bounds__(1024) void k_lu_pivot_z(LuStep st) { lu_pivot_body<dz>(st); }
 __global__ __launch_bounds__(1024) void k_lu_pivot_c(LuStep st) { lu_pivot_body<fz>(st); }

@@ -141,6 +141,20 @@ constexpr int kLuNB = 64;
 constexpr int kColT = 4;        // lanes per row in the panel column kernel
 constexpr int kColRows = 64;    // rows per thread block of the panel column kernel (256 / kColT)
 constexpr int kLuMaxDom = 8;
+// The bulk update leaves compute units to the next pair's panels on the side
+// stream (k_lu_gemm2q: as many blocks as the chip holds take the tiles in
+// turn) when the panels' tournament nodes fill a whole compute unit each:
+// beside one block per tile, whose next block takes every half unit that
+// falls free, such a node starts only when the update is over.  Above
+// kGemm2QueueMax tiles the unit per shader engine costs the update more than
+// the panels it hides.  Factor, FP64, N = 15,840 (15,000 tiles at first):
+// 119 ms with one unit per shader engine, 123 with two, 130 with three, 141
+// with a block per tile; FP32, six cells of up to 5,500 unknowns (wide
+// nodes): 50.7 against 53.4.  FP32, N = 37,376, whose nodes take half a unit:
+// 442 against 385, so not for those.
+constexpr int kGemm2FreeCus = 1;      // per shader engine, of its 8
+constexpr int kGemm2Slots = 512;      // blocks of k_lu_gemm2 that the 256 compute units hold at once
+constexpr int kGemm2QueueMax = 50000;
 constexpr int kGemm2Threads = 512;   // threads per block of the two-panel trailing update (k_lu_gemm2)
 // Tournament nodes: 256 rows and four children per node; a row takes two
 // lanes for FP64 factors (512 threads), one lane for FP32 (256 threads).  The
@@ -153,6 +167,7 @@ constexpr int kTsFanZ = 4, kTsFanC = 4, kTsFanW = 8;
 constexpr int kTsRowsZ = kTsFanZ * kLuNB, kTsRowsC = kTsFanC * kLuNB, kTsRowsW = kTsFanW * kLuNB;
 constexpr int kTsLprZ = 2, kTsLprC = 1;
 constexpr int kTsWideMax = 8192;
+constexpr int kLuQueue = 160;   // counters of a tile queue: 8 lists, blocks gone, blocks ended, 16 ints apart
 struct LuDom {
   void *A;            // the domain's block (dz or fz), row-major, leading dimension ld, factored in place
   int64_t ld;
@@ -175,6 +190,9 @@ struct LuStep {
   int all_cols;       // k_lu_swap columns: 0 all but the panel's, 1 all, 2 only [c_lo, c_hi), 3 all but [c_lo, c_hi)
   int gcol0, gcols;   // k_lu_gemm: column tiles gcol0 .. gcol0 + gcols - 1 of A22 (gcols <= 0: to the end)
   int c_lo, c_hi;     // k_lu_swap column range (modes 2, 3); k_lu_trsm: columns [c_lo, c_hi) if c_hi > 0
+  int *queue;         // k_lu_gemm2: kLuQueue counters, zero between launches, of a launch whose blocks take tiles in
+                      // turn and leave free_cus compute units per shader engine to other kernels (nullptr: one tile each)
+  int free_cus;
 };
 #define VIE_DECL_LU(T)                       \
   __global__ void k_lu_pivot_##T(LuStep st); \
@@ -183,6 +201,7 @@ struct LuStep {
   __global__ void k_lu_trsm_##T(LuStep st);  \
   __global__ void k_lu_gemm_##T(LuStep st);  \
   __global__ void k_lu_gemm2_##T(LuStep st); \
+  __global__ void k_lu_gemm2q_##T(LuStep st); \
   __global__ void k_lu_tsel_##T(LuStep st);  \
   __global__ void k_lu_tfin_##T(LuStep st);
 VIE_DECL_LU(z)

@@ -192,3 +192,28 @@ def test_fp32_tournament_at_node_edges(vie, nx, ny, nz):
         z = s.precond_apply(v)
         err.append(np.linalg.norm(z - ref) / np.linalg.norm(ref))
     assert err[1] < 1e-3 and err[0] < 3 * err[1] + 1e-6, err
+
+
+@pytest.mark.parametrize("mixed", [False, True])
+@pytest.mark.parametrize("nx,ny,nz", [(4, 4, 2), (5, 5, 2), (8, 8, 6)])
+def test_bulk_update_tiles_taken_in_turn(vie, mixed, nx, ny, nz):
+    """The bulk update whose blocks take tiles in turn: fewer tiles than blocks
+    (N = 416, 650) and several per block (N = 4,736).  Every tile is one
+    block's, so repeated factorisations give the same bits, which also shows
+    the counters back at zero; FP64 against a dense solve as above."""
+    m = W.slab_mesh(nx=nx, ny=ny, nz=nz)
+    s = vie.Solver()
+    s.upload_mesh(m)
+    s.bind(vie.VIE_MIXED_FP32 if mixed else vie.VIE_FP64, 20)
+    s.fill(600.0, 0.3, 0.2, W.slab_eps(m))
+    N = s.num_unknowns()
+    rng = np.random.default_rng(8)
+    v = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    z = []
+    for _ in range(3):
+        s.factor()
+        z.append(s.precond_apply(v))
+    assert np.array_equal(z[0], z[1]) and np.array_equal(z[0], z[2])
+    if not mixed:
+        ref = np.linalg.solve(read_block(s, 0, N), v)
+        assert np.linalg.norm(z[0] - ref) < 1e-10 * np.linalg.norm(ref), N
