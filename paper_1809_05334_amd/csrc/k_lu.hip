@@ -13,13 +13,13 @@
 // per type (suffix _z: FP64, _c: FP32).
 #include <hip/hip_runtime.h>
 
+#include <utility>
+
 #include "kernels.h"
 
 namespace vie {
 
-typedef double v4d __attribute__((ext_vector_type(4)));
 
-typedef float v4f __attribute__((ext_vector_type(4)));
 
 __device__ __forceinline__ double cabs1(dz a) { return fabs(a.re) + fabs(a.im); }
 __device__ __forceinline__ double cabs1(fz a) { return (double)(fabsf(a.re) + fabsf(a.im)); }
@@ -234,51 +234,158 @@ __device__ __forceinline__ void lu_swap_body(const LuStep &st) {
   }
 }
 
+// Operand layouts of the 16 x 16 x 4 matrix instructions:
+//   v_mfma_f64_16x16x4f64 operand layout (lane l): A[i = l%16][k = l/16],
+//   B[k = l/16][j = l%16]; result register r holds D[i = 4*r + l/16][j = l%16].
+//   v_mfma_f32_16x16x4f32: the same operands; result register r holds
+//   D[i = 4*(l/16) + r][j = l%16].
+typedef double v4d __attribute__((ext_vector_type(4)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+template <typename C> struct Mfma;
+template <> struct Mfma<dz> {
+  typedef double R;
+  typedef v4d Acc;
+  static __device__ __forceinline__ Acc mma(R a, R b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int row(int r, int lane) { return 4 * r + (lane >> 4); }
+  static constexpr int reg(int i) { return i >> 2; }    // row i of a tile: its result register and
+  static constexpr int group(int i) { return i & 3; }   // 16-lane row of the wave
+};
+template <> struct Mfma<fz> {
+  typedef float R;
+  typedef v4f Acc;
+  static __device__ __forceinline__ Acc mma(R a, R b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
+  static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + r; }
+  static constexpr int reg(int i) { return i & 3; }
+  static constexpr int group(int i) { return i >> 2; }
+};
+
+
+// f(integral_constant<0>), .. f(integral_constant<N - 1>)
+template <int N, class F, int... I>
+__device__ __forceinline__ void static_for_seq(F &&f, std::integer_sequence<int, I...>) {
+  (f(std::integral_constant<int, I>()), ...);
+}
+template <int N, class F>
+__device__ __forceinline__ void static_for(F &&f) { static_for_seq<N>(f, std::make_integer_sequence<int, N>()); }
+
+// A wave's 16-lane row G of v in all four rows (v_permlane16_swap exchanges the
+// odd rows of its first operand with the even ones of its second,
+// v_permlane32_swap the upper half of the first with the lower of the second).
+template <int G>
+__device__ __forceinline__ unsigned row_bcast(unsigned v) {
+  const auto a = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // rows 0 0 2 2 and 1 1 3 3
+  const unsigned h = a[G & 1];
+  const auto b = __builtin_amdgcn_permlane32_swap(h, h, false, false);
+  return b[G >> 1];
+}
+template <int G>
+__device__ __forceinline__ float row_bcast(float v) { return __uint_as_float(row_bcast<G>(__float_as_uint(v))); }
+template <int G>
+__device__ __forceinline__ double row_bcast(double v) {
+  const unsigned lo = row_bcast<G>((unsigned)__double2loint(v)), hi = row_bcast<G>((unsigned)__double2hiint(v));
+  return __hiloint2double((int)hi, (int)lo);
+}
+
+// x - l p as four fused multiply-adds
+template <typename C>
+__device__ __forceinline__ C fms(C x, C l, C p) {
+  return cx<C>::make(fma(-l.im, -p.im, fma(-l.re, p.re, x.re)), fma(-l.im, p.re, fma(-l.re, p.im, x.im)));
+}
+
+// X = T^{-1} X for a lower triangle T of order 64 and 16 columns per wave:
+// lane l holds column l % 16, and of the rows 16 b .. 16 b + 15 those of a
+// 16 x 16 matrix-instruction result, in re[b], im[b].  T(i, l) gives an entry;
+// rinv the reciprocals of the diagonal (nullptr: unit).  The rows go in blocks
+// of 16: a block's own triangle takes 16 steps, in which the row that is ready
+// goes to the other lanes of its column; then the blocks below take its
+// product with their part of T on the matrix cores, whose second operand is
+// the block's registers as they are.  Blocks nblk .. 3 are not touched.
+template <typename C, class TF>
+__device__ __forceinline__ void tri_solve(TF T, const C *rinv, int nblk, typename Mfma<C>::Acc (&re)[4],
+                                          typename Mfma<C>::Acc (&im)[4]) {
+  typedef Mfma<C> M;
+  typedef typename M::R R;
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int b = 0; b < 4; ++b) {
+    if (b >= nblk) break;
+    const auto step = [&](auto kc) {
+      constexpr int k = decltype(kc)::value, q0 = M::reg(k), g = M::group(k);
+      C x = cx<C>::make(re[b][q0], im[b][q0]);
+      if (rinv) {
+        x = x * rinv[16 * b + k];
+        if (lane >> 4 == g) {
+          re[b][q0] = x.re;
+          im[b][q0] = x.im;
+        }
+      }
+      x = cx<C>::make(row_bcast<g>(x.re), row_bcast<g>(x.im));
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = M::row(q, lane);
+        const C t = T(16 * b + i, 16 * b + k);
+        const C v = fms(cx<C>::make(re[b][q], im[b][q]), t, x);
+        re[b][q] = i > k ? v.re : re[b][q];
+        im[b][q] = i > k ? v.im : im[b][q];
+      }
+    };
+    static_for<16>(step);
+#pragma unroll
+    for (int c = b + 1; c < 4; ++c) {
+      if (c >= nblk) break;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const C t = T(16 * c + (lane & 15), 16 * b + M::row(q, lane));
+        re[c] = M::mma(-t.re, re[b][q], re[c]);
+        im[c] = M::mma(-t.re, im[b][q], im[c]);
+        re[c] = M::mma(t.im, im[b][q], re[c]);
+        im[c] = M::mma(-t.im, re[b][q], im[c]);
+      }
+    }
+  }
+}
+
 // U12 = L11^{-1} A12 (L11 unit lower, jb <= 64) for the columns right of the
-// panel (or those of them in [c_lo, c_hi)), kColRows columns per thread
-// block: L11 staged in LDS, kColT lanes per column (lane t owns the rows
-// i = t (mod kColT) of its column), the dot products of the forward
-// substitution split over the lanes and combined by shuffles.
+// panel (or those of them in [c_lo, c_hi)), kColRows columns per thread block,
+// 16 per wave, L11 in LDS.  The chain of 64 rows bounds it: 16 us in FP32,
+// 19 in FP64; with four lanes per column, the dot products over shuffles, 33.
 template <typename C>
 __device__ __forceinline__ void lu_trsm_body(const LuStep &st) {
+  typedef Mfma<C> M;
   __shared__ C Lt[kLuNB][kLuNB + 1];
   const LuDom &D = st.d[lu_domain(st)];
   const int k0 = st.k0, n = D.n, jb = min(kLuNB, n - k0);
   const int64_t ld = D.ld;
   C *A = (C *)D.A;
-  const int tid = threadIdx.x;
-  for (int e = tid; e < jb * jb; e += 256) {
-    const int r = e / jb, c = e - r * jb;
-    Lt[r][c] = A[(int64_t)(k0 + r) * ld + k0 + c];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int cbeg = st.c_hi > 0 ? max(st.c_lo, k0 + jb) : k0 + jb, cend = st.c_hi > 0 ? min(st.c_hi, n) : n;
+  const int c = cbeg + (blockIdx.x - D.first_block) * kColRows + (tid >> 6) * 16 + (lane & 15);
+  const bool ok = c < cend;
+  typename M::Acc re[4], im[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int i = 16 * b + M::row(q, lane);
+      const C v = A[(int64_t)(k0 + min(i, jb - 1)) * ld + min(c, n - 1)];
+      re[b][q] = ok && i < jb ? v.re : 0;
+      im[b][q] = ok && i < jb ? v.im : 0;
+    }
+  for (int e = tid; e < kLuNB * kLuNB; e += 256) {
+    const int r = e / kLuNB, l = e % kLuNB;
+    const C v = A[(int64_t)(k0 + min(r, jb - 1)) * ld + k0 + min(l, jb - 1)];
+    Lt[r][l] = r < jb && l < jb ? v : cx<C>::make(0, 0);
   }
   __syncthreads();
-  constexpr int kPer = kLuNB / kColT;
-  const int t = tid % kColT;
-  const int cbeg = st.c_hi > 0 ? max(st.c_lo, k0 + jb) : k0 + jb, cend = st.c_hi > 0 ? min(st.c_hi, n) : n;
-  const int c = cbeg + (blockIdx.x - D.first_block) * kColRows + tid / kColT;
-  const bool ok = c < cend;
-  C x[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u)
-    x[u] = (ok && kColT * u + t < jb) ? A[(int64_t)(k0 + kColT * u + t) * ld + c] : cx<C>::make(0, 0);
-#pragma clang loop unroll(full)
-  for (int i = 1; i < kLuNB; ++i) {
-    if (i < jb) {
-      C s = cx<C>::make(0, 0);
-#pragma clang loop unroll(full)
-      for (int u = 0; u < kPer; ++u)
-        if (kColT * u < i && kColT * u + t < i) s = s + Lt[i][kColT * u + t] * x[u];
-      s.re += __shfl_xor(s.re, 1);
-      s.im += __shfl_xor(s.im, 1);
-      s.re += __shfl_xor(s.re, 2);
-      s.im += __shfl_xor(s.im, 2);
-      if (t == i % kColT) x[i / kColT] = x[i / kColT] - s;
-    }
-  }
+  tri_solve<C>([&](int i, int l) { return Lt[i][l]; }, nullptr, (jb + 15) / 16, re, im);
   if (ok)
 #pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (kColT * u + t < jb) A[(int64_t)(k0 + kColT * u + t) * ld + c] = x[u];
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int i = 16 * b + M::row(q, lane);
+        if (i < jb) A[(int64_t)(k0 + i) * ld + c] = cx<C>::make(re[b][q], im[b][q]);
+      }
 }
 
 // ------------------------------------------------------------ tournament panel
@@ -359,12 +466,6 @@ __device__ __forceinline__ dz dpp_pair(dz v) { return mk(dpp_pair(v.re), dpp_pai
 __device__ __forceinline__ fz dpp_pair(fz v) {
   return fz{__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.re), 0xb1, 0xf, 0xf, false)),
             __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.im), 0xb1, 0xf, 0xf, false))};
-}
-
-// x - l p as four fused multiply-adds
-template <typename C>
-__device__ __forceinline__ C fms(C x, C l, C p) {
-  return cx<C>::make(fma(-l.im, -p.im, fma(-l.re, p.re, x.re)), fma(-l.im, p.re, fma(-l.re, p.im, x.im)));
 }
 
 // Pivot candidate: the magnitude rounded to FP32 (its bits order like the
@@ -674,57 +775,55 @@ __device__ __forceinline__ void lu_tsel_body(const LuStep &st) {
 }
 
 // Store the factored top block (thread block 0 of the domain) and solve
-// x U11 = a for every row below it, kColT lanes per row: lane t owns the
-// columns j = t (mod kColT), the dot products are split over the lanes and
-// combined by shuffles.
+// x U11 = a for every row below it, kColRows rows per thread block, 16 per
+// wave: U11^T x^T = a^T, the rows of A as columns.  23 us in FP32, 27 in FP64 (33 as the
+// column dot products of four lanes per row).
 template <typename C>
 __device__ __forceinline__ void lu_tfin_body(const LuStep &st) {
+  typedef Mfma<C> M;
   __shared__ C U[kLuNB][kLuNB + 1];
   __shared__ C rinv[kLuNB];
   const LuDom &D = st.d[lu_domain(st)];
   const int k0 = st.k0, n = D.n, jb = min(kLuNB, n - k0);
   const int blk = blockIdx.x - D.first_block;
-  const int tid = threadIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
   const C *T = (const C *)D.tblk;
   C *A = (C *)D.A;
-  for (int e = tid; e < jb * jb; e += 256) {
-    const int r = e / jb, c = e - r * jb;
-    U[r][c] = T[r * kLuNB + c];
+  const int i = k0 + jb + blk * kColRows + (tid >> 6) * 16 + (lane & 15);
+  const bool ok = i < n;
+  C *row = A + (int64_t)min(i, n - 1) * D.ld + k0;
+  typename M::Acc re[4], im[4];
+#pragma unroll
+  for (int b = 0; b < 4; ++b)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int j = 16 * b + M::row(q, lane);
+      const C v = row[min(j, jb - 1)];
+      re[b][q] = ok && j < jb ? v.re : 0;
+      im[b][q] = ok && j < jb ? v.im : 0;
+    }
+  for (int e = tid; e < kLuNB * kLuNB; e += 256) {
+    const int r = e / kLuNB, c = e % kLuNB;
+    const C v = T[min(r, jb - 1) * kLuNB + min(c, jb - 1)];
+    U[r][c] = r < jb && c < jb ? v : cx<C>::make(0, 0);
   }
   __syncthreads();
-  if (tid < jb) rinv[tid] = cinv(U[tid][tid]);
+  if (tid < kLuNB) rinv[tid] = cinv(U[tid][tid]);
   if (blk == 0)
     for (int e = tid; e < jb * jb; e += 256) {
       const int r = e / jb, c = e - r * jb;
       A[(int64_t)(k0 + r) * D.ld + k0 + c] = U[r][c];
     }
   __syncthreads();
-  constexpr int kPer = kLuNB / kColT;
-  const int t = tid % kColT;
-  const int i = k0 + jb + blk * kColRows + tid / kColT;
-  const bool ok = i < n;
-  C *row = A + (int64_t)(ok ? i : 0) * D.ld + k0;
-  C x[kPer];
-#pragma unroll
-  for (int u = 0; u < kPer; ++u) x[u] = (ok && kColT * u + t < jb) ? row[kColT * u + t] : cx<C>::make(0, 0);
-#pragma clang loop unroll(full)
-  for (int j = 0; j < kLuNB; ++j) {
-    if (j < jb) {
-      C s = cx<C>::make(0, 0);
-#pragma clang loop unroll(full)
-      for (int u = 0; u < kPer; ++u)
-        if (kColT * u < j && kColT * u + t < j) s = s + x[u] * U[kColT * u + t][j];
-      s.re += __shfl_xor(s.re, 1);
-      s.im += __shfl_xor(s.im, 1);
-      s.re += __shfl_xor(s.re, 2);
-      s.im += __shfl_xor(s.im, 2);
-      if (t == j % kColT) x[j / kColT] = (x[j / kColT] - s) * rinv[j];
-    }
-  }
+  tri_solve<C>([&](int r, int l) { return U[l][r]; }, rinv, (jb + 15) / 16, re, im);
   if (ok)
 #pragma unroll
-    for (int u = 0; u < kPer; ++u)
-      if (kColT * u + t < jb) row[kColT * u + t] = x[u];
+    for (int b = 0; b < 4; ++b)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int j = 16 * b + M::row(q, lane);
+        if (j < jb) row[j] = cx<C>::make(re[b][q], im[b][q]);
+      }
 }
 
 // A22 -= L21 U12 on the matrix cores.  Tile 64 x 64 per block of 4 waves
@@ -733,25 +832,7 @@ __device__ __forceinline__ void lu_tfin_body(const LuStep &st) {
 // the current one is multiplied.  Every global load is unconditional, from
 // an address clamped into the block, with out-of-range values zeroed: a load
 // under a branch is waited for inside the branch.
-//   v_mfma_f64_16x16x4f64 operand layout (lane l): A[i = l%16][k = l/16],
-//   B[k = l/16][j = l%16]; result register r holds D[i = 4*r + l/16][j = l%16].
-//   v_mfma_f32_16x16x4f32: the same operands; result register r holds
-//   D[i = 4*(l/16) + r][j = l%16].
 constexpr int kGemmKC = 16;
-
-template <typename C> struct Mfma;
-template <> struct Mfma<dz> {
-  typedef double R;
-  typedef v4d Acc;
-  static __device__ __forceinline__ Acc mma(R a, R b, Acc c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
-  static __device__ __forceinline__ int row(int r, int lane) { return 4 * r + (lane >> 4); }
-};
-template <> struct Mfma<fz> {
-  typedef float R;
-  typedef v4f Acc;
-  static __device__ __forceinline__ Acc mma(R a, R b, Acc c) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0); }
-  static __device__ __forceinline__ int row(int r, int lane) { return 4 * (lane >> 4) + r; }
-};
 
 template <typename C>
 __device__ __forceinline__ void lu_gemm_body(const LuStep &st) {

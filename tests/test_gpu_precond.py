@@ -217,3 +217,26 @@ def test_bulk_update_tiles_taken_in_turn(vie, mixed, nx, ny, nz):
     if not mixed:
         ref = np.linalg.solve(read_block(s, 0, N), v)
         assert np.linalg.norm(z[0] - ref) < 1e-10 * np.linalg.norm(ref), N
+
+
+@pytest.mark.parametrize("nx,ny,nz", [(3, 2, 1), (2, 2, 2), (5, 3, 2), (4, 3, 2), (3, 3, 2)])
+def test_panel_solves_at_sixteen_row_remainders(vie, nx, ny, nz):
+    """Last panels of 20, 40, 6, 56 and 42 columns, factors against a dense
+    solve: FP64 by the bar above; FP32 with either pivoting (both use the
+    panel's triangular solves) by FP32 u times N times the condition (below
+    1e3): 6e-8 * 4e2 * 1e3 = 0.02."""
+    m = W.slab_mesh(nx=nx, ny=ny, nz=nz)
+    for mixed, bar in ((False, 1e-10), (True, 0.02)):
+        s = vie.Solver()
+        s.upload_mesh(m)
+        s.bind(vie.VIE_MIXED_FP32 if mixed else vie.VIE_FP64, 20)
+        s.fill(600.0, 0.3, 0.2, W.slab_eps(m))
+        N = s.num_unknowns()
+        rng = np.random.default_rng(9)
+        v = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+        ref = np.linalg.solve(read_block(s, 0, N), v)
+        for pivot in (0, 1):
+            s.set_option(vie.VIE_OPT_LU_PIVOT, pivot)
+            s.factor()
+            err = np.linalg.norm(s.precond_apply(v) - ref) / np.linalg.norm(ref)
+            assert err < bar, (N, mixed, pivot, err)
