@@ -1130,9 +1130,9 @@ void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &d
         else hipLaunchKernelGGL(k_lu_gemm2_z, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         break;
       case LU_TSEL:
-        if (f32 && all_cols) hipLaunchKernelGGL(k_lu_tsel_wide_c, dim3(total), dim3(kTsRowsW * kTsLprC), 0, sm, st);
-        else if (f32) hipLaunchKernelGGL(k_lu_tsel_c, dim3(total), dim3(kTsRowsC * kTsLprC), 0, sm, st);
-        else hipLaunchKernelGGL(k_lu_tsel_z, dim3(total), dim3(kTsRowsZ * kTsLprZ), 0, sm, st);
+        if (f32 && all_cols) hipLaunchKernelGGL(k_lu_tsel_wide_c, dim3(total), dim3(kTsRowsW / kTsWaveC * 64), 0, sm, st);
+        else if (f32) hipLaunchKernelGGL(k_lu_tsel_c, dim3(total), dim3(kTsRowsC / kTsWaveC * 64), 0, sm, st);
+        else hipLaunchKernelGGL(k_lu_tsel_z, dim3(total), dim3(kTsRowsZ / kTsWaveZ * 64), 0, sm, st);
         break;
       case LU_TFIN:
         if (f32) hipLaunchKernelGGL(k_lu_tfin_c, dim3(total), dim3(256), 0, sm, st);

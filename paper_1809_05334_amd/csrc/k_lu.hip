@@ -408,41 +408,46 @@ __device__ __forceinline__ void lu_trsm_body(const LuStep &st) {
 // tree depth (the panel height over the leaf slice, in powers of the fan-in)
 // sets the panel's latency.
 //
-// Inside a node the rows stay in registers: TsCfg::lpr lanes per row, lane t
-// owning the contiguous columns [t W, (t+1) W), W = kLuNB / lpr.  Rows are not
-// moved: a pivot row is marked used and its step recorded.  Columns go in
-// blocks of kTsBlk: a step works on its block alone (one barrier: every wave
-// publishes its best candidate, a 64-bit key of the magnitude and the row,
-// that row's part of the block and its reciprocal pivot in LDS, double-buffered
-// by the step's parity, and every wave then picks the winner), and after the
-// block the other columns take its up to kTsBlk steps at once.  The chain of
-// steps bounds a panel, so a step does as little as it can: updating all 64
-// columns in each step, with the whole row published by one lane, a 64-bit
-// maximum and the pivot's division behind the barrier cost 3,200 cycles a step
-// (FP32) to 5,500 (FP64).  Alone, per panel: N = 15,840, FP64, 0.51 ms
-// (0.68 before); N = 37,376, FP32, 512-row nodes, 0.30 ms (0.44).
+// Inside a node the rows stay in registers, TsCfg::wrows per wave, as results
+// of the 16 x 16 matrix instructions.  Rows are not moved: a pivot row is
+// marked used and its step recorded.  Columns go in blocks of kTsBlk = 8: the
+// block goes through LDS to one lane per row, which takes its 8 steps (one
+// barrier each: every wave publishes its best candidate, a 64-bit key of the
+// magnitude and the row, that row's part of the block and its reciprocal
+// pivot in LDS, double-buffered by the step's parity, and every wave then
+// picks the winner); the rows' multipliers go back through LDS as the first
+// operand of the matrix instructions that apply the 8 steps to the columns
+// right of the block (zero for used rows), the 8 pivot rows, solved against
+// each other one column per thread, as the second.  The chain of steps bounds
+// a panel, so a step does as little as it can.  Mean time per panel, against one
+// or two lanes per row that held all 64 columns and took the 8 steps by FMAs:
+// FP64, N = 6,272, 242 us (387), N = 15,840, 358 (597); FP32, 512-row nodes,
+// N = 3,038, 158 (172).
 template <typename C, bool WIDE> struct TsCfg;
 template <> struct TsCfg<dz, false> {
-  static constexpr int lpr = kTsLprZ, fan = kTsFanZ, rows = kTsRowsZ;
+  static constexpr int wrows = kTsWaveZ, fan = kTsFanZ, rows = kTsRowsZ;
 };
 template <> struct TsCfg<fz, false> {
-  static constexpr int lpr = kTsLprC, fan = kTsFanC, rows = kTsRowsC;
+  static constexpr int wrows = kTsWaveC, fan = kTsFanC, rows = kTsRowsC;
 };
 template <> struct TsCfg<fz, true> {
-  static constexpr int lpr = kTsLprC, fan = kTsFanW, rows = kTsRowsW;
+  static constexpr int wrows = kTsWaveC, fan = kTsFanW, rows = kTsRowsW;
 };
 constexpr int kTsBlk = 8;
 template <typename C, bool WIDE>
 struct TsShared {
   typedef C T;
-  static constexpr int kFan = TsCfg<C, WIDE>::fan, kRows = TsCfg<C, WIDE>::rows, kLpr = TsCfg<C, WIDE>::lpr,
-                       kThreads = kRows * kLpr, kWaves = kThreads / 64, kW = kLuNB / kLpr;
-  C crow[2][kWaves][kTsBlk];          // each wave's best candidate row, columns j .. of the block, by step parity
-  C crinv[2][kWaves];                 // reciprocal of its pivot
-  unsigned long long key[2][kWaves];
+  static constexpr int kFan = TsCfg<C, WIDE>::fan, kRows = TsCfg<C, WIDE>::rows, kWRows = TsCfg<C, WIDE>::wrows,
+                       kStepWaves = kRows / 64,   // waves that hold a row per lane in the steps
+                       kPLd = kRows + 4;
+  C P[kTsBlk][kPLd];                  // the block's columns, then the rows' multipliers
   C U[kTsBlk][kLuNB];                 // the block's pivot rows, columns right of the block
   C L11[kTsBlk][kTsBlk];              // the pivot rows' multipliers inside the block
+  C crow[2][kStepWaves][kTsBlk];      // each wave's best candidate row, by step parity
+  C crinv[2][kStepWaves];             // reciprocal of its pivot
+  unsigned long long key[2][kStepWaves];
   int rid[kRows];                     // the node's rows (rows of the domain)
+  int step[kRows];                    // the step each row was the pivot of, -1 if none
   int order[kLuNB];                   // node rows in pivot order
   int zero;                           // first zero pivot of the last elimination (1-based), 0 if none
   int flag;
@@ -456,16 +461,6 @@ __device__ __forceinline__ C cinv(C d) {
   if (!(den > R(0))) return cx<C>::make(0, 0);
   const R s = R(1) / den;
   return cx<C>::make(d.re * s, -d.im * s);
-}
-
-// the value of the neighbouring lane (lane ^ 1)
-__device__ __forceinline__ double dpp_pair(double v) {
-  return __longlong_as_double((long long)dpp64<0xb1>((unsigned long long)__double_as_longlong(v)));
-}
-__device__ __forceinline__ dz dpp_pair(dz v) { return mk(dpp_pair(v.re), dpp_pair(v.im)); }
-__device__ __forceinline__ fz dpp_pair(fz v) {
-  return fz{__int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.re), 0xb1, 0xf, 0xf, false)),
-            __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v.im), 0xb1, 0xf, 0xf, false))};
 }
 
 // Pivot candidate: the magnitude rounded to FP32 (its bits order like the
@@ -485,171 +480,219 @@ __device__ __forceinline__ unsigned wave_max_u32(unsigned v) {
   return max(max(a, b), max(c, d));
 }
 
-// This lane's columns of its row (row tid / lpr of S.rid, m valid rows; a
-// row outside the domain is read as zeros).
+// Partial-pivoting elimination of the m x jb matrix of the rows S.rid[0 .. m)
+// (m <= kRows; a row outside the domain is read as zeros): on return
+// S.order[0 .. min(m, jb)) lists the pivot rows in order.  At the root of the
+// tree, L\U of the panel restricted to the pivot rows goes to T.  Ties go to
+// the smaller row (rows ascend with the lanes and the waves).
 template <class Sh, typename C = typename Sh::T>
-__device__ __forceinline__ void ts_load(const Sh &S, const C *__restrict__ A, int64_t ld, int n, int k0, int m, int jb,
-                                        C (&x)[Sh::kW]) {
-  constexpr int L = Sh::kLpr, W = Sh::kW;
-  const int r = threadIdx.x / L, t = threadIdx.x % L;
-  const int g = r < m ? S.rid[r] : -1;
-  const bool ok = g >= 0 && g < n;
-  const C *row = A + (int64_t)(ok ? g : 0) * ld + k0 + t * W;
-#pragma unroll
-  for (int i = 0; i < W; ++i) x[i] = (ok && t * W + i < jb) ? row[i] : cx<C>::make(0, 0);
-}
-
-// Partial-pivoting elimination of the m x jb matrix held in x (m <= kRows
-// rows, S.rid): on return S.order[0 .. min(m, jb)) lists the pivot rows in
-// order, *step is this row's pivot step (-1 if none) and x holds L\U of the
-// panel restricted to the pivot rows.  Step j works on column j in block
-// b = (j mod W) / 8 of its owner lane o = j / W; the owner keeps column j in
-// the first register of that block by rotating the block one register per
-// step, so every register index is static with only the loop over blocks
-// unrolled (the loop over the 8 steps of a block is not: small code).  Ties go
-// to the smaller row (rows ascend with the lanes and the waves).
-template <class Sh, typename C = typename Sh::T>
-__device__ __forceinline__ void ts_gepp(Sh &S, C (&x)[Sh::kW], int m, int jb, int *step) {
-  constexpr int L = Sh::kLpr, W = Sh::kW, NB = W / kTsBlk, NW = Sh::kWaves;
-  static_assert(kTsBlk == 8 && NW <= 8, "blocks of 8 registers; the waves' keys are reduced over 8 lanes");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int r = tid / L, t = tid % L;
-  const bool valid = r < m;
+__device__ __forceinline__ void ts_gepp(Sh &S, const C *__restrict__ A, int64_t ld, int n, int k0, int m, int jb, bool root,
+                                        C *__restrict__ T) {
+  typedef Mfma<C> M;
+  typedef typename M::Acc Acc;
+  constexpr int MB = Sh::kWRows / 16, CT = kLuNB / 16, PW = Sh::kStepWaves;
+  static_assert(kTsBlk == 8 && (PW == 4 || PW == 8), "half a tile of columns; the waves' keys are reduced over 4 or 8 lanes");
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, lc = lane & 15;
   const int steps = min(m, jb);
-  bool used = !valid;
+  // row of accumulator register q of row tile a: wr0 + 16 a + M::row(q, lane)
+  const int wr0 = wave * Sh::kWRows;
+  Acc re[MB][CT], im[MB][CT];
+#pragma unroll
+  for (int a = 0; a < MB; ++a)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = wr0 + 16 * a + M::row(q, lane);
+      const int g = r < m ? S.rid[r] : -1;
+      const bool ok = g >= 0 && g < n;
+      const C *row = A + (int64_t)(ok ? g : 0) * ld + k0;
+#pragma unroll
+      for (int t = 0; t < CT; ++t) {
+        const C v = row[min(16 * t + lc, jb - 1)];
+        re[a][t][q] = ok && 16 * t + lc < jb ? v.re : 0;
+        im[a][t][q] = ok && 16 * t + lc < jb ? v.im : 0;
+      }
+    }
+  const bool stepper = wave < PW;   // this wave's lanes hold rows tid in the steps
+  bool used = tid >= m;
   int zero = 0;
-  *step = -1;
+  if (stepper) S.step[tid] = -1;
+#pragma unroll 1
+  for (int j0 = 0; j0 < steps; j0 += kTsBlk) {
+    const int tb = j0 / 16, half = j0 >> 3 & 1, nk = min(kTsBlk, steps - j0);
+    // the block's columns to one lane per row (a wave's own rows of P are free)
 #pragma unroll
-  for (int o = 0; o < L; ++o) {
-    const bool owner = t == o;
+    for (int t = 0; t < CT; ++t)
+      if (t == tb && lc >> 3 == half) {
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int j0 = o * W + 8 * b;
-      if (j0 >= steps) break;
-      const int nk = min(8, steps - j0);   // steps of this block
-      const bool before = used;            // pivot rows of earlier blocks and rows past m: untouched from here on
-#pragma clang loop unroll(disable)
-      for (int jt = 0; jt < 8; ++jt) {
-        const int j = j0 + jt;
-        if (jt < nk) {
-          const int buf = j & 1;
-          const unsigned mag = owner && !used ? ts_mag(cabs1(x[8 * b])) : 0u;
-          const C ri = cinv(x[8 * b]);   // (of every lane's own entry: ready when the winner is known)
+        for (int a = 0; a < MB; ++a)
+#pragma unroll
+          for (int q = 0; q < 4; ++q)
+            S.P[lc & 7][wr0 + 16 * a + M::row(q, lane)] = cx<C>::make(re[a][t][q], im[a][t][q]);
+      }
+    __syncthreads();
+    const bool before = used;   // pivot rows of earlier blocks and rows past m: untouched from here on
+    int own = -1;               // this row's step in the block
+    C x[kTsBlk];
+    if (stepper) {
+#pragma unroll
+      for (int k = 0; k < kTsBlk; ++k) x[k] = S.P[k][tid];
+    }
+#pragma unroll
+    for (int jt = 0; jt < kTsBlk; ++jt) {
+      if (jt < nk) {
+        const int buf = jt & 1;
+        if (stepper) {
+          const unsigned mag = !used ? ts_mag(cabs1(x[jt])) : 0u;
+          const C ri = cinv(x[jt]);   // (of every lane's own entry: ready when the winner is known)
           const unsigned top = wave_max_u32(mag);
-          const unsigned long long at = __ballot(mag == top);
-          const int cl = __ffsll((long long)at) - 1;
+          const int cl = __ffsll((long long)__ballot(mag == top)) - 1;
           if (top != 0u && lane == cl) {
 #pragma unroll
-            for (int kk = 0; kk < 8; ++kk) S.crow[buf][wave][kk] = x[8 * b + kk];
+            for (int k = jt + 1; k < kTsBlk; ++k) S.crow[buf][wave][k] = x[k];
             S.crinv[buf][wave] = ri;
           }
-          if (lane == 0)
-            S.key[buf][wave] = (unsigned long long)top << 32 | (unsigned)((wave * 64 + cl) / L);
-          __syncthreads();
-          const unsigned long long kw = S.key[buf][lane & (NW - 1)];
+          if (lane == 0) S.key[buf][wave] = (unsigned long long)top << 32 | (unsigned)(wave * 64 + cl);
+        }
+        __syncthreads();
+        if (stepper) {
+          const unsigned long long kw = S.key[buf][lane & (PW - 1)];
           const unsigned hi = (unsigned)(kw >> 32);
           unsigned best = dpp_max<0x4e>(dpp_max<0xb1>(hi));
-          if (NW > 4) best = dpp_max<0x141>(best);
+          if (PW > 4) best = dpp_max<0x141>(best);
           best = (unsigned)__builtin_amdgcn_readfirstlane((int)best);
-          const int wb = (__ffsll((long long)__ballot(hi == best)) - 1) & (NW - 1);
+          const int wb = (__ffsll((long long)__ballot(hi == best)) - 1) & (PW - 1);
           const int p = __builtin_amdgcn_readlane((int)(unsigned)kw, wb);
           const bool nonzero = best > 1u;
-          if (!nonzero && zero == 0) zero = j + 1;
-          const bool now = r == p && best != 0u;
-          if (now) *step = j;   // the pivot row: not updated any more
-          used = used || now;
-          if (tid == 0) S.order[j] = best != 0u ? p : -1;
-          if (owner && !used && nonzero) {
-            const C *prow = S.crow[buf][wb];
-            const C l = x[8 * b] * S.crinv[buf][wb];
-            C pv[8];
-#pragma unroll
-            for (int kk = 1; kk < 8; ++kk) pv[kk] = prow[kk];
-#pragma unroll
-            for (int kk = 1; kk < 8; ++kk)
-              if (kk + jt < 8) x[8 * b + kk] = fms(x[8 * b + kk], l, pv[kk]);
-            x[8 * b] = l;
+          if (!nonzero && zero == 0) zero = j0 + jt + 1;
+          if (tid == p && best != 0u) {   // the pivot row: not updated any more
+            own = jt;
+            used = true;
           }
-        }
-        // the owner rotates its block: column j + 1 to the front (after 8
-        // steps the block is back in column order)
-        if (owner) {
-          const C f = x[8 * b];
+          if (tid == 0) S.order[j0 + jt] = best != 0u ? p : -1;
+          if (!used && nonzero) {
+            const C l = x[jt] * S.crinv[buf][wb];
 #pragma unroll
-          for (int kk = 0; kk < 7; ++kk) x[8 * b + kk] = x[8 * b + kk + 1];
-          x[8 * b + 7] = f;
-        }
-      }
-      if (j0 + 8 >= kLuNB) break;   // nothing right of the last block
-      // The block's steps on the columns right of it.  The pivot rows' parts
-      // and multipliers go to LDS, one thread per column solves for the U rows
-      // (each pivot row takes the steps before its own), and every other row
-      // takes them all.
-      const int own = *step - j0;   // this row's step in the block
-      const bool mine = !before && own >= 0 && own < 8;
-      if (mine) {
-        if (owner) {
-#pragma unroll
-          for (int kk = 0; kk < 8; ++kk) S.L11[own][kk] = x[8 * b + kk];
-#pragma unroll
-          for (int i = 8 * (b + 1); i < W; ++i) S.U[own][o * W + i] = x[i];
-        } else if (t > o) {
-#pragma unroll
-          for (int i = 0; i < W; ++i) S.U[own][t * W + i] = x[i];
-        }
-      }
-      C l[8];
-#pragma unroll
-      for (int kk = 0; kk < 8; ++kk) {
-        l[kk] = x[8 * b + kk];
-        if (L == 2 && o == 0) {   // the row's other lane takes the owner's multipliers (a pair of lanes)
-          const C v = dpp_pair(l[kk]);
-          if (!owner) l[kk] = v;
-        }
-      }
-      __syncthreads();
-      {
-        const int c = j0 + 8 + tid;
-        if (c < kLuNB) {
-          C u[8];
-#pragma unroll
-          for (int k = 0; k < 8; ++k)
-            if (k < nk) u[k] = S.U[k][c];
-#pragma unroll
-          for (int k = 1; k < 8; ++k)
-            if (k < nk) {
-#pragma unroll
-              for (int q = 0; q < k; ++q) u[k] = fms(u[k], S.L11[k][q], u[q]);
-              S.U[k][c] = u[k];
-            }
-        }
-      }
-      __syncthreads();
-      if (!before && t >= o) {
-#pragma unroll
-        for (int bb = 0; bb < NB; ++bb) {
-          if (t == o && bb <= b) continue;
-          const C *u = &S.U[0][t * W + 8 * bb];
-          if (mine) {
-#pragma unroll
-            for (int i = 0; i < 8; ++i) x[8 * bb + i] = u[own * kLuNB + i];
-          } else {
-#pragma unroll
-            for (int k = 0; k < 8; ++k)
-              if (k < nk) {
-                C pv[8];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) pv[i] = u[k * kLuNB + i];
-#pragma unroll
-                for (int i = 0; i < 8; ++i) x[8 * bb + i] = fms(x[8 * bb + i], l[k], pv[i]);
-              }
+            for (int k = jt + 1; k < kTsBlk; ++k) x[k] = fms(x[k], l, S.crow[buf][wb][k]);
+            x[jt] = l;
           }
         }
       }
     }
+    if (stepper && own >= 0) {
+      S.step[tid] = j0 + own;
+#pragma unroll
+      for (int k = 0; k < kTsBlk; ++k) S.L11[own][k] = x[k];
+    }
+    if (root) {   // keep the block's columns of the rows it worked on in their registers
+      if (stepper && !before) {
+#pragma unroll
+        for (int k = 0; k < kTsBlk; ++k) S.P[k][tid] = x[k];
+      }
+      __syncthreads();
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+        if (t == tb && lc >> 3 == half) {
+#pragma unroll
+          for (int a = 0; a < MB; ++a)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const int r = wr0 + 16 * a + M::row(q, lane), sr = S.step[r];
+              if (sr < 0 || sr >= j0) {
+                const C v = S.P[lc & 7][r];
+                re[a][t][q] = v.re;
+                im[a][t][q] = v.im;
+              }
+            }
+        }
+      __syncthreads();
+    }
+    if (nk < kTsBlk || j0 + kTsBlk >= jb) break;   // no column right of the block that is still read
+    if (stepper) {
+#pragma unroll
+      for (int k = 0; k < kTsBlk; ++k) S.P[k][tid] = used ? cx<C>::make(0, 0) : x[k];
+    }
+    __syncthreads();
+    // the pivot rows' columns right of the block
+    const int c0 = j0 + kTsBlk;
+#pragma unroll
+    for (int a = 0; a < MB; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int sr = S.step[wr0 + 16 * a + M::row(q, lane)] - j0;
+        if (sr >= 0) {
+#pragma unroll
+          for (int t = 0; t < CT; ++t) S.U[sr][16 * t + lc] = cx<C>::make(re[a][t][q], im[a][t][q]);
+        }
+      }
+    __syncthreads();
+    if (tid < kLuNB && tid >= c0) {
+      C u[kTsBlk];
+#pragma unroll
+      for (int k = 0; k < kTsBlk; ++k) u[k] = S.U[k][tid];
+#pragma unroll
+      for (int k = 1; k < kTsBlk; ++k) {
+#pragma unroll
+        for (int i = 0; i < k; ++i) u[k] = fms(u[k], S.L11[k][i], u[i]);
+        S.U[k][tid] = u[k];
+      }
+    }
+    __syncthreads();
+    if (root) {
+#pragma unroll
+      for (int a = 0; a < MB; ++a)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int sr = S.step[wr0 + 16 * a + M::row(q, lane)] - j0;
+          if (sr >= 0) {
+#pragma unroll
+            for (int t = 0; t < CT; ++t)
+              if (16 * t + lc >= c0) {
+                const C v = S.U[sr][16 * t + lc];
+                re[a][t][q] = v.re;
+                im[a][t][q] = v.im;
+              }
+          }
+        }
+    }
+#pragma unroll
+    for (int h = 0; h < kTsBlk / 4; ++h) {
+      const int k = 4 * h + (lane >> 4);
+      C l[MB];
+#pragma unroll
+      for (int a = 0; a < MB; ++a) l[a] = S.P[k][wr0 + 16 * a + lc];
+#pragma unroll
+      for (int t = 0; t < CT; ++t)
+        if (16 * t + 15 >= c0) {
+          C u = S.U[k][16 * t + lc];
+          if (16 * t + lc < c0) u = cx<C>::make(0, 0);
+#pragma unroll
+          for (int a = 0; a < MB; ++a) {
+            re[a][t] = M::mma(-l[a].re, u.re, re[a][t]);
+            im[a][t] = M::mma(-l[a].re, u.im, im[a][t]);
+          }
+#pragma unroll
+          for (int a = 0; a < MB; ++a) {
+            re[a][t] = M::mma(l[a].im, u.im, re[a][t]);
+            im[a][t] = M::mma(-l[a].im, u.re, im[a][t]);
+          }
+        }
+    }
   }
-  __syncthreads();   // S.order complete; the LDS rows may be reused
+  __syncthreads();   // S.order and S.step complete; the LDS rows may be reused
   if (tid == 0) S.zero = zero;
+  if (root) {
+#pragma unroll
+    for (int a = 0; a < MB; ++a)
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const int r = wr0 + 16 * a + M::row(q, lane), sr = S.step[r];
+        if (sr >= 0) {
+#pragma unroll
+          for (int t = 0; t < CT; ++t)
+            if (16 * t + lc < jb) T[sr * kLuNB + 16 * t + lc] = cx<C>::make(re[a][t][q], im[a][t][q]);
+        }
+      }
+  }
 }
 
 // The row of the domain chosen at step j of the last elimination, -1 if the
@@ -671,8 +714,6 @@ __device__ __forceinline__ void lu_tsel_body(const LuStep &st) {
   const int k0 = st.k0, n = D.n, jb = min(kLuNB, n - k0);
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   int q = blockIdx.x - D.first_block;
-  C x[Sh::kW];
-  int step;
   // leaf: rows k0 + q kRows ...
   const int r0 = k0 + q * kRows;
   int m = min(kRows, n - r0);
@@ -682,8 +723,7 @@ __device__ __forceinline__ void lu_tsel_body(const LuStep &st) {
   int base = 0;                             // first node id of this level
   // one elimination per node this block takes: its leaf, then each merge
   for (;;) {
-    ts_load(S, A, D.ld, n, k0, m, jb, x);
-    ts_gepp(S, x, m, jb, &step);
+    ts_gepp(S, A, D.ld, n, k0, m, jb, cnt == 1, (C *)D.tblk);   // (one node on its level: the root)
     bool merged = false;
     while (cnt > 1 && !merged) {
       const int nc = min(m, jb);
@@ -725,16 +765,6 @@ __device__ __forceinline__ void lu_tsel_body(const LuStep &st) {
       q /= kFan;
     }
     if (!merged) break;   // cnt == 1: this block holds the root
-  }
-  // root: the pivot rows in S.order, their LU in the registers of their lanes
-  {
-    constexpr int L = Sh::kLpr, W = Sh::kW;
-    C *T = (C *)D.tblk;
-    const int t = tid % L;
-    if (step >= 0)
-#pragma unroll
-      for (int i = 0; i < W; ++i)
-        if (t * W + i < jb) T[step * kLuNB + t * W + i] = x[i];
   }
   // LAPACK-order swaps, by wave 0 alone: step j swaps position k0+j with the
   // current position of winner j.  Lane e holds entry e of the list of rows
@@ -1186,9 +1216,9 @@ __global__ __launch_bounds__(256) void k_lu_swap_z(LuStep st) { lu_swap_body<dz>
 __global__ __launch_bounds__(256) void k_lu_swap_c(LuStep st) { lu_swap_body<fz>(st); }
 __global__ __launch_bounds__(256) void k_lu_trsm_z(LuStep st) { lu_trsm_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_lu_trsm_c(LuStep st) { lu_trsm_body<fz>(st); }
-__global__ __launch_bounds__(kTsRowsZ * kTsLprZ) void k_lu_tsel_z(LuStep st) { lu_tsel_body<dz, false>(st); }
-__global__ __launch_bounds__(kTsRowsC * kTsLprC) void k_lu_tsel_c(LuStep st) { lu_tsel_body<fz, false>(st); }
-__global__ __launch_bounds__(kTsRowsW * kTsLprC) void k_lu_tsel_wide_c(LuStep st) { lu_tsel_body<fz, true>(st); }
+__global__ __launch_bounds__(kTsRowsZ / kTsWaveZ * 64) void k_lu_tsel_z(LuStep st) { lu_tsel_body<dz, false>(st); }
+__global__ __launch_bounds__(kTsRowsC / kTsWaveC * 64, 2) void k_lu_tsel_c(LuStep st) { lu_tsel_body<fz, false>(st); }
+__global__ __launch_bounds__(kTsRowsW / kTsWaveC * 64) void k_lu_tsel_wide_c(LuStep st) { lu_tsel_body<fz, true>(st); }
 __global__ __launch_bounds__(256) void k_lu_tfin_z(LuStep st) { lu_tfin_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_lu_tfin_c(LuStep st) { lu_tfin_body<fz>(st); }
 

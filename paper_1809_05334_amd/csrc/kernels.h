@@ -148,24 +148,24 @@ constexpr int kLuMaxDom = 8;
 // falls free, such a node starts only when the update is over.  Above
 // kGemm2QueueMax tiles the unit per shader engine costs the update more than
 // the panels it hides.  Factor, FP64, N = 15,840 (15,000 tiles at first):
-// 119 ms with one unit per shader engine, 123 with two, 130 with three, 141
+// 91 ms with one unit per shader engine, 97 with two, 106 with three, 106
 // with a block per tile; FP32, six cells of up to 5,500 unknowns (wide
-// nodes): 50.7 against 53.4.  FP32, N = 37,376, whose nodes take half a unit:
-// 442 against 385, so not for those.
+// nodes): 44.8 against 47.5.  FP32, N = 37,376, whose nodes take half a unit
+// and so share them with the update: 442 against 385 when it was tried, so
+// not for those.
 constexpr int kGemm2FreeCus = 1;      // per shader engine, of its 8
 constexpr int kGemm2Slots = 512;      // blocks of k_lu_gemm2 that the 256 compute units hold at once
 constexpr int kGemm2QueueMax = 50000;
 constexpr int kGemm2Threads = 512;   // threads per block of the two-panel trailing update (k_lu_gemm2)
-// Tournament nodes: 256 rows and four children per node; a row takes two
-// lanes for FP64 factors (512 threads), one lane for FP32 (256 threads).  The
-// wide FP32 nodes, 512 rows and eight children, need fewer levels of 64 steps
-// but a whole CU per node, for which they queue behind the bulk update that
-// runs beside them: taken while the largest domain has at most kTsWideMax
-// unknowns (factor of six cells of up to 5,500: 56 ms against 62; N = 37,376,
-// largest domain 21,482: 427 ms against 386).
+// Tournament nodes: 256 rows and four children per node, in 8 waves for FP64
+// factors (a whole compute unit's registers), 4 for FP32.  The wide FP32
+// nodes, 512 rows and eight children, need fewer levels of 64 steps but a
+// whole unit per node: taken while the largest domain has at most kTsWideMax
+// unknowns (factor of six cells of up to 5,500: 45 ms against 50; N = 37,376,
+// largest domain 21,482: 383 ms against 356).
 constexpr int kTsFanZ = 4, kTsFanC = 4, kTsFanW = 8;
 constexpr int kTsRowsZ = kTsFanZ * kLuNB, kTsRowsC = kTsFanC * kLuNB, kTsRowsW = kTsFanW * kLuNB;
-constexpr int kTsLprZ = 2, kTsLprC = 1;
+constexpr int kTsWaveZ = 32, kTsWaveC = 64;   // rows of a node per wave
 constexpr int kTsWideMax = 8192;
 constexpr int kLuQueue = 160;   // counters of a tile queue: 8 lists, blocks gone, blocks ended, 16 ints apart
 struct LuDom {
