@@ -1204,7 +1204,7 @@ int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms) {
     poff += n;
     pvoff += nblk(n, kColRows);
     if (n == 0) continue;
-    const dim3 cg(nblk(n, 256), std::min(n, 32768)), ng(nblk(n, 256)), b256(256);
+    const dim3 cg(nblk(n, 256), std::min(n, 32768)), ng(nblk(n, 4)), b256(256);
     if (f32) {
       hipLaunchKernelGGL(k_copy_block_c, cg, b256, 0, ctx->stream, zo, (int64_t)t.dstart[d], n, (fz *)D.A, D.ld);
       if (!zo.Z) hipLaunchKernelGGL(k_add_near_c, ng, b256, 0, ctx->stream, zo, (int64_t)t.dstart[d], n, (fz *)D.A, D.ld);
@@ -1368,16 +1368,11 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
 }
 
 // After the panels: the inverses of the 512-row diagonal blocks of L and U and
-// the coupling blocks of the triangular solves, the pivots read back (zero pivot: VIE_ESINGULAR), each block's row
-// permutation built on the host and uploaded; the context becomes S_FACTORED.
-int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
-  const MeshTopology &t = ctx->topo;
+// the coupling blocks of the triangular solves of ctx's domains, appended to
+// prep for factor_blocks.
+void factor_prep(vie_ctx *ctx, const std::vector<LuDom> &doms, std::vector<TrsvPrepDom> &prep) {
   const Layout &L = ctx->L;
-  const bool f32 = fp32_factors(ctx);
-  int32_t *ipiv = ctx->ptr<int32_t>(L.ipiv), *perm = ctx->ptr<int32_t>(L.perm), *info = ctx->ptr<int32_t>(L.info);
-  // the inverses, then the coupling blocks: L's of a domain, then U's
-  std::vector<TrsvPrepDom> prep;
-  for (int d = 0; d < t.ndom; ++d) {
+  for (int d = 0; d < ctx->topo.ndom; ++d) {
     const int n = doms[d].n;
     if (n == 0) continue;
     const int64_t nbk = (n + kTrsvNB - 1) / kTrsvNB, mlast = n - (nbk - 1) * kTrsvNB, nb2 = (nbk - 1) * kTrsvNB * kTrsvNB;
@@ -1385,6 +1380,11 @@ int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
                     factor_ptr(ctx, L.dinv, L.doff[d] + nb2 + mlast * mlast), factor_ptr(ctx, L.gcpl, L.goff[d]),
                     factor_ptr(ctx, L.gcpl, L.goff[d] + nb2)});
   }
+}
+
+// The inverses of prep's domains (any number of contexts', all FP32 or all
+// FP64 factors), then their coupling blocks.
+int factor_blocks(vie_ctx *ctx, const std::vector<TrsvPrepDom> &prep, bool f32, hipStream_t stream) {
   for (int pass = 0; pass < 2; ++pass) {
     TrsvPrep st{};
     int total = 0;
@@ -1392,11 +1392,11 @@ int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
       if (st.ndom == 0) return;
       const dim3 ig(total, kTrsvNB / 16, 2), cg(total, (kTrsvNB / 64) * (kTrsvNB / 64), 2), b256(256);
       if (pass == 0) {
-        if (f32) hipLaunchKernelGGL(k_diag_inv_c, ig, b256, 0, ctx->stream, st);
-        else hipLaunchKernelGGL(k_diag_inv_z, ig, b256, 0, ctx->stream, st);
+        if (f32) hipLaunchKernelGGL(k_diag_inv_c, ig, b256, 0, stream, st);
+        else hipLaunchKernelGGL(k_diag_inv_z, ig, b256, 0, stream, st);
       } else {
-        if (f32) hipLaunchKernelGGL(k_trsv_coupling_c, cg, b256, 0, ctx->stream, st);
-        else hipLaunchKernelGGL(k_trsv_coupling_z, cg, b256, 0, ctx->stream, st);
+        if (f32) hipLaunchKernelGGL(k_trsv_coupling_c, cg, b256, 0, stream, st);
+        else hipLaunchKernelGGL(k_trsv_coupling_z, cg, b256, 0, stream, st);
       }
       st.ndom = total = 0;
     };
@@ -1411,6 +1411,15 @@ int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
     flush();
     LAUNCHCK();
   }
+  return VIE_OK;
+}
+
+// The pivots read back (zero pivot: VIE_ESINGULAR), each block's row
+// permutation built on the host and uploaded; the context becomes S_FACTORED.
+int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms) {
+  const MeshTopology &t = ctx->topo;
+  const Layout &L = ctx->L;
+  int32_t *ipiv = ctx->ptr<int32_t>(L.ipiv), *perm = ctx->ptr<int32_t>(L.perm), *info = ctx->ptr<int32_t>(L.info);
   HIPCK(hipEventRecord(ctx->ev1, ctx->stream));
   HIPCK(hipMemcpyAsync(ctx->pinned, info, 4 * t.ndom, hipMemcpyDeviceToHost, ctx->stream));
   // pivots and permutation staged in pinned memory, or pageable memory after a no-allocation bind
@@ -1476,6 +1485,9 @@ int vie_precond_factor(vie_ctx *ctx) {
   if (int rc = factor_panels(ctx, doms, fp32_factors(ctx), ctx->lu_pivot, ctx->stream, ctx->side, ctx->ev_la,
                              ctx->ev_ts))
     return rc;
+  std::vector<TrsvPrepDom> prep;
+  factor_prep(ctx, doms, prep);
+  if (int rc = factor_blocks(ctx, prep, fp32_factors(ctx), ctx->stream)) return rc;
   return factor_finish(ctx, doms);
 }
 

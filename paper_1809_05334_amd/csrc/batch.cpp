@@ -434,6 +434,9 @@ int vie_batch_factor(vie_batch *b) {
   vie_ctx *x0 = b->cells[0];
   if (int rc = factor_panels(x0, all, fp32_factors(x0), 0, b->stream, b->side, b->ev_la, b->ev_ts))
     return cell_fail(b, 0, rc);
+  std::vector<TrsvPrepDom> prep;
+  for (int c = 0; c < nc; ++c) factor_prep(b->cells[c], per[c], prep);
+  if (int rc = factor_blocks(x0, prep, fp32_factors(x0), b->stream)) return cell_fail(b, 0, rc);
   for (int c = 0; c < nc; ++c)
     if (int rc = factor_finish(b->cells[c], per[c])) return cell_fail(b, c, rc);
   BCK(hipEventRecord(b->ev1, b->stream));

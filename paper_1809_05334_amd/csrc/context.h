@@ -198,6 +198,8 @@ int fill_finish(vie_ctx *ctx, bool timed);
 int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms);
 int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot, hipStream_t stream, hipStream_t side,
                   hipEvent_t ev_la, hipEvent_t ev_ts);
+void factor_prep(vie_ctx *ctx, const std::vector<LuDom> &doms, std::vector<TrsvPrepDom> &prep);
+int factor_blocks(vie_ctx *ctx, const std::vector<TrsvPrepDom> &prep, bool f32, hipStream_t stream);
 int factor_finish(vie_ctx *ctx, const std::vector<LuDom> &doms);
 
 }  // namespace vie

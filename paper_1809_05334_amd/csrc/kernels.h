@@ -140,7 +140,7 @@ __global__ void k_add_near_c(ZOut Z, int64_t start, int n, fz *A, int64_t lda);
 constexpr int kLuNB = 64;
 constexpr int kColT = 4;        // lanes per row in the panel column kernel
 constexpr int kColRows = 64;    // rows per thread block of the panel column kernel (256 / kColT)
-constexpr int kLuMaxDom = 8;
+constexpr int kLuMaxDom = 32;   // (a launch's descriptors: 3.1 KB of the 4 KB of kernel arguments)
 // The bulk update leaves compute units to the next pair's panels on the side
 // stream (k_lu_gemm2q: as many blocks as the chip holds take the tiles in
 // turn) when the panels' tournament nodes fill a whole compute unit each:
@@ -194,6 +194,7 @@ struct LuStep {
                       // turn and leave free_cus compute units per shader engine to other kernels (nullptr: one tile each)
   int free_cus;
 };
+static_assert(sizeof(LuStep) <= 4096, "kernel arguments");
 #define VIE_DECL_LU(T)                       \
   __global__ void k_lu_pivot_##T(LuStep st); \
   __global__ void k_lu_col_##T(LuStep st);   \

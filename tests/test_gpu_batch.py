@@ -104,3 +104,19 @@ def test_fused_symmetric_fill():
     sym = run_fused(vie, cases, vie.VIE_FP64, 1e-12, graph=True, sym=True)
     for (_, A, R, T, _), (_, sA, sR, sT, _) in zip(plain, sym):
         assert np.max(np.abs(sA - A)) <= 1e-9 and abs(sR - R) <= 1e-9 and abs(sT - T) <= 1e-9
+
+
+@pytest.mark.parametrize("copies", [2, 3, 4])
+def test_fused_batch_of_more_domains_than_a_launch_takes(copies):
+    """12 domains per copy of the cells: 24, 36 and 48, the factorisation's
+    launches taking 32 each.  Bars as above."""
+    from paper_1809_05334_amd import vie
+    cases = cells()
+    fused = run_fused(vie, cases * copies, vie.VIE_MIXED_FP32, 1e-12, graph=False)
+    for k, case in enumerate(cases):
+        info, A, R, T, x = run_alone(vie, case, vie.VIE_MIXED_FP32, 1e-12)
+        for c in range(copies):
+            fi, fA, fR, fT, fx = fused[c * len(cases) + k]
+            assert info["converged"] and fi["converged"]
+            assert np.max(np.abs(fA - A)) <= 1e-9 and abs(fR - R) <= 1e-9 and abs(fT - T) <= 1e-9
+            assert np.linalg.norm(fx - x) <= 1e-9 * np.linalg.norm(x)
