@@ -128,16 +128,18 @@ __global__ __launch_bounds__(256) void k_diag_inv_c(TrsvPrep st) { diag_inv_body
 // another in the sweep's order (b >= 1 for L, b <= nbk - 2 for U), with p =
 // b - 1 (L) or b + 1 (U), G_b = T[b, p] inv(T_pp), a kTrsvNB x kTrsvNB
 // product in FP64 (rounded to the factor type), written to slot b - 1 (L) or
-// b (U) of nb^2 entries, leading dimension nb.  A
-// thread block forms a 64 x 64 tile, 4 x 4 entries per thread, through
-// 16-deep slices of both operands in shared memory; entries past the blocks'
-// sizes are zero.  All domains' L and U blocks share a launch (one domain and
-// one triangle at a time left most CUs idle: a batch of six cells, 24 launches
-// of 0.21 ms).
+// b (U) of nb^2 entries, leading dimension nb.  A thread block forms a 64 x 64
+// tile on the FP64 matrix cores, 2 x 2 waves of 2 x 2 instruction tiles, through
+// 16-deep slices of both operands in shared memory, the next slice's loads in
+// flight; entries past the blocks' sizes are zero, and slices in which the
+// triangle inv(T_pp) is zero are left out (half of them).  All domains' L and U
+// blocks share a launch.  The matrix cores' FP64 rate bounds it: N = 15,840, FP64, 0.72
+// ms, six FP32 cells of up to 5,500 1.19 ms (1.80 and 2.41 with FMAs, 4 x 4
+// entries per thread, over all slices).
 template <typename C>
 __device__ __forceinline__ void coupling_body(const TrsvPrep &st) {
-  constexpr int nb = kTrsvNB, TS = 64, KS = 16;
-  __shared__ dz As[TS][KS + 1], Bs[KS][TS + 1];
+  constexpr int nb = kTrsvNB, TS = 64, KS = 16, kPer = TS * KS / 256;
+  __shared__ double Ar[TS][KS + 1], Ai[TS][KS + 1], Br[KS][TS + 1], Bi[KS][TS + 1];
   int dd = 0;
   while (dd + 1 < st.ndom && (int)blockIdx.x >= st.d[dd + 1].first_block) ++dd;
   const TrsvPrepDom &D = st.d[dd];
@@ -150,49 +152,76 @@ __device__ __forceinline__ void coupling_body(const TrsvPrep &st) {
   const int p = lower ? b - 1 : b + 1;
   const int b0 = b * nb, p0 = p * nb;
   const int mr = min(nb, n - b0), mc = min(nb, n - p0);
-  const int tr = blockIdx.y / (nb / TS), tc = blockIdx.y % (nb / TS);
-  const int tid = threadIdx.x, ty = tid >> 4, tx = tid & 15;
+  const int r0 = blockIdx.y / (nb / TS) * TS, c0 = blockIdx.y % (nb / TS) * TS;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int wr = (wave >> 1) * 32, wc = (wave & 1) * 32, li = lane & 15, lg = lane >> 4;
   const C *__restrict__ Ip = INV + (int64_t)p * nb * nb;   // mc x mc, leading dimension mc
-  dz acc[4][4];
+  v4d cre[2][2], cim[2][2];
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 4; ++v) acc[u][v] = mk(0, 0);
-  for (int k0 = 0; k0 < nb; k0 += KS) {
-    // A slice: rows tr*TS .. +TS of T[b, p], columns k0 .. k0+KS; B slice: rows k0 .. of inv(T_pp)
+    for (int v = 0; v < 2; ++v) cre[u][v] = cim[u][v] = v4d{0, 0, 0, 0};
+  // inv(T_pp) is zero above (L) or below (U) its diagonal: rows k of column tile c0
+  const int kbeg = lower ? c0 : 0, kend = r0 < mr && c0 < mc ? min(mc, lower ? nb : c0 + TS) : 0;
+  C va[kPer], vb[kPer];
+  const auto fetch = [&](int k0) {
 #pragma unroll
-    for (int e = tid; e < TS * KS; e += 256) {
-      const int rr = e / KS, kk = e % KS;
-      const int gr = tr * TS + rr, gk = k0 + kk;
-      As[rr][kk] = gr < mr && gk < mc ? to_dz(F[(int64_t)(b0 + gr) * ld + p0 + gk]) : mk(0, 0);
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + 256 * u;
+      va[u] = F[(int64_t)(b0 + min(r0 + e / KS, mr - 1)) * ld + p0 + min(k0 + e % KS, mc - 1)];
+      vb[u] = Ip[(int64_t)min(k0 + e / TS, mc - 1) * mc + min(c0 + e % TS, mc - 1)];
     }
+  };
+  if (kbeg < kend) fetch(kbeg);
+  for (int k0 = kbeg; k0 < kend; k0 += KS) {
+    __syncthreads();   // the previous slice's shared reads are done
 #pragma unroll
-    for (int e = tid; e < KS * TS; e += 256) {
-      const int kk = e / TS, cc = e % TS;
-      const int gk = k0 + kk, gc = tc * TS + cc;
-      Bs[kk][cc] = gk < mc && gc < mc ? to_dz(Ip[(int64_t)gk * mc + gc]) : mk(0, 0);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int kk = 0; kk < KS; ++kk) {
-      dz a[4], bb[4];
-#pragma unroll
-      for (int u = 0; u < 4; ++u) a[u] = As[ty * 4 + u][kk];
-#pragma unroll
-      for (int v = 0; v < 4; ++v) bb[v] = Bs[kk][tx * 4 + v];
-#pragma unroll
-      for (int u = 0; u < 4; ++u)
-#pragma unroll
-        for (int v = 0; v < 4; ++v) cmac(acc[u][v], a[u], bb[v]);
+    for (int u = 0; u < kPer; ++u) {
+      const int e = tid + 256 * u;
+      const bool ka = r0 + e / KS < mr && k0 + e % KS < mc, kb = k0 + e / TS < mc && c0 + e % TS < mc;
+      const dz a = to_dz(va[u]), v = to_dz(vb[u]);
+      Ar[e / KS][e % KS] = ka ? a.re : 0.0;
+      Ai[e / KS][e % KS] = ka ? a.im : 0.0;
+      Br[e / TS][e % TS] = kb ? v.re : 0.0;
+      Bi[e / TS][e % TS] = kb ? v.im : 0.0;
     }
     __syncthreads();
+    fetch(min(k0 + KS, mc - 1));   // the next slice (clamped; unused past the end)
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int kk = 0; kk < KS; kk += 4) {
+      double are[2], aim[2], bre[2], bim[2];
+#pragma unroll
+      for (int u = 0; u < 2; ++u) {
+        are[u] = Ar[wr + 16 * u + li][kk + lg];
+        aim[u] = Ai[wr + 16 * u + li][kk + lg];
+        bre[u] = Br[kk + lg][wc + 16 * u + li];
+        bim[u] = Bi[kk + lg][wc + 16 * u + li];
+      }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          cre[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(are[u], bre[v], cre[u][v], 0, 0, 0);
+          cim[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(are[u], bim[v], cim[u][v], 0, 0, 0);
+        }
+#pragma unroll
+      for (int u = 0; u < 2; ++u)
+#pragma unroll
+        for (int v = 0; v < 2; ++v) {
+          cre[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(-aim[u], bim[v], cre[u][v], 0, 0, 0);
+          cim[u][v] = __builtin_amdgcn_mfma_f64_16x16x4f64(aim[u], bre[v], cim[u][v], 0, 0, 0);
+        }
+    }
   }
   C *__restrict__ Gb = G + (int64_t)(lower ? b - 1 : b) * nb * nb;   // slots of the sweep's nbk - 1 blocks
 #pragma unroll
-  for (int u = 0; u < 4; ++u)
+  for (int u = 0; u < 2; ++u)
 #pragma unroll
-    for (int v = 0; v < 4; ++v)
-      Gb[(int64_t)(tr * TS + ty * 4 + u) * nb + tc * TS + tx * 4 + v] = cx<C>::of(acc[u][v]);
+    for (int v = 0; v < 2; ++v)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        Gb[(int64_t)(r0 + wr + 16 * u + 4 * q + lg) * nb + c0 + wc + 16 * v + li] = cx<C>::of(mk(cre[u][v][q], cim[u][v][q]));
 }
 __global__ __launch_bounds__(256) void k_trsv_coupling_z(TrsvPrep st) { coupling_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_trsv_coupling_c(TrsvPrep st) { coupling_body<fz>(st); }
