@@ -961,7 +961,7 @@ int fill_kernels(vie_ctx *ctx) {
                              kappa, zo);
         LAUNCHCK();
       }
-      hipLaunchKernelGGL(k_face_face, dim3(nblk(ctx->nface, 64), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_,
+      hipLaunchKernelGGL(k_face_face, dim3(nblk(ctx->nface, kFaceChunk), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_,
                          pkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, ctx->nface, sigma, zo);
       LAUNCHCK();
     }

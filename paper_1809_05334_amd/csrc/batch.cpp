@@ -370,7 +370,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       if (!x->nface || !x->nhalf) continue;
       const auto c = P(x);
       FaceFaceSeg s{c.pk, c.pkl, c.qr, c.fg, c.half, x->nhalf, x->nface, c.sigma, c.zo, 0, 0};
-      ff.add(s, (int)nblk(x->nface, 64), (int)nblk(x->nhalf, 4), x->fill_lds);
+      ff.add(s, (int)nblk(x->nface, kFaceChunk), (int)nblk(x->nhalf, 4), x->fill_lds);
     }
     put(ff, K_FF);
   }

@@ -671,12 +671,15 @@ __global__ __launch_bounds__(256, 2) void k_face_tet_near(const double *__restri
 }
 
 // half-SWG test face x surface-charge face: Z[m_F, n_G] += sigma_G M0.  A wave
-// takes one test face and 64 source faces: first the far pairs, one lane each
-// (3 x 3 points; none with no dense part in the destination, the
+// takes one test face and kFaceChunk = 21 source faces, three lanes each: first
+// the far pairs, lane 3 s + i the point i of the test face with the source
+// face's three points (none with no dense part in the destination, the
 // structured-grid operator, whose far pairs come from its FFT tables), then
 // the few touching ones, three at a time: outer 7-point rule, lane 21 s + 3 p +
 // j the outer point p of the s-th pair and the inner point j of the 3-point
-// rule for the remainder, the closed form int_G 1/R with j = 0.
+// rule for the remainder, the closed form int_G 1/R with j = 0.  On small cells
+// one wave's chain is the launch: N = 416, 122 us (199 with 64 source faces
+// per wave, the points of a far pair in turn).
 __device__ __forceinline__ void k_face_face_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
                                                    const FaceGeom *__restrict__ fg,
                                                    const int32_t *__restrict__ half_list, int nhalf, int nface,
@@ -686,36 +689,37 @@ __device__ __forceinline__ void k_face_face_body(const double *__restrict__ pack
   stage_table(pack, packlen, s_tab);
   const double *__restrict__ P = s_tab;
 
-  const int lane = threadIdx.x & 63;
+  const int lane = threadIdx.x & 63, ls = lane / 3, li = lane - 3 * ls;   // (lane 63: ls = 21, idle)
   const int hi = uniform(by_ * 4 + (threadIdx.x >> 6));
-  const int gi = bx_ * 64 + lane;
+  const int gi = bx_ * kFaceChunk + ls;
   if (hi >= nhalf) return;
   const FaceGeom &f = fg[uniform(half_list[hi])];
   const FaceGeom &gl = fg[min(gi, nface - 1)];
-  const int mask = gi < nface ? touch_mask(f.canon, f.off, 3, gl.canon, gl.off, 3) : 0;
+  const bool ok = ls < kFaceChunk && gi < nface;
+  const int mask = ok ? touch_mask(f.canon, f.off, 3, gl.canon, gl.off, 3) : 0;
   if (out.Z || out.Zs) {
-    if (gi < nface && mask == 0) {
-      dz acc = mk(0, 0);
-#pragma unroll 1
-      for (int i = 0; i < 3; ++i) {
-        double sep[3][3];
+    dz acc = mk(0, 0);
+    if (ok && mask == 0) {
+      double sep[3][3];
 #pragma unroll
-        for (int d = 0; d < 3; ++d) {
-          const double r = qr->tri3[i][0] * f.v[0][d] + qr->tri3[i][1] * f.v[1][d] + qr->tri3[i][2] * f.v[2][d];
+      for (int d = 0; d < 3; ++d) {
+        const double r = qr->tri3[li][0] * f.v[0][d] + qr->tri3[li][1] * f.v[1][d] + qr->tri3[li][2] * f.v[2][d];
 #pragma unroll
-          for (int j = 0; j < 3; ++j)
-            sep[j][d] = r - (qr->tri3[j][0] * gl.v[0][d] + qr->tri3[j][1] * gl.v[1][d] + qr->tri3[j][2] * gl.v[2][d]);
-        }
-        dz g[3];
-        pgf_eval_w<false, 3>(P, sep, 0, g);
-        acc = acc + (g[0] + g[1] + g[2]);
+        for (int j = 0; j < 3; ++j)
+          sep[j][d] = r - (qr->tri3[j][0] * gl.v[0][d] + qr->tri3[j][1] * gl.v[1][d] + qr->tri3[j][2] * gl.v[2][d]);
       }
-      zput(out, f.unknown, gl.unknown, sigma[gi] * ((f.area / 3.0 * (gl.area / 3.0)) * acc), false);
+      dz g[3];
+      pgf_eval_w<false, 3>(P, sep, 0, g);
+      acc = g[0] + g[1] + g[2];
     }
+    const dz a1 = mk(__shfl_down(acc.re, 1), __shfl_down(acc.im, 1)), a2 = mk(__shfl_down(acc.re, 2), __shfl_down(acc.im, 2));
+    acc = (acc + a1) + a2;
+    if (ok && mask == 0 && li == 0)
+      zput(out, f.unknown, gl.unknown, sigma[gi] * ((f.area / 3.0 * (gl.area / 3.0)) * acc), false);
   }
   const int s3 = min(lane / 21, 2), p = (lane - 21 * s3) / 3, j = (lane - 21 * s3) % 3;   // (lane 63: p = 7, idle)
-  for (unsigned long long todo = __ballot(mask != 0); todo != 0;) {
-    // the next three touching lanes (fewer at the end: the last one again, not stored)
+  for (unsigned long long todo = __ballot(mask != 0 && li == 0); todo != 0;) {
+    // the next three touching faces' lanes (fewer at the end: the last one again, not stored)
     int src[3], np = 0;
     for (int s = 0; s < 3; ++s) {
       if (todo != 0) {
@@ -727,7 +731,7 @@ __device__ __forceinline__ void k_face_face_body(const double *__restrict__ pack
       }
     }
     const int mine = s3 == 0 ? src[0] : (s3 == 1 ? src[1] : src[2]);
-    const int tm = __shfl(mask, mine), ti = bx_ * 64 + mine;
+    const int tm = __shfl(mask, mine), ti = bx_ * kFaceChunk + mine / 3;
     const FaceGeom &g = fg[ti];
     const int pp = min(p, 6);
     double r[3], sep[1][3];

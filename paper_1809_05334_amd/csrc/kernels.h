@@ -54,6 +54,7 @@ inline int far_tper(int64_t nsrc, int64_t ntest) {
 // and its local block (bx, by) = ((b - first) % gx, (b - first) / gx).
 // Segments are ordered by `first`.  The dynamic LDS of the launch is the
 // largest of its cells' lattice-sum tables.
+constexpr int kFaceChunk = 21;   // source faces per wave of k_face_face
 struct FarSeg {
   const double *pack; int packlen; const QuadRules *qr; const TetGeom *tg; const TetFace *t2f;
   const int32_t *test_list; int ntest; const int32_t *src_list; int nsrc;
