@@ -421,10 +421,11 @@ __device__ __forceinline__ void lu_trsm_body(const LuStep &st) {
 // operand of the matrix instructions that apply the 8 steps to the columns
 // right of the block (zero for used rows), the 8 pivot rows, solved against
 // each other one column per thread, as the second.  The chain of steps bounds
-// a panel, so a step does as little as it can.  Mean time per panel, against one
-// or two lanes per row that held all 64 columns and took the 8 steps by FMAs:
-// FP64, N = 6,272, 242 us (387), N = 15,840, 358 (597); FP32, 512-row nodes,
-// N = 3,038, 158 (172).
+// a panel, so a step does as little as it can: the winner's row is read at once
+// (one entry after another, as the registers allowed, cost a tenth of a panel).
+// Mean time per panel, against one or two lanes per row that held all 64 columns
+// and took the 8 steps by FMAs: FP64, N = 6,272, 214 us (387), N = 15,840, 316
+// (597); FP32, 512-row nodes, N = 3,038, 153 (172).
 template <typename C, bool WIDE> struct TsCfg;
 template <> struct TsCfg<dz, false> {
   static constexpr int wrows = kTsWaveZ, fan = kTsFanZ, rows = kTsRowsZ;
@@ -442,11 +443,11 @@ struct TsShared {
   static constexpr int kFan = TsCfg<C, WIDE>::fan, kRows = TsCfg<C, WIDE>::rows, kWRows = TsCfg<C, WIDE>::wrows,
                        kStepWaves = kRows / 64,   // waves that hold a row per lane in the steps
                        kPLd = kRows + 4;
-  C P[kTsBlk][kPLd];                  // the block's columns, then the rows' multipliers
-  C U[kTsBlk][kLuNB];                 // the block's pivot rows, columns right of the block
-  C L11[kTsBlk][kTsBlk];              // the pivot rows' multipliers inside the block
-  C crow[2][kStepWaves][kTsBlk];      // each wave's best candidate row, by step parity
-  C crinv[2][kStepWaves];             // reciprocal of its pivot
+  alignas(16) C P[kTsBlk][kPLd];               // the block's columns, then the rows' multipliers
+  alignas(16) C U[kTsBlk][kLuNB];              // the block's pivot rows, columns right of the block
+  alignas(16) C L11[kTsBlk][kTsBlk];           // the pivot rows' multipliers inside the block
+  alignas(16) C crow[2][kStepWaves][kTsBlk];   // each wave's best candidate row, by step parity
+  alignas(16) C crinv[2][kStepWaves];          // reciprocal of its pivot
   unsigned long long key[2][kStepWaves];
   int rid[kRows];                     // the node's rows (rows of the domain)
   int step[kRows];                    // the step each row was the pivot of, -1 if none
@@ -565,6 +566,12 @@ __device__ __forceinline__ void ts_gepp(Sh &S, const C *__restrict__ A, int64_t 
           const int wb = (__ffsll((long long)__ballot(hi == best)) - 1) & (PW - 1);
           const int p = __builtin_amdgcn_readlane((int)(unsigned)kw, wb);
           const bool nonzero = best > 1u;
+          // the winner's row, all its reads in flight at once
+          const C rp = S.crinv[buf][wb];
+          C pv[kTsBlk];
+#pragma unroll
+          for (int k = jt + 1; k < kTsBlk; ++k) pv[k] = S.crow[buf][wb][k];
+          __builtin_amdgcn_sched_barrier(0);
           if (!nonzero && zero == 0) zero = j0 + jt + 1;
           if (tid == p && best != 0u) {   // the pivot row: not updated any more
             own = jt;
@@ -572,9 +579,9 @@ __device__ __forceinline__ void ts_gepp(Sh &S, const C *__restrict__ A, int64_t 
           }
           if (tid == 0) S.order[j0 + jt] = best != 0u ? p : -1;
           if (!used && nonzero) {
-            const C l = x[jt] * S.crinv[buf][wb];
+            const C l = x[jt] * rp;
 #pragma unroll
-            for (int k = jt + 1; k < kTsBlk; ++k) x[k] = fms(x[k], l, S.crow[buf][wb][k]);
+            for (int k = jt + 1; k < kTsBlk; ++k) x[k] = fms(x[k], l, pv[k]);
             x[jt] = l;
           }
         }

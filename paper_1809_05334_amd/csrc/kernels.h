@@ -150,7 +150,7 @@ constexpr int kLuMaxDom = 32;   // (a launch's descriptors: 3.1 KB of the 4 KB o
 // kGemm2QueueMax tiles the unit per shader engine costs the update more than
 // the panels it hides.  Factor, FP64, N = 15,840 (15,000 tiles at first):
 // 91 ms with one unit per shader engine, 97 with two, 106 with three, 106
-// with a block per tile; FP32, six cells of up to 5,500 unknowns (wide
+// with a block per tile (88 now, by faster tournament steps); FP32, six cells of up to 5,500 unknowns (wide
 // nodes): 44.8 against 47.5.  FP32, N = 37,376, whose nodes take half a unit
 // and so share them with the update: 442 against 385 when it was tried, so
 // not for those.
