@@ -91,7 +91,7 @@ class Server:
         self._stop = False
         self.done = []
         self.peak_used = 0.0
-        self.peak_running = 0
+        self.peak_running = 0            # most requests in service at once: admitted, or prepared towards a free slot
         self.admit_order = []
         self._workers = []
 
@@ -165,6 +165,10 @@ class Server:
             self._cv.notify_all()
 
     def _enqueue(self, req, t_arrival):
+        with self._cv:
+            # its host preparation (a fifth of a small request's time) is part of its service
+            if self._free:
+                self.peak_running = max(self.peak_running, self._running + 1)
         prep, fp = self.backend.prepare(req)
         job = _Job(req, prep, fp, t_arrival)
         with self._cv:
