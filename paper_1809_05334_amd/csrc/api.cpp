@@ -208,7 +208,6 @@ Layout make_layout(const MeshTopology &t, int restart, int64_t nnear, int nface,
   put(L.kv, 8 * 3 * 2 * 32);
   // solver scratch; also the reduction target of the R/T projections (6 doubles per k-vector, <= 64)
   put(L.idx, std::max<size_t>(16 * (size_t)N, 8 * 6 * 64));
-  put(L.luq, 4 * (size_t)kLuQueue);
   L.total = off;
   return L;
 }
@@ -709,7 +708,6 @@ int bind_impl(vie_ctx *ctx, void *dev_ptr, size_t bytes, int precision, int rest
   if (rc) return rc;
   // the panel and tournament counters start (and always end) at zero
   HIPCK(hipMemsetAsync(ctx->ws + L.lucnt.off, 0, L.lucnt.bytes, ctx->stream));
-  HIPCK(hipMemsetAsync(ctx->ws + L.luq.off, 0, L.luq.bytes, ctx->stream));
   HIPCK(hipMemsetAsync(ctx->ws + L.ttcnt.off, 0, L.ttcnt.bytes, ctx->stream));
   HIPCK(hipStreamSynchronize(ctx->stream));   // host staging vectors go out of scope
   ctx->state = S_BOUND;
@@ -1089,7 +1087,6 @@ void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &d
                int all_cols = 0, int gcol0 = 0, int gcols = 0, int c_lo = 0, int c_hi = 0, int *queue = nullptr) {
   LuStep st{};
   st.queue = queue;
-  st.free_cus = kGemm2FreeCus;
   st.j = j;
   st.k0 = k0;
   st.all_cols = all_cols;
@@ -1122,8 +1119,8 @@ void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &d
         else hipLaunchKernelGGL(k_lu_gemm_z, dim3(total), dim3(256), 0, sm, st);
         break;
       case LU_GEMM2:
-        // a block per tile and per slot of the units left free (32 shader engines, two slots per unit)
-        if (queue) total = std::min(total + 64 * kGemm2FreeCus, kGemm2Slots);
+        // a block per tile and per slot of the units left free (two each)
+        if (queue) total = std::min(total + 2 * kGemm2FreeUnits, kGemm2Slots);
         if (queue && f32) hipLaunchKernelGGL(k_lu_gemm2q_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         else if (queue) hipLaunchKernelGGL(k_lu_gemm2q_z, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         else if (f32) hipLaunchKernelGGL(k_lu_gemm2_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
@@ -1214,6 +1211,44 @@ int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms) {
     }
     LAUNCHCK();
   }
+  return VIE_OK;
+}
+
+// A side stream for the panels beside `stream`'s bulk updates, kept while the
+// factorisations stay on that stream.  HIP maps the streams of a process onto
+// four hardware queues, and two streams on one queue run one after the other
+// (factor, FP64, N = 15,840: 114 ms instead of 90), so a new stream is tried
+// with a pair of small kernels and up to three more are made to find one that
+// runs beside.  ctx: any bound context of the device (16 B of Krylov scratch).
+int side_stream(vie_ctx *ctx, hipStream_t stream, hipStream_t *side, hipStream_t *side_of) {
+  if (*side && *side_of == stream) return VIE_OK;
+  if (*side) {
+    HIPCK(hipStreamSynchronize(*side));
+    HIPCK(hipStreamDestroy(*side));
+    *side = nullptr;
+  }
+  int *flag = ctx->ptr<int>(ctx->L.K[0].vw);
+  hipStream_t tried[4];
+  int n = 0, seen = 0;
+  hipError_t e = hipSuccess;
+  while (n < 4 && !seen) {
+    if ((e = hipStreamCreateWithFlags(&tried[n], hipStreamNonBlocking)) != hipSuccess) break;
+    ++n;
+    hipLaunchKernelGGL(k_side_set, dim3(1), dim3(1), 0, tried[n - 1], flag);   // (its hardware queue may be made only now)
+    if ((e = hipStreamSynchronize(tried[n - 1])) != hipSuccess) break;
+    if ((e = hipMemsetAsync(flag, 0, 8, stream)) != hipSuccess) break;
+    if ((e = hipStreamSynchronize(stream)) != hipSuccess) break;
+    hipLaunchKernelGGL(k_side_wait, dim3(1), dim3(1), 0, stream, flag);
+    hipLaunchKernelGGL(k_side_set, dim3(1), dim3(1), 0, tried[n - 1], flag);
+    if ((e = hipGetLastError()) != hipSuccess) break;
+    if ((e = hipMemcpyAsync(&seen, flag + 1, 4, hipMemcpyDeviceToHost, stream)) != hipSuccess) break;
+    if ((e = hipStreamSynchronize(stream)) != hipSuccess) break;
+    if ((e = hipStreamSynchronize(tried[n - 1])) != hipSuccess) break;
+  }
+  for (int i = 0; i + 1 < n; ++i) (void)hipStreamDestroy(tried[i]);
+  if (n > 0) *side = tried[n - 1];
+  if (e != hipSuccess) return fail(ctx, VIE_EDEVICE, "side stream: %s", hipGetErrorString(e));
+  *side_of = stream;
   return VIE_OK;
 }
 
@@ -1308,7 +1343,9 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
       ++ctx->upd_n;
       return VIE_OK;
     };
-    int *queue = ctx->ptr<int>(ctx->L.luq);
+    // the tile queue's counters, in the scratch of ctx's first Krylov process (16 N bytes: with a tile N > 128)
+    int *queue = ctx->ptr<int>(ctx->L.K[0].vw);
+    if (ctx->L.K[0].vw.bytes >= 4 * (size_t)kLuQueue) HIPCK(hipMemsetAsync(queue, 0, 4 * (size_t)kLuQueue, stream));
     constexpr int kBig = 1 << 30;
     auto panels = [&](int k0, hipStream_t sm) {
       const int kb = k0 + kLuNB, pe = k0 + 2 * kLuNB;
@@ -1481,7 +1518,7 @@ extern "C" {
 int vie_precond_factor(vie_ctx *ctx) {
   std::vector<LuDom> doms;
   if (int rc = factor_prepare(ctx, doms)) return rc;
-  if (!ctx->side) HIPCK(hipStreamCreateWithFlags(&ctx->side, hipStreamNonBlocking));
+  if (int rc = side_stream(ctx, ctx->stream, &ctx->side, &ctx->side_of)) return rc;
   if (int rc = factor_panels(ctx, doms, fp32_factors(ctx), ctx->lu_pivot, ctx->stream, ctx->side, ctx->ev_la,
                              ctx->ev_ts))
     return rc;

@@ -29,7 +29,7 @@ struct vie_batch {
   double *pin_res = nullptr;        // pinned: residual estimates / norms, one per cell
   int *pin_act = nullptr;           // pinned: Arnoldi-step flags, one per cell
   int pin_cap = 0;                  // cells the pinned buffers hold
-  hipStream_t side = nullptr;
+  hipStream_t side = nullptr, side_of = nullptr;
   hipEvent_t ev0 = nullptr, ev1 = nullptr, ev_la = nullptr, ev_ts = nullptr;
   int graph = 1;                    // capture the fused Arnoldi step in a HIP graph
   hipGraphExec_t gexec = nullptr;
@@ -122,7 +122,6 @@ int vie_batch_create(vie_batch **out, int device, void *hip_stream) {
   BCK(hipSetDevice(device));
   BCK(hipEventCreate(&b->ev0));
   BCK(hipEventCreate(&b->ev1));
-  BCK(hipStreamCreateWithFlags(&b->side, hipStreamNonBlocking));
   BCK(hipEventCreateWithFlags(&b->ev_la, hipEventDisableTiming));
   BCK(hipEventCreateWithFlags(&b->ev_ts, hipEventDisableTiming));
   *out = b;
@@ -432,6 +431,7 @@ int vie_batch_factor(vie_batch *b) {
     all.insert(all.end(), per[c].begin(), per[c].end());
   }
   vie_ctx *x0 = b->cells[0];
+  if (int rc = side_stream(x0, b->stream, &b->side, &b->side_of)) return cell_fail(b, 0, rc);
   if (int rc = factor_panels(x0, all, fp32_factors(x0), 0, b->stream, b->side, b->ev_la, b->ev_ts))
     return cell_fail(b, 0, rc);
   std::vector<TrsvPrepDom> prep;

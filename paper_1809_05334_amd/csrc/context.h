@@ -37,7 +37,7 @@ struct Layout {
   Region tg, t2f, area, dom, fg, half, ctp, ctm, utet, uk, colors, near_t, near_s, near_m, near_tf, near_ft, quad, pgf,
       pack;
   Region eps, alpha, gsrc, kappa, inveps, sigma;
-  Region Z, Zt, nrow, ncol, nval, F, ipiv, perm, rpiv, info, lupv, lupi, lucnt, luq, tcand, ttcnt, tblk, dinv, gcpl, trr, tbsum,
+  Region Z, Zt, nrow, ncol, nval, F, ipiv, perm, rpiv, info, lupv, lupi, lucnt, tcand, ttcnt, tblk, dinv, gcpl, trr, tbsum,
       plans;
   // structured-grid operator (VIE_GRID_FP64): geometry, element maps, kernel
   // tables (kGridSub^2 x nf), source and potential fields (kGridFields x nf)
@@ -122,6 +122,7 @@ struct vie_ctx {
   // block LU look-ahead: the next panel's tournament on a stream of its own
   // (default priority) while the rest of the trailing update runs
   hipStream_t side = nullptr;
+  hipStream_t side_of = nullptr;    // the stream that `side` was found to run beside
   hipEvent_t ev_la = nullptr, ev_ts = nullptr;
   vie_fill_stats fstats{};
   // timing of the factorisation's K = 128 trailing updates: one event pair per
@@ -196,6 +197,7 @@ ZOut zout_staging(vie_ctx *ctx);
 int fill_kernels(vie_ctx *ctx);
 int fill_finish(vie_ctx *ctx, bool timed);
 int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms);
+int side_stream(vie_ctx *ctx, hipStream_t stream, hipStream_t *side, hipStream_t *side_of);
 int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot, hipStream_t stream, hipStream_t side,
                   hipEvent_t ev_la, hipEvent_t ev_ts);
 void factor_prep(vie_ctx *ctx, const std::vector<LuDom> &doms, std::vector<TrsvPrepDom> &prep);

@@ -1000,16 +1000,18 @@ __global__ __launch_bounds__(256) void k_lu_gemm_c(LuStep st) { lu_gemm_body<fz>
 //
 // With QUEUE a launch has at most kGemm2Slots blocks, which take tiles in
 // turn from the lists of the eight XCDs (their own first), and a block that
-// starts on one of the compute units left to the panels of the next pair ends
-// at once: those units stay free for the side stream's kernels while the
-// update runs.  Which units those are is only a hint: at most half the blocks
-// may go, and the others take every tile wherever they run.
+// starts on one of the compute units left to the panels of the next pair, one
+// per shader engine (whichever is reached first: the units' numbers differ from
+// chip to chip), ends at once: those units stay free for the side stream's
+// kernels while the update runs.  Which units those are is only a hint: at most
+// half the blocks may go, and the others take every tile wherever they run.
 template <typename C> struct Gemm2Cfg;
 template <> struct Gemm2Cfg<fz> { static constexpr int TM = 128, TN = 128, WR = 2, WC = 4; };
 template <> struct Gemm2Cfg<dz> { static constexpr int TM = 128, TN = 64, WR = 4, WC = 2; };
 constexpr int kGemm2K = 2 * kLuNB, kGemm2Group = 8;
-constexpr int kHwRegHwId = 4 | 0 << 6 | 31 << 11;   // s_getreg: the whole HW_ID register (compute unit in bits 11:8)
-constexpr int kGemm2FreeCu = 2;   // first of the compute units left free, by its number in its shader engine
+// s_getreg: the whole HW_ID register (compute unit in bits 11:8, shader engine in 15:13) and XCC_ID
+constexpr int kHwRegHwId = 4 | 0 << 6 | 31 << 11, kHwRegXccId = 20 | 0 << 6 | 31 << 11;
+static_assert(kLuQueue <= kGemm2Threads, "a counter per thread");
 
 // Tiles of domain d in a launch.
 template <typename C>
@@ -1054,7 +1056,7 @@ __device__ __forceinline__ void lu_gemm2_body(const LuStep &st) {
   constexpr int kPerA = TM * kGemmKC / NT, kPerB = kGemmKC * TN / NT;
   __shared__ R As[2][TM][kGemmKC + 1];   // [0]: real, [1]: imaginary parts
   __shared__ R Bs[2][kGemmKC][TN + 1];
-  __shared__ int s_next;
+  __shared__ int s_next, s_last;
   int d, t;
   unsigned done = 0;
   if (!QUEUE) {
@@ -1064,10 +1066,14 @@ __device__ __forceinline__ void lu_gemm2_body(const LuStep &st) {
     if (t >= total) return;
   } else {
     if (threadIdx.x == 0) {
-      // a block on one of the compute units left to the side stream's panels
-      // goes away, unless too many have
-      const int cu = __builtin_amdgcn_s_getreg(kHwRegHwId) >> 8 & 15;
-      const bool leave = cu >= kGemm2FreeCu && cu < kGemm2FreeCu + st.free_cus &&
+      // the first block of a shader engine leaves its compute unit to the side
+      // stream's panels; a block on such a unit goes away, unless too many have
+      const int id = __builtin_amdgcn_s_getreg(kHwRegHwId), cu = (id >> 8 & 15) + 1;
+      int *unit = st.queue + kLuQueueUnits + 8 * (__builtin_amdgcn_s_getreg(kHwRegXccId) & 7) + (id >> 13 & 7);
+      int left = 0;
+      const bool leave = (__hip_atomic_compare_exchange_strong(unit, &left, cu, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
+                                                               __HIP_MEMORY_SCOPE_AGENT) ||
+                          left == cu) &&
                          __hip_atomic_fetch_add(st.queue + 128, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <
                              (int)gridDim.x / 2;
       s_next = leave ? -1 : gemm2_claim<C>(st, blockIdx.x & 7, done);
@@ -1206,10 +1212,12 @@ __device__ __forceinline__ void lu_gemm2_body(const LuStep &st) {
   if (!QUEUE) return;
   }
   // the last block of the launch puts the counters back to zero
-  if (threadIdx.x == 0 &&
-      __hip_atomic_fetch_add(st.queue + 144, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1) {
-    for (int x = 0; x < 10; ++x) __hip_atomic_store(st.queue + 16 * x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  }
+  // (s_last, not s_next: a slower wave may still be about to read that)
+  if (threadIdx.x == 0)
+    s_last = __hip_atomic_fetch_add(st.queue + 144, 1, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT) == (int)gridDim.x - 1;
+  __syncthreads();
+  if (s_last && threadIdx.x < kLuQueue)
+    __hip_atomic_store(st.queue + threadIdx.x, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
 __global__ __launch_bounds__(kGemm2Threads, 4) void k_lu_gemm2_z(LuStep st) { lu_gemm2_body<dz, false>(st); }
@@ -1221,6 +1229,18 @@ __global__ __launch_bounds__(1024) void k_lu_pivot_z(LuStep st) { lu_pivot_body<
 __global__ __launch_bounds__(1024) void k_lu_pivot_c(LuStep st) { lu_pivot_body<fz>(st); }
 __global__ __launch_bounds__(256) void k_lu_col_z(LuStep st) { lu_col_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_lu_col_c(LuStep st) { lu_col_body<fz>(st); }
+// Whether another stream's kernels run beside this one's: waits until *flag is
+// set there, for at most 0.2 ms (the counter runs at 100 MHz), and keeps what it saw.
+__global__ void k_side_wait(int *flag) {
+  const unsigned long long t0 = wall_clock64();
+  int v = 0;
+  do {
+    v = __hip_atomic_load(flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } while (v == 0 && wall_clock64() - t0 < 20000ull);
+  flag[1] = v;
+}
+__global__ void k_side_set(int *flag) { __hip_atomic_store(flag, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); }
+
 __global__ __launch_bounds__(256) void k_lu_swap_z(LuStep st) { lu_swap_body<dz>(st); }
 __global__ __launch_bounds__(256) void k_lu_swap_c(LuStep st) { lu_swap_body<fz>(st); }
 __global__ __launch_bounds__(256) void k_lu_trsm_z(LuStep st) { lu_trsm_body<dz>(st); }

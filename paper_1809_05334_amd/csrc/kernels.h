@@ -142,19 +142,19 @@ constexpr int kLuNB = 64;
 constexpr int kColT = 4;        // lanes per row in the panel column kernel
 constexpr int kColRows = 64;    // rows per thread block of the panel column kernel (256 / kColT)
 constexpr int kLuMaxDom = 32;   // (a launch's descriptors: 3.1 KB of the 4 KB of kernel arguments)
-// The bulk update leaves compute units to the next pair's panels on the side
-// stream (k_lu_gemm2q: as many blocks as the chip holds take the tiles in
-// turn) when the panels' tournament nodes fill a whole compute unit each:
-// beside one block per tile, whose next block takes every half unit that
-// falls free, such a node starts only when the update is over.  Above
-// kGemm2QueueMax tiles the unit per shader engine costs the update more than
-// the panels it hides.  Factor, FP64, N = 15,840 (15,000 tiles at first):
-// 91 ms with one unit per shader engine, 97 with two, 106 with three, 106
-// with a block per tile (88 now, by faster tournament steps); FP32, six cells of up to 5,500 unknowns (wide
-// nodes): 44.8 against 47.5.  FP32, N = 37,376, whose nodes take half a unit
-// and so share them with the update: 442 against 385 when it was tried, so
-// not for those.
-constexpr int kGemm2FreeCus = 1;      // per shader engine, of its 8
+// The bulk update leaves one compute unit per shader engine to the next pair's
+// panels on the side stream (k_lu_gemm2q: as many blocks as the chip holds take
+// the tiles in turn) when the panels' tournament nodes fill a whole compute
+// unit each: beside one block per tile, whose next block takes every half unit
+// that falls free, such a node starts only when the update is over.  Above
+// kGemm2QueueMax tiles the units cost the update more than the panels they
+// hide.  Factor, FP64, N = 15,840 (15,000 tiles at first): 88-90 ms, 106 with a
+// block per tile, 97 and 106 with two and three units; with the unit of one
+// fixed number, which some shader engines of a chip may lack, up to 102.  FP32,
+// six cells of up to 5,500 unknowns (wide nodes): 33.0 against 35.5.  FP32, N =
+// 37,376, whose nodes take half a unit and so share them with the update: 442
+// against 385 when it was tried, so not for those.
+constexpr int kGemm2FreeUnits = 32;   // one of each of the 4 shader engines of 8 XCDs
 constexpr int kGemm2Slots = 512;      // blocks of k_lu_gemm2 that the 256 compute units hold at once
 constexpr int kGemm2QueueMax = 50000;
 constexpr int kGemm2Threads = 512;   // threads per block of the two-panel trailing update (k_lu_gemm2)
@@ -168,7 +168,8 @@ constexpr int kTsFanZ = 4, kTsFanC = 4, kTsFanW = 8;
 constexpr int kTsRowsZ = kTsFanZ * kLuNB, kTsRowsC = kTsFanC * kLuNB, kTsRowsW = kTsFanW * kLuNB;
 constexpr int kTsWaveZ = 32, kTsWaveC = 64;   // rows of a node per wave
 constexpr int kTsWideMax = 8192;
-constexpr int kLuQueue = 160;   // counters of a tile queue: 8 lists, blocks gone, blocks ended, 16 ints apart
+constexpr int kLuQueueUnits = 160, kLuQueue = kLuQueueUnits + 64;   // counters of a tile queue: 8 lists, blocks gone, blocks
+                                                                    // ended, 16 ints apart; the unit left free per shader engine
 struct LuDom {
   void *A;            // the domain's block (dz or fz), row-major, leading dimension ld, factored in place
   int64_t ld;
@@ -192,8 +193,7 @@ struct LuStep {
   int gcol0, gcols;   // k_lu_gemm: column tiles gcol0 .. gcol0 + gcols - 1 of A22 (gcols <= 0: to the end)
   int c_lo, c_hi;     // k_lu_swap column range (modes 2, 3); k_lu_trsm: columns [c_lo, c_hi) if c_hi > 0
   int *queue;         // k_lu_gemm2: kLuQueue counters, zero between launches, of a launch whose blocks take tiles in
-                      // turn and leave free_cus compute units per shader engine to other kernels (nullptr: one tile each)
-  int free_cus;
+                      // turn and leave a compute unit per shader engine to other kernels (nullptr: one tile each)
 };
 static_assert(sizeof(LuStep) <= 4096, "kernel arguments");
 #define VIE_DECL_LU(T)                       \
@@ -210,6 +210,8 @@ VIE_DECL_LU(z)
 VIE_DECL_LU(c)
 #undef VIE_DECL_LU
 __global__ void k_lu_tsel_wide_c(LuStep st);
+__global__ void k_side_wait(int *flag);   // flag[1] = flag[0] once set, or 0 after 0.2 ms
+__global__ void k_side_set(int *flag);
 // (k_trsv.hip)
 __global__ void k_permute(int n, int64_t off, const int32_t *perm, const dz *v, dz *z);
 // Inverses of the diagonal blocks of L (blockIdx.z 0) and U (1) of up to

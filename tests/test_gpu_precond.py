@@ -240,3 +240,19 @@ def test_panel_solves_at_sixteen_row_remainders(vie, nx, ny, nz):
             s.factor()
             err = np.linalg.norm(s.precond_apply(v) - ref) / np.linalg.norm(ref)
             assert err < bar, (N, mixed, pivot, err)
+
+
+@pytest.mark.parametrize("contexts", [2, 6])
+def test_factors_do_not_depend_on_the_contexts_made_before(vie, contexts):
+    """More contexts than the process has hardware queues, all alive: each
+    finds a side stream for its panels, and the factors are the same bits."""
+    m = W.slab_mesh(nx=5, ny=5, nz=5)
+    alive, first = [], None
+    for _ in range(contexts):
+        s = solver(vie, m, 20)
+        s.fill(600.0, 0.3, 0.2, W.slab_eps(m))
+        s.factor()
+        z = s.precond_apply(np.arange(s.num_unknowns()) + 1j)
+        first = z if first is None else first
+        assert np.array_equal(z, first)
+        alive.append(s)
