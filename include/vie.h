@@ -297,7 +297,7 @@ enum {
                              * the device at the same time (a cooperative grid holds every CU). */
   VIE_OPT_LU_PIVOT = 5,     /* row pivoting of the next vie_precond_factor: 0 (default) tournament
                              * pivoting, the pivot rows of each 64-column panel chosen by a
-                             * reduction tree of partial-pivoting eliminations on 256-row slices;
+                             * reduction tree of partial-pivoting eliminations on slices of 256 or 512 rows;
                              * 1: partial pivoting column by column.  Both give P A = L U; the
                              * factors, and so the rounding of M^{-1} v, differ between them */
   VIE_OPT_SYM_FILL = 6,     /* 1: the workspace bound next also holds a second N x ld copy of Z's
