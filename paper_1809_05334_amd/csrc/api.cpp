@@ -90,7 +90,7 @@ Layout make_layout(const MeshTopology &t, int restart, int64_t nnear, int nface,
   put(L.near_tf, 4 * std::max<size_t>(1, nested_size(t.near_tf)));
   put(L.near_ft, 4 * std::max<size_t>(1, nested_size(t.near_ft)));
   put(L.quad, sizeof(QuadRules));
-  put(L.pgf, sizeof(PgfTable));
+  put(L.fpack, precision == VIE_MIXED_FP32 ? 8 * (size_t)kMaxPack : 0);
   put(L.pack, 8 * (size_t)kMaxPack);
   put(L.eps, 16 * nt);
   put(L.alpha, 16 * 4 * nt);
@@ -779,7 +779,8 @@ int fill_tables(vie_ctx *ctx, double lambda_nm, double theta, double phi, const 
   if (!eps_per_tet || !(lambda_nm > 0) || !(std::fabs(theta) < 1.5533)) return fail(ctx, VIE_EINVAL, "bad fill arguments");
   const MeshTopology &t = ctx->topo;
   double margin = 0;
-  std::string e = build_pgf_table(*ctx->tab, t.a, t.b, t.zmax - t.zmin, lambda_nm, theta, phi, &margin);
+  std::string e = build_pgf_table(*ctx->tab, t.a, t.b, t.zmax - t.zmin, lambda_nm, theta, phi, &margin,
+                                  precision == VIE_MIXED_FP32 ? PgfTerms::fixed : PgfTerms::series);
   if (!e.empty()) return fail(ctx, VIE_EINVAL, "%s", e.c_str());
   if (margin < 0.02) return fail(ctx, VIE_EWOOD, "Floquet order near grazing (margin %.3g < 0.02)", margin);
   ctx->lambda = lambda_nm;
@@ -796,6 +797,11 @@ int fill_tables(vie_ctx *ctx, double lambda_nm, double theta, double phi, const 
   if ((int)ctx->pack.size() > kMaxPack)
     return fail(ctx, VIE_EINVAL, "lattice-sum table needs %zu doubles (> %d)", ctx->pack.size(), kMaxPack);
   ctx->packlen = (int)ctx->pack.size();
+  if (precision == VIE_MIXED_FP32) {
+    pack_pgf_fixed(*ctx->tab, ctx->fpack);
+    if ((int)ctx->fpack.size() > kMaxPack)
+      return fail(ctx, VIE_EINVAL, "lattice-sum table needs %zu doubles (> %d)", ctx->fpack.size(), kMaxPack);
+  }
   return VIE_OK;
 }
 
@@ -814,7 +820,10 @@ int fill_upload(vie_ctx *ctx) {
   const double lambda_nm = ctx->lambda, theta = ctx->theta, phi = ctx->phi;
   // the previous fill's kernels may still read the tables: wait before overwriting
   HIPCK(hipStreamSynchronize(ctx->stream));
-  HIPCK(hipMemcpyAsync(ctx->ws + L.pgf.off, ctx->tab, sizeof(PgfTable), hipMemcpyHostToDevice, ctx->stream));
+  const bool mixed = ctx->precision == VIE_MIXED_FP32;
+  if (mixed)
+    HIPCK(hipMemcpyAsync(ctx->ws + L.fpack.off, ctx->fpack.data(), 8 * ctx->fpack.size(), hipMemcpyHostToDevice,
+                         ctx->stream));
   HIPCK(hipMemcpyAsync(ctx->ws + L.pack.off, ctx->pack.data(), 8 * ctx->pack.size(), hipMemcpyHostToDevice,
                        ctx->stream));
   HIPCK(hipMemcpyAsync(ctx->ws + L.eps.off, ctx->eps_int.data(), 16 * t.nt, hipMemcpyHostToDevice, ctx->stream));
@@ -831,6 +840,7 @@ int fill_upload(vie_ctx *ctx) {
   ctx->fill_ky = ky;
   ctx->jdiag_ok = false;
   ctx->fill_lds = 8 * (size_t)ctx->packlen;
+  ctx->fill_flds = mixed ? 8 * ctx->fpack.size() : 0;
 
   hipLaunchKernelGGL(k_prep, dim3(nblk(t.nt, 256)), dim3(256), 0, ctx->stream, (int64_t)t.nt, t2f, tg,
                      ctx->ptr<double>(L.area), ctx->ptr<dz>(L.eps), kx, ky, t.a, t.b, alpha, gsrc, kappa, inveps);
@@ -846,7 +856,9 @@ int fill_upload(vie_ctx *ctx) {
   // half-SWG face) pair likewise yields the (face, tet) entry, by the same
   // two forms.  Zt is added transposed after the face kernels.
   const bool kt0 = kx == 0.0 && ky == 0.0;
-  ctx->fill_sym = L.Zt.bytes > 0;
+  // (mixed precision at oblique incidence keeps 32 KB per block of the swapped
+  // moments in LDS beside the table; a table too large for both runs the plain fill)
+  ctx->fill_sym = L.Zt.bytes > 0 && (!mixed || kt0 || ctx->fill_flds + kFarRevLds <= 65536);
   ctx->fill_sym_face = ctx->fill_sym;
   ctx->fill_rev = kt0 ? 0 : 1;
   ctx->last_sym = ctx->fill_sym;
@@ -891,6 +903,13 @@ int fill_kernels(vie_ctx *ctx) {
   const int32_t *colors = ctx->ptr<int32_t>(L.colors);
   // the grid operator takes every far pair from its FFT tables (built below)
   const bool grid = ctx->precision == VIE_GRID_FP64;
+  // mixed precision: the far pairs' FP32 entries by the kernels of k_far_c.hip
+  const bool mixed = ctx->precision == VIE_MIXED_FP32;
+  const double *fpk = ctx->ptr<double>(L.fpack);
+  const int fpkl = (int)ctx->fpack.size();
+  const size_t flds = ctx->fill_flds;
+  ZOut znear = zo;   // k_face_face takes the touching pairs alone where there is no dense part
+  if (mixed) znear.Zs = nullptr;
   HIPCK(hipEventRecord(ctx->ev2, ctx->stream));
   int far_launches = 0;
   for (int ct = 0; ct < (grid ? 0 : C); ++ct)
@@ -898,6 +917,16 @@ int fill_kernels(vie_ctx *ctx) {
       if (sym && cs < ct) continue;   // covered by the launch of (cs, ct)
       const int nT = ctx->color_off[ct + 1] - ctx->color_off[ct], nS = ctx->color_off[cs + 1] - ctx->color_off[cs];
       const int mode = !sym ? 0 : (ct == cs ? 2 : 1);
+      if (mixed) {
+        const FarSeg s{fpk, fpkl, qr, tg, t2f, colors + ctx->color_off[ct], nT, colors + ctx->color_off[cs], nS, alpha,
+                       gsrc, kappa, k0sq9, zo, zt, mode, 1, 0, 0};
+        const dim3 mgrid(nblk(nS, 64), nblk(nT, 4));
+        if (sym && rev) hipLaunchKernelGGL(k_tt_far_rev_c, mgrid, dim3(256), flds + kFarRevLds, ctx->stream, s);
+        else hipLaunchKernelGGL(k_tt_far_c, mgrid, dim3(256), flds, ctx->stream, s);
+        LAUNCHCK();
+        ++far_launches;
+        continue;
+      }
       const int tper = far_tper(nS, nT);
       const dim3 fgrid(nblk(nS, 8), nblk(nT, 4 * tper));
       if (sym && rev)
@@ -928,9 +957,14 @@ int fill_kernels(vie_ctx *ctx) {
     // (one lane each, so no wave mixes the two kinds)
     for (int ct = 0; ct < C; ++ct) {
       const int nT = ctx->color_off[ct + 1] - ctx->color_off[ct];
-      if (grid)
-        ;
-      else if (sym_face && rev)
+      if (grid) {
+      } else if (mixed) {
+        const TetFaceSeg s{fpk, fpkl, qr, tg, t2f, colors + ctx->color_off[ct], nT, fg, ctx->nface, alpha, sigma, gsrc,
+                           kappa, zo, zt, sym_face ? 1 : 0, 0, 0};
+        const dim3 mgrid(nblk(ctx->nface, 64), nblk(nT, 4));
+        if (sym_face && rev) hipLaunchKernelGGL(k_tet_face_rev_c, mgrid, dim3(256), flds, ctx->stream, s);
+        else hipLaunchKernelGGL(k_tet_face_c, mgrid, dim3(256), flds, ctx->stream, s);
+      } else if (sym_face && rev)
         hipLaunchKernelGGL(k_tet_face_rev, dim3(nblk(ctx->nface, 16), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
                            qr, tg, t2f, colors + ctx->color_off[ct], nT, fg, ctx->nface, alpha, sigma, gsrc, kappa, zo, zt);
       else
@@ -947,7 +981,12 @@ int fill_kernels(vie_ctx *ctx) {
     if (ctx->nhalf) {
       for (int cs = 0; cs < C; ++cs) {
         const int nS = ctx->color_off[cs + 1] - ctx->color_off[cs];
-        if (!sym_face && !grid)   // (with the staging the far pairs came from k_tet_face)
+        // (with the staging the far pairs came from k_tet_face)
+        if (!sym_face && mixed)
+          hipLaunchKernelGGL(k_face_tet_c, dim3(nblk(nS, 64), nblk(ctx->nhalf, 4)), dim3(256), flds, ctx->stream,
+                             FaceTetSeg{fpk, fpkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, tg, t2f,
+                                        colors + ctx->color_off[cs], nS, gsrc, kappa, zo, 0, 0});
+        else if (!sym_face && !grid)
           hipLaunchKernelGGL(k_face_tet, dim3(nblk(nS, 16), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
                              qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, tg, t2f, colors + ctx->color_off[cs], nS,
                              gsrc, kappa, zo);
@@ -959,8 +998,11 @@ int fill_kernels(vie_ctx *ctx) {
                              kappa, zo);
         LAUNCHCK();
       }
+      if (mixed)
+        hipLaunchKernelGGL(k_face_face_c, dim3(nblk(ctx->nface, 64), nblk(ctx->nhalf, 4)), dim3(256), flds, ctx->stream,
+                           FaceFaceSeg{fpk, fpkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, ctx->nface, sigma, zo, 0, 0});
       hipLaunchKernelGGL(k_face_face, dim3(nblk(ctx->nface, kFaceChunk), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_,
-                         pkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, ctx->nface, sigma, zo);
+                         pkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, ctx->nface, sigma, znear);
       LAUNCHCK();
     }
   }
@@ -1021,21 +1063,26 @@ int fill_finish(vie_ctx *ctx, bool timed) {
   // counted as 8, R and the fit argument 3, Horner, scale and accumulate 5);
   // two sincos counted as 40 each (three at oblique incidence); per order
   // 2 + 2 deg (twice the Horner for a complex order, + 4), 4 per order for the
-  // phases and 8 per row; final phases 14.  Per tet pair:
+  // phases and 8 per row; final phases 14.  In mixed precision: per image 27 +
+  // 3 deg (X, Y, Clenshaw), set-up of the orders 212 (four sincos; 132 at
+  // normal incidence, two), per order 13 + 3 deg (twice the Clenshaw for a
+  // complex order, + 4), final phase 6.  Per tet pair:
   // 16 point pairs + 1200 for moments and the 16-entry scatter (+ 1200 for
   // the swapped pair's scatter when one evaluation serves both).  At oblique
   // incidence one evaluation serving both also forms g_p at the reversed
   // separations (per point pair 4 per propagating order + 10) and the swapped
   // pair's moments (16 x 36 per tet pair).
-  double pp = 12 + (rev ? 120 : 80) + 14 + 8 * kPgfSide;
+  const bool mixed = ctx->precision == VIE_MIXED_FP32;
+  const int per_deg = mixed ? 3 : 2, per_img = mixed ? 27 : 21, per_mode = mixed ? 13 : 6;
+  double pp = 12 + (mixed ? (rev ? 212 : 132) + 6 : (rev ? 120 : 80) + 14 + 8 * kPgfSide);
   const PgfTable &tb = *ctx->tab;
-  for (int i = 0; i < tb.nimg; ++i) pp += 21 + 2 * tb.img[i].deg;
+  for (int i = 0; i < tb.nimg; ++i) pp += per_img + per_deg * tb.img[i].deg;
   int nmodes = 0, ncplx = 0;
   for (int i = 0; i < kPgfTerms; ++i)
     if (tb.mode[i].deg >= 0) {
       ++nmodes;
       ncplx += tb.mode[i].cplx ? 1 : 0;
-      pp += 6 + 2 * tb.mode[i].deg * (tb.mode[i].cplx ? 2 : 1) + (tb.mode[i].cplx ? 4 : 0);
+      pp += per_mode + per_deg * tb.mode[i].deg * (tb.mode[i].cplx ? 2 : 1) + (tb.mode[i].cplx ? 4 : 0);
     }
   if (sym && rev) pp += 10 + 4 * ncplx;
   int64_t nnear = 0;

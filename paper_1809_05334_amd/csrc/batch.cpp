@@ -246,7 +246,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
   std::vector<Rec> recs;
   int maxC = 0;
   for (vie_ctx *x : b->cells) maxC = std::max(maxC, x->topo.ncolors);
-  enum { K_FAR, K_FAR_REV, K_NEAR, K_TF, K_TF_REV, K_TFN, K_FT, K_FTN, K_FF };
+  enum { K_FAR, K_FAR_REV, K_NEAR, K_TF, K_TF_REV, K_TFN, K_FT, K_FTN, K_FF, K_FF_FAR };
   auto put = [&](const auto &L, int kind) {
     if (L.segs.empty()) return;
     recs.push_back({st.add(L.segs.data(), sizeof(L.segs[0]) * L.segs.size()), (int)L.segs.size(), L.blocks, L.lds,
@@ -262,7 +262,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       const dz *alpha, *gsrc, *kappa, *inveps, *sigma;
       const FaceGeom *fg;
       const int32_t *colors, *half;
-      ZOut zo, zt;
+      ZOut zo, zt, znear;   // znear: without the dense part in mixed precision (k_face_face)
     } c;
     const Layout &L = x->L;
     c.pk = x->ptr<double>(L.pack);
@@ -280,8 +280,20 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
     c.half = x->ptr<int32_t>(L.half);
     c.zo = zout(x);
     c.zt = zout_staging(x);
+    c.znear = c.zo;
+    c.znear.Zs = nullptr;
     return c;
   };
+  // (mixed precision: the far pairs by the kernels of k_far_c.hip and their own
+  // table, 64 sources x 4 test elements per block)
+  const bool mixed = b->precision == VIE_MIXED_FP32;
+  auto far_table = [&](vie_ctx *x, auto &s) {
+    if (!mixed) return;
+    s.pack = x->ptr<double>(x->L.fpack);
+    s.packlen = (int)x->fpack.size();
+  };
+  const int per = mixed ? 64 : 16;
+  auto far_lds = [&](vie_ctx *x) { return mixed ? x->fill_flds : x->fill_lds; };
   // far tet pairs, per colour pair (ct, cs)
   for (int ct = 0; ct < maxC; ++ct)
     for (int cs = 0; cs < maxC; ++cs) {
@@ -293,7 +305,11 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
         const int nT = x->color_off[ct + 1] - x->color_off[ct], nS = x->color_off[cs + 1] - x->color_off[cs];
         FarSeg s{c.pk, c.pkl, c.qr, c.tg, c.t2f, c.colors + x->color_off[ct], nT, c.colors + x->color_off[cs], nS,
                  c.alpha, c.gsrc, c.kappa, x->fill_k0sq9, c.zo, c.zt, !x->fill_sym ? 0 : (ct == cs ? 2 : 1), far_tper(nS, nT), 0, 0};
-        (x->fill_sym && x->fill_rev ? rev : plain).add(s, (int)nblk(nS, 8), (int)nblk(nT, 4 * s.tper), x->fill_lds);
+        const bool r = x->fill_sym && x->fill_rev;
+        if (mixed) s.tper = 1;
+        far_table(x, s);
+        (r ? rev : plain).add(s, (int)nblk(nS, mixed ? 64 : 8), (int)nblk(nT, 4 * s.tper),
+                              far_lds(x) + (r && mixed ? kFarRevLds : 0));
       }
       put(plain, K_FAR);
       put(rev, K_FAR_REV);
@@ -327,7 +343,8 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       const int nT = x->color_off[ct + 1] - x->color_off[ct];
       TetFaceSeg s{c.pk, c.pkl, c.qr, c.tg, c.t2f, c.colors + x->color_off[ct], nT, c.fg, x->nface, c.alpha,
                    c.sigma, c.gsrc, c.kappa, c.zo, c.zt, x->fill_sym_face ? (x->fill_rev ? 2 : 1) : 0, 0, 0};
-      (s.swap == 2 ? tfr : tf).add(s, (int)nblk(x->nface, 16), (int)nblk(nT, 4), x->fill_lds);
+      far_table(x, s);
+      (s.swap == 2 ? tfr : tf).add(s, (int)nblk(x->nface, per), (int)nblk(nT, 4), far_lds(x));
       const int np = x->tf_off[ct + 1] - x->tf_off[ct];
       if (np) {
         TetFaceNearSeg n{c.pk, c.pkl, c.qr, c.tg, c.t2f,
@@ -350,7 +367,8 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
       if (!x->fill_sym_face) {
         FaceTetSeg s{c.pk, c.pkl, c.qr, c.fg, c.half, x->nhalf, c.tg, c.t2f, c.colors + x->color_off[cs], nS,
                      c.gsrc, c.kappa, c.zo, 0, 0};
-        ft.add(s, (int)nblk(nS, 16), (int)nblk(x->nhalf, 4), x->fill_lds);
+        far_table(x, s);
+        ft.add(s, (int)nblk(nS, per), (int)nblk(x->nhalf, 4), far_lds(x));
       }
       const int np = x->ft_off[cs + 1] - x->ft_off[cs];
       if (np) {
@@ -364,13 +382,18 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
     put(ftn, K_FTN);
   }
   {
-    Launch<FaceFaceSeg> ff;
+    Launch<FaceFaceSeg> ff, fff;
     for (vie_ctx *x : b->cells) {
       if (!x->nface || !x->nhalf) continue;
       const auto c = P(x);
-      FaceFaceSeg s{c.pk, c.pkl, c.qr, c.fg, c.half, x->nhalf, x->nface, c.sigma, c.zo, 0, 0};
+      FaceFaceSeg s{c.pk, c.pkl, c.qr, c.fg, c.half, x->nhalf, x->nface, c.sigma, c.znear, 0, 0};
       ff.add(s, (int)nblk(x->nface, kFaceChunk), (int)nblk(x->nhalf, 4), x->fill_lds);
+      if (!mixed) continue;
+      FaceFaceSeg f{c.pk, c.pkl, c.qr, c.fg, c.half, x->nhalf, x->nface, c.sigma, c.zo, 0, 0};
+      far_table(x, f);
+      fff.add(f, (int)nblk(x->nface, 64), (int)nblk(x->nhalf, 4), far_lds(x));
     }
+    put(fff, K_FF_FAR);
     put(ff, K_FF);
   }
   if (int rc = upload(b, st)) return rc;
@@ -378,19 +401,30 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
     const void *p = b->ws + r.off;
     const dim3 g(r.blocks), t(256);
     switch (r.kind) {
-      case K_FAR: hipLaunchKernelGGL(k_tt_far_seg, g, t, r.lds, b->stream, (const FarSeg *)p, r.nseg); break;
-      case K_FAR_REV: hipLaunchKernelGGL(k_tt_far_rev_seg, g, t, r.lds, b->stream, (const FarSeg *)p, r.nseg); break;
+      case K_FAR:
+        hipLaunchKernelGGL(mixed ? k_tt_far_c_seg : k_tt_far_seg, g, t, r.lds, b->stream, (const FarSeg *)p, r.nseg);
+        break;
+      case K_FAR_REV:
+        hipLaunchKernelGGL(mixed ? k_tt_far_rev_c_seg : k_tt_far_rev_seg, g, t, r.lds, b->stream, (const FarSeg *)p, r.nseg);
+        break;
       case K_NEAR: hipLaunchKernelGGL(k_tt_near_seg, g, t, r.lds, b->stream, (const NearSeg *)p, r.nseg); break;
-      case K_TF: hipLaunchKernelGGL(k_tet_face_seg, g, t, r.lds, b->stream, (const TetFaceSeg *)p, r.nseg); break;
+      case K_TF:
+        hipLaunchKernelGGL(mixed ? k_tet_face_c_seg : k_tet_face_seg, g, t, r.lds, b->stream, (const TetFaceSeg *)p, r.nseg);
+        break;
       case K_TF_REV:
-        hipLaunchKernelGGL(k_tet_face_rev_seg, g, t, r.lds, b->stream, (const TetFaceSeg *)p, r.nseg);
+        hipLaunchKernelGGL(mixed ? k_tet_face_rev_c_seg : k_tet_face_rev_seg, g, t, r.lds, b->stream, (const TetFaceSeg *)p, r.nseg);
         break;
       case K_TFN:
         hipLaunchKernelGGL(k_tet_face_near_seg, g, t, r.lds, b->stream, (const TetFaceNearSeg *)p, r.nseg);
         break;
-      case K_FT: hipLaunchKernelGGL(k_face_tet_seg, g, t, r.lds, b->stream, (const FaceTetSeg *)p, r.nseg); break;
+      case K_FT:
+        hipLaunchKernelGGL(mixed ? k_face_tet_c_seg : k_face_tet_seg, g, t, r.lds, b->stream, (const FaceTetSeg *)p, r.nseg);
+        break;
       case K_FTN:
         hipLaunchKernelGGL(k_face_tet_near_seg, g, t, r.lds, b->stream, (const FaceTetNearSeg *)p, r.nseg);
+        break;
+      case K_FF_FAR:
+        hipLaunchKernelGGL(k_face_face_c_seg, g, t, r.lds, b->stream, (const FaceFaceSeg *)p, r.nseg);
         break;
       case K_FF: hipLaunchKernelGGL(k_face_face_seg, g, t, r.lds, b->stream, (const FaceFaceSeg *)p, r.nseg); break;
     }

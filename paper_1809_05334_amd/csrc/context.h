@@ -34,7 +34,7 @@ struct Region {
 };
 
 struct Layout {
-  Region tg, t2f, area, dom, fg, half, ctp, ctm, utet, uk, colors, near_t, near_s, near_m, near_tf, near_ft, quad, pgf,
+  Region tg, t2f, area, dom, fg, half, ctp, ctm, utet, uk, colors, near_t, near_s, near_m, near_tf, near_ft, quad, fpack,
       pack;
   Region eps, alpha, gsrc, kappa, inveps, sigma;
   Region Z, Zt, nrow, ncol, nval, F, ipiv, perm, rpiv, info, lupv, lupi, lucnt, tcand, ttcnt, tblk, dinv, gcpl, trr, tbsum,
@@ -81,6 +81,7 @@ struct vie_ctx {
   std::vector<dz> eps_int;
   std::vector<double> pack;         // packed lattice-sum table of the last fill
   int packlen = 0;
+  std::vector<double> fpack;        // mixed precision: the far kernels' copy (k_far_c.hip)
   std::vector<int32_t> near_off;    // offsets of the near lists per colour pair
   std::vector<int32_t> tf_off, ft_off;   // offsets (in pairs) of the touching tet-face / face-tet lists per colour
   int mv_rpw = 4;                   // matvec rows per wave (2, 4, 8)
@@ -136,6 +137,7 @@ struct vie_ctx {
   bool fill_sym = false, fill_sym_face = false;
   int fill_rev = 0;
   size_t fill_lds = 0;
+  size_t fill_flds = 0;             // mixed precision: bytes of the far kernels' table
   double fill_k0sq9 = 0;
   double fill_kx = 0, fill_ky = 0;  // transverse wavevector of the fill
   // structured-grid operator: the mesh's grid analysis (built on first use,

@@ -76,10 +76,15 @@ inline int touching_mask(const int32_t *ct, const int32_t *ot, int nt_, const in
 
 void build_quadrature(QuadRules &q);
 
+// How the fitted functions are evaluated: their expansion in the wavenumber
+// (2 ms per table), or the quadratures whose every coefficient the
+// mixed-precision operator holds to.
+enum class PgfTerms { series, fixed };
+
 // Ewald split and per-fill tables.  zspan = zmax - zmin of the mesh.
 // Returns "" or an error; sets *wood_margin = min_{(p,q)!=(0,0)} |gamma_pq|/k0.
 std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, double lambda, double theta,
-                            double phi, double *wood_margin);
+                            double phi, double *wood_margin, PgfTerms terms = PgfTerms::series);
 
 // Compact copy of the table for the kernels (staged into LDS): only the
 // fitted coefficients of the significant terms, in doubles.  A series is
@@ -102,5 +107,21 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
 constexpr int kPackRows = 29;
 constexpr int kPackImages = 40;
 void pack_pgf_table(const PgfTable &tab, std::vector<double> &out);
+
+// The copy for the far kernels of the mixed-precision operator, every fit as it is:
+//   [0..10)  E, a, b, 1/a, 1/b, kx, ky, 2pi/a, 2pi/b, ws
+//   [10..19) Re phase0[9], [19..28) Im phase0[9], [28] nimg
+//   [32..113) per order (p,q) grid index: offset of its record or 0 (low
+//             word), K | cplx << 16 (high word)
+//   [116..125) per row p of the order grid: q_lo | (q_hi + 1) << 8, the
+//             first and last q with an order (0 | 0 << 8: none)
+//   image records from kFixedImages on, each
+//     [E xs, -(xa xs + 1), cre, cim, m, n, K, len] f[0..K] (pad to 4) [HK, 0, 0, 0] h[0..HK] (pad to 4)
+//     (the H block only for touching classes; len = record length)
+//   order records [K, cplx, 0, 0] kre[0..K] (pad) kim[0..K] (pad, complex orders only)
+// K, HK are the degrees rounded up to a multiple of 4 (zero coefficients).
+constexpr int kFixedRows = 116;
+constexpr int kFixedImages = 128;
+void pack_pgf_fixed(const PgfTable &tab, std::vector<double> &out);
 
 }  // namespace vie

@@ -19,35 +19,9 @@
 // deterministic.
 #include <hip/hip_runtime.h>
 
-#include "kernels.h"
+#include "fill.h"
 
 namespace vie {
-
-static constexpr double kInv4Pi = 0.079577471545947667884;
-
-__device__ __forceinline__ int uniform(int v) { return __builtin_amdgcn_readfirstlane(v); }
-
-// Z[m][n] += v into the destination of this fill (see ZOut).  In mixed
-// precision a far contribution is added to the FP32 entry in FP64 and rounded
-// once; a near one goes to its slot of the sorted CSR row.
-__device__ __forceinline__ void zput(const ZOut &o, int64_t m, int64_t n, dz v, bool near) {
-  if (o.Z) {
-    dz *p = o.Z + m * o.ld + n;
-    *p = *p + v;
-  } else if (near) {
-    int64_t lo = o.rowptr[m], hi = o.rowptr[m + 1];
-    while (lo < hi) {
-      const int64_t mid = (lo + hi) >> 1;
-      if (o.cols[mid] < n) lo = mid + 1;
-      else hi = mid;
-    }
-    if (lo < o.rowptr[m + 1] && o.cols[lo] == n) o.vals[lo] = o.vals[lo] + v;
-  } else {
-    fz *p = o.Zs + m * o.ld + n;
-    const fz z = *p;
-    *p = fz{(float)((double)z.re + v.re), (float)((double)z.im + v.im)};
-  }
-}
 
 // ------------------------------------------------------------ per-fill coefficients
 __global__ void k_prep(int64_t nt, const TetFace *__restrict__ t2f, const TetGeom *__restrict__ tg,
@@ -88,16 +62,6 @@ __global__ void k_zero(dz *__restrict__ p, int64_t n) {
 }
 
 // ------------------------------------------------------------ tet-pair moments
-struct Moments {
-  dz m0, mu[3], mv[3], muv;
-};
-
-__device__ __forceinline__ void moments_zero(Moments &M) {
-  M.m0 = mk(0, 0);
-  M.muv = mk(0, 0);
-  for (int d = 0; d < 3; ++d) M.mu[d] = M.mv[d] = mk(0, 0);
-}
-
 // Lane sums by DPP moves: over a quad (quad swaps), and of lanes l and 7 - l
 // of eight (half-row mirror).
 template <int CTRL>
@@ -772,24 +736,6 @@ __global__ __launch_bounds__(256, 2) void k_face_face(const double *__restrict__
 }
 
 // ------------------------------------------------------------ fused multi-cell fill
-// The segment of fused-grid block b (segments ordered by their first block).
-template <class S>
-__device__ __forceinline__ int seg_of(const S *__restrict__ segs, int nseg, int b) {
-  int lo = 0, hi = nseg - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (segs[mid].first <= b) lo = mid;
-    else hi = mid - 1;
-  }
-  return uniform(lo);
-}
-
-#define VIE_SEG_BEGIN(S)                                  \
-  const int s_ = seg_of(segs, nseg, (int)blockIdx.x);     \
-  const S &A = segs[s_];                                  \
-  const int lb_ = (int)blockIdx.x - A.first;              \
-  const int bx = lb_ % A.gx, by = lb_ / A.gx;
-
 __global__ __launch_bounds__(256, kFarWaves) void k_tt_far_seg(const FarSeg *__restrict__ segs, int nseg) {
   VIE_SEG_BEGIN(FarSeg)
   tt_far_body<false>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.src_list, A.nsrc, A.alpha, A.gsrc,
@@ -833,7 +779,6 @@ __global__ __launch_bounds__(256, 2) void k_face_face_seg(const FaceFaceSeg *__r
   VIE_SEG_BEGIN(FaceFaceSeg)
   k_face_face_body(A.pack, A.packlen, A.qr, A.fg, A.half_list, A.nhalf, A.nface, A.sigma, A.out, bx, by);
 }
-#undef VIE_SEG_BEGIN
 
 // ------------------------------------------------------------ right-hand side
 // b_m = sum_{T in m} chi s a_m/(3 V_T) int_T (r - p).E^i dV, 14-point rule;

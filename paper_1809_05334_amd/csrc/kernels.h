@@ -93,6 +93,21 @@ __global__ void k_tt_far_rev_seg(const FarSeg *segs, int nseg);
 __global__ void k_tt_near_seg(const NearSeg *segs, int nseg);
 __global__ void k_tet_face_seg(const TetFaceSeg *segs, int nseg);       // swap 0, 1
 __global__ void k_tet_face_rev_seg(const TetFaceSeg *segs, int nseg);   // swap 2
+// Mixed precision: the far pairs (k_far_c.hip), 64 sources x 4 test elements per
+// block, one cell's segment as the argument (gx, first unused) or a table of
+// them; k_tt_far_rev_c also takes 16 doubles per thread of dynamic LDS after
+// the table (kFarRevLds bytes).
+constexpr int kFarRevLds = 16 * 256 * 8 + 8;
+#define VIE_DECL_FAR_C(NAME, SEG)  \
+  __global__ void NAME(SEG seg);   \
+  __global__ void NAME##_seg(const SEG *segs, int nseg);
+VIE_DECL_FAR_C(k_tt_far_c, FarSeg)
+VIE_DECL_FAR_C(k_tt_far_rev_c, FarSeg)
+VIE_DECL_FAR_C(k_tet_face_c, TetFaceSeg)
+VIE_DECL_FAR_C(k_tet_face_rev_c, TetFaceSeg)
+VIE_DECL_FAR_C(k_face_tet_c, FaceTetSeg)
+VIE_DECL_FAR_C(k_face_face_c, FaceFaceSeg)
+#undef VIE_DECL_FAR_C
 __global__ void k_tet_face_near_seg(const TetFaceNearSeg *segs, int nseg);
 __global__ void k_face_tet_seg(const FaceTetSeg *segs, int nseg);
 __global__ void k_face_tet_near_seg(const FaceTetNearSeg *segs, int nseg);

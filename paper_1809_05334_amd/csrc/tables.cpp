@@ -3,6 +3,8 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <atomic>
+#include <thread>
 #include <vector>
 
 #include "host.h"
@@ -42,6 +44,162 @@ static ld tail_sum(ld x, ld c, int first, int n0) {
     coef *= c / (n + 1);
   }
   return sum;
+}
+
+// The same functions by Gauss-Legendre quadrature of erfcx(z) = (2 / sqrt(pi))
+// int_0^inf exp(-s^2 - 2 z s) ds (Re z >= 0; composite, up to where the
+// integrand falls below 1e-20) and erf(z) = (2 z / sqrt(pi)) int_0^1
+// exp(-z^2 t^2) dt, in extended precision.  The mixed-precision operator takes
+// its terms from these (PgfTerms::fixed): both evaluations are good to some
+// 1e-19, and so differ in the last bit of one coefficient in a few hundred,
+// which is enough to move isolated FP32 entries of Z to their neighbours.
+using zl = std::complex<long double>;
+
+// Nodes and weights on [0, 1] by Newton iteration on the Legendre three-term
+// recurrence.
+static void gauss_legendre01(int n, std::vector<ld> &x, std::vector<ld> &w) {
+  x.resize(n);
+  w.resize(n);
+  const ld pi = 3.141592653589793238462643383279502884L;
+  for (int i = 0; i < n; ++i) {
+    ld z = std::cos(pi * (i + 0.75L) / (n + 0.5L));
+    ld dp = 1;
+    for (int it = 0; it < 100; ++it) {
+      ld p0 = 1, p1 = 0;
+      for (int k = 1; k <= n; ++k) {
+        ld p2 = p1;
+        p1 = p0;
+        p0 = ((2 * k - 1) * z * p1 - (k - 1) * p2) / k;
+      }
+      dp = n * (z * p0 - p1) / (z * z - 1);
+      ld dz = p0 / dp;
+      z -= dz;
+      if (std::fabs(dz) < 1e-19L) break;
+    }
+    ld p0 = 1, p1 = 0;
+    for (int k = 1; k <= n; ++k) {
+      ld p2 = p1;
+      p1 = p0;
+      p0 = ((2 * k - 1) * z * p1 - (k - 1) * p2) / k;
+    }
+    dp = n * (z * p0 - p1) / (z * z - 1);
+    x[i] = 0.5L * (1 - z);
+    w[i] = 1.0L / ((1 - z * z) * dp * dp);  // (2 / ((1-z^2) P'^2)) / 2
+  }
+}
+
+struct GL {
+  std::vector<ld> x32, w32, x24, w24;
+  GL() {
+    gauss_legendre01(32, x32, w32);
+    gauss_legendre01(24, x24, w24);
+  }
+};
+static const GL &gl() {
+  static const GL g;
+  return g;
+}
+
+constexpr int kErfcxPanels = 12;
+static ld erfcx_range(ld x) { return -x + std::sqrt(x * x + 46.0L); }
+
+static zl erfcx_integral(zl z) {
+  const GL &g = gl();
+  const ld S = erfcx_range(z.real());
+  zl acc = 0;
+  for (int p = 0; p < kErfcxPanels; ++p) {
+    const ld lo = S * p / kErfcxPanels, h = S / kErfcxPanels;
+    for (size_t i = 0; i < g.x24.size(); ++i) {
+      const ld s = lo + h * g.x24[i];
+      acc += h * g.w24[i] * std::exp(-s * s - 2.0L * z * s);
+    }
+  }
+  return acc * (2.0L / kSqrtPiL);
+}
+
+// the real part alone, with the same operations (im = 0: a real argument)
+static ld erfcx_real_part(ld x, ld im) {
+  const GL &g = gl();
+  const ld S = erfcx_range(x);
+  ld acc = 0;
+  for (int p = 0; p < kErfcxPanels; ++p) {
+    const ld lo = S * p / kErfcxPanels, h = S / kErfcxPanels;
+    for (size_t i = 0; i < g.x24.size(); ++i) {
+      const ld s = lo + h * g.x24[i];
+      const ld e = std::exp(-s * s - 2.0L * x * s);
+      acc += h * g.w24[i] * (im == 0 ? e : e * std::cos(2.0L * im * s));
+    }
+  }
+  return acc * (2.0L / kSqrtPiL);
+}
+
+static zl erf_integral(zl z) {
+  const GL &g = gl();
+  zl acc = 0;
+  for (size_t i = 0; i < g.x32.size(); ++i) {
+    const ld t = g.x32[i];
+    acc += g.w32[i] * std::exp(-z * z * (t * t));
+  }
+  return acc * z * (2.0L / kSqrtPiL);
+}
+
+static ld erfcx_real(ld x) {
+  return x >= 0 ? erfcx_real_part(x, 0) : 2.0L * std::exp(x * x) - erfcx_real_part(-x, 0);
+}
+
+static zl erfc_l(zl z) {
+  if (z.real() >= 0.5L) return std::exp(-z * z) * erfcx_integral(z);
+  if (z.real() <= -0.5L) return 2.0L - std::exp(-z * z) * erfcx_integral(-z);
+  return 1.0L - erf_integral(z);
+}
+
+static ld erfi_l(ld y) {
+  const GL &g = gl();
+  ld acc = 0;
+  for (size_t i = 0; i < g.x32.size(); ++i) {
+    const ld t = g.x32[i];
+    acc += g.w32[i] * std::exp(y * y * t * t);
+  }
+  return acc * y * (2.0L / kSqrtPiL);
+}
+
+// F and H of the images (see build_pgf_table) from these, at y = k0 / 2E.
+struct FixedImages {
+  ld y, erfi_y;
+  explicit FixedImages(ld y) : y(y), erfi_y(erfi_l(y)) {}
+  ld tail(ld x) const { return std::exp(y * y - x * x) * erfcx_real_part(x, -y); }   // F(x) for x >= 0.5
+  ld H(ld x) const {
+    // (F(x) - 1) / x = [-2 sin^2(xy) + sin(2xy) erfi(y) - Re(e^{-2jxy} I(x))] / x,
+    // I(x) = (2 / sqrt(pi)) int_0^x exp(-(s - jy)^2) ds  (no cancellation near x = 0)
+    if (x > 3.0) return (tail(x) - 1.0L) / x;
+    if (x == 0.0) return 2 * y * erfi_y - 2 * std::exp(y * y) / kSqrtPiL;
+    const GL &g = gl();
+    zl I = 0;
+    for (size_t i = 0; i < g.x32.size(); ++i) {
+      const ld s = x * g.x32[i];
+      const zl d(s, -y);
+      I += g.w32[i] * std::exp(-d * d);
+    }
+    I *= x * 2.0L / kSqrtPiL;
+    const ld sxy = std::sin(x * y);
+    const ld val = -2 * sxy * sxy + std::sin(2 * x * y) * erfi_y - (std::exp(zl(0, -2 * x * y)) * I).real();
+    return val / x;
+  }
+  ld F(ld x) const { return x >= 0.5 ? tail(x) : 1.0L + x * H(x); }
+};
+
+// Run body(i) for i in [0, n) on up to 16 host threads.
+template <class Fn>
+static void parallel_for(int n, Fn body) {
+  const int nth = std::max(1, std::min<int>({16, n, (int)std::thread::hardware_concurrency()}));
+  std::atomic<int> next(0);
+  auto work = [&]() {
+    for (int i = next++; i < n; i = next++) body(i);
+  };
+  std::vector<std::thread> th;
+  for (int k = 1; k < nth; ++k) th.emplace_back(work);
+  work();
+  for (auto &t : th) t.join();
 }
 
 // ---------------------------------------------------------------- quadrature
@@ -173,13 +331,15 @@ void build_quadrature(QuadRules &q) {
 // the last eight coefficients sit at that noise level.  The kept degree is
 // the last counting coefficient.  Returns the degree, or -1 if neither 48 nor
 // 96 nodes converge within maxdeg.
-// cos(pi i / 2n), i < 4n, for n = 48 and 96: the nodes and the transform
+// cos(pi k (j + 1/2) / n), j < n, at k n + j for n = 48 and 96: the nodes
+// (k = 1) and the transform
 struct CosTable {
   std::vector<ld> c48, c96;
   CosTable() {
     const ld pi = 3.141592653589793238462643383279502884L;
-    for (int i = 0; i < 4 * 48; ++i) c48.push_back(std::cos(pi * i / (2 * 48)));
-    for (int i = 0; i < 4 * 96; ++i) c96.push_back(std::cos(pi * i / (2 * 96)));
+    for (int n : {48, 96})
+      for (int k = 0; k < n; ++k)
+        for (int j = 0; j < n; ++j) (n == 48 ? c48 : c96).push_back(std::cos(pi * k * (j + 0.5L) / n));
   }
 };
 
@@ -192,17 +352,13 @@ static int cheb_fit(F f, double lo, double hi, double abs_tol, double rel_tol, d
     double c[96];
     double fmax = 0;
     for (int j = 0; j < n; ++j) {
-      const double t = (double)cs[2 * j + 1];
+      const double t = (double)cs[n + j];
       fx[j] = f(lo + 0.5 * (t + 1) * (hi - lo));
       fmax = std::max(fmax, (double)std::fabs(fx[j]));
     }
     for (int k = 0; k < n; ++k) {
       ld s = 0;
-      for (int j = 0, i = k; j < n; ++j) {
-        s += fx[j] * cs[i];   // i = k (2j + 1) mod 4n
-        i += 2 * k;
-        if (i >= 4 * n) i -= 4 * n;
-      }
+      for (int j = 0; j < n; ++j) s += fx[j] * cs[(size_t)k * n + j];
       c[k] = (double)(2.0L * s / n);
     }
     c[0] *= 0.5;
@@ -226,7 +382,7 @@ static int cheb_fit(F f, double lo, double hi, double abs_tol, double rel_tol, d
 
 // ---------------------------------------------------------------- Ewald tables
 std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, double lambda, double theta,
-                            double phi, double *wood_margin) {
+                            double phi, double *wood_margin, PgfTerms terms) {
   std::memset(&tab, 0, sizeof(tab));
   const double k0 = 2 * kPi / lambda;
   const double kx = k0 * std::sin(theta) * std::cos(phi), ky = k0 * std::sin(theta) * std::sin(phi);
@@ -273,13 +429,18 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
   // F(x) = (2x / sqrt(pi)) int_1^inf exp(-x^2 s^2 + y^2 / s^2) ds, and H = (F - 1) / x with
   // the n = 0 term erfc(x) - 1 = -erf(x) taken out: no cancellation near x = 0
   const ld yl = y;
-  auto Fx = [&](double x) -> ld { return std::erfc((ld)x) + 2 * (ld)x / kSqrtPiL * tail_sum(x, yl * yl, 0, 1); };
+  const bool fixed = terms == PgfTerms::fixed;
+  const FixedImages fim(yl);
+  auto Fx = [&](double x) -> ld {
+    return fixed ? fim.F(x) : std::erfc((ld)x) + 2 * (ld)x / kSqrtPiL * tail_sum(x, yl * yl, 0, 1);
+  };
   auto Hx = [&](double x) -> ld {
+    if (fixed) return fim.H(x);
     const ld xl = x, e0 = x == 0.0 ? 2 / kSqrtPiL : std::erf(xl) / xl;
     return 2 / kSqrtPiL * tail_sum(xl, yl * yl, 0, 1) - e0;
   };
 
-  // ---- spatial images: significance cut first, then the fits in parallel
+  // ---- spatial images: significance cut first
   struct ImgJob {
     int m, n;
     double xlo, xhi;
@@ -298,75 +459,126 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
       jobs.push_back({m, n, xlo, xhi, touching_class});
     }
   tab.nimg = (int)jobs.size();
-  bool bad = false;
-  for (int i = 0; i < tab.nimg; ++i) {
-    const ImgJob &jb = jobs[i];
-    PgfImage &im = tab.img[i];
-    // the fit depends on |m|, |n| alone: an earlier image with the same gives it
-    for (int k = 0; k < i; ++k)
-      if (std::abs(jobs[k].m) == std::abs(jb.m) && std::abs(jobs[k].n) == std::abs(jb.n)) {
-        im = tab.img[k];
-        break;
-      }
-    if (im.xs == 0) {
-      im.xa = jb.xlo;
-      im.xs = 2.0 / (jb.xhi - jb.xlo);
-      im.deg = cheb_fit(Fx, jb.xlo, jb.xhi, fit_abs, fit_rel, im.f, kPgfMaxDeg - 1);
-      im.hdeg = -1;
-      if (jb.touching) im.hdeg = cheb_fit(Hx, jb.xlo, jb.xhi, 0.0, fit_rel, im.h, kPgfMaxDeg - 1);
-      if (im.deg < 0 || (jb.touching && im.hdeg < 0)) bad = true;
-    }
-    im.m = jb.m;
-    im.n = jb.n;
-    double ph = kx * jb.m * a + ky * jb.n * b;
-    im.cre = std::cos(ph) / (4 * kPi);
-    im.cim = std::sin(ph) / (4 * kPi);
-  }
-  if (bad) return "lattice-sum table: spatial fit did not converge";
-
   // ---- spectral modes, K_pq as a function of w = (z E)^2 on [0, (zspan E)^2]
   const double wmax = std::max(1e-30, zspan * E * zspan * E) * (1 + 1e-9);
   tab.ws = 2.0 / wmax;
-  for (int idx = 0; idx < kPgfTerms; ++idx) {
-      const int p = idx / kPgfSide - kPgfM, q = idx % kPgfSide - kPgfM;
-      double tx = kx + 2 * kPi * p / a, ty = ky + 2 * kPi * q / b;
-      double kt2 = tx * tx + ty * ty;
-      PgfMode &md = tab.mode[(p + kPgfM) * kPgfSide + (q + kPgfM)];
-      md.deg = -1;
-      md.p = p;
-      md.q = q;
-      if (kt2 > k0 * k0) {
-        double gam = std::sqrt(kt2 - k0 * k0);
-        double u = gam / (2 * E);
-        double pref = 1.0 / (4 * a * b * gam);
-        auto K = [&](double w) -> ld {
-          const ld v = std::sqrt(std::max(0.0L, (ld)w)), ul = u;
-          return (ld)pref * (std::exp(2 * ul * v) * std::erfc(ul + v) + std::exp(-2 * ul * v) * std::erfc(ul - v));
-        };
-        if ((double)K(0.0) < sig) continue;  // K falls with z; deg stays -1
-        md.cplx = 0;
-        md.deg = cheb_fit(K, 0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
-        if (md.deg < 0) bad = true;
-      } else {
-        // propagating order, gamma = +j beta: the whole transform e^{-j beta z} / (2 j beta)
-        // less its part beyond the split, int_E^inf exp(-z^2 s^2 + beta^2 / 4 s^2) / (2 sqrt(pi) s^2) ds
-        const double beta = std::sqrt(k0 * k0 - kt2);
-        const ld bb = beta / (2 * E), area = a * b;
-        md.cplx = 1;
-        const int d1 = cheb_fit(
-            [&](double w) {
-              const ld v = std::sqrt(std::max(0.0L, (ld)w));
-              return -(std::sin(2 * bb * v) / (2 * beta) + tail_sum(v, bb * bb, 1, 0) / (2 * kSqrtPiL * E)) / area;
-            },
-            0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
-        const int d2 = cheb_fit(
-            [&](double w) { return -std::cos(2 * bb * std::sqrt(std::max(0.0L, (ld)w))) / (2 * beta * area); }, 0.0,
-            wmax, sig, fit_rel, md.kim, kPgfMaxDeg - 1);
-        if (d1 < 0 || d2 < 0) bad = true;
-        md.deg = std::max(d1, d2);
-      }
+  const auto kt2_of = [&](int idx) {
+    const int p = idx / kPgfSide - kPgfM, q = idx % kPgfSide - kPgfM;
+    const double tx = kx + 2 * kPi * p / a, ty = ky + 2 * kPi * q / b;
+    return tx * tx + ty * ty;
+  };
+
+  // The fits, each distinct one once: an image's depends on |m|, |n| alone, an
+  // order's on |k_t|^2.
+  const auto same_image = [&](int i, int k) {
+    return std::abs(jobs[k].m) == std::abs(jobs[i].m) && std::abs(jobs[k].n) == std::abs(jobs[i].n);
+  };
+  int first_img[kPgfTerms], first_mode[kPgfTerms];
+  enum Fit { FIT_F, FIT_H, FIT_K };
+  std::vector<std::pair<Fit, int>> todo;
+  for (int i = 0; i < kPgfTerms; ++i) {   // (the propagating orders, which take longest, first)
+    first_mode[i] = 0;
+    while (kt2_of(first_mode[i]) != kt2_of(i)) ++first_mode[i];
+    if (first_mode[i] == i && kt2_of(i) <= k0 * k0) todo.push_back({FIT_K, i});
   }
-  if (bad) return "lattice-sum table: spectral fit did not converge";
+  for (int i = 0; i < tab.nimg; ++i) {
+    int k = 0;
+    while (!same_image(i, k)) ++k;
+    first_img[i] = k;
+    if (k < i) continue;
+    todo.push_back({FIT_F, i});
+    tab.img[i].hdeg = -1;
+    if (jobs[i].touching) todo.push_back({FIT_H, i});
+  }
+  for (int i = 0; i < kPgfTerms; ++i)
+    if (first_mode[i] == i && kt2_of(i) > k0 * k0) todo.push_back({FIT_K, i});
+  std::atomic<bool> bad_image(false), bad_mode(false);
+  const auto fit_image = [&](Fit fit, int i) {
+    const ImgJob &jb = jobs[i];
+    PgfImage &im = tab.img[i];
+    int &deg = fit == FIT_H ? im.hdeg : im.deg;
+    if (fit == FIT_H) deg = cheb_fit(Hx, jb.xlo, jb.xhi, 0.0, fit_rel, im.h, kPgfMaxDeg - 1);
+    else deg = cheb_fit(Fx, jb.xlo, jb.xhi, fit_abs, fit_rel, im.f, kPgfMaxDeg - 1);
+    if (deg < 0) bad_image = true;
+  };
+  const auto fit_mode = [&](int idx) {
+    const double kt2 = kt2_of(idx);
+    PgfMode &md = tab.mode[idx];
+    md.deg = -1;
+    if (kt2 > k0 * k0) {
+      double gam = std::sqrt(kt2 - k0 * k0);
+      double u = gam / (2 * E);
+      double pref = 1.0 / (4 * a * b * gam);
+      auto K = [&](double w) -> ld {
+        const ld v = std::sqrt(std::max(0.0L, (ld)w)), ul = u;
+        if (fixed) {
+          const ld e = std::exp(-ul * ul - v * v);
+          return (ld)pref * (e * erfcx_real(ul + v) + e * erfcx_real(ul - v));
+        }
+        return (ld)pref * (std::exp(2 * ul * v) * std::erfc(ul + v) + std::exp(-2 * ul * v) * std::erfc(ul - v));
+      };
+      if ((double)K(0.0) < sig) return;  // K falls with z; deg stays -1
+      md.deg = cheb_fit(K, 0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
+      if (md.deg < 0) bad_mode = true;
+    } else {
+      // propagating order, gamma = +j beta: the whole transform e^{-j beta z} / (2 j beta)
+      // less its part beyond the split, int_E^inf exp(-z^2 s^2 + beta^2 / 4 s^2) / (2 sqrt(pi) s^2) ds
+      const double beta = std::sqrt(k0 * k0 - kt2);
+      const ld bb = beta / (2 * E), area = a * b;
+      const zl pref = 1.0L / (4.0L * a * b * zl(0, beta));
+      // the same by erfc of complex arguments, whose values serve both parts' fits
+      std::vector<std::pair<double, zl>> seen;
+      const auto Kc = [&](double w) -> zl {
+        for (const auto &s : seen)
+          if (s.first == w) return s.second;
+        const ld v = std::sqrt(std::max(0.0L, (ld)w));
+        const zl e1 = std::exp(zl(0, 2 * bb * v)), e2 = std::exp(zl(0, -2 * bb * v));
+        seen.push_back({w, pref * (e1 * erfc_l(zl(v, bb)) + e2 * erfc_l(zl(-v, bb)))});
+        return seen.back().second;
+      };
+      md.cplx = 1;
+      const int d1 = cheb_fit(
+          [&](double w) -> ld {
+            if (fixed) return Kc(w).real();
+            const ld v = std::sqrt(std::max(0.0L, (ld)w));
+            return -(std::sin(2 * bb * v) / (2 * beta) + tail_sum(v, bb * bb, 1, 0) / (2 * kSqrtPiL * E)) / area;
+          },
+          0.0, wmax, sig, fit_rel, md.kre, kPgfMaxDeg - 1);
+      const int d2 = cheb_fit(
+          [&](double w) -> ld {
+            if (fixed) return Kc(w).imag();
+            return -std::cos(2 * bb * std::sqrt(std::max(0.0L, (ld)w))) / (2 * beta * area);
+          },
+          0.0, wmax, sig, fit_rel, md.kim, kPgfMaxDeg - 1);
+      if (d1 < 0 || d2 < 0) bad_mode = true;
+      md.deg = std::max(d1, d2);
+    }
+  };
+  const auto fit = [&](int i) {
+    if (todo[i].first == FIT_K) fit_mode(todo[i].second);
+    else fit_image(todo[i].first, todo[i].second);
+  };
+  // (the quadratures take 100 ms of one thread, the series 2)
+  if (fixed) parallel_for((int)todo.size(), fit);
+  else for (int i = 0; i < (int)todo.size(); ++i) fit(i);
+  if (bad_image) return "lattice-sum table: spatial fit did not converge";
+  if (bad_mode) return "lattice-sum table: spectral fit did not converge";
+  for (int i = 0; i < tab.nimg; ++i) {
+    PgfImage &im = tab.img[i];
+    if (first_img[i] != i) im = tab.img[first_img[i]];
+    im.xa = jobs[i].xlo;
+    im.xs = 2.0 / (jobs[i].xhi - jobs[i].xlo);
+    im.m = jobs[i].m;
+    im.n = jobs[i].n;
+    double ph = kx * im.m * a + ky * im.n * b;
+    im.cre = std::cos(ph) / (4 * kPi);
+    im.cim = std::sin(ph) / (4 * kPi);
+  }
+  for (int i = 0; i < kPgfTerms; ++i) {
+    if (first_mode[i] != i) tab.mode[i] = tab.mode[first_mode[i]];
+    tab.mode[i].p = i / kPgfSide - kPgfM;
+    tab.mode[i].q = i % kPgfSide - kPgfM;
+  }
   return "";
 }
 
@@ -530,6 +742,51 @@ void pack_pgf_table(const PgfTable &tab, std::vector<double> &out) {
   }
   out[28] = ibits((int)props, nprop);
   out.insert(out.end(), 4, 0.0);   // a series reads one pair past its end
+}
+
+void pack_pgf_fixed(const PgfTable &tab, std::vector<double> &out) {
+  auto pad4 = [](int n) { return (n + 3) & ~3; };
+  out.assign(kFixedImages, 0.0);
+  const double hdr[10] = {tab.E, tab.a, tab.b, tab.inv_a, tab.inv_b, tab.kx, tab.ky, tab.two_pi_a, tab.two_pi_b, tab.ws};
+  for (int i = 0; i < 10; ++i) out[i] = hdr[i];
+  for (int i = 0; i < 9; ++i) {
+    out[10 + i] = tab.ph0re[i];
+    out[19 + i] = tab.ph0im[i];
+  }
+  out[28] = ibits(tab.nimg);
+  for (int i = 0; i < tab.nimg; ++i) {
+    const PgfImage &im = tab.img[i];
+    const int K = pad4(im.deg), HK = im.hdeg >= 0 ? pad4(im.hdeg) : -1;
+    const size_t start = out.size();
+    // the fit's argument t = (x - xa) xs - 1 with x = E R, stored as t = R (E xs) - (xa xs + 1)
+    out.insert(out.end(), {tab.E * im.xs, -(im.xa * im.xs + 1.0), im.cre, im.cim, ibits(im.m), ibits(im.n), ibits(K), 0.0});
+    for (int k = 0; k < pad4(K + 1); ++k) out.push_back(k <= im.deg ? im.f[k] : 0.0);
+    if (HK >= 0) {
+      out.insert(out.end(), {ibits(HK), 0.0, 0.0, 0.0});
+      for (int k = 0; k < pad4(HK + 1); ++k) out.push_back(k <= im.hdeg ? im.h[k] : 0.0);
+    }
+    out[start + 7] = ibits((int)(out.size() - start));
+  }
+  for (int idx = 0; idx < kPgfTerms; ++idx) {
+    const PgfMode &md = tab.mode[idx];
+    if (md.deg < 0) continue;
+    const int K = pad4(md.deg);
+    out[32 + idx] = ibits((int)out.size(), K | (md.cplx ? 1 << 16 : 0));
+    out.insert(out.end(), {ibits(K), ibits(md.cplx), 0.0, 0.0});
+    for (int k = 0; k < pad4(K + 1); ++k) out.push_back(k <= md.deg ? md.kre[k] : 0.0);
+    if (md.cplx)
+      for (int k = 0; k < pad4(K + 1); ++k) out.push_back(k <= md.deg ? md.kim[k] : 0.0);
+  }
+  // each row's range of q with a mode, so that a pass over the grid skips the rest
+  for (int p = 0; p < kPgfSide; ++p) {
+    int lo = kPgfSide, hi = -1;
+    for (int q = 0; q < kPgfSide; ++q)
+      if (tab.mode[p * kPgfSide + q].deg >= 0) {
+        lo = std::min(lo, q);
+        hi = std::max(hi, q);
+      }
+    out[kFixedRows + p] = ibits(hi < 0 ? 0 : lo | (hi + 1) << 8);
+  }
 }
 
 }  // namespace vie
