@@ -171,6 +171,7 @@ Layout make_layout(const MeshTopology &t, int restart, int64_t nnear, int nface,
   put(L.lupv, 8 * (size_t)std::max<int64_t>(1, npart));
   put(L.lupi, 4 * (size_t)std::max<int64_t>(1, npart));
   put(L.lucnt, 4 * (size_t)std::max(1, t.ndom));
+  put(L.luq, 4 * (size_t)(kLuQueue + kSideFlag));
   // tournament pivoting: nodes of the tree of the first (tallest) panel, the
   // largest tree of the factorisation: leaves, then ceil(count / fan-in) per level
   int64_t nodes = 0;
@@ -1266,7 +1267,7 @@ int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms) {
 // four hardware queues, and two streams on one queue run one after the other
 // (factor, FP64, N = 15,840: 114 ms instead of 90), so a new stream is tried
 // with a pair of small kernels and up to three more are made to find one that
-// runs beside.  ctx: any bound context of the device (16 B of Krylov scratch).
+// runs beside.  ctx: any bound context of the device (its luq region).
 int side_stream(vie_ctx *ctx, hipStream_t stream, hipStream_t *side, hipStream_t *side_of) {
   if (*side && *side_of == stream) return VIE_OK;
   if (*side) {
@@ -1274,7 +1275,7 @@ int side_stream(vie_ctx *ctx, hipStream_t stream, hipStream_t *side, hipStream_t
     HIPCK(hipStreamDestroy(*side));
     *side = nullptr;
   }
-  int *flag = ctx->ptr<int>(ctx->L.K[0].vw);
+  int *flag = ctx->ptr<int>(ctx->L.luq) + kLuQueue;
   hipStream_t tried[4];
   int n = 0, seen = 0;
   hipError_t e = hipSuccess;
@@ -1390,9 +1391,9 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
       ++ctx->upd_n;
       return VIE_OK;
     };
-    // the tile queue's counters, in the scratch of ctx's first Krylov process (16 N bytes: with a tile N > 128)
-    int *queue = ctx->ptr<int>(ctx->L.K[0].vw);
-    if (ctx->L.K[0].vw.bytes >= 4 * (size_t)kLuQueue) HIPCK(hipMemsetAsync(queue, 0, 4 * (size_t)kLuQueue, stream));
+    // the tile queue's counters, in a region that every context has (ctx may be the smallest cell of a batch)
+    int *queue = ctx->ptr<int>(ctx->L.luq);
+    HIPCK(hipMemsetAsync(queue, 0, 4 * (size_t)kLuQueue, stream));
     constexpr int kBig = 1 << 30;
     auto panels = [&](int k0, hipStream_t sm) {
       const int kb = k0 + kLuNB, pe = k0 + 2 * kLuNB;

@@ -37,7 +37,7 @@ struct Layout {
   Region tg, t2f, area, dom, fg, half, ctp, ctm, utet, uk, colors, near_t, near_s, near_m, near_tf, near_ft, quad, fpack,
       pack;
   Region eps, alpha, gsrc, kappa, inveps, sigma;
-  Region Z, Zt, nrow, ncol, nval, F, ipiv, perm, rpiv, info, lupv, lupi, lucnt, tcand, ttcnt, tblk, dinv, gcpl, trr, tbsum,
+  Region Z, Zt, nrow, ncol, nval, F, ipiv, perm, rpiv, info, lupv, lupi, lucnt, luq, tcand, ttcnt, tblk, dinv, gcpl, trr, tbsum,
       plans;
   // structured-grid operator (VIE_GRID_FP64): geometry, element maps, kernel
   // tables (kGridSub^2 x nf), source and potential fields (kGridFields x nf)

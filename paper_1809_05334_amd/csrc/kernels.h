@@ -185,6 +185,7 @@ constexpr int kTsWaveZ = 32, kTsWaveC = 64;   // rows of a node per wave
 constexpr int kTsWideMax = 8192;
 constexpr int kLuQueueUnits = 160, kLuQueue = kLuQueueUnits + 64;   // counters of a tile queue: 8 lists, blocks gone, blocks
                                                                     // ended, 16 ints apart; the unit left free per shader engine
+constexpr int kSideFlag = 2;   // ints of the side stream's probe (k_side_wait), after the counters
 struct LuDom {
   void *A;            // the domain's block (dz or fz), row-major, leading dimension ld, factored in place
   int64_t ld;

@@ -120,3 +120,46 @@ def test_fused_batch_of_more_domains_than_a_launch_takes(copies):
             assert info["converged"] and fi["converged"]
             assert np.max(np.abs(fA - A)) <= 1e-9 and abs(fR - R) <= 1e-9 and abs(fT - T) <= 1e-9
             assert np.linalg.norm(fx - x) <= 1e-9 * np.linalg.norm(x)
+
+
+def five_tet_cell():
+    """A 2 x 2 x 1 grid of bricks of five tetrahedra, alternately mirrored: N = 48."""
+    from paper_1809_05334_amd import workloads as W
+    xs, zs = np.array([0.0, 20.0, 40.0]), np.array([0.0, 20.0])
+    verts = np.array([[x, y, z] for z in zs for y in xs for x in xs])
+    even = [["000", "100", "010", "001"], ["110", "100", "010", "111"], ["101", "100", "001", "111"],
+            ["011", "010", "001", "111"], ["100", "010", "001", "111"]]
+    tets = []
+    for j in range(2):
+        for i in range(2):
+            for t in even:
+                ids = []
+                for c in t:
+                    u, v, w = (int(d) for d in c)
+                    u = u if (i + j) % 2 == 0 else 1 - u
+                    ids.append((i + u) + 3 * (j + v) + 9 * w)
+                p = verts[ids]
+                if np.linalg.det(p[1:] - p[0]) < 0:
+                    ids[0], ids[1] = ids[1], ids[0]
+                tets.append(ids)
+    tets = np.array(tets, np.int32)
+    return W.Mesh(verts, tets, np.zeros(len(tets), np.int32), 1, 40.0, 40.0, (xs, xs, zs))
+
+
+@pytest.mark.parametrize("precision", ["fp64", "mixed"])
+def test_first_cell_smaller_than_the_tile_queue(precision):
+    """A first cell of 48 unknowns (a Krylov vector of 768 bytes) before cells
+    whose factorisations take tiles from the queue, twice.  Bars as above."""
+    from paper_1809_05334_amd import vie
+    from paper_1809_05334_amd import workloads as W
+    prec = vie.VIE_FP64 if precision == "fp64" else vie.VIE_MIXED_FP32
+    tiny, slab = five_tet_cell(), W.slab_mesh(nx=5, ny=5, nz=5)
+    cases = [(tiny, W.slab_eps(tiny), 600.0, 0.3, 0.2, 1), (slab, W.slab_eps(slab), 600.0, 0.3, 0.2, 1),
+             (slab, W.slab_eps(slab), 650.0, 0.0, 0.0, 0)]
+    alone = [run_alone(vie, c, prec, 1e-12) for c in cases]
+    assert len(alone[0][4]) == 48 and len(alone[1][4]) > 512
+    for _ in range(2):
+        for (info, A, R, T, x), (fi, fA, fR, fT, fx) in zip(alone, run_fused(vie, cases, prec, 1e-12, graph=True)):
+            assert info["converged"] and fi["converged"]
+            assert np.max(np.abs(fA - A)) <= 1e-9 and abs(fR - R) <= 1e-9 and abs(fT - T) <= 1e-9
+            assert np.linalg.norm(fx - x) <= 1e-9 * np.linalg.norm(x)
