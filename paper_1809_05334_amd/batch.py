@@ -199,7 +199,7 @@ def run_batch(requests, precision, slots=2, budget_gb=200.0, tol=1e-8, restart=1
     t0 = time.perf_counter()
     res = srv.run_trace(requests)
     dt = time.perf_counter() - t0
-    return res, dt, {"peak_gb": srv.peak_used / 1e9, "peak_running": srv.peak_running}
+    return res, dt, {"peak_gb": srv.peak_used / 1e9, "peak_running": srv.peak_admitted}
 
 
 def main():

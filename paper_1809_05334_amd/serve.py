@@ -91,7 +91,10 @@ class Server:
         self._stop = False
         self.done = []
         self.peak_used = 0.0
-        self.peak_running = 0            # most requests in service at once: admitted, or prepared towards a free slot
+        self.peak_admitted = 0           # most admitted requests at once
+        # most requests in service at once: admitted, or (with a slot free) in the
+        # host preparation that their admission followed without a wait
+        self.peak_running = 0
         self.admit_order = []
         self._workers = []
 
@@ -150,6 +153,7 @@ class Server:
                 self._used += job.footprint
                 self._running += 1
                 self.peak_used = max(self.peak_used, self._used)
+                self.peak_admitted = max(self.peak_admitted, self._running)
                 self.peak_running = max(self.peak_running, self._running)
                 self.admit_order.append(job.req["rid"])
                 self._inbox[wid].append(job)
@@ -166,9 +170,7 @@ class Server:
 
     def _enqueue(self, req, t_arrival):
         with self._cv:
-            # its host preparation (a fifth of a small request's time) is part of its service
-            if self._free:
-                self.peak_running = max(self.peak_running, self._running + 1)
+            beside = self._running if self._free else 0   # admitted requests that run while this one is prepared
         prep, fp = self.backend.prepare(req)
         job = _Job(req, prep, fp, t_arrival)
         with self._cv:
@@ -179,6 +181,8 @@ class Server:
                 return
             self._pending.append(job)
             self._admit_locked(self.clock())
+            if job not in self._pending:
+                self.peak_running = max(self.peak_running, beside + 1)
 
     def run_trace(self, requests, time_scale=1.0, progress_s=0.0):
         """Replay requests at their `arrival` times (s, scaled); returns the
@@ -303,7 +307,7 @@ def main():
         res = srv.run_trace(trace, progress_s=30.0)
         out = summarize(res, srv.t_end - srv.t_start)
         out.update({"rate_req_s": rate, "precision": args.precision, "slots": args.slots,
-                    "budget_gb": args.budget_gb, "peak_gb": srv.peak_used / 1e9, "peak_running": srv.peak_running,
+                    "budget_gb": args.budget_gb, "peak_gb": srv.peak_used / 1e9, "peak_running": srv.peak_admitted,
                     "sym_fill": args.sym_fill, "failed": [r.error for r in res if not r.ok][:3]})
         print(json.dumps(out), flush=True)
         per[str(rate)] = [{"rid": r.rid, "ok": r.ok, "N": r.N, "A": r.A, "R": r.R, "T": r.T, "iters": r.iters,

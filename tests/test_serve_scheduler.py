@@ -115,3 +115,36 @@ def test_failures_are_isolated_and_oversized_requests_rejected():
 def test_bad_configuration():
     with pytest.raises(ValueError):
         Server(FakeBackend(), slots=0)
+
+
+@pytest.mark.parametrize("second", [800, 5000], ids=["held back by the budget", "rejected"])
+def test_a_request_that_never_ran_beside_another_is_not_counted(second):
+    be = FakeBackend(service_s=0.1)
+    trace = reqs([(0.0, 800, {}), (0.02, second, {})])
+    srv = Server(be, slots=3, hbm_budget=1000)
+    srv.run_trace(trace)
+    assert be.max_live == 1
+    assert srv.peak_running == 1 and srv.peak_admitted == 1
+
+
+def test_preparation_beside_a_running_request_counts_once_admitted():
+    """The second request is prepared while the first runs and admitted as soon
+    as that is done, when the first has ended: in service beside it, never
+    admitted beside it."""
+    class Slow(FakeBackend):
+        def prepare(self, req):
+            time.sleep(req.get("prep", 0.0))
+            return super().prepare(req)
+
+    be = Slow(service_s=0.1)
+    srv = Server(be, slots=2, hbm_budget=1000)
+    srv.run_trace(reqs([(0.0, 100, {}), (0.02, 100, {"prep": 0.2})]))
+    assert be.max_live == 1
+    assert srv.peak_running == 2 and srv.peak_admitted == 1
+
+
+def test_no_more_in_service_than_slots():
+    be = FakeBackend(service_s=0.05)
+    srv = Server(be, slots=2, hbm_budget=1000)
+    srv.run_trace(reqs([(0.01 * i, 100, {}) for i in range(8)]))
+    assert be.max_live == 2 and srv.peak_running == 2 and srv.peak_admitted == 2
