@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "context.h"
+#include "side.h"
 
 using namespace vie;
 
@@ -462,9 +463,9 @@ int vie_destroy(vie_ctx *ctx) {
   if (ctx->ev2) (void)hipEventDestroy(ctx->ev2);
   if (ctx->ev3) (void)hipEventDestroy(ctx->ev3);
   if (ctx->ev4) (void)hipEventDestroy(ctx->ev4);
-  if (ctx->side) {
-    (void)hipStreamSynchronize(ctx->side);
-    (void)hipStreamDestroy(ctx->side);
+  if (ctx->side.s) {
+    (void)hipStreamSynchronize(ctx->side.s);
+    (void)hipStreamDestroy(ctx->side.s);
   }
   if (ctx->ev_la) (void)hipEventDestroy(ctx->ev_la);
   if (ctx->ev_ts) (void)hipEventDestroy(ctx->ev_ts);
@@ -1206,23 +1207,35 @@ extern "C" {
 
 namespace vie {
 
-// The domain descriptors of the block factorisation (Sec. 2.3, Eq. 6) and
-// each diagonal block A_dd copied (with the FP64 near part in mixed
-// precision) into the factor storage; records ev0.
-int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms) {
+// Whether the context's fill can be factored; its device becomes current.
+int factor_check(vie_ctx *ctx) {
   if (int r = check(ctx, S_FILLED, "vie_precond_factor")) return r;
   if (ctx->precision == VIE_GRID_FP64)
     return fail(ctx, VIE_EINVAL, "VIE_GRID_FP64 stores no diagonal blocks to factor (solve with VIE_OPT_PRECOND 1)");
-  // the factors of an earlier factorisation of this fill are overwritten from
-  // here on: until this one succeeds, no solve or apply may use them
-  ctx->factored = false;
   const MeshTopology &t = ctx->topo;
   for (int d = 0; d < t.ndom; ++d)
     if (t.dend[d] - t.dstart[d] > (int64_t)kTrsvChunksMax * kTrsvSumCols)
       return fail(ctx, VIE_EINVAL, "domain %d has %lld unknowns; the block preconditioner takes at most %d", d,
                   (long long)(t.dend[d] - t.dstart[d]), kTrsvChunksMax * kTrsvSumCols);
   HIPCK(hipSetDevice(ctx->device));
+  return VIE_OK;
+}
+
+int max_domain(const vie_ctx *ctx) {
+  int n = 0;
+  for (int d = 0; d < ctx->topo.ndom; ++d) n = std::max(n, (int)(ctx->topo.dend[d] - ctx->topo.dstart[d]));
+  return n;
+}
+
+// The domain descriptors of the block factorisation (Sec. 2.3, Eq. 6) and
+// each diagonal block A_dd copied (with the FP64 near part in mixed
+// precision) into the factor storage, after factor_check; records ev0.
+int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms) {
+  const MeshTopology &t = ctx->topo;
   const Layout &L = ctx->L;
+  // the factors of an earlier factorisation of this fill are overwritten from
+  // here on: until this one succeeds, no solve or apply may use them
+  ctx->factored = false;
   const ZOut zo = zout(ctx);
   const bool f32 = fp32_factors(ctx);
   int32_t *ipiv = ctx->ptr<int32_t>(L.ipiv), *info = ctx->ptr<int32_t>(L.info);
@@ -1264,39 +1277,44 @@ int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms) {
 
 // A side stream for the panels beside `stream`'s bulk updates, kept while the
 // factorisations stay on that stream.  HIP maps the streams of a process onto
-// four hardware queues, and two streams on one queue run one after the other
-// (factor, FP64, N = 15,840: 114 ms instead of 90), so a new stream is tried
-// with a pair of small kernels and up to three more are made to find one that
-// runs beside.  ctx: any bound context of the device (its luq region).
-int side_stream(vie_ctx *ctx, hipStream_t stream, hipStream_t *side, hipStream_t *side_of) {
-  if (*side && *side_of == stream) return VIE_OK;
-  if (*side) {
-    HIPCK(hipStreamSynchronize(*side));
-    HIPCK(hipStreamDestroy(*side));
-    *side = nullptr;
-  }
+// four hardware queues, and two streams on one queue run one after the other:
+// one new stream in six did so, which cost the factorisation 0 to 0.7 ms of 9 at
+// N = 3,038 (largest domain 1,600), 3 of 18 at 6,272 (FP64; 3,500), 24 of 90 at
+// 15,840.  A stream is therefore tried with a pair of small kernels, and up to
+// three more are made to find one that runs beside; that takes 0.1 ms on an idle
+// device and up to 1.5 ms on a busy one, whose answer may also be wrong.  So it
+// is done only where a domain has more than kSideProbe unknowns, and an answer
+// that cannot be had leaves the first stream in use.  ctx: any bound context of
+// the device (its luq region).
+constexpr int kSideProbe = 2048;
+int side_stream(vie_ctx *ctx, hipStream_t stream, int max_domain, SideStream &side) {
+  const bool probe = max_domain > kSideProbe;
+  if (side.s && side.of == stream && (side.probed || !probe)) return VIE_OK;
+  if (!side.s) HIPCK(hipStreamCreateWithFlags(&side.s, hipStreamNonBlocking));
+  side.of = stream;
+  side.probed = probe;
+  if (!probe) return VIE_OK;
   int *flag = ctx->ptr<int>(ctx->L.luq) + kLuQueue;
-  hipStream_t tried[4];
-  int n = 0, seen = 0;
-  hipError_t e = hipSuccess;
-  while (n < 4 && !seen) {
-    if ((e = hipStreamCreateWithFlags(&tried[n], hipStreamNonBlocking)) != hipSuccess) break;
-    ++n;
-    hipLaunchKernelGGL(k_side_set, dim3(1), dim3(1), 0, tried[n - 1], flag);   // (its hardware queue may be made only now)
-    if ((e = hipStreamSynchronize(tried[n - 1])) != hipSuccess) break;
-    if ((e = hipMemsetAsync(flag, 0, 8, stream)) != hipSuccess) break;
-    if ((e = hipStreamSynchronize(stream)) != hipSuccess) break;
-    hipLaunchKernelGGL(k_side_wait, dim3(1), dim3(1), 0, stream, flag);
-    hipLaunchKernelGGL(k_side_set, dim3(1), dim3(1), 0, tried[n - 1], flag);
-    if ((e = hipGetLastError()) != hipSuccess) break;
-    if ((e = hipMemcpyAsync(&seen, flag + 1, 4, hipMemcpyDeviceToHost, stream)) != hipSuccess) break;
-    if ((e = hipStreamSynchronize(stream)) != hipSuccess) break;
-    if ((e = hipStreamSynchronize(tried[n - 1])) != hipSuccess) break;
-  }
-  for (int i = 0; i + 1 < n; ++i) (void)hipStreamDestroy(tried[i]);
-  if (n > 0) *side = tried[n - 1];
-  if (e != hipSuccess) return fail(ctx, VIE_EDEVICE, "side stream: %s", hipGetErrorString(e));
-  *side_of = stream;
+  pick_side(
+      side.s, 4,
+      [](hipStream_t *s) { return hipStreamCreateWithFlags(s, hipStreamNonBlocking) == hipSuccess; },
+      [](hipStream_t s) {
+        (void)hipStreamSynchronize(s);
+        (void)hipStreamDestroy(s);
+      },
+      [&](hipStream_t s) {
+        int seen = 0;
+        hipLaunchKernelGGL(k_side_set, dim3(1), dim3(1), 0, s, flag);   // (its hardware queue may be made only now)
+        if (hipStreamSynchronize(s) != hipSuccess) return -1;
+        if (hipMemsetAsync(flag, 0, 4 * kSideFlag, stream) != hipSuccess) return -1;
+        if (hipStreamSynchronize(stream) != hipSuccess) return -1;
+        hipLaunchKernelGGL(k_side_wait, dim3(1), dim3(1), 0, stream, flag);
+        hipLaunchKernelGGL(k_side_set, dim3(1), dim3(1), 0, s, flag);
+        if (hipMemcpyAsync(&seen, flag + 1, 4, hipMemcpyDeviceToHost, stream) != hipSuccess) return -1;
+        if (hipStreamSynchronize(stream) != hipSuccess || hipStreamSynchronize(s) != hipSuccess) return -1;
+        return seen ? 1 : 0;
+      });
+  (void)hipGetLastError();   // (a further stream that could not be made)
   return VIE_OK;
 }
 
@@ -1565,9 +1583,10 @@ extern "C" {
 
 int vie_precond_factor(vie_ctx *ctx) {
   std::vector<LuDom> doms;
+  if (int rc = factor_check(ctx)) return rc;
+  if (int rc = side_stream(ctx, ctx->stream, max_domain(ctx), ctx->side)) return rc;
   if (int rc = factor_prepare(ctx, doms)) return rc;
-  if (int rc = side_stream(ctx, ctx->stream, &ctx->side, &ctx->side_of)) return rc;
-  if (int rc = factor_panels(ctx, doms, fp32_factors(ctx), ctx->lu_pivot, ctx->stream, ctx->side, ctx->ev_la,
+  if (int rc = factor_panels(ctx, doms, fp32_factors(ctx), ctx->lu_pivot, ctx->stream, ctx->side.s, ctx->ev_la,
                              ctx->ev_ts))
     return rc;
   std::vector<TrsvPrepDom> prep;

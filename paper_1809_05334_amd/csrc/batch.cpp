@@ -29,7 +29,7 @@ struct vie_batch {
   double *pin_res = nullptr;        // pinned: residual estimates / norms, one per cell
   int *pin_act = nullptr;           // pinned: Arnoldi-step flags, one per cell
   int pin_cap = 0;                  // cells the pinned buffers hold
-  hipStream_t side = nullptr, side_of = nullptr;
+  SideStream side;
   hipEvent_t ev0 = nullptr, ev1 = nullptr, ev_la = nullptr, ev_ts = nullptr;
   int graph = 1;                    // capture the fused Arnoldi step in a HIP graph
   hipGraphExec_t gexec = nullptr;
@@ -136,9 +136,9 @@ int vie_batch_destroy(vie_batch *b) {
   release_graph(b);
   if (b->pin_res) (void)hipHostFree(b->pin_res);
   if (b->pin_act) (void)hipHostFree(b->pin_act);
-  if (b->side) {
-    (void)hipStreamSynchronize(b->side);
-    (void)hipStreamDestroy(b->side);
+  if (b->side.s) {
+    (void)hipStreamSynchronize(b->side.s);
+    (void)hipStreamDestroy(b->side.s);
   }
   for (hipEvent_t e : {b->ev0, b->ev1, b->ev_la, b->ev_ts})
     if (e) (void)hipEventDestroy(e);
@@ -459,14 +459,19 @@ int vie_batch_factor(vie_batch *b) {
   const int nc = (int)b->cells.size();
   std::vector<std::vector<LuDom>> per(nc);
   std::vector<LuDom> all;
+  vie_ctx *x0 = b->cells[0];
+  int maxn = 0;
+  for (int c = 0; c < nc; ++c) {
+    if (int rc = factor_check(b->cells[c])) return cell_fail(b, c, rc);
+    maxn = std::max(maxn, max_domain(b->cells[c]));
+  }
+  if (int rc = side_stream(x0, b->stream, maxn, b->side)) return cell_fail(b, 0, rc);
   BCK(hipEventRecord(b->ev0, b->stream));
   for (int c = 0; c < nc; ++c) {
     if (int rc = factor_prepare(b->cells[c], per[c])) return cell_fail(b, c, rc);
     all.insert(all.end(), per[c].begin(), per[c].end());
   }
-  vie_ctx *x0 = b->cells[0];
-  if (int rc = side_stream(x0, b->stream, &b->side, &b->side_of)) return cell_fail(b, 0, rc);
-  if (int rc = factor_panels(x0, all, fp32_factors(x0), 0, b->stream, b->side, b->ev_la, b->ev_ts))
+  if (int rc = factor_panels(x0, all, fp32_factors(x0), 0, b->stream, b->side.s, b->ev_la, b->ev_ts))
     return cell_fail(b, 0, rc);
   std::vector<TrsvPrepDom> prep;
   for (int c = 0; c < nc; ++c) factor_prep(b->cells[c], per[c], prep);

@@ -29,6 +29,13 @@ constexpr int kMaxPlans = 4;      // cached cooperative triangular-solve plans p
 
 inline size_t align256(size_t x) { return (x + 255) & ~size_t(255); }
 
+// The side stream of the factorisations on one stream (side_stream).
+struct SideStream {
+  hipStream_t s = nullptr;
+  hipStream_t of = nullptr;   // the stream that s was made for
+  bool probed = false;        // whether s was chosen for running beside it
+};
+
 struct Region {
   size_t off = 0, bytes = 0;
 };
@@ -122,8 +129,7 @@ struct vie_ctx {
   bool static_ws = false;            // bound to the library's own workspace (vie_bind_static_workspace)
   // block LU look-ahead: the next panel's tournament on a stream of its own
   // (default priority) while the rest of the trailing update runs
-  hipStream_t side = nullptr;
-  hipStream_t side_of = nullptr;    // the stream that `side` was found to run beside
+  SideStream side;
   hipEvent_t ev_la = nullptr, ev_ts = nullptr;
   vie_fill_stats fstats{};
   // timing of the factorisation's K = 128 trailing updates: one event pair per
@@ -198,8 +204,10 @@ int fill_prepare(vie_ctx *ctx, double lambda_nm, double theta, double phi, const
 ZOut zout_staging(vie_ctx *ctx);
 int fill_kernels(vie_ctx *ctx);
 int fill_finish(vie_ctx *ctx, bool timed);
+int factor_check(vie_ctx *ctx);
+int max_domain(const vie_ctx *ctx);
 int factor_prepare(vie_ctx *ctx, std::vector<LuDom> &doms);
-int side_stream(vie_ctx *ctx, hipStream_t stream, hipStream_t *side, hipStream_t *side_of);
+int side_stream(vie_ctx *ctx, hipStream_t stream, int max_domain, SideStream &side);
 int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot, hipStream_t stream, hipStream_t side,
                   hipEvent_t ev_la, hipEvent_t ev_ts);
 void factor_prep(vie_ctx *ctx, const std::vector<LuDom> &doms, std::vector<TrsvPrepDom> &prep);
