@@ -404,6 +404,7 @@ int init_ctx(vie_ctx *ctx) {
   ctx->tab = new PgfTable();
   build_quadrature(ctx->quad);
   HIPCK(hipSetDevice(ctx->device));
+  HIPCK(hipDeviceGetAttribute(&ctx->cus, hipDeviceAttributeMultiprocessorCount, ctx->device));
   HIPCK(hipHostMalloc((void **)&ctx->pinned, 4096, hipHostMallocDefault));
   HIPCK(hipEventCreate(&ctx->ev0));
   HIPCK(hipEventCreate(&ctx->ev1));
@@ -1133,7 +1134,8 @@ enum LuKernel { LU_PIVOT, LU_COL, LU_SWAP, LU_TRSM, LU_GEMM, LU_GEMM2, LU_TSEL, 
 // gcols - 1 of the trailing matrix, gcols <= 0 for all from gcol0.)
 template <typename BlocksOf>
 void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &doms, int j, int k0, BlocksOf blocks_of,
-               int all_cols = 0, int gcol0 = 0, int gcols = 0, int c_lo = 0, int c_hi = 0, int *queue = nullptr) {
+               int all_cols = 0, int gcol0 = 0, int gcols = 0, int c_lo = 0, int c_hi = 0, int *queue = nullptr,
+               int queue_blocks = 0) {
   LuStep st{};
   st.queue = queue;
   st.j = j;
@@ -1168,8 +1170,8 @@ void lu_launch(bool f32, hipStream_t sm, LuKernel k, const std::vector<LuDom> &d
         else hipLaunchKernelGGL(k_lu_gemm_z, dim3(total), dim3(256), 0, sm, st);
         break;
       case LU_GEMM2:
-        // a block per tile and per slot of the units left free (two each)
-        if (queue) total = std::min(total + 2 * kGemm2FreeUnits, kGemm2Slots);
+        // a block per tile and per slot of the units left free
+        if (queue) total = std::min(total + kGemm2PerCu * kGemm2FreeUnits, queue_blocks);
         if (queue && f32) hipLaunchKernelGGL(k_lu_gemm2q_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         else if (queue) hipLaunchKernelGGL(k_lu_gemm2q_z, dim3(total), dim3(kGemm2Threads), 0, sm, st);
         else if (f32) hipLaunchKernelGGL(k_lu_gemm2_c, dim3(total), dim3(kGemm2Threads), 0, sm, st);
@@ -1404,7 +1406,7 @@ int factor_panels(vie_ctx *ctx, std::vector<LuDom> &doms, bool f32, int lu_pivot
       }
       HIPCK(hipEventRecord(ctx->upd_ev[2 * ctx->upd_n], stream));
       lu_launch(f32, stream, LU_GEMM2, doms, k0, k0, [&](int d) { return gemm2_blocks(d, k0, gcol0, gcols); }, 0, gcol0,
-                gcols, 0, 0, queue);
+                gcols, 0, 0, queue, kGemm2PerCu * ctx->cus);
       HIPCK(hipEventRecord(ctx->upd_ev[2 * ctx->upd_n + 1], stream));
       ++ctx->upd_n;
       return VIE_OK;

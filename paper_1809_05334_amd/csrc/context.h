@@ -130,6 +130,7 @@ struct vie_ctx {
   // block LU look-ahead: the next panel's tournament on a stream of its own
   // (default priority) while the rest of the trailing update runs
   SideStream side;
+  int cus = 0;                      // compute units of the device
   hipEvent_t ev_la = nullptr, ev_ts = nullptr;
   vie_fill_stats fstats{};
   // timing of the factorisation's K = 128 trailing updates: one event pair per

@@ -998,7 +998,7 @@ __global__ __launch_bounds__(256) void k_lu_gemm_c(LuStep st) { lu_gemm_body<fz>
 // groups of 8 column tiles row by row, so the 64 or so blocks an XCD holds at
 // once share 8 row panels of L21 and 8 column panels of U12 in its L2.
 //
-// With QUEUE a launch has at most kGemm2Slots blocks, which take tiles in
+// With QUEUE a launch has at most the blocks that the chip holds, which take tiles in
 // turn from the lists of the eight XCDs (their own first), and a block that
 // starts on one of the compute units left to the panels of the next pair, one
 // per shader engine (whichever is reached first: the units' numbers differ from

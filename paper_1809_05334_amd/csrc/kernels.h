@@ -163,26 +163,31 @@ constexpr int kLuMaxDom = 32;   // (a launch's descriptors: 3.1 KB of the 4 KB o
 // unit each: beside one block per tile, whose next block takes every half unit
 // that falls free, such a node starts only when the update is over.  Above
 // kGemm2QueueMax tiles the units cost the update more than the panels they
-// hide.  Factor, FP64, N = 15,840 (15,000 tiles at first): 88-90 ms, 106 with a
-// block per tile, 97 and 106 with two and three units; with the unit of one
+// hide.  Factor, FP64, ms, with no update taking tiles in turn / those of up to
+// 5,000 / 10,000 / 15,000 / 22,000 / 50,000 tiles: N = 15,840 101 / 94 / 90.5 / 90.7 /
+// 90.1 / -, N = 18,590 130 / 124 / 120.4 / 120.1 / 120.9 / -, N = 30,150 417 / 409 /
+// 403.6 / 403.5 / 408 / 471, N = 37,376 738 / 730 / 722 / - / 724 / 789 (885 with all).
+// N = 15,840 with two and three units left: 97 and 106; with the unit of one
 // fixed number, which some shader engines of a chip may lack, up to 102.  FP32,
-// six cells of up to 5,500 unknowns (wide nodes): 33.0 against 35.5.  FP32, N =
-// 37,376, whose nodes take half a unit and so share them with the update: 442
-// against 385 when it was tried, so not for those.
+// six cells of up to 5,500 unknowns (wide nodes): 33.0 against 35.5.  The narrow
+// FP32 nodes take half a unit and so share them with the update: 71, 84 and 111 ms
+// against 67, 79 and 104 without (N = 15,840, 18,590, 20,618), so not for those.
 constexpr int kGemm2FreeUnits = 32;   // one of each of the 4 shader engines of 8 XCDs
-constexpr int kGemm2Slots = 512;      // blocks of k_lu_gemm2 that the 256 compute units hold at once
-constexpr int kGemm2QueueMax = 50000;
+constexpr int kGemm2PerCu = 2;        // blocks of k_lu_gemm2 that a compute unit holds at once
+constexpr int kGemm2QueueMax = 15000;
 constexpr int kGemm2Threads = 512;   // threads per block of the two-panel trailing update (k_lu_gemm2)
 // Tournament nodes: 256 rows and four children per node, in 8 waves for FP64
 // factors (a whole compute unit's registers), 4 for FP32.  The wide FP32
 // nodes, 512 rows and eight children, need fewer levels of 64 steps but a
-// whole unit per node: taken while the largest domain has at most kTsWideMax
-// unknowns (factor of six cells of up to 5,500: 45 ms against 50; N = 37,376,
-// largest domain 21,482: 383 ms against 356).
+// whole unit per node: taken while the largest domain of the factorisation (of
+// all cells of a batch, which share the panel launches) has at most kTsWideMax
+// unknowns.  Factor, ms, wide / narrow, by the largest domain: 6,912 42.5 / 48.9,
+// 9,524 72 / 79, 12,020 98 / 103.5, 13,400 109 / 115, 15,602 172 / 166, 17,666
+// 210 / 197, 21,024 329 / 289.
 constexpr int kTsFanZ = 4, kTsFanC = 4, kTsFanW = 8;
 constexpr int kTsRowsZ = kTsFanZ * kLuNB, kTsRowsC = kTsFanC * kLuNB, kTsRowsW = kTsFanW * kLuNB;
 constexpr int kTsWaveZ = 32, kTsWaveC = 64;   // rows of a node per wave
-constexpr int kTsWideMax = 8192;
+constexpr int kTsWideMax = 14336;
 constexpr int kLuQueueUnits = 160, kLuQueue = kLuQueueUnits + 64;   // counters of a tile queue: 8 lists, blocks gone, blocks
                                                                     // ended, 16 ints apart; the unit left free per shader engine
 constexpr int kSideFlag = 2;   // ints of the side stream's probe (k_side_wait), after the counters
