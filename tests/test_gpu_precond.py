@@ -256,3 +256,27 @@ def test_factors_do_not_depend_on_the_contexts_made_before(vie, contexts):
         first = z if first is None else first
         assert np.array_equal(z, first)
         alive.append(s)
+
+
+def test_narrow_fp32_tournament_nodes(vie):
+    """One domain of N = 17,666 unknowns, above the size up to which the FP32
+    panels take 512-row nodes: 256-row nodes in trees of 70 leaves downwards
+    (four levels, lone children on every one).  With one domain M^{-1} is
+    Z^{-1}: the residual of Z (M^{-1} v) = v, by the bar of the wider nodes."""
+    m = W.slab_mesh(200.0, 200.0, 200.0, 11, 11, 12)
+    s = vie.Solver()
+    s.upload_mesh(m)
+    s.set_option(vie.VIE_OPT_SYM_FILL, 1)
+    s.bind(vie.VIE_MIXED_FP32, 20)
+    s.fill(600.0, 0.3, 0.2, W.slab_eps(m))
+    N = s.num_unknowns()
+    assert N > 14336
+    rng = np.random.default_rng(10)
+    v = rng.standard_normal(N) + 1j * rng.standard_normal(N)
+    err = []
+    for pivot in (0, 1):
+        s.set_option(vie.VIE_OPT_LU_PIVOT, pivot)
+        s.factor()
+        err.append(np.linalg.norm(s.apply_Z(s.precond_apply(v)) - v) / np.linalg.norm(v))
+    s.close()
+    assert err[1] < 1e-3 and err[0] < 3 * err[1] + 1e-6, err
