@@ -66,8 +66,8 @@ def case_of_step(i, all_cases):
 
 
 FP32_MFMA_PEAK_TFLOPS = 157.3   # dense FP32 matrix-core peak
-FAR_PROFILE = os.path.join(ROOT, "profiles", "k_tt_far_rev_counters_osc_cell_N77600.md")
-FAR_SOURCES = ["k_fill.hip", "device_math.h", "common.h", "tables.cpp"]   # kernel code and the tables that set its work
+FAR_PROFILE = os.path.join(ROOT, "profiles", "k_tt_far_rev_c_counters_osc_cell_N77600.md")
+FAR_SOURCES = ["k_far_c.hip", "fill.h", "device_math.h", "common.h", "tables.cpp"]   # kernel code and the tables that set its work
 LU_PROFILE = os.path.join(ROOT, "profiles", "k_lu_gemm2_counters_osc_cell_N77600.md")
 LU_SOURCES = ["k_lu.hip"]
 
@@ -296,16 +296,16 @@ def main():
         return flops, ms, launches
 
     # the far tet-pair fill kernel of the oblique cases (with the symmetric
-    # fill: k_tt_far_rev, one lattice sum per unordered pair; normal-incidence
-    # cases run k_tt_far and are left out)
+    # fill: k_tt_far_rev_c, one lattice sum per unordered pair; normal-incidence
+    # cases run k_tt_far_c and are left out)
     obl = [f for f in mixed["fills"] if f["oblique"]] or mixed["fills"]
-    far_kernel = "k_tt_far_rev" if mixed["sym"] and obl[0]["oblique"] else "k_tt_far"
+    far_kernel = "k_tt_far_rev_c" if mixed["sym"] and obl[0]["oblique"] else "k_tt_far_c"
     far_flops, far_ms, far_launches = far_rate(obl)
     far_tflops = far_flops / (far_ms * 1e-3) / 1e12
     mv32_bytes = 8.0 * N * N + 32.0 * N
     mv64_bytes = 16.0 * N * N + 32.0 * N
     mv32_gbs = mv32_bytes / (mixed["mv_ms"] * 1e-3) / 1e9
-    counters = profile_counters(FAR_PROFILE, FAR_SOURCES) if far_kernel == "k_tt_far_rev" else None
+    counters = profile_counters(FAR_PROFILE, FAR_SOURCES) if far_kernel == "k_tt_far_rev_c" else None
     avg_ms = far_ms / far_launches
     far_roofline = {"bound": "alu", "kernel": far_kernel, "achieved": far_tflops, "peak": FP64_VECTOR_PEAK_TFLOPS,
                     "unit": "TFLOP/s", "frac": far_tflops / FP64_VECTOR_PEAK_TFLOPS,

@@ -4,6 +4,7 @@
 #include <cmath>
 #include <cstring>
 #include <atomic>
+#include <system_error>
 #include <thread>
 #include <vector>
 
@@ -188,20 +189,6 @@ struct FixedImages {
   ld F(ld x) const { return x >= 0.5 ? tail(x) : 1.0L + x * H(x); }
 };
 
-// Run body(i) for i in [0, n) on up to 16 host threads.
-template <class Fn>
-static void parallel_for(int n, Fn body) {
-  const int nth = std::max(1, std::min<int>({16, n, (int)std::thread::hardware_concurrency()}));
-  std::atomic<int> next(0);
-  auto work = [&]() {
-    for (int i = next++; i < n; i = next++) body(i);
-  };
-  std::vector<std::thread> th;
-  for (int k = 1; k < nth; ++k) th.emplace_back(work);
-  work();
-  for (auto &t : th) t.join();
-}
-
 // ---------------------------------------------------------------- quadrature
 static double tet14_residual(const double p[6], double r[6]) {
   // exactness on one homogeneous degree-5 barycentric monomial per partition
@@ -342,12 +329,15 @@ struct CosTable {
         for (int j = 0; j < n; ++j) (n == 48 ? c48 : c96).push_back(std::cos(pi * k * (j + 0.5L) / n));
   }
 };
+static const CosTable &cosines() {
+  static const CosTable c;
+  return c;
+}
 
 template <class F>
 static int cheb_fit(F f, double lo, double hi, double abs_tol, double rel_tol, double *out, int maxdeg) {
-  static const CosTable cosines;
   for (int n : {48, 96}) {
-    const std::vector<ld> &cs = n == 48 ? cosines.c48 : cosines.c96;
+    const std::vector<ld> &cs = n == 48 ? cosines().c48 : cosines().c96;
     ld fx[96];
     double c[96];
     double fmax = 0;
@@ -378,6 +368,25 @@ static int cheb_fit(F f, double lo, double hi, double abs_tol, double rel_tol, d
     }
   }
   return -1;
+}
+
+// Run body(i) for i in [0, n) on up to 16 host threads.
+template <class Fn>
+static void parallel_for(int n, Fn body) {
+  const int nth = std::max(1, std::min<int>({16, n, (int)std::thread::hardware_concurrency()}));
+  std::atomic<int> next(0);
+  (void)cosines();   // (made here, not by the first thread to need them)
+  auto work = [&]() {
+    for (int i = next++; i < n; i = next++) body(i);
+  };
+  std::vector<std::thread> th;
+  th.reserve(nth);
+  try {
+    for (int k = 1; k < nth; ++k) th.emplace_back(work);
+  } catch (const std::system_error &) {   // no more threads to be had: fewer do it
+  }
+  work();
+  for (auto &t : th) t.join();
 }
 
 // ---------------------------------------------------------------- Ewald tables
@@ -527,14 +536,16 @@ std::string build_pgf_table(PgfTable &tab, double a, double b, double zspan, dou
       const ld bb = beta / (2 * E), area = a * b;
       const zl pref = 1.0L / (4.0L * a * b * zl(0, beta));
       // the same by erfc of complex arguments, whose values serve both parts' fits
-      std::vector<std::pair<double, zl>> seen;
+      std::pair<double, zl> seen[48 + 96];
+      int nseen = 0;
       const auto Kc = [&](double w) -> zl {
-        for (const auto &s : seen)
-          if (s.first == w) return s.second;
+        for (int i = 0; i < nseen; ++i)
+          if (seen[i].first == w) return seen[i].second;
         const ld v = std::sqrt(std::max(0.0L, (ld)w));
         const zl e1 = std::exp(zl(0, 2 * bb * v)), e2 = std::exp(zl(0, -2 * bb * v));
-        seen.push_back({w, pref * (e1 * erfc_l(zl(v, bb)) + e2 * erfc_l(zl(-v, bb)))});
-        return seen.back().second;
+        const zl K = pref * (e1 * erfc_l(zl(v, bb)) + e2 * erfc_l(zl(-v, bb)));
+        if (nseen < 48 + 96) seen[nseen++] = {w, K};
+        return K;
       };
       md.cplx = 1;
       const int d1 = cheb_fit(
