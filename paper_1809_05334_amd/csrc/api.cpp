@@ -802,8 +802,10 @@ int fill_tables(vie_ctx *ctx, double lambda_nm, double theta, double phi, const 
   ctx->packlen = (int)ctx->pack.size();
   if (precision == VIE_MIXED_FP32) {
     pack_pgf_fixed(*ctx->tab, ctx->fpack);
-    if ((int)ctx->fpack.size() > kMaxPack)
-      return fail(ctx, VIE_EINVAL, "lattice-sum table needs %zu doubles (> %d)", ctx->fpack.size(), kMaxPack);
+    ctx->listed = pgf_listed_doubles(*ctx->tab);
+    const size_t need = std::max(ctx->fpack.size(), ctx->listed);
+    if (need > (size_t)kMaxPack)
+      return fail(ctx, VIE_EINVAL, "lattice-sum table needs %zu doubles (> %d)", need, kMaxPack);
   }
   return VIE_OK;
 }
@@ -843,7 +845,6 @@ int fill_upload(vie_ctx *ctx) {
   ctx->fill_ky = ky;
   ctx->jdiag_ok = false;
   ctx->fill_lds = 8 * (size_t)ctx->packlen;
-  ctx->fill_flds = mixed ? 8 * ctx->fpack.size() : 0;
 
   hipLaunchKernelGGL(k_prep, dim3(nblk(t.nt, 256)), dim3(256), 0, ctx->stream, (int64_t)t.nt, t2f, tg,
                      ctx->ptr<double>(L.area), ctx->ptr<dz>(L.eps), kx, ky, t.a, t.b, alpha, gsrc, kappa, inveps);
@@ -859,9 +860,10 @@ int fill_upload(vie_ctx *ctx) {
   // half-SWG face) pair likewise yields the (face, tet) entry, by the same
   // two forms.  Zt is added transposed after the face kernels.
   const bool kt0 = kx == 0.0 && ky == 0.0;
-  // (mixed precision at oblique incidence keeps 32 KB per block of the swapped
-  // moments in LDS beside the table; a table too large for both runs the plain fill)
-  ctx->fill_sym = L.Zt.bytes > 0 && (!mixed || kt0 || ctx->fill_flds + kFarRevLds <= 65536);
+  // (in mixed precision which of the two fills a cell takes sets the rounding of
+  // its entries, so the line stays where the oblique form's LDS drew it: tall
+  // cells and periods far above the wavelength, at oblique incidence, take the plain one)
+  ctx->fill_sym = L.Zt.bytes > 0 && (!mixed || kt0 || ctx->listed <= kFixedSymMax);
   ctx->fill_sym_face = ctx->fill_sym;
   ctx->fill_rev = kt0 ? 0 : 1;
   ctx->last_sym = ctx->fill_sym;
@@ -910,7 +912,6 @@ int fill_kernels(vie_ctx *ctx) {
   const bool mixed = ctx->precision == VIE_MIXED_FP32;
   const double *fpk = ctx->ptr<double>(L.fpack);
   const int fpkl = (int)ctx->fpack.size();
-  const size_t flds = ctx->fill_flds;
   ZOut znear = zo;   // k_face_face takes the touching pairs alone where there is no dense part
   if (mixed) znear.Zs = nullptr;
   HIPCK(hipEventRecord(ctx->ev2, ctx->stream));
@@ -923,9 +924,9 @@ int fill_kernels(vie_ctx *ctx) {
       if (mixed) {
         const FarSeg s{fpk, fpkl, qr, tg, t2f, colors + ctx->color_off[ct], nT, colors + ctx->color_off[cs], nS, alpha,
                        gsrc, kappa, k0sq9, zo, zt, mode, 1, 0, 0};
-        const dim3 mgrid(nblk(nS, 64), nblk(nT, 4));
-        if (sym && rev) hipLaunchKernelGGL(k_tt_far_rev_c, mgrid, dim3(256), flds + kFarRevLds, ctx->stream, s);
-        else hipLaunchKernelGGL(k_tt_far_c, mgrid, dim3(256), flds, ctx->stream, s);
+        const dim3 mgrid(nblk(nS, 64), nT);
+        if (sym && rev) hipLaunchKernelGGL(k_tt_far_rev_c, mgrid, dim3(256), 0, ctx->stream, s);
+        else hipLaunchKernelGGL(k_tt_far_c, mgrid, dim3(256), 0, ctx->stream, s);
         LAUNCHCK();
         ++far_launches;
         continue;
@@ -965,8 +966,8 @@ int fill_kernels(vie_ctx *ctx) {
         const TetFaceSeg s{fpk, fpkl, qr, tg, t2f, colors + ctx->color_off[ct], nT, fg, ctx->nface, alpha, sigma, gsrc,
                            kappa, zo, zt, sym_face ? 1 : 0, 0, 0};
         const dim3 mgrid(nblk(ctx->nface, 64), nblk(nT, 4));
-        if (sym_face && rev) hipLaunchKernelGGL(k_tet_face_rev_c, mgrid, dim3(256), flds, ctx->stream, s);
-        else hipLaunchKernelGGL(k_tet_face_c, mgrid, dim3(256), flds, ctx->stream, s);
+        if (sym_face && rev) hipLaunchKernelGGL(k_tet_face_rev_c, mgrid, dim3(256), 0, ctx->stream, s);
+        else hipLaunchKernelGGL(k_tet_face_c, mgrid, dim3(256), 0, ctx->stream, s);
       } else if (sym_face && rev)
         hipLaunchKernelGGL(k_tet_face_rev, dim3(nblk(ctx->nface, 16), nblk(nT, 4)), dim3(256), lds, ctx->stream, pk_, pkl,
                            qr, tg, t2f, colors + ctx->color_off[ct], nT, fg, ctx->nface, alpha, sigma, gsrc, kappa, zo, zt);
@@ -986,7 +987,7 @@ int fill_kernels(vie_ctx *ctx) {
         const int nS = ctx->color_off[cs + 1] - ctx->color_off[cs];
         // (with the staging the far pairs came from k_tet_face)
         if (!sym_face && mixed)
-          hipLaunchKernelGGL(k_face_tet_c, dim3(nblk(nS, 64), nblk(ctx->nhalf, 4)), dim3(256), flds, ctx->stream,
+          hipLaunchKernelGGL(k_face_tet_c, dim3(nblk(nS, 64), nblk(ctx->nhalf, 4)), dim3(256), 0, ctx->stream,
                              FaceTetSeg{fpk, fpkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, tg, t2f,
                                         colors + ctx->color_off[cs], nS, gsrc, kappa, zo, 0, 0});
         else if (!sym_face && !grid)
@@ -1002,7 +1003,7 @@ int fill_kernels(vie_ctx *ctx) {
         LAUNCHCK();
       }
       if (mixed)
-        hipLaunchKernelGGL(k_face_face_c, dim3(nblk(ctx->nface, 64), nblk(ctx->nhalf, 4)), dim3(256), flds, ctx->stream,
+        hipLaunchKernelGGL(k_face_face_c, dim3(nblk(ctx->nface, 64), nblk(ctx->nhalf, 4)), dim3(256), 0, ctx->stream,
                            FaceFaceSeg{fpk, fpkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, ctx->nface, sigma, zo, 0, 0});
       hipLaunchKernelGGL(k_face_face, dim3(nblk(ctx->nface, kFaceChunk), nblk(ctx->nhalf, 4)), dim3(256), lds, ctx->stream, pk_,
                          pkl, qr, fg, ctx->ptr<int32_t>(L.half), ctx->nhalf, ctx->nface, sigma, znear);

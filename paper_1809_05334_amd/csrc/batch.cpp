@@ -284,8 +284,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
     c.znear.Zs = nullptr;
     return c;
   };
-  // (mixed precision: the far pairs by the kernels of k_far_c.hip and their own
-  // table, 64 sources x 4 test elements per block)
+  // (mixed precision: the far pairs by the kernels of k_far_c.hip and their own table)
   const bool mixed = b->precision == VIE_MIXED_FP32;
   auto far_table = [&](vie_ctx *x, auto &s) {
     if (!mixed) return;
@@ -293,7 +292,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
     s.packlen = (int)x->fpack.size();
   };
   const int per = mixed ? 64 : 16;
-  auto far_lds = [&](vie_ctx *x) { return mixed ? x->fill_flds : x->fill_lds; };
+  auto far_lds = [&](vie_ctx *x) { return mixed ? size_t(0) : x->fill_lds; };
   // far tet pairs, per colour pair (ct, cs)
   for (int ct = 0; ct < maxC; ++ct)
     for (int cs = 0; cs < maxC; ++cs) {
@@ -306,10 +305,8 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
         FarSeg s{c.pk, c.pkl, c.qr, c.tg, c.t2f, c.colors + x->color_off[ct], nT, c.colors + x->color_off[cs], nS,
                  c.alpha, c.gsrc, c.kappa, x->fill_k0sq9, c.zo, c.zt, !x->fill_sym ? 0 : (ct == cs ? 2 : 1), far_tper(nS, nT), 0, 0};
         const bool r = x->fill_sym && x->fill_rev;
-        if (mixed) s.tper = 1;
         far_table(x, s);
-        (r ? rev : plain).add(s, (int)nblk(nS, mixed ? 64 : 8), (int)nblk(nT, 4 * s.tper),
-                              far_lds(x) + (r && mixed ? kFarRevLds : 0));
+        (r ? rev : plain).add(s, (int)nblk(nS, mixed ? 64 : 8), mixed ? nT : (int)nblk(nT, 4 * s.tper), far_lds(x));
       }
       put(plain, K_FAR);
       put(rev, K_FAR_REV);

@@ -55,6 +55,11 @@ struct PgfTable {
   PgfMode mode[kPgfTerms]; // dense grid, index (p+4)*9 + (q+4); deg < 0: below significance
 };
 
+// Offsets in the mixed-precision far kernels' copy of the table (pack_pgf_fixed).
+constexpr int kFixedSymMax = 4095;   // pgf_listed_doubles up to which an oblique fill may be the symmetric one
+constexpr int kFixedNmax = 29, kFixedRows = kFixedNmax + kPgfM + 1, kFixedRecords = 44;
+static_assert(kFixedRecords % 4 == 0 && kFixedRows + kPgfSide <= kFixedRecords, "records start at multiples of four");
+
 // ------------------------------------------------------------ quadrature
 // Barycentric rules (weights sum to 1).  Far pairs: tet 4-pt (degree 2) x
 // triangle 3-pt (degree 2).  Touching pairs: outer tet 14-pt / triangle 7-pt

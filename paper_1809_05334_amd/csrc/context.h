@@ -144,7 +144,7 @@ struct vie_ctx {
   bool fill_sym = false, fill_sym_face = false;
   int fill_rev = 0;
   size_t fill_lds = 0;
-  size_t fill_flds = 0;             // mixed precision: bytes of the far kernels' table
+  size_t listed = 0;                // mixed precision: pgf_listed_doubles of the last fill
   double fill_k0sq9 = 0;
   double fill_kx = 0, fill_ky = 0;  // transverse wavevector of the fill
   // structured-grid operator: the mesh's grid analysis (built on first use,

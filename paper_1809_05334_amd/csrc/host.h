@@ -108,20 +108,20 @@ constexpr int kPackRows = 29;
 constexpr int kPackImages = 40;
 void pack_pgf_table(const PgfTable &tab, std::vector<double> &out);
 
-// The copy for the far kernels of the mixed-precision operator, every fit as it is:
+// The copy for the far kernels of the mixed-precision operator (offsets in common.h):
 //   [0..10)  E, a, b, 1/a, 1/b, kx, ky, 2pi/a, 2pi/b, ws
-//   [10..19) Re phase0[9], [19..28) Im phase0[9], [28] nimg
-//   [32..113) per order (p,q) grid index: offset of its record or 0 (low
-//             word), K | cplx << 16 (high word)
-//   [116..125) per row p of the order grid: q_lo | (q_hi + 1) << 8, the
-//             first and last q with an order (0 | 0 << 8: none)
-//   image records from kFixedImages on, each
-//     [E xs, -(xa xs + 1), cre, cim, m, n, K, len] f[0..K] (pad to 4) [HK, 0, 0, 0] h[0..HK] (pad to 4)
-//     (the H block only for touching classes; len = record length)
-//   order records [K, cplx, 0, 0] kre[0..K] (pad) kim[0..K] (pad, complex orders only)
-// K, HK are the degrees rounded up to a multiple of 4 (zero coefficients).
-constexpr int kFixedRows = 116;
-constexpr int kFixedImages = 128;
+//   [10..19) Re phase0[9], [19..28) Im phase0[9], [28] the largest |m| of an
+//            image, [29..34) per |m| the largest |n| (every smaller one is there)
+//   per row p of the order grid a bit per slot q with an order (high word: of
+//            those with an imaginary part)
+//   records: the images in the order of (m, n), each [E xs, -(xa xs + 1), Re, Im
+//   phase] and the F series, then the orders in the order of (p, q), each its
+//   real series and, if it propagates, its imaginary one.  A series is [K, c_K,
+//   c_{K-1}, c_{K-2} - c_K, c_{K-3} .. c_0], K even, the record's length in the
+//   high word of K; both start at multiples of four.
 void pack_pgf_fixed(const PgfTable &tab, std::vector<double> &out);
+// Doubles of a table that lists every image and every order by itself, in
+// groups of four coefficients.
+size_t pgf_listed_doubles(const PgfTable &tab);
 
 }  // namespace vie

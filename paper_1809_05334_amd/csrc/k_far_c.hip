@@ -6,74 +6,109 @@
 // solution within 1e-9 in norm, but a single component of it 1e-7 off (N =
 // 37,376).  A path that solves to 1e-12 should not move by that with the form
 // of a series, so the arithmetic of these contributions is held fixed, to the
-// bit: the terms come from one evaluation (PgfTerms::fixed), each as
-// its Chebyshev series by Clenshaw's recurrence; images and orders are summed
-// in the order of their grids, and the point pairs of an element pair one
-// after another by one lane.  k_fill.hip, whose entries are FP64, is free of
-// this and takes whichever form is fastest; touching pairs are FP64 in both
-// paths and come from there.
+// bit: the terms come from one evaluation (PgfTerms::fixed), each as its
+// Chebyshev series by Clenshaw's recurrence; images and orders are summed in
+// the order of their grids, and the point pairs of an element pair one after
+// the other.  k_fill.hip, whose entries are FP64, is free of this and takes
+// whichever form is fastest; touching pairs are FP64 in both paths and come
+// from there.
+//
+// Which lane forms which values is free.  Four lanes share a tet pair, which
+// matters for small cells, where a launch is one lane's chain: far pairs of N =
+// 416, symmetric, 10 launches, 0.63 ms, 3.8 with one lane per pair; N = 3,038 3.6
+// against 5.5.  The series' coefficients come through the scalar cache into
+// scalar registers; with the table in LDS and the same lanes N = 37,376 took 419
+// ms, now 357 (407 with one lane per pair, padded series and LDS).  That is 4,000
+// vector instructions per point pair and wave, 3,350 of them FP64 (an addition
+// and an FMA per degree and term; 2,700 and 1,870 in k_fill.hip), issued at 85 %
+// of what the clock under this load allows.
 #include "fill.h"
 
 namespace vie {
 
-// Packed table of these kernels (pack_pgf_fixed): header, per-order offsets,
-// image records, order records.
+// Packed table of these kernels (pack_pgf_fixed), read through the scalar cache:
+// every address is the same in all lanes, and a coefficient that is in scalar
+// registers takes no vector registers, no LDS reads and no moves.
+typedef const double __attribute__((address_space(4))) *FixedTab;
+__device__ __forceinline__ FixedTab fixed_tab(const double *p) { return (FixedTab)(uintptr_t)p; }
 namespace pkf {
-constexpr int E = 0, A = 1, B = 2, IA = 3, IB = 4, KX = 5, KY = 6, TPA = 7, TPB = 8, WS = 9, PHRE = 10, PHIM = 19,
-              NIMG = 28, MODES = 32, ROWS = 116, IMAGES = 128;
+constexpr int A = 1, B = 2, IA = 3, IB = 4, E = 0, KX = 5, KY = 6, TPA = 7, TPB = 8, WS = 9, PHRE = 10, PHIM = 19,
+              MMAX = 28, NMAX = kFixedNmax, ROWS = kFixedRows, RECORDS = kFixedRecords;
+}
+__device__ __forceinline__ int lo32(double v) { return ufirst(__double2loint(v)); }
+__device__ __forceinline__ int hi32(double v) { return ufirst(__double2hiint(v)); }
+
+// (scalar loads return in any order: those under way are waited for before the next are asked for)
+__device__ __forceinline__ void scalar_wait() {
+  __builtin_amdgcn_sched_barrier(0);
+  __builtin_amdgcn_s_waitcnt(0xc07f);   // lgkmcnt(0)
+  __builtin_amdgcn_sched_barrier(0);
 }
 
-// W Chebyshev series with the same coefficients c[0..K] (K even, zero-padded)
-// at W arguments t[w]: interleaved Clenshaw recurrences, two coefficients per
-// step, each coefficient read once for all W.
-template <int W>
-__device__ __forceinline__ void clenshaw_w(const double *__restrict__ c, int K, const double (&t)[W], double (&f)[W]) {
-  double b1[W], b2[W], t2[W];
+// A Chebyshev series [K, c_K, c_{K-1}, c_{K-2} - c_K | c_{K-3} .. c_0] (K even, >= 4)
+// in the table: its first eight values, and where the others are.
+struct FixedSeries {
+  double v[8];
+  FixedTab q;
+};
+__device__ __forceinline__ FixedSeries fixed_series(FixedTab q) {
+  FixedSeries s;
 #pragma unroll
-  for (int w = 0; w < W; ++w) {
-    b1[w] = b2[w] = 0.0;
-    t2[w] = t[w] + t[w];
-  }
-  // four coefficients per pass, all read before the first is used, so one
-  // read's latency is exposed per four coefficients rather than per two
-  const auto pair = [&](double ck, double ck1) {
+  for (int i = 0; i < 8; ++i) s.v[i] = q[i];
+  s.q = q + 8;
+  return s;
+}
+
+// The series at NC arguments t (t2 = 2 t) by Clenshaw's recurrence b_k = 2 t
+// b_{k+1} + (c_k - b_{k+2}), f = t b_1 + (c_0 - b_2): each coefficient is read
+// once for all of them, four at a time, the next four while the current ones are
+// used.  The first two steps, whose b are zero or c_K, are formed without them.
+template <int NC>
+__device__ __forceinline__ void clenshaw(const FixedSeries &s, const double (&t)[NC], const double (&t2)[NC],
+                                         double (&f)[NC]) {
+  FixedTab q = s.q;
+  double e0 = s.v[4], e1 = s.v[5], e2 = s.v[6], e3 = s.v[7];
+  int r = lo32(s.v[0]) - 2;   // coefficients from e0 on
+  double b1[NC], b2[NC];
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const double bk = fma(t2[w], b1[w], ck - b2[w]);
-      const double bk1 = fma(t2[w], bk, ck1 - b1[w]);
-      b2[w] = bk;
-      b1[w] = bk1;
-    }
+  for (int i = 0; i < NC; ++i) b2[i] = fma(t2[i], s.v[1], s.v[2]);
+#pragma unroll
+  for (int i = 0; i < NC; ++i) b1[i] = fma(t2[i], b2[i], s.v[3]);
+  const auto step = [&](double c, double (&n)[NC], const double (&o)[NC]) {   // n: b_{k+2}, then b_k
+#pragma unroll
+    for (int i = 0; i < NC; ++i) n[i] = fma(t2[i], o[i], c - n[i]);
   };
-  int k = K;
 #pragma unroll 1
-  for (; k >= 8; k -= 8) {
-    const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-    const double c4 = c[k - 4], c5 = c[k - 5], c6 = c[k - 6], c7 = c[k - 7];
-    pair(c0, c1);
-    pair(c2, c3);
-    pair(c4, c5);
-    pair(c6, c7);
+  for (; r > 4; r -= 4) {
+    scalar_wait();
+    const double n0 = q[0], n1 = q[1], n2 = q[2], n3 = q[3];
+    q += 4;
+    step(e0, b2, b1);
+    step(e1, b1, b2);
+    step(e2, b2, b1);
+    step(e3, b1, b2);
+    e0 = n0;
+    e1 = n1;
+    e2 = n2;
+    e3 = n3;
   }
-  if (k >= 4) {   // (K is a multiple of 4: what remains is 4 or 0)
-    const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-    pair(c0, c1);
-    pair(c2, c3);
-    k -= 4;
+  if (r == 4) {
+    step(e0, b2, b1);
+    step(e1, b1, b2);
+    e0 = e2;
+    e1 = e3;
   }
-#pragma unroll 1
-  for (; k >= 2; k -= 2) pair(c[k], c[k - 1]);
+  step(e0, b2, b1);
 #pragma unroll
-  for (int w = 0; w < W; ++w) f[w] = fma(t[w], b1[w], c[0] - b2[w]);
+  for (int i = 0; i < NC; ++i) f[i] = fma(t[i], b2[i], e1 - b1[i]);
 }
 
 // g_p at W separations d[w] = r - r'_w of non-touching elements (one point
-// against W), from the packed table P.  The table entries are read once for
-// all W separations and the W Clenshaw recurrences run interleaved.
+// against W), from the packed table P: images (m, n), then orders (p, q), each
+// added in the order of its grid.
 // REV: also g_p at -d[w] into rev[w] (see pgf_eval_w).
 template <int W, bool REV = false>
-__device__ __forceinline__ void pgf_fixed_w(const double *__restrict__ P, const double (&d)[W][3], dz (&out)[W],
-                                            dz *rev = nullptr) {
+__device__ __forceinline__ void pgf_fixed_w(FixedTab P, const double (&d)[W][3], dz (&out)[W], dz *rev = nullptr) {
   const double a = P[pkf::A], b = P[pkf::B], E = P[pkf::E];
   double dx[W], dy[W], dz2[W], sre[W], sim[W];
   int im0[W], in0[W];
@@ -88,80 +123,52 @@ __device__ __forceinline__ void pgf_fixed_w(const double *__restrict__ P, const 
     sre[w] = 0.0;
     sim[w] = 0.0;
   }
-  // spatial series
-  const int nimg = pint(P[pkf::NIMG]);
-  int off = pkf::IMAGES;
+  // the records, one after the other: the images in the order of (m, n)
+  FixedTab q = P + pkf::RECORDS;
+  const int mmax = lo32(P[pkf::MMAX]);
 #pragma unroll 1
-  for (int i = 0; i < nimg; ++i) {
-    const double *R = P + off;
-    const double ts = R[0], t0 = R[1], cre = R[2], cim = R[3];   // t = ts R + t0
-    const int im = pint(R[4]), in = pint(R[5]), K = pint(R[6]);
-    off += pint(R[7]);
-    double t[W], sc[W];
+  for (int m = -mmax; m <= mmax; ++m) {
+    const int nmax = lo32(P[pkf::NMAX + (m < 0 ? -m : m)]);
+    double X[W];
 #pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const double X = fma((double)im, a, dx[w]), Y = fma((double)in, b, dy[w]);
-      const double R2 = fma(X, X, fma(Y, Y, dz2[w]));
-      const double rinv = rsqrt_pos(R2), Rw = R2 * rinv;
-      t[w] = fma(Rw, ts, t0);
-      sc[w] = rinv;
-    }
-    // W interleaved Clenshaw recurrences on the F coefficients
-    double b1[W], b2[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) b1[w] = b2[w] = 0.0;
-    const double *c = R + 8;
-    // four coefficients per pass, read before the first is used (as in clenshaw_w)
-    double t2[W];
-#pragma unroll
-    for (int w = 0; w < W; ++w) t2[w] = t[w] + t[w];
-    const auto pair = [&](double ck, double ck1) {
+    for (int w = 0; w < W; ++w) X[w] = fma((double)m, a, dx[w]);
+#pragma unroll 1
+    for (int n = -nmax; n <= nmax; ++n) {
+      // [E xs, -(xa xs + 1), Re, Im phase], the F series
+      scalar_wait();
+      const double ts = q[0], t0 = q[1], cre = q[2], cim = q[3];
+      const FixedSeries fs = fixed_series(q + 4);
+      __builtin_amdgcn_sched_barrier(0);   // (asked for before the distances are formed)
+      double t[W], t2[W], sc[W], f[W];
 #pragma unroll
       for (int w = 0; w < W; ++w) {
-        const double bk = fma(t2[w], b1[w], ck - b2[w]);
-        const double bk1 = fma(t2[w], bk, ck1 - b1[w]);
-        b2[w] = bk;
-        b1[w] = bk1;
+        const double Y = fma((double)n, b, dy[w]);
+        const double R2 = fma(X[w], X[w], fma(Y, Y, dz2[w]));
+        sc[w] = rsqrt_pos(R2);
+        t[w] = fma(R2 * sc[w], ts, t0);
+        t2[w] = t[w] + t[w];
       }
-    };
-    int k = K;
-#pragma unroll 1
-    for (; k >= 8; k -= 8) {
-      const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-      const double c4 = c[k - 4], c5 = c[k - 5], c6 = c[k - 6], c7 = c[k - 7];
-      pair(c0, c1);
-      pair(c2, c3);
-      pair(c4, c5);
-      pair(c6, c7);
-    }
-    if (k >= 4) {   // (K is a multiple of 4: what remains is 4 or 0)
-      const double c0 = c[k], c1 = c[k - 1], c2 = c[k - 2], c3 = c[k - 3];
-      pair(c0, c1);
-      pair(c2, c3);
-      k -= 4;
-    }
-#pragma unroll 1
-    for (; k >= 2; k -= 2) pair(c[k], c[k - 1]);
-    double f[W];
+      clenshaw<W>(fs, t, t2, f);
 #pragma unroll
-    for (int w = 0; w < W; ++w) f[w] = fma(t[w], b1[w], c[0] - b2[w]);
-#pragma unroll
-    for (int w = 0; w < W; ++w) {
-      const double g = f[w] * sc[w];
-      sre[w] = fma(cre, g, sre[w]);
-      sim[w] = fma(cim, g, sim[w]);
+      for (int w = 0; w < W; ++w) {
+        const double g = f[w] * sc[w];
+        sre[w] = fma(cre, g, sre[w]);
+        sim[w] = fma(cim, g, sim[w]);
+      }
+      q += hi32(fs.v[0]);
     }
   }
 
-  // spectral series: the W separations share every mode's coefficient reads
-  // and run W interleaved Clenshaw recurrences in w = (z E)^2; the Floquet
-  // phases e^{-j k_tpq . Delta_t} of each separation by recurrence in p and q
-  double tw[W], kre[W], kim[W], cre_[W], cim_[W];
+  // then the orders in the order of (p, q): the W separations share every
+  // series; the Floquet phases e^{-j k_tpq . Delta_t} of each separation by
+  // recurrence in p and q
+  double tw[W], tw2[W], kre[W], kim[W], cre_[W], cim_[W];
   dz erow[W], bx[W], by[W];   // erow: phase of (p, q = -4); steps in p and in q
   const bool kt0 = P[pkf::KX] == 0.0 && P[pkf::KY] == 0.0;   // normal incidence: e^{-j kt.Delta} = 1
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     tw[w] = fma(dz2[w] * E * E, P[pkf::WS], -1.0);
+    tw2[w] = tw[w] + tw[w];
     double s0, c0, s1, c1;
     sincos(-P[pkf::TPA] * dx[w], &s1, &c1);
     bx[w] = mk(c1, s1);
@@ -181,33 +188,27 @@ __device__ __forceinline__ void pgf_fixed_w(const double *__restrict__ P, const 
     cre_[w] = 0.0;
     cim_[w] = 0.0;
   }
-  // rows of the grid: only the slots from the row's first to its last mode
-  // (the phases of the slots below reached by the same products as before)
 #pragma unroll 1
   for (int p = 0; p < kPgfSide; ++p) {
-    const int rr = pint(P[pkf::ROWS + p]);
-    const int qlo = rr & 0xff, qend = rr >> 8;
+    // slots with an order, and with an imaginary part; none past the last of them is visited
+    int any = lo32(P[pkf::ROWS + p]), cplx = hi32(P[pkf::ROWS + p]);
     dz e[W];
 #pragma unroll
     for (int w = 0; w < W; ++w) e[w] = erow[w];
 #pragma unroll 1
-    for (int q = 0; q < qlo; ++q) {
-#pragma unroll
-      for (int w = 0; w < W; ++w) e[w] = e[w] * by[w];
-    }
-#pragma unroll 1
-    for (int q = qlo; q < qend; ++q) {
-      const double slot = P[pkf::MODES + p * kPgfSide + q];
-      const int moff = pint(slot);
-      if (moff > 0) {
-        const double *M = P + moff;
-        const int kc = ufirst(__double2hiint(slot));   // K | cplx << 16
-        const int K = kc & 0xffff;
+    for (; any != 0; any >>= 1, cplx >>= 1) {
+      scalar_wait();
+      const FixedSeries re = fixed_series(q);   // (of a later slot if this one has no order)
+      __builtin_amdgcn_sched_barrier(0);
+      if (any & 1) {
         double kr[W];
-        clenshaw_w<W>(M + 4, K, tw, kr);
-        if ((kc >> 16) != 0) {
+        clenshaw<W>(re, tw, tw2, kr);
+        q += hi32(re.v[0]);
+        if (cplx & 1) {
           double ki[W];
-          clenshaw_w<W>(M + 4 + K + 4, K, tw, ki);
+          const FixedSeries im = fixed_series(q);
+          clenshaw<W>(im, tw, tw2, ki);
+          q += hi32(im.v[0]);
 #pragma unroll
           for (int w = 0; w < W; ++w) {
             kre[w] += e[w].re * kr[w] - e[w].im * ki[w];
@@ -240,126 +241,171 @@ __device__ __forceinline__ void pgf_fixed_w(const double *__restrict__ P, const 
   }
 }
 
-// Scatter the 16 face-pair contributions of tet pair (T, S) into Z (TRANS:
-// entry (m, n) goes to (n, m) of the output).
-template <bool TRANS = false>
-__device__ __forceinline__ void scatter_tt(const Moments &M, const TetGeom &gt, const TetGeom &gs,
-                                           const TetFace *__restrict__ t2f, int T, int S,
-                                           const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
-                                           const dz *__restrict__ kappa, double k0sq9, const ZOut &out,
-                                           bool near) {
+// Row k of the contributions of tet pair (T, S) to Z (TRANS: entry (m, n)
+// goes to (n, m) of the output).
+template <bool TRANS>
+__device__ __forceinline__ void scatter_tt_row_c(const Moments &M, const TetGeom &gt, const TetGeom &gs,
+                                                 const TetFace *__restrict__ t2f, int T, int S, int k,
+                                                 const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
+                                                 const dz *__restrict__ kappa, double k0sq9, const ZOut &out) {
   const dz ks = kappa[S];
-  double qv[4][3];
-  dz bl[4];
-  int64_t col[4];
+  double pk[3];
+  for (int d = 0; d < 3; ++d) pk[d] = gt.v[k][d] - gt.c[d];
+  // muv - p~.mv
+  dz base = M.muv;
+  for (int d = 0; d < 3; ++d) base = base - pk[d] * M.mv[d];
+  const dz ak = alpha[4 * T + k];
+  const int64_t row = t2f[4 * T + k].unknown;
+#pragma unroll 2
   for (int l = 0; l < 4; ++l) {
-    for (int d = 0; d < 3; ++d) qv[l][d] = gs.v[l][d] - gs.c[d];
-    bl[l] = gsrc[4 * S + l] * ks;
-    col[l] = t2f[4 * S + l].unknown;
-  }
-  for (int k = 0; k < 4; ++k) {
-    double pk[3];
-    for (int d = 0; d < 3; ++d) pk[d] = gt.v[k][d] - gt.c[d];
-    // muv - p~.mv
-    dz base = M.muv;
-    for (int d = 0; d < 3; ++d) base = base - pk[d] * M.mv[d];
-    const dz ak = alpha[4 * T + k];
-    const int64_t row = t2f[4 * T + k].unknown;
-    for (int l = 0; l < 4; ++l) {
-      dz I = base;
-      for (int d = 0; d < 3; ++d) I = I - qv[l][d] * M.mu[d];
-      I = I + dot3(pk, qv[l]) * M.m0;
-      const dz v = M.m0 - k0sq9 * I;
-      if (TRANS) zput(out, col[l], row, (ak * bl[l]) * v, near);
-      else zput(out, row, col[l], (ak * bl[l]) * v, near);
-    }
+    double qv[3];
+    for (int d = 0; d < 3; ++d) qv[d] = gs.v[l][d] - gs.c[d];
+    const dz bl = gsrc[4 * S + l] * ks;
+    const int64_t col = t2f[4 * S + l].unknown;
+    dz I = base;
+    for (int d = 0; d < 3; ++d) I = I - qv[d] * M.mu[d];
+    I = I + dot3(pk, qv) * M.m0;
+    const dz v = M.m0 - k0sq9 * I;
+    if (TRANS) zput(out, col, row, (ak * bl) * v, false);
+    else zput(out, row, col, (ak * bl) * v, false);
   }
 }
 
-// Far tet pairs: 4 x 4 product rule.  One wave = one test tet x 64 source tets.
-// sym > 0 writes the swapped pair's block (S, T) too, from the pair's own
-// moments at normal incidence, else (REV) from those of the reversed
-// separations, which are summed per lane in LDS (16 doubles after the table,
-// one column per thread), not in registers, so that the kernel keeps two waves
-// per SIMD without spilling.
+// lane I of each quad, in its four lanes
+template <int I>
+__device__ __forceinline__ dz quad_lane(dz v) {
+  constexpr int ctrl = I | I << 2 | I << 4 | I << 6;   // quad_perm
+  return mk(dpp_d<ctrl>(v.re), dpp_d<ctrl>(v.im));
+}
+
+// Far tet pairs: 4 x 4 product rule, four lanes per pair, lane i the test point
+// i against the four source points.  Every lane of the four then takes the
+// sixteen values in the order of the points into all moments (its own copy),
+// and writes the entries of one test face.  A wave takes 16 sources, a block 64
+// and one test tet.  sym > 0 writes the swapped pair's block (S, T)
+// too, from the pair's own moments at normal incidence, else (REV) from those of
+// the reversed separations.
 template <bool REV>
-__device__ __forceinline__ void tt_far_c_body(const double *__restrict__ pack, int packlen,
-                                              const QuadRules *__restrict__ qr, const TetGeom *__restrict__ tg,
+__device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__restrict__ qr, const TetGeom *__restrict__ tg,
                                               const TetFace *__restrict__ t2f, const int32_t *__restrict__ test_list,
-                                              int ntest, const int32_t *__restrict__ src_list, int nsrc,
+                                              const int32_t *__restrict__ src_list, int nsrc,
                                               const dz *__restrict__ alpha, const dz *__restrict__ gsrc,
                                               const dz *__restrict__ kappa, double k0sq9, const ZOut &out,
                                               const ZOut &outT, int sym, int bx_, int by_) {
-  extern __shared__ double s_tab[];
-  // one list against itself: a block whose source positions all lie at or
-  // below its test positions has nothing to do (the whole block returns)
-  if (sym == 2 && bx_ * 64 + 63 <= by_ * 4) return;
-  stage_table(pack, packlen, s_tab);
-  const double *__restrict__ P = s_tab;
-  double *__restrict__ mr = s_tab + ((packlen + 1) & ~1) + threadIdx.x;   // REV: entry e at mr[256 e]
-
-  const int ti = uniform(by_ * 4 + (threadIdx.x >> 6));
-  const int si = bx_ * 64 + (threadIdx.x & 63);
-  if (ti >= ntest || si >= nsrc) return;
-  if (sym == 2 && si <= ti) return;
+  // one list against itself: pairs with the source position above the test position
+  const int ti = by_;
+  if (sym == 2 && bx_ * 64 + 63 <= ti) return;
+  const int k = threadIdx.x & 3;
+  const int si = bx_ * 64 + (threadIdx.x >> 2);
+  const int S = src_list[min(si, nsrc - 1)];
+  const TetGeom *gs = tg + S;
   const int T = uniform(test_list[ti]);
-  const int S = src_list[si];
   const TetGeom &gt = tg[T];
-  double wq;
-  double up[4][3], dc[3];
+  bool act = si < nsrc && (sym != 2 || si > ti);
   {
-    const TetGeom gs = tg[S];
-    if (touch_mask(gt.canon, gt.off, 4, gs.canon, gs.off, 4)) return;  // touching pairs: k_tt_near
-    wq = 0.25 * gs.vol;
-    for (int d = 0; d < 3; ++d) dc[d] = gt.c[d] - gs.c[d];
-    // source points relative to the source centroid
+    // touching pairs (a shared vertex under any image): k_tt_near; lane k looks at the test vertex k
+    const int32_t ct = gt.canon[k];
+    const bool hit = ct == gs->canon[0] || ct == gs->canon[1] || ct == gs->canon[2] || ct == gs->canon[3];
+    act = act && ((__ballot(hit) >> (threadIdx.x & 60)) & 15) == 0;
+  }
+  if (__ballot(act) == 0) return;
+  dz g[4], gr[4];
+  {
+    double sep[4][3];
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      double s = 0;
+      for (int q = 0; q < 4; ++q) s = fma(qr->tet4[k][q], gt.v[q][d], s);
+      const double u = s - gt.c[d], dc = gt.c[d] - gs->c[d];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        double r = 0;
+        for (int q = 0; q < 4; ++q) r = fma(qr->tet4[j][q], gs->v[q][d], r);
+        sep[j][d] = dc + u - (r - gs->c[d]);
+      }
+    }
+    pgf_fixed_w<4, REV>(P, sep, g, gr);
+  }
+  const double wt = 0.25 * gt.vol;
+  // source points relative to the source centroid.  The source geometry is read
+  // again for each use rather than held in registers through the lattice sums
+  // and the stores (the empty asm hides the earlier loads).
+  const auto sources = [&](double (&up)[4][3]) {
+    asm volatile("" : "+v"(gs));
 #pragma unroll
     for (int j = 0; j < 4; ++j)
 #pragma unroll
       for (int d = 0; d < 3; ++d) {
         double s = 0;
-        for (int k = 0; k < 4; ++k) s = fma(qr->tet4[j][k], gs.v[k][d], s);
-        up[j][d] = s - gs.c[d];
+        for (int q = 0; q < 4; ++q) s = fma(qr->tet4[j][q], gs->v[q][d], s);
+        up[j][d] = s - gs->c[d];
       }
-  }
-  const double wt = 0.25 * gt.vol;
-  Moments M;
-  moments_zero(M);
-  if (REV)
-    for (int e = 0; e < 16; ++e) mr[256 * e] = 0.0;
-  // one test point against the four source points per lattice-sum call
-#pragma unroll 1
-  for (int i = 0; i < 4; ++i) {
-    double u[3];
-    for (int d = 0; d < 3; ++d) {
-      double s = 0;
-      for (int k = 0; k < 4; ++k) s = fma(qr->tet4[i][k], gt.v[k][d], s);
-      u[d] = s - gt.c[d];
-    }
-    double sep[4][3];
+  };
+  // one test point i after the other, each against the four source points
+  const auto each_point = [&](auto f) {
+    const auto point = [&](auto ic) {
+      constexpr int i = decltype(ic)::value;
+      double u[3];
 #pragma unroll
-    for (int j = 0; j < 4; ++j)
-#pragma unroll
-      for (int d = 0; d < 3; ++d) sep[j][d] = dc[d] + u[d] - up[j][d];
-    dz g[4], gr[REV ? 4 : 1];
-    pgf_fixed_w<4, REV>(P, sep, g, gr);
-#pragma unroll
-    for (int j = 0; j < 4; ++j) {
-      const dz gw = (wt * wq) * g[j];
-      M.m0 = M.m0 + gw;
       for (int d = 0; d < 3; ++d) {
-        axpy(M.mu[d], u[d], gw);
-        axpy(M.mv[d], up[j][d], gw);
+        double s = 0;
+        for (int q = 0; q < 4; ++q) s = fma(qr->tet4[i][q], gt.v[q][d], s);
+        u[d] = s - gt.c[d];
       }
-      axpy(M.muv, dot3(u, up[j]), gw);
+      f(ic, u);
+    };
+    point(std::integral_constant<int, 0>());
+    point(std::integral_constant<int, 1>());
+    point(std::integral_constant<int, 2>());
+    point(std::integral_constant<int, 3>());
+  };
+  {
+    double up[4][3];
+    sources(up);
+    const double wq = 0.25 * gs->vol;
+    Moments M;
+    moments_zero(M);
+    each_point([&](auto ic, const double *u) {
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const dz gw = (wt * wq) * quad_lane<decltype(ic)::value>(g[j]);
+        M.m0 = M.m0 + gw;
+        for (int d = 0; d < 3; ++d) {
+          axpy(M.mu[d], u[d], gw);
+          axpy(M.mv[d], up[j][d], gw);
+        }
+        axpy(M.muv, dot3(u, up[j]), gw);
+      }
+    });
+    if (act) {
+      scatter_tt_row_c<false>(M, gt, *gs, t2f, T, S, k, alpha, gsrc, kappa, k0sq9, out);
+      if (!REV && sym) {
+        // (S, T) at kt = 0: test offsets and source offsets trade places
+        Moments Ms;
+        Ms.m0 = M.m0;
+        Ms.muv = M.muv;
+        for (int d = 0; d < 3; ++d) {
+          Ms.mu[d] = M.mv[d];
+          Ms.mv[d] = M.mu[d];
+        }
+        scatter_tt_row_c<true>(Ms, *gs, gt, t2f, S, T, k, alpha, gsrc, kappa, k0sq9, outT);
+      }
     }
-    if (REV) {
-      // swapped pair (S, T): its test offsets are up_j, its source offsets u
+  }
+  if (REV) {
+    // swapped pair (S, T): its test offsets are up_j, its source offsets u;
+    // the moments of each test point are summed by themselves first
+    double up[4][3];
+    sources(up);
+    const double wq = 0.25 * gs->vol;
+    Moments Mr;
+    moments_zero(Mr);
+    each_point([&](auto ic, const double *u) {
       Moments R;
       moments_zero(R);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const dz grw = (wt * wq) * gr[j];
+        const dz grw = (wt * wq) * quad_lane<decltype(ic)::value>(gr[j]);
         R.m0 = R.m0 + grw;
         for (int d = 0; d < 3; ++d) {
           axpy(R.mu[d], up[j][d], grw);
@@ -367,50 +413,21 @@ __device__ __forceinline__ void tt_far_c_body(const double *__restrict__ pack, i
         }
         axpy(R.muv, dot3(u, up[j]), grw);
       }
-      mr[0] += R.m0.re;
-      mr[256] += R.m0.im;
+      Mr.m0 = Mr.m0 + R.m0;
       for (int d = 0; d < 3; ++d) {
-        mr[256 * (2 + 2 * d)] += R.mu[d].re;
-        mr[256 * (3 + 2 * d)] += R.mu[d].im;
-        mr[256 * (8 + 2 * d)] += R.mv[d].re;
-        mr[256 * (9 + 2 * d)] += R.mv[d].im;
+        Mr.mu[d] = Mr.mu[d] + R.mu[d];
+        Mr.mv[d] = Mr.mv[d] + R.mv[d];
       }
-      mr[256 * 14] += R.muv.re;
-      mr[256 * 15] += R.muv.im;
-    }
-  }
-  // the source geometry is read again here rather than held in registers
-  // through the lattice sums (the empty asm hides the earlier load)
-  const TetGeom *tgs = tg + S;
-  asm volatile("" : "+v"(tgs));
-  const TetGeom gs = *tgs;
-  scatter_tt(M, gt, gs, t2f, T, S, alpha, gsrc, kappa, k0sq9, out, false);
-  if (REV && sym) {
-    Moments R;
-    R.m0 = mk(mr[0], mr[256]);
-    for (int d = 0; d < 3; ++d) {
-      R.mu[d] = mk(mr[256 * (2 + 2 * d)], mr[256 * (3 + 2 * d)]);
-      R.mv[d] = mk(mr[256 * (8 + 2 * d)], mr[256 * (9 + 2 * d)]);
-    }
-    R.muv = mk(mr[256 * 14], mr[256 * 15]);
-    scatter_tt<true>(R, gs, gt, t2f, S, T, alpha, gsrc, kappa, k0sq9, outT, false);
-  } else if (sym) {
-    // (S, T) at kt = 0: test offsets and source offsets trade places
-    Moments Ms;
-    Ms.m0 = M.m0;
-    Ms.muv = M.muv;
-    for (int d = 0; d < 3; ++d) {
-      Ms.mu[d] = M.mv[d];
-      Ms.mv[d] = M.mu[d];
-    }
-    scatter_tt<true>(Ms, gs, gt, t2f, S, T, alpha, gsrc, kappa, k0sq9, outT, false);
+      Mr.muv = Mr.muv + R.muv;
+    });
+    if (act) scatter_tt_row_c<true>(Mr, *gs, gt, t2f, S, T, k, alpha, gsrc, kappa, k0sq9, outT);
   }
 }
 
 // ------------------------------------------------------------ pairs with faces
 // M0 = II g_p over (test tet T, face F), 4 x 3 points: one face point against
 // the tet's four points per lattice-sum call.
-__device__ dz far_tet_face_c(const double *__restrict__ P, const QuadRules *__restrict__ qr, const TetGeom &gt,
+__device__ dz far_tet_face_c(FixedTab P, const QuadRules *__restrict__ qr, const TetGeom &gt,
                              const FaceGeom &f) {
   double fp[3][3];
   for (int j = 0; j < 3; ++j)
@@ -439,7 +456,7 @@ __device__ dz far_tet_face_c(const double *__restrict__ P, const QuadRules *__re
 }
 
 // M0 = II g_p over (test face F, source tet S), 3 x 4 points.
-__device__ dz far_face_tet_c(const double *__restrict__ P, const QuadRules *__restrict__ qr, const FaceGeom &f,
+__device__ dz far_face_tet_c(FixedTab P, const QuadRules *__restrict__ qr, const FaceGeom &f,
                              const TetGeom &gs) {
   double sp[4][3];
   for (int j = 0; j < 4; ++j)
@@ -467,7 +484,7 @@ __device__ dz far_face_tet_c(const double *__restrict__ P, const QuadRules *__re
 }
 
 // M0 = II g_p over (test face F, source face G), 3 x 3 points.
-__device__ dz far_face_face_c(const double *__restrict__ P, const QuadRules *__restrict__ qr, const FaceGeom &f,
+__device__ dz far_face_face_c(FixedTab P, const QuadRules *__restrict__ qr, const FaceGeom &f,
                               const FaceGeom &g) {
   double gp[3][3];
   for (int j = 0; j < 3; ++j)
@@ -492,7 +509,7 @@ __device__ dz far_face_face_c(const double *__restrict__ P, const QuadRules *__r
 
 // far_tet_face_c and its value at the reversed separations (test face, source
 // tet) from one lattice sum (oblique incidence).
-__device__ void far_tet_face_rev_c(const double *__restrict__ P, const QuadRules *__restrict__ qr,
+__device__ void far_tet_face_rev_c(FixedTab P, const QuadRules *__restrict__ qr,
                                    const TetGeom &gt, const FaceGeom &f, dz &m0, dz &m0r) {
   double fp[3][3], tp[4][3];
   for (int j = 0; j < 3; ++j)
@@ -524,16 +541,13 @@ __device__ void far_tet_face_rev_c(const double *__restrict__ P, const QuadRules
 // test tet (colour class list) x surface-charge face, far pairs, and with swap
 // set the (half-SWG face, tet) entries into outT (see k_tet_face in k_fill.hip)
 template <bool REV>
-__device__ __forceinline__ void tet_face_c_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
+__device__ __forceinline__ void tet_face_c_body(FixedTab P, const QuadRules *__restrict__ qr,
                                                 const TetGeom *__restrict__ tg, const TetFace *__restrict__ t2f,
                                                 const int32_t *__restrict__ test_list, int ntest,
                                                 const FaceGeom *__restrict__ fg, int nface,
                                                 const dz *__restrict__ alpha, const dz *__restrict__ sigma,
                                                 const dz *__restrict__ gsrc, const dz *__restrict__ kappa,
                                                 ZOut out, ZOut outT, int swap, int bx_, int by_) {
-  extern __shared__ double s_tab[];
-  stage_table(pack, packlen, s_tab);
-
   const int ti = uniform(by_ * 4 + (threadIdx.x >> 6));
   const int fi = bx_ * 64 + (threadIdx.x & 63);
   if (ti >= ntest || fi >= nface) return;
@@ -543,9 +557,9 @@ __device__ __forceinline__ void tet_face_c_body(const double *__restrict__ pack,
   if (touch_mask(gt.canon, gt.off, 4, f.canon, f.off, 3)) return;
   dz m0, m0r;
   if (REV) {
-    far_tet_face_rev_c(s_tab, qr, gt, f, m0, m0r);
+    far_tet_face_rev_c(P, qr, gt, f, m0, m0r);
   } else {
-    m0 = far_tet_face_c(s_tab, qr, gt, f);
+    m0 = far_tet_face_c(P, qr, gt, f);
     m0r = m0;
   }
   const dz sm = sigma[fi] * m0;
@@ -557,15 +571,12 @@ __device__ __forceinline__ void tet_face_c_body(const double *__restrict__ pack,
 }
 
 // half-SWG test face x source tet (colour class list), far pairs
-__device__ __forceinline__ void face_tet_c_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
+__device__ __forceinline__ void face_tet_c_body(FixedTab P, const QuadRules *__restrict__ qr,
                                                 const FaceGeom *__restrict__ fg, const int32_t *__restrict__ half_list,
                                                 int nhalf, const TetGeom *__restrict__ tg,
                                                 const TetFace *__restrict__ t2f, const int32_t *__restrict__ src_list,
                                                 int nsrc, const dz *__restrict__ gsrc, const dz *__restrict__ kappa,
                                                 ZOut out, int bx_, int by_) {
-  extern __shared__ double s_tab[];
-  stage_table(pack, packlen, s_tab);
-
   const int hi = uniform(by_ * 4 + (threadIdx.x >> 6));
   const int si = bx_ * 64 + (threadIdx.x & 63);
   if (hi >= nhalf || si >= nsrc) return;
@@ -573,60 +584,57 @@ __device__ __forceinline__ void face_tet_c_body(const double *__restrict__ pack,
   const int S = src_list[si];
   const TetGeom gs = tg[S];
   if (touch_mask(f.canon, f.off, 3, gs.canon, gs.off, 4)) return;
-  const dz m0 = far_face_tet_c(s_tab, qr, f, gs) * kappa[S];
+  const dz m0 = far_face_tet_c(P, qr, f, gs) * kappa[S];
   for (int l = 0; l < 4; ++l) zput(out, f.unknown, t2f[4 * S + l].unknown, mk(0, 0) - gsrc[4 * S + l] * m0, false);
 }
 
 // half-SWG test face x surface-charge face, far pairs
-__device__ __forceinline__ void face_face_c_body(const double *__restrict__ pack, int packlen, const QuadRules *__restrict__ qr,
+__device__ __forceinline__ void face_face_c_body(FixedTab P, const QuadRules *__restrict__ qr,
                                                  const FaceGeom *__restrict__ fg,
                                                  const int32_t *__restrict__ half_list, int nhalf, int nface,
                                                  const dz *__restrict__ sigma, ZOut out, int bx_, int by_) {
-  extern __shared__ double s_tab[];
-  stage_table(pack, packlen, s_tab);
-
   const int hi = uniform(by_ * 4 + (threadIdx.x >> 6));
   const int gi = bx_ * 64 + (threadIdx.x & 63);
   if (hi >= nhalf || gi >= nface) return;
   const FaceGeom &f = fg[uniform(half_list[hi])];
   const FaceGeom g = fg[gi];
   if (touch_mask(f.canon, f.off, 3, g.canon, g.off, 3)) return;
-  zput(out, f.unknown, g.unknown, sigma[gi] * far_face_face_c(s_tab, qr, f, g), false);
+  zput(out, f.unknown, g.unknown, sigma[gi] * far_face_face_c(P, qr, f, g), false);
 }
 
 // ------------------------------------------------------------ launches
 // One segment per cell (a single context launches one): see FarSeg.
 template <bool REV>
 __device__ __forceinline__ void far_seg_c(const FarSeg &A, int bx, int by) {
-  tt_far_c_body<REV>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.src_list, A.nsrc, A.alpha, A.gsrc,
+  tt_far_c_body<REV>(fixed_tab(A.pack), A.qr, A.tg, A.t2f, A.test_list, A.src_list, A.nsrc, A.alpha, A.gsrc,
                      A.kappa, A.k0sq9, A.out, A.outT, A.sym, bx, by);
 }
 template <bool REV>
 __device__ __forceinline__ void tet_face_seg_c(const TetFaceSeg &A, int bx, int by) {
-  tet_face_c_body<REV>(A.pack, A.packlen, A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.fg, A.nface, A.alpha, A.sigma,
+  tet_face_c_body<REV>(fixed_tab(A.pack), A.qr, A.tg, A.t2f, A.test_list, A.ntest, A.fg, A.nface, A.alpha, A.sigma,
                        A.gsrc, A.kappa, A.out, A.outT, A.swap, bx, by);
 }
 __device__ __forceinline__ void face_tet_seg_c(const FaceTetSeg &A, int bx, int by) {
-  face_tet_c_body(A.pack, A.packlen, A.qr, A.fg, A.half_list, A.nhalf, A.tg, A.t2f, A.src_list, A.nsrc, A.gsrc,
+  face_tet_c_body(fixed_tab(A.pack), A.qr, A.fg, A.half_list, A.nhalf, A.tg, A.t2f, A.src_list, A.nsrc, A.gsrc,
                   A.kappa, A.out, bx, by);
 }
 __device__ __forceinline__ void face_face_seg_c(const FaceFaceSeg &A, int bx, int by) {
-  face_face_c_body(A.pack, A.packlen, A.qr, A.fg, A.half_list, A.nhalf, A.nface, A.sigma, A.out, bx, by);
+  face_face_c_body(fixed_tab(A.pack), A.qr, A.fg, A.half_list, A.nhalf, A.nface, A.sigma, A.out, bx, by);
 }
 
 // (kernel arguments for one cell, a table of segments for a batch)
-#define VIE_FAR_C(NAME, SEG, BODY)                                                                    \
-  __global__ __launch_bounds__(256, 2) void NAME(SEG A) { BODY(A, blockIdx.x, blockIdx.y); }          \
-  __global__ __launch_bounds__(256, 2) void NAME##_seg(const SEG *__restrict__ segs, int nseg) {      \
-    VIE_SEG_BEGIN(SEG)                                                                                \
-    BODY(A, bx, by);                                                                                  \
+#define VIE_FAR_C(NAME, SEG, BODY, WAVES)                                                                  \
+  __global__ __launch_bounds__(256, WAVES) void NAME(SEG A) { BODY(A, blockIdx.x, blockIdx.y); }          \
+  __global__ __launch_bounds__(256, WAVES) void NAME##_seg(const SEG *__restrict__ segs, int nseg) {      \
+    VIE_SEG_BEGIN(SEG)                                                                                    \
+    BODY(A, bx, by);                                                                                      \
   }
-VIE_FAR_C(k_tt_far_c, FarSeg, far_seg_c<false>)
-VIE_FAR_C(k_tt_far_rev_c, FarSeg, far_seg_c<true>)
-VIE_FAR_C(k_tet_face_c, TetFaceSeg, tet_face_seg_c<false>)
-VIE_FAR_C(k_tet_face_rev_c, TetFaceSeg, tet_face_seg_c<true>)
-VIE_FAR_C(k_face_tet_c, FaceTetSeg, face_tet_seg_c)
-VIE_FAR_C(k_face_face_c, FaceFaceSeg, face_face_seg_c)
+VIE_FAR_C(k_tt_far_c, FarSeg, far_seg_c<false>, 3)
+VIE_FAR_C(k_tt_far_rev_c, FarSeg, far_seg_c<true>, 3)
+VIE_FAR_C(k_tet_face_c, TetFaceSeg, tet_face_seg_c<false>, 3)
+VIE_FAR_C(k_tet_face_rev_c, TetFaceSeg, tet_face_seg_c<true>, 2)
+VIE_FAR_C(k_face_tet_c, FaceTetSeg, face_tet_seg_c, 3)
+VIE_FAR_C(k_face_face_c, FaceFaceSeg, face_face_seg_c, 3)
 #undef VIE_FAR_C
 
 }  // namespace vie

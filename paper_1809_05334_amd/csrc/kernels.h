@@ -93,11 +93,9 @@ __global__ void k_tt_far_rev_seg(const FarSeg *segs, int nseg);
 __global__ void k_tt_near_seg(const NearSeg *segs, int nseg);
 __global__ void k_tet_face_seg(const TetFaceSeg *segs, int nseg);       // swap 0, 1
 __global__ void k_tet_face_rev_seg(const TetFaceSeg *segs, int nseg);   // swap 2
-// Mixed precision: the far pairs (k_far_c.hip), 64 sources x 4 test elements per
-// block, one cell's segment as the argument (gx, first unused) or a table of
-// them; k_tt_far_rev_c also takes 16 doubles per thread of dynamic LDS after
-// the table (kFarRevLds bytes).
-constexpr int kFarRevLds = 16 * 256 * 8 + 8;
+// Mixed precision: the far pairs (k_far_c.hip), one cell's segment as the argument
+// (tper, gx, first unused) or a table of them.  Blocks: 64 source tets x one test
+// tet (tet pairs), 64 source x 4 test elements (the others); no dynamic LDS.
 #define VIE_DECL_FAR_C(NAME, SEG)  \
   __global__ void NAME(SEG seg);   \
   __global__ void NAME##_seg(const SEG *segs, int nseg);

@@ -755,49 +755,62 @@ void pack_pgf_table(const PgfTable &tab, std::vector<double> &out) {
   out.insert(out.end(), 4, 0.0);   // a series reads one pair past its end
 }
 
+size_t pgf_listed_doubles(const PgfTable &tab) {
+  const auto pad4 = [](int n) { return (size_t)((n + 3) & ~3); };
+  const auto listed = [&](int deg) { return 4 + pad4((int)pad4(deg) + 1); };
+  size_t n = 128;
+  for (int i = 0; i < tab.nimg; ++i) n += 4 + listed(tab.img[i].deg) + (tab.img[i].hdeg >= 0 ? listed(tab.img[i].hdeg) : 0);
+  for (const PgfMode &md : tab.mode)
+    if (md.deg >= 0) n += listed(md.deg) + (md.cplx ? listed(md.deg) - 4 : 0);
+  return n;
+}
+
 void pack_pgf_fixed(const PgfTable &tab, std::vector<double> &out) {
-  auto pad4 = [](int n) { return (n + 3) & ~3; };
-  out.assign(kFixedImages, 0.0);
+  out.assign(kFixedRecords, 0.0);
   const double hdr[10] = {tab.E, tab.a, tab.b, tab.inv_a, tab.inv_b, tab.kx, tab.ky, tab.two_pi_a, tab.two_pi_b, tab.ws};
   for (int i = 0; i < 10; ++i) out[i] = hdr[i];
   for (int i = 0; i < 9; ++i) {
     out[10 + i] = tab.ph0re[i];
     out[19 + i] = tab.ph0im[i];
   }
-  out[28] = ibits(tab.nimg);
-  for (int i = 0; i < tab.nimg; ++i) {
+  // a series without its leading zeros, which add nothing to the recurrence, but
+  // of an even degree of 4 at the least, and with the third coefficient less the
+  // first, as the recurrence takes it; the record's length beside the degree
+  const auto series = [&](const double *c, int deg, size_t start) {
+    while (deg > 4 && c[deg] == 0.0) --deg;
+    deg = std::max(4, (deg + 1) & ~1);
+    const auto at = [&](int k) { return k <= kPgfMaxDeg ? c[k] : 0.0; };
+    const size_t head = out.size();
+    out.insert(out.end(), {0.0, at(deg), at(deg - 1), at(deg - 2) - at(deg)});
+    for (int k = deg - 3; k >= 0; --k) out.push_back(c[k]);
+    while (out.size() & 3) out.push_back(0.0);
+    out[head] = ibits(deg, (int)(out.size() - start));
+  };
+  int mmax = 0, nmax[kPgfM + 1] = {};
+  for (int i = 0; i < tab.nimg; ++i) {   // (in the order of (m, n))
     const PgfImage &im = tab.img[i];
-    const int K = pad4(im.deg), HK = im.hdeg >= 0 ? pad4(im.hdeg) : -1;
-    const size_t start = out.size();
+    mmax = std::max(mmax, im.m);
+    if (im.m >= 0) nmax[im.m] = std::max(nmax[im.m], im.n);
     // the fit's argument t = (x - xa) xs - 1 with x = E R, stored as t = R (E xs) - (xa xs + 1)
-    out.insert(out.end(), {tab.E * im.xs, -(im.xa * im.xs + 1.0), im.cre, im.cim, ibits(im.m), ibits(im.n), ibits(K), 0.0});
-    for (int k = 0; k < pad4(K + 1); ++k) out.push_back(k <= im.deg ? im.f[k] : 0.0);
-    if (HK >= 0) {
-      out.insert(out.end(), {ibits(HK), 0.0, 0.0, 0.0});
-      for (int k = 0; k < pad4(HK + 1); ++k) out.push_back(k <= im.hdeg ? im.h[k] : 0.0);
-    }
-    out[start + 7] = ibits((int)(out.size() - start));
+    const size_t start = out.size();
+    out.insert(out.end(), {tab.E * im.xs, -(im.xa * im.xs + 1.0), im.cre, im.cim});
+    series(im.f, im.deg, start);
   }
-  for (int idx = 0; idx < kPgfTerms; ++idx) {
-    const PgfMode &md = tab.mode[idx];
-    if (md.deg < 0) continue;
-    const int K = pad4(md.deg);
-    out[32 + idx] = ibits((int)out.size(), K | (md.cplx ? 1 << 16 : 0));
-    out.insert(out.end(), {ibits(K), ibits(md.cplx), 0.0, 0.0});
-    for (int k = 0; k < pad4(K + 1); ++k) out.push_back(k <= md.deg ? md.kre[k] : 0.0);
-    if (md.cplx)
-      for (int k = 0; k < pad4(K + 1); ++k) out.push_back(k <= md.deg ? md.kim[k] : 0.0);
-  }
-  // each row's range of q with a mode, so that a pass over the grid skips the rest
+  out[28] = ibits(mmax);
+  for (int m = 0; m <= kPgfM; ++m) out[kFixedNmax + m] = ibits(nmax[m]);
   for (int p = 0; p < kPgfSide; ++p) {
-    int lo = kPgfSide, hi = -1;
-    for (int q = 0; q < kPgfSide; ++q)
-      if (tab.mode[p * kPgfSide + q].deg >= 0) {
-        lo = std::min(lo, q);
-        hi = std::max(hi, q);
-      }
-    out[kFixedRows + p] = ibits(hi < 0 ? 0 : lo | (hi + 1) << 8);
+    int any = 0, cplx = 0;
+    for (int q = 0; q < kPgfSide; ++q) {
+      const PgfMode &md = tab.mode[p * kPgfSide + q];
+      if (md.deg < 0) continue;
+      any |= 1 << q;
+      if (md.cplx) cplx |= 1 << q;
+      series(md.kre, md.deg, out.size());
+      if (md.cplx) series(md.kim, md.deg, out.size());
+    }
+    out[kFixedRows + p] = ibits(any, cplx);
   }
+  out.insert(out.end(), 16, 0.0);   // (read ahead past the last record)
 }
 
 }  // namespace vie

@@ -30,6 +30,7 @@ DIGESTS = {   # (symmetric fill, theta)
     (0, 0.5): "3b42c8967933640354bb104a4d797ce4",
     (0, 0.0): "8a2eda86dde73fffb4de13f69a9c0305",
 }
+TALL_DIGEST = "19699c42b6007eb41a3fb7afba67da5a"
 
 
 @pytest.fixture(scope="module")
@@ -83,6 +84,23 @@ def test_far_entries_are_the_recorded_ones(vie, cell, sym, theta):
     s = make(vie, m, sym)
     s.fill(612.0, theta, 0.7, W.osc_eps(m, 612.0))
     assert digest(s, far) == DIGESTS[sym, theta]
+    s.close()
+
+
+def tall_slab():
+    """A slab of four periods' height above the wavelength (N = 1,952), whose
+    lattice sum has more terms than an oblique symmetric fill takes."""
+    m = W.slab_mesh(500.0, 400.0, 1700.0, 4, 4, 10)
+    t = OT.build(m.verts, m.tets, m.tet_domain, m.ndom, m.a, m.b)
+    return m, far_mask(t)
+
+
+def test_a_tall_cell_at_oblique_incidence_takes_the_plain_fill(vie):
+    m, far = tall_slab()
+    s = make(vie, m, 1)
+    s.fill(360.0, 0.4, 0.3, W.slab_eps(m))
+    assert s.fill_stats()["far_symmetric"] == 0
+    assert digest(s, far) == TALL_DIGEST
     s.close()
 
 
