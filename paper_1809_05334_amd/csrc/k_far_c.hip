@@ -15,13 +15,14 @@
 //
 // Which lane forms which values is free.  Four lanes share a tet pair, which
 // matters for small cells, where a launch is one lane's chain: far pairs of N =
-// 416, symmetric, 10 launches, 0.63 ms, 3.8 with one lane per pair; N = 3,038 3.6
+// 416, symmetric, 10 launches, 0.60 ms, 3.8 with one lane per pair; N = 3,038 3.4
 // against 5.5.  The series' coefficients come through the scalar cache into
-// scalar registers; with the table in LDS and the same lanes N = 37,376 took 419
-// ms, now 357 (407 with one lane per pair, padded series and LDS).  That is 4,000
-// vector instructions per point pair and wave, 3,350 of them FP64 (an addition
-// and an FMA per degree and term; 2,700 and 1,870 in k_fill.hip), issued at 85 %
-// of what the clock under this load allows.
+// scalar registers (the table in LDS, the same lanes: 419 ms at N = 37,376), and
+// the values of a pair wait in LDS, not in registers, for its moments (357; the
+// reversed form spilled 284 B per lane).  Now 332 ms there (407 with one lane per
+// pair, padded series and the table in LDS): 3,940 vector instructions per point
+// pair and wave, 3,410 of them FP64 (an addition and an FMA per degree and term;
+// 2,700 and 1,870 in k_fill.hip), issued at 82 % of the rate at 2.4 GHz.
 #include "fill.h"
 
 namespace vie {
@@ -111,15 +112,14 @@ template <int W, bool REV = false>
 __device__ __forceinline__ void pgf_fixed_w(FixedTab P, const double (&d)[W][3], dz (&out)[W], dz *rev = nullptr) {
   const double a = P[pkf::A], b = P[pkf::B], E = P[pkf::E];
   double dx[W], dy[W], dz2[W], sre[W], sim[W];
-  int im0[W], in0[W];
+  int shift[W];   // the nearest image's phase
 #pragma unroll
   for (int w = 0; w < W; ++w) {
     const double m0 = rint(d[w][0] * P[pkf::IA]), n0 = rint(d[w][1] * P[pkf::IB]);
     dx[w] = fma(-m0, a, d[w][0]);
     dy[w] = fma(-n0, b, d[w][1]);
     dz2[w] = d[w][2] * d[w][2];
-    im0[w] = (int)m0;
-    in0[w] = (int)n0;
+    shift[w] = ((int)m0 + 1) * 3 + ((int)n0 + 1);
     sre[w] = 0.0;
     sim[w] = 0.0;
   }
@@ -234,11 +234,17 @@ __device__ __forceinline__ void pgf_fixed_w(FixedTab P, const double (&d)[W][3],
   }
 #pragma unroll
   for (int w = 0; w < W; ++w) {
-    const int pi = (im0[w] + 1) * 3 + (in0[w] + 1);
-    const dz ph = mk(P[pkf::PHRE + pi], P[pkf::PHIM + pi]);
+    const dz ph = mk(P[pkf::PHRE + shift[w]], P[pkf::PHIM + shift[w]]);
     out[w] = ph * mk(sre[w] + kre[w], sim[w] + kim[w]);
     if (REV) rev[w] = conjz(out[w]) + conjz(ph) * mk(-2.0 * cim_[w], 2.0 * cre_[w]);
   }
+}
+
+// Z[m][n] += v, formed in FP64 and rounded.
+__device__ __forceinline__ void zput_c(const ZOut &o, int64_t m, int64_t n, dz v) {
+  fz *p = o.Zs + m * o.ld + n;
+  const fz z = *p;
+  *p = fz{(float)((double)z.re + v.re), (float)((double)z.im + v.im)};
 }
 
 // Row k of the contributions of tet pair (T, S) to Z (TRANS: entry (m, n)
@@ -266,22 +272,16 @@ __device__ __forceinline__ void scatter_tt_row_c(const Moments &M, const TetGeom
     for (int d = 0; d < 3; ++d) I = I - qv[d] * M.mu[d];
     I = I + dot3(pk, qv) * M.m0;
     const dz v = M.m0 - k0sq9 * I;
-    if (TRANS) zput(out, col, row, (ak * bl) * v, false);
-    else zput(out, row, col, (ak * bl) * v, false);
+    if (TRANS) zput_c(out, col, row, (ak * bl) * v);
+    else zput_c(out, row, col, (ak * bl) * v);
   }
 }
 
-// lane I of each quad, in its four lanes
-template <int I>
-__device__ __forceinline__ dz quad_lane(dz v) {
-  constexpr int ctrl = I | I << 2 | I << 4 | I << 6;   // quad_perm
-  return mk(dpp_d<ctrl>(v.re), dpp_d<ctrl>(v.im));
-}
-
 // Far tet pairs: 4 x 4 product rule, four lanes per pair, lane i the test point
-// i against the four source points.  Every lane of the four then takes the
-// sixteen values in the order of the points into all moments (its own copy),
-// and writes the entries of one test face.  A wave takes 16 sources, a block 64
+// i against the four source points.  The sixteen values meet in LDS (the pairs of
+// a wave 33 values apart: no bank conflicts), and every lane of the four takes
+// them in the order of the points into all moments (its own copy) and writes
+// the entries of one test face.  A wave takes 16 sources, a block 64
 // and one test tet.  sym > 0 writes the swapped pair's block (S, T)
 // too, from the pair's own moments at normal incidence, else (REV) from those of
 // the reversed separations.
@@ -309,8 +309,10 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
     act = act && ((__ballot(hit) >> (threadIdx.x & 60)) & 15) == 0;
   }
   if (__ballot(act) == 0) return;
-  dz g[4], gr[4];
+  __shared__ dz s_g[64 * (REV ? 33 : 17)];
+  dz *mine = s_g + (threadIdx.x >> 2) * (REV ? 33 : 17);
   {
+    dz g[4], gr[4];
     double sep[4][3];
 #pragma unroll
     for (int d = 0; d < 3; ++d) {
@@ -325,7 +327,13 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
       }
     }
     pgf_fixed_w<4, REV>(P, sep, g, gr);
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      mine[4 * k + j] = g[j];
+      if (REV) mine[16 + 4 * k + j] = gr[j];
+    }
   }
+  __builtin_amdgcn_wave_barrier();   // (a wave reads what it wrote)
   const double wt = 0.25 * gt.vol;
   // source points relative to the source centroid.  The source geometry is read
   // again for each use rather than held in registers through the lattice sums
@@ -341,23 +349,13 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
         up[j][d] = s - gs->c[d];
       }
   };
-  // one test point i after the other, each against the four source points
-  const auto each_point = [&](auto f) {
-    const auto point = [&](auto ic) {
-      constexpr int i = decltype(ic)::value;
-      double u[3];
+  const auto test_point = [&](int i, double (&u)[3]) {   // relative to the test centroid
 #pragma unroll
-      for (int d = 0; d < 3; ++d) {
-        double s = 0;
-        for (int q = 0; q < 4; ++q) s = fma(qr->tet4[i][q], gt.v[q][d], s);
-        u[d] = s - gt.c[d];
-      }
-      f(ic, u);
-    };
-    point(std::integral_constant<int, 0>());
-    point(std::integral_constant<int, 1>());
-    point(std::integral_constant<int, 2>());
-    point(std::integral_constant<int, 3>());
+    for (int d = 0; d < 3; ++d) {
+      double s = 0;
+      for (int q = 0; q < 4; ++q) s = fma(qr->tet4[i][q], gt.v[q][d], s);
+      u[d] = s - gt.c[d];
+    }
   };
   {
     double up[4][3];
@@ -365,10 +363,13 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
     const double wq = 0.25 * gs->vol;
     Moments M;
     moments_zero(M);
-    each_point([&](auto ic, const double *u) {
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i) {
+      double u[3];
+      test_point(i, u);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const dz gw = (wt * wq) * quad_lane<decltype(ic)::value>(g[j]);
+        const dz gw = (wt * wq) * mine[4 * i + j];
         M.m0 = M.m0 + gw;
         for (int d = 0; d < 3; ++d) {
           axpy(M.mu[d], u[d], gw);
@@ -376,7 +377,7 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
         }
         axpy(M.muv, dot3(u, up[j]), gw);
       }
-    });
+    }
     if (act) {
       scatter_tt_row_c<false>(M, gt, *gs, t2f, T, S, k, alpha, gsrc, kappa, k0sq9, out);
       if (!REV && sym) {
@@ -400,12 +401,15 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
     const double wq = 0.25 * gs->vol;
     Moments Mr;
     moments_zero(Mr);
-    each_point([&](auto ic, const double *u) {
+#pragma unroll 1
+    for (int i = 0; i < 4; ++i) {
+      double u[3];
+      test_point(i, u);
       Moments R;
       moments_zero(R);
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        const dz grw = (wt * wq) * quad_lane<decltype(ic)::value>(gr[j]);
+        const dz grw = (wt * wq) * mine[16 + 4 * i + j];
         R.m0 = R.m0 + grw;
         for (int d = 0; d < 3; ++d) {
           axpy(R.mu[d], up[j][d], grw);
@@ -419,7 +423,7 @@ __device__ __forceinline__ void tt_far_c_body(FixedTab P, const QuadRules *__res
         Mr.mv[d] = Mr.mv[d] + R.mv[d];
       }
       Mr.muv = Mr.muv + R.muv;
-    });
+    }
     if (act) scatter_tt_row_c<true>(Mr, *gs, gt, t2f, S, T, k, alpha, gsrc, kappa, k0sq9, outT);
   }
 }
@@ -563,10 +567,10 @@ __device__ __forceinline__ void tet_face_c_body(FixedTab P, const QuadRules *__r
     m0r = m0;
   }
   const dz sm = sigma[fi] * m0;
-  for (int k = 0; k < 4; ++k) zput(out, t2f[4 * T + k].unknown, f.unknown, mk(0, 0) - alpha[4 * T + k] * sm, false);
+  for (int k = 0; k < 4; ++k) zput_c(out, t2f[4 * T + k].unknown, f.unknown, mk(0, 0) - alpha[4 * T + k] * sm);
   if (swap && f.half) {
     const dz km = m0r * kappa[T];
-    for (int l = 0; l < 4; ++l) zput(outT, t2f[4 * T + l].unknown, f.unknown, mk(0, 0) - gsrc[4 * T + l] * km, false);
+    for (int l = 0; l < 4; ++l) zput_c(outT, t2f[4 * T + l].unknown, f.unknown, mk(0, 0) - gsrc[4 * T + l] * km);
   }
 }
 
@@ -585,7 +589,7 @@ __device__ __forceinline__ void face_tet_c_body(FixedTab P, const QuadRules *__r
   const TetGeom gs = tg[S];
   if (touch_mask(f.canon, f.off, 3, gs.canon, gs.off, 4)) return;
   const dz m0 = far_face_tet_c(P, qr, f, gs) * kappa[S];
-  for (int l = 0; l < 4; ++l) zput(out, f.unknown, t2f[4 * S + l].unknown, mk(0, 0) - gsrc[4 * S + l] * m0, false);
+  for (int l = 0; l < 4; ++l) zput_c(out, f.unknown, t2f[4 * S + l].unknown, mk(0, 0) - gsrc[4 * S + l] * m0);
 }
 
 // half-SWG test face x surface-charge face, far pairs
@@ -599,7 +603,7 @@ __device__ __forceinline__ void face_face_c_body(FixedTab P, const QuadRules *__
   const FaceGeom &f = fg[uniform(half_list[hi])];
   const FaceGeom g = fg[gi];
   if (touch_mask(f.canon, f.off, 3, g.canon, g.off, 3)) return;
-  zput(out, f.unknown, g.unknown, sigma[gi] * far_face_face_c(P, qr, f, g), false);
+  zput_c(out, f.unknown, g.unknown, sigma[gi] * far_face_face_c(P, qr, f, g));
 }
 
 // ------------------------------------------------------------ launches
