@@ -218,7 +218,7 @@ int vie_batch_fill(vie_batch *b, const double *lambda_nm, const double *theta, c
   if (!lambda_nm || !theta || !phi || !eps_per_tet) return bfail(b, VIE_EINVAL, "null argument");
   BCK(hipSetDevice(b->device));
   const int nc = (int)b->cells.size();
-  // host: the tables of every cell (each fit is itself spread over host threads)
+  // host: the tables of every cell, up to four at a time (in mixed precision each spreads its fits over threads)
   {
     std::vector<int> rc(nc, VIE_OK);
     const int nthr = std::max(1, std::min(nc, 4));

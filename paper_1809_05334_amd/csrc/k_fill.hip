@@ -113,11 +113,12 @@ __device__ __forceinline__ void scatter_tt_row(const Moments &M, const TetGeom &
 // held through them; after the sums each lane of a quad writes the entries of
 // one test face.  Bound by the issue of FP64 instructions: at three waves a
 // SIMD takes one every five cycles at best, 5,500 per wave (128 point pairs)
-// run at 80 % of that.  N = 37,376, mixed, oblique: 311 ms per fill, 406 ms with
-// one lane per pair, the Clenshaw form of every series and one image at a
-// time (pgf_eval_w); N = 18,590, FP64, ordered pairs: 138 ms, 189 before.  On
-// small cells a launch's chain counts, an eighth of one lane per pair: N = 416,
-// 16 launches, 0.5 ms, 6.1 before.
+// run at 72 % of that.  N = 37,376, symmetric, oblique: 344 ms per fill, 442 ms
+// with one lane per pair, the Clenshaw form of every series and one image at a
+// time (pgf_eval_w); N = 18,590, ordered pairs: 145 ms, 196 before.  On small
+// cells a launch's chain counts, an eighth of one lane per pair: N = 416, 16
+// launches, 0.5 ms, 6.2 before.  (FP64 entries only: mixed precision takes
+// k_far_c.hip.)
 // sym > 0 writes the swapped pair's block (S, T) too (see the declaration):
 // the second quad of the eight forms and writes it beside the first.  At
 // normal incidence the lattice sum is even in the separation (the phases

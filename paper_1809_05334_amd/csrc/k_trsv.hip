@@ -39,7 +39,7 @@ typedef double v4d __attribute__((ext_vector_type(4)));
 
 template <typename C>
 __device__ __forceinline__ void diag_inv_body(const TrsvPrep &st) {
-  constexpr int S = 16, NS = kTrsvNB / S;
+  constexpr int S = 16;
   __shared__ dz X[kTrsvNB][S];
   __shared__ dz P[4][S][S];
   __shared__ dz Td[S][S + 1];

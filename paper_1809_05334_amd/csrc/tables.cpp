@@ -27,7 +27,8 @@ using ld = long double;
 // e^{-x^2}, so a sum is good to some 1e-19 absolute (extended precision),
 // where the fits resolve 1e-15.  This is a few dozen operations per value:
 // quadrature of the complex erfcx integrals took 60 ms of host time per fill
-// (16-18 ms on 16 threads), the tables now take 2 ms on one.
+// (16-18 ms on 16 threads), the tables now take 2 ms on one.  The far entries of
+// the mixed operator keep to the quadratures below (PgfTerms::fixed).
 // Sum over n >= n0 of c^n / n! J_{n + first}(x), n0 + first >= 1.
 static const ld kSqrtPiL = 1.772453850905516027298167483341145183L;
 
